@@ -165,6 +165,66 @@ void plan_groups(qgbe_ctx* c) {
   }
 }
 
+struct Chunking {
+  int chunk;  // observed nodes per workgroup
+  int split;  // waves that share a node
+};
+
+// Observed nodes per workgroup of the FP32 kernel.
+Chunking plan_chunks(const qgbe_ctx* c, const Group& g, int l, int n_samples, bool queue, bool learned) {
+  const int waves = collide_f32_waves(queue), nb = collide_f32_node_block(queue, learned);
+  const long long nodes = c->G.nodes, pairs = (long long)c->G.cells * g.count;
+  if (pairs >= c->n_cu) {
+    // Enough (cell, channel) pairs to give every compute unit one: the nodes
+    // of a pair are split over at most two workgroups per compute unit in all,
+    // as each zeroes and flushes its accumulators (on the pure-gluon 16x16x1
+    // grid: 4096 -> 512 workgroups, 71.0 -> 68.0 ms).  A chunk is a multiple
+    // of the waves; a small one of a variant that hands nodes to its waves in
+    // blocks, whole blocks for every wave (36 nodes in blocks of 4 would leave
+    // 3 of 12 waves idle).  Large chunks keep the finer multiple: C2's two
+    // chunks per cell of 4032 and 3968 nodes instead of 4008 and 3992 cost
+    // 0.5% (compute units that ran two long ones).
+    const long long per_pair = std::max(1LL, 2LL * c->n_cu / pairs);
+    long long chunk = std::max<long long>(waves, (nodes + per_pair - 1) / per_pair);
+    const int unit = chunk < 16LL * waves * nb ? waves * nb : waves;
+    chunk = (chunk + unit - 1) / unit * unit;
+    chunk = std::min(chunk, (nodes + unit - 1) / unit * unit);
+    return {(int)chunk, 1};
+  }
+  // Fewer pairs than compute units.  A workgroup has its compute unit to
+  // itself (LDS and registers), so the workgroups number a multiple of the
+  // compute units, rounded down: one round while the samples of a workgroup
+  // are few beside the accumulators it zeroes and flushes, up to eight where
+  // they outweigh them, so that heavier and lighter nodes balance (20^3 nodes
+  // of one gluon cell, 512 samples: 167 workgroups 156 us, 256 shared ones 120).
+  const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
+  const long long samples = pairs * nodes * n_samples / c->n_cu;
+  const long long rounds = acc > 0 ? std::max(1LL, std::min(8LL, samples / (4 * acc))) : 8;
+  const long long per_pair = std::max(1LL, rounds * c->n_cu / pairs);
+  const int chunk = (int)std::max(1LL, (nodes + per_pair - 1) / per_pair);
+  // Waves per node: the one that leaves a wave the fewest sample iterations,
+  // counting per node about two more for its constants, sums and partly
+  // filled batches.
+  Chunking best{0, 1};
+  long long least = 0;
+  for (int split = 1; split <= waves; ++split) {
+    if (waves % split || (split > 1 && chunk > kSplitNodes)) continue;
+    // split 1: chunks start on node blocks and waves take whole blocks
+    const int blk = split == 1 ? std::max(nb, collide_f32_node_block(true, true)) : 1;
+    const long long ch = std::min((chunk + blk - 1) / blk * (long long)blk, (nodes + blk - 1) / blk * blk);
+    const long long wgs = pairs * ((nodes + ch - 1) / ch);
+    const int step = split == 1 ? nb : 1;
+    const long long turns = (ch + (long long)step * (waves / split) - 1) / ((long long)step * (waves / split)) * step;
+    const long long iters = (n_samples + 64LL * split - 1) / (64LL * split) + 2;
+    const long long cost = (wgs + c->n_cu - 1) / c->n_cu * turns * iters;
+    if (!best.chunk || cost < least) {
+      best = {(int)ch, split};
+      least = cost;
+    }
+  }
+  return best;
+}
+
 // Enqueue the collision kernels accumulating into A (zeroed by the caller).
 qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, double* scale, double* items) {
   const bool learned = sampler == QGBE_SAMPLER_LEARNED;
@@ -202,44 +262,11 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
     a.n_group = g.count;
     // the compacting variant when the whole group fits in LDS next to its queues
     const bool queue = !learned && g.queue;
-    const int waves = collide_f32_waves(queue);
-    const long long items = (long long)c->G.cells * g.count * c->G.nodes;
-    long long chunk = items / 2048;
-    chunk = std::max<long long>(waves, std::min<long long>(512, chunk));
-    // Every workgroup zeroes and flushes its LDS accumulators; with few
-    // samples per point that costs as much as the samples themselves, so the
-    // chunk grows until the flush entries are at most a quarter of the
-    // workgroup's samples (measured: a quarter beats an eighth, a half and
-    // one), keeping at least two workgroups per compute unit, or one where
-    // even then the flush would outweigh the samples.
-    const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
-    if (acc > 0 && chunk * n_samples < 4 * acc) {
-      const long long want = (4 * acc + n_samples - 1) / n_samples;
-      long long fill = items / (2LL * c->n_cu);
-      if (fill * n_samples < acc) fill = items / c->n_cu;
-      chunk = std::max(chunk, std::min(want, fill));
-    }
-    // With enough (cell, channel) pairs to give every compute unit one, the
-    // nodes of a pair are split over at most two workgroups per compute unit
-    // in all: fewer workgroups zero and flush their accumulators (on the
-    // pure-gluon 16x16x1 grid: 4096 -> 512 workgroups, 71.0 -> 68.0 ms;
-    // grids with fewer pairs than compute units keep the chunks above).
-    const long long pairs = (long long)c->G.cells * g.count;
-    if (pairs >= c->n_cu) {
-      const long long per_pair = std::max(1LL, 2LL * c->n_cu / pairs);
-      chunk = std::max(chunk, (c->G.nodes + per_pair - 1) / per_pair);
-    }
-    // A multiple of the waves; a small chunk of a variant that hands nodes to
-    // its waves in blocks, whole blocks for every wave (36 nodes in blocks of 4
-    // would leave 3 of 12 waves idle).  Large chunks keep the finer multiple:
-    // C2's two chunks per cell of 4032 and 3968 nodes instead of 4008 and 3992
-    // cost 0.5% (compute units that ran two long ones).
-    const int nb = collide_f32_node_block(queue, learned);
-    const int unit = chunk < 16LL * waves * nb ? waves * nb : waves;
-    chunk = (chunk + unit - 1) / unit * unit;
-    chunk = std::min<long long>(chunk, (c->G.nodes + unit - 1) / unit * unit);
-    a.chunk_items = (int)chunk;
-    a.n_chunks = (int)((c->G.nodes + chunk - 1) / chunk);
+    const Chunking ck = plan_chunks(c, g, l, n_samples, queue, learned);
+    a.split = ck.split;
+    const int chunk = ck.chunk;
+    a.chunk_items = chunk;
+    a.n_chunks = (c->G.nodes + chunk - 1) / chunk;
     // Deposit slots whose FP64 accumulators do not all fit in LDS are split
     // over launches that each keep their slots' accumulators in LDS: the
     // samples are recomputed (same draws), which costs far less than global

@@ -13,6 +13,9 @@ constexpr int kStripes = 64;
 // component constants is laid out for this many); the FP64 path takes 16.
 constexpr int kMixKF32 = 8;
 
+// Most observed nodes of a workgroup whose waves share nodes (split > 1).
+constexpr int kSplitNodes = 64;
+
 struct CollideArgs {
   Grid G;
   const Channel* chans;   // device channel table (all channels)
@@ -21,6 +24,8 @@ struct CollideArgs {
   int n_channels;         // total channels (layout of items)
   int n_chunks;           // workgroups per (cell, channel) (FP32 kernel)
   int chunk_items;        // observed nodes per workgroup (FP32 kernel)
+  int split;              // waves that share a node, each a part of its samples (FP32 kernel): divides
+                          // the workgroup's waves; > 1 only with chunk_items <= kSplitNodes
   int lds_tiles;          // f tiles staged in LDS (FP32 kernel)
   int lds_acc;            // FP64 deposit accumulators in LDS (FP32 kernel)
   int slot_lo, slot_hi;   // deposit slots [lo, hi) written by this launch (FP32 kernel); the

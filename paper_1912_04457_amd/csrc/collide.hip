@@ -1183,8 +1183,18 @@ constexpr int kNodeBlock = 4;
 // kUser: some row of the matrix-element table is replaced by user terms; the
 // variants without them carry no code for the user-term evaluation (which
 // otherwise holds registers across the sample loop: 6% of the 7-species term).
-template <bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kUser>
+// kShort: short items.  The (cell, channel) constants are computed once per
+// workgroup, the item's sums reduce through DPP without LDS round trips, and
+// several waves may share a node (A.split).  The learned sampler is always
+// in this form; a long uniform item is not: those constants held across its
+// item loop cost more spilled registers in the sample loop than they save.
+// Short items are bound by latency (three wavefronts per SIMD, an item's
+// constants, sums and partial batch each a serial chain); one gluon cell,
+// collision term: 10^3 nodes x 1000 samples 255 -> 46 us, 16^3 x 2048 547 ->
+// 203 us, 20^3 x 256 98 -> 78 us; 7 species, 30^3 x 128 20.9 -> 19.5 ms.
+template <bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kUser, bool kShort>
 __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideArgs A) {
+  static_assert(!kLearned || kShort, "the learned sampler's items are short");
   static_assert(!kQueue || (kSym && kAllLds && !kLearned), "the queue serves the uniform sampler, slots in LDS");
   // kAllLds: every f tile and accumulator in LDS (the queue variant: every
   // accumulator; f from the quads)
@@ -1200,6 +1210,7 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
   constexpr int kNB = kQueue || kLearned ? kNodeBlock : 1;  // nodes per block (as collide_f32_node_block)
   __shared__ double d_stage[kNB > 1 ? kF32Threads / kWave : 1][kNB];  // direct sums of a wave's current block
   static_assert(f32_block(kQueue) % (kWave * kNB) == 0, "a multiple of the waves is one of the block");
+  __shared__ double it_sum[3][kShort ? kSplitNodes : 1];  // A.split > 1: S_i, sum v^2 and the gain+loss sum of the chunk's items
   const Grid& G = A.G;
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = threadIdx.x / kWave;
@@ -1245,6 +1256,9 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
   if (threadIdx.x < 2) mc_wg[threadIdx.x] = 0.0;
   if (threadIdx.x == 0) ok_wg = 0ull;
   if (kNB > 1 && lane < kNB) d_stage[wid][lane] = 0.0;
+  const int split = kShort ? A.split : 1;
+  if (kShort && split > 1)
+    for (int i = threadIdx.x; i < 3 * kSplitNodes; i += blockDim.x) it_sum[i / kSplitNodes][i % kSplitNodes] = 0.0;
   for (int k = 0; k < n_tiles; ++k)
     for (int i = threadIdx.x; i < nodes; i += blockDim.x) tiles[k * nodes + i] = A.f32[goff[k] + i];
   __syncthreads();
@@ -1255,12 +1269,8 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
   const bool g3 = is_gluon(ch.sp[2]), g4 = is_gluon(ch.sp[3]);
   const int first = chunk * A.chunk_items;
   const int last = min(first + A.chunk_items, nodes);
-  // Learned sampler (short items): the (cell, channel) constants once per
-  // workgroup.  The uniform sampler's long items recompute them per item:
-  // held across its item loop they cost more spilled registers in the
-  // sample loop than they save.
   Item pair;
-  if (kLearned) item_pair(pair, A, ch, cell);
+  if (kShort) item_pair(pair, A, ch, cell);
   // After the item at node p, the last of its node block (or of the chunk):
   // the wave adds the block's staged direct sums to the output, the lanes of
   // one atomic instruction covering consecutive nodes.
@@ -1275,10 +1285,15 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
     wave_lds_sync();
   };
   // Wave w takes the node blocks w, w + nw, w + 2 nw, ... of the chunk (the
-  // chunk starts on a block boundary), the nodes of a block in turn.
-  for (int p1_lin = first + kNB * wid; p1_lin < last; p1_lin += (p1_lin & (kNB - 1)) == kNB - 1 ? kNB * (nw - 1) + 1 : 1) {
+  // chunk starts on a block boundary), the nodes of a block in turn.  With
+  // few items (A.split > 1) `split` waves share a node, each its part of the
+  // samples, and the groups of waves take the chunk's nodes in turn.
+  const int s_first = split > 1 ? (wid % split) * kWave : 0, s_step = split * kWave;
+  const int n_grp = nw / split;
+  for (int p1_lin = first + (split > 1 ? wid / split : kNB * wid); p1_lin < last;
+       p1_lin += split > 1 ? n_grp : ((p1_lin & (kNB - 1)) == kNB - 1 ? kNB * (nw - 1) + 1 : 1)) {
     Item it;
-    if (kLearned) {
+    if (kShort) {
       it = pair;
       item_node(it, A, ch, p1_lin);
     } else {
@@ -1286,7 +1301,7 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
     }
     if (!(it.E1 > 0.0)) {  // massless p = 0 node: zero measure
       if (lane == 0 && A.items && A.direct) A.items[((size_t)cell * A.n_channels + ci) * nodes + p1_lin] = 0.0;
-      flush_block(p1_lin);
+      if (split == 1) flush_block(p1_lin);
       continue;
     }
     const float f1 = (float)it.f1;
@@ -1303,8 +1318,7 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     // Queue mode: the deposits of the last evaluated batch, issued while the
-    // next samples' geometry runs (lanes without a sample in a partial batch
-    // deposit zeros).
+    // next samples' geometry runs.
     Stencil<float> pd2{}, pd3{}, pd4{};
     float pdv = 0.0f;
     bool pending = false;
@@ -1366,7 +1380,7 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
         finish(g, m * q_f[wid][3][slot]);
       };
       unsigned head = 0, tail = 0;  // ring positions (wave-uniform)
-      for (int base = 0; base < A.n_samples; base += kWave) {
+      for (int base = s_first; base < A.n_samples; base += s_step) {
         const int s = base + lane;
         uint32_t x0 = (uint32_t)s, x1 = (uint32_t)p1_lin, x2 = (uint32_t)cell, x3 = ((uint32_t)ch.code << 8);
         philox4x32_10(x0, x1, x2, x3, A.key0, A.key1);
@@ -1396,7 +1410,6 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
         tail += (unsigned)__popcll(mask);
         if (tail - head >= (unsigned)kWave) {
           wave_lds_sync();
-          pdv = 0.0f;
           finish_queued((head + lane) & (kQueueLen - 1));
           pending = true;
           head += kWave;
@@ -1412,16 +1425,20 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
                            nodes, G.ox, G.oy, win_lo, win_n);
       };
       if (pending) flush();  // the last full batch
-      if (tail != head) {    // the last, partial batch
+      // the last, partial batch: only the lanes that hold a sample deposit (zeros
+      // of the idle lanes, all at one address, took 60 us of an 88 us launch of
+      // 7722 items x 100 samples)
+      if (tail != head) {
         wave_lds_sync();
-        pdv = 0.0f;
-        if ((unsigned)lane < tail - head) finish_queued((head + lane) & (kQueueLen - 1));
-        flush();
+        if ((unsigned)lane < tail - head) {
+          finish_queued((head + lane) & (kQueueLen - 1));
+          flush();
+        }
         wave_lds_sync();
       }
       pending = false;
     } else
-    for (int s = lane; s < A.n_samples; s += kWave) {
+    for (int s = s_first + lane; s < A.n_samples; s += s_step) {
       uint32_t x0 = (uint32_t)s, x1 = (uint32_t)p1_lin, x2 = (uint32_t)cell, x3 = ((uint32_t)ch.code << 8);
       philox4x32_10(x0, x1, x2, x3, A.key0, A.key1);
       double u[5];
@@ -1440,7 +1457,7 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
     }
     if (!A.direct) continue;
     int ok_total;
-    if (kLearned) {  // short items (few hundred samples): DPP sums, no LDS round trips
+    if (kShort) {
       dsum = wave_sum_dpp(dsum);
       if (kScale) ssum = wave_sum_dpp(ssum);
       dsq = wave_sum_dpp(dsq);
@@ -1450,6 +1467,16 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
       if (kScale) ssum = wave_sum(ssum);
       dsq = wave_sum(dsq);
       ok_total = wave_count(n_ok);
+    }
+    if (kShort && split > 1) {  // this wave's part of the item
+      if (lane == 0) {
+        const int i = p1_lin - first;
+        __hip_atomic_fetch_add(&ok_wg, (unsigned long long)ok_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(&it_sum[0][i], dsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(&it_sum[1][i], dsq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (kScale) __hip_atomic_fetch_add(&it_sum[2][i], ssum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      continue;
     }
     if (lane == 0) {
       __hip_atomic_fetch_add(&ok_wg, (unsigned long long)ok_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1466,6 +1493,20 @@ __global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideA
     flush_block(p1_lin);
   }
   __syncthreads();
+  if (kShort && split > 1 && A.direct) {  // the chunk's items from their waves' parts, a node per lane
+    const int i = threadIdx.x, p1_lin = first + i;
+    if (p1_lin < last) {
+      const double dsum = it_sum[0][i];
+      __hip_atomic_fetch_add(&mc_wg[0], item_variance(dsum, it_sum[1][i], A.n_samples), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(&mc_wg[1], dsum * dsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const size_t at = ((size_t)ch.sp[0] * G.cells + cell) * nodes + p1_lin;
+      if (dsum != 0.0) atomicAdd(A.A + at, dsum);
+      if (kScale) atomicAdd(A.scale + at, it_sum[2][i]);
+      if (A.items) A.items[((size_t)cell * A.n_channels + ci) * nodes + p1_lin] = dsum;
+    }
+    __syncthreads();
+  }
   const int stripe = blockIdx.x % kStripes;
   if (threadIdx.x < 2 && A.mc_acc && A.direct) atomicAdd(&A.mc_acc[2 * stripe + threadIdx.x], mc_wg[threadIdx.x]);
   if (threadIdx.x == 0 && A.n_accepted && A.direct) atomicAdd(A.n_accepted + stripe, ok_wg);
@@ -1594,32 +1635,40 @@ hipError_t launch_collide_f64(const CollideArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue>
+// Uniform sampler: the short-item form when waves share nodes, and below
+// kShortSamples samples per item (at 2048 samples on 256 cells of gluons the
+// compiled long form is 1.8% faster, 65.8 against 67.0 ms; at 128 samples on
+// the 70 channels of a 30^3 cell the short one 3.5%, 20.2 against 19.5 ms).
+constexpr int kShortSamples = 1024;
+bool f32_short(const CollideArgs& a) { return a.split > 1 || a.n_samples < kShortSamples; }
+
+template <bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kShort>
 void launch_f32_user(const CollideArgs& a, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
   if (a.msq_mask)
-    hipLaunchKernelGGL((collide_f32_kernel<kSym, kScale, kAllLds, kLearned, kQueue, true>), grid, block, lds, st, a);
+    hipLaunchKernelGGL((collide_f32_kernel<kSym, kScale, kAllLds, kLearned, kQueue, true, kShort>), grid, block, lds, st, a);
   else
-    hipLaunchKernelGGL((collide_f32_kernel<kSym, kScale, kAllLds, kLearned, kQueue, false>), grid, block, lds, st, a);
+    hipLaunchKernelGGL((collide_f32_kernel<kSym, kScale, kAllLds, kLearned, kQueue, false, kShort>), grid, block, lds, st, a);
 }
 
-template <bool kSym, bool kScale, bool kLearned>
+template <bool kSym, bool kScale, bool kLearned, bool kShort>
 void launch_f32_variant(const CollideArgs& a, bool all_lds, bool queue, dim3 grid, dim3 block, size_t lds,
                         hipStream_t st) {
   if constexpr (kSym && !kLearned) {
     if (queue) {
-      launch_f32_user<true, kScale, true, false, true>(a, grid, block, lds, st);
+      launch_f32_user<true, kScale, true, false, true, kShort>(a, grid, block, lds, st);
       return;
     }
   }
-  if (all_lds) launch_f32_user<kSym, kScale, true, kLearned, false>(a, grid, block, lds, st);
-  else launch_f32_user<kSym, kScale, false, kLearned, false>(a, grid, block, lds, st);
+  if (all_lds) launch_f32_user<kSym, kScale, true, kLearned, false, kShort>(a, grid, block, lds, st);
+  else launch_f32_user<kSym, kScale, false, kLearned, false, kShort>(a, grid, block, lds, st);
 }
 
 template <bool kSym, bool kScale>
 void launch_f32_sampler(const CollideArgs& a, bool all_lds, bool queue, dim3 grid, dim3 block, size_t lds,
                         hipStream_t st) {
-  if (a.learned) launch_f32_variant<kSym, kScale, true>(a, all_lds, false, grid, block, lds, st);
-  else launch_f32_variant<kSym, kScale, false>(a, all_lds, queue, grid, block, lds, st);
+  if (a.learned) launch_f32_variant<kSym, kScale, true, true>(a, all_lds, false, grid, block, lds, st);
+  else if (f32_short(a)) launch_f32_variant<kSym, kScale, false, true>(a, all_lds, queue, grid, block, lds, st);
+  else launch_f32_variant<kSym, kScale, false, false>(a, all_lds, queue, grid, block, lds, st);
 }
 
 int collide_f32_waves(bool queue) { return f32_block(queue) / kWave; }
@@ -1637,7 +1686,9 @@ hipError_t launch_collide_f32(const CollideArgs& a, int nslot, bool queue, hipSt
   const size_t lds = (size_t)n_acc * a.win_n * sizeof(double) + (size_t)n_tiles * a.G.nodes * sizeof(float);
   const long long blocks = (long long)a.G.cells * a.n_group * a.n_chunks;
   if (blocks <= 0) return hipSuccess;
-  if (a.chunk_items % kNodeBlock != 0) return hipErrorInvalidValue;  // chunks start on node blocks
+  if (a.split < 1 || (threads / kWave) % a.split) return hipErrorInvalidValue;  // whole groups of waves
+  if (a.split > 1 ? a.chunk_items > kSplitNodes : a.chunk_items % kNodeBlock != 0)
+    return hipErrorInvalidValue;  // a shared chunk's sums fit in it_sum; other chunks start on node blocks
   const dim3 grid((unsigned)blocks), block(threads);
   if (a.symmetric) {
     if (a.scale) launch_f32_sampler<true, true>(a, all_lds, queue, grid, block, lds, stream);
@@ -1655,18 +1706,20 @@ hipError_t set_collide_lds_limit(size_t lds_max, size_t* budget_plain, size_t* b
   // runtime's default; after a refusal the budget is the limit in force.
   // Groups: 0 uniform sampler, 1 learned sampler, 2 the compacting variant.
   struct Fn { const void* fn; int group; };
-#define QGBE_F32_PAIR(S, Sc, L, Le, Q, G) \
-  {(const void*)collide_f32_kernel<S, Sc, L, Le, Q, false>, G}, {(const void*)collide_f32_kernel<S, Sc, L, Le, Q, true>, G}
-  const Fn fns[36] = {
-      QGBE_F32_PAIR(true, true, true, false, false, 0),   QGBE_F32_PAIR(true, false, true, false, false, 0),
-      QGBE_F32_PAIR(false, true, true, false, false, 0),  QGBE_F32_PAIR(false, false, true, false, false, 0),
-      QGBE_F32_PAIR(true, true, false, false, false, 0),  QGBE_F32_PAIR(true, false, false, false, false, 0),
-      QGBE_F32_PAIR(false, true, false, false, false, 0), QGBE_F32_PAIR(false, false, false, false, false, 0),
-      QGBE_F32_PAIR(true, true, true, true, false, 1),    QGBE_F32_PAIR(true, false, true, true, false, 1),
-      QGBE_F32_PAIR(false, true, true, true, false, 1),   QGBE_F32_PAIR(false, false, true, true, false, 1),
-      QGBE_F32_PAIR(true, true, false, true, false, 1),   QGBE_F32_PAIR(true, false, false, true, false, 1),
-      QGBE_F32_PAIR(false, true, false, true, false, 1),  QGBE_F32_PAIR(false, false, false, true, false, 1),
-      QGBE_F32_PAIR(true, true, true, false, true, 2),    QGBE_F32_PAIR(true, false, true, false, true, 2)};
+#define QGBE_F32_PAIR(S, Sc, L, Le, Q, Sh, G)                          \
+  {(const void*)collide_f32_kernel<S, Sc, L, Le, Q, false, Sh>, G},    \
+      {(const void*)collide_f32_kernel<S, Sc, L, Le, Q, true, Sh>, G}
+#define QGBE_F32_SYM(L, Le, Q, Sh, G)                                               \
+  QGBE_F32_PAIR(true, true, L, Le, Q, Sh, G), QGBE_F32_PAIR(true, false, L, Le, Q, Sh, G)
+#define QGBE_F32_ALL(L, Le, Sh, G)                                                   \
+  QGBE_F32_SYM(L, Le, false, Sh, G), QGBE_F32_PAIR(false, true, L, Le, false, Sh, G), \
+      QGBE_F32_PAIR(false, false, L, Le, false, Sh, G)
+  const Fn fns[] = {
+      QGBE_F32_ALL(true, false, false, 0), QGBE_F32_ALL(false, false, false, 0), QGBE_F32_ALL(true, false, true, 0),
+      QGBE_F32_ALL(false, false, true, 0), QGBE_F32_ALL(true, true, true, 1),    QGBE_F32_ALL(false, true, true, 1),
+      QGBE_F32_SYM(true, false, true, false, 2), QGBE_F32_SYM(true, false, true, true, 2)};
+#undef QGBE_F32_ALL
+#undef QGBE_F32_SYM
 #undef QGBE_F32_PAIR
   size_t budget[3] = {lds_max, lds_max, lds_max};
   for (const Fn& f : fns) {

@@ -294,3 +294,34 @@ def test_mc_error_estimate_matches_replicas(precision):
     emp = np.sqrt(I.var(0, ddof=1).sum() / (I.mean(0) ** 2).sum())
     print(f"[mc error] estimate {np.mean(est):.4f} (spread {np.std(est):.4f}), replicas {emp:.4f}", flush=True)
     assert 0.8 < np.mean(est) / emp < 1.25
+
+
+@pytest.mark.parametrize("n_x,n_p,mask,N", [((1, 1, 1), (2, 2, 2), 1 << 6, 1000), ((1, 1, 1), (9, 8, 7), 1 << 6, 130),
+                                            ((1, 1, 1), (16, 16, 16), 0x41, 65), ((3, 1, 1), (5, 6, 7), 0x7F, 193),
+                                            ((1, 1, 1), (16, 15, 17), 1 << 6, 1100)],
+                         ids=["8nodes", "one_pair", "three_channels", "pairs_and_cus", "long_items"])
+def test_waves_share_nodes_fp32(O, n_x, n_p, mask, N):
+    """Fewer (cell, channel) pairs than compute units: several waves of a
+    workgroup share a node, each a part of its samples (some waves with none,
+    the last part short), and the item sums and the error estimate come from
+    the parts; the scale output takes the same way."""
+    _case(f"shared nodes {n_x} {n_p} mask={mask:#x} N={N}")
+    wl = W.Workload("shared", n_x, n_p, (3.0, 3.0, 3.0), (2.0, 2.5, 1.5), mask, N, "f32", 1, 0.01)
+    f = W.random_f(25, wl.cells, wl.nodes, species_mask=mask)
+    r = _run_pair(O, wl, f, N, qgbe.FP32, step=2)
+    _compare(r["A"], r["A_ref"], r["S_ref"], TOL[qgbe.FP32], "A")
+    scale_items = np.abs(r["I_ref"]).max()
+    assert np.allclose(r["I"], r["I_ref"], rtol=TOL[qgbe.FP32], atol=TOL[qgbe.FP32] * scale_items)
+    with qgbe.Solver(**_grid_kw(wl), precision=qgbe.FP64, seed=SEED) as s:
+        s.set_f(f)
+        qgbe.qgbe_set_step_index(s.ctx, 2)
+        _, S, _, st = s.collision(N, scale=True)
+    with qgbe.Solver(**_grid_kw(wl), precision=qgbe.FP32, seed=SEED) as s:
+        s.set_f(f)
+        qgbe.qgbe_set_step_index(s.ctx, 2)
+        A2, S2, _, st2 = s.collision(N, scale=True)
+    _compare(A2, r["A_ref"], r["S_ref"], TOL[qgbe.FP32], "A with scale")
+    assert np.all(np.abs(S2 - S) <= TOL[qgbe.FP32] * S + 1e-300)
+    assert st2.n_accepted == st.n_accepted == r["st"].n_accepted
+    if np.isfinite(st.mc_err_est):
+        assert st2.mc_err_est == pytest.approx(st.mc_err_est, rel=1e-2)
