@@ -74,7 +74,7 @@ def traffic_profile(workload: str) -> str:
     return os.path.join(ROOT, "profiles", f"collide_f32_{workload}_hbm_counters.md")
 
 
-KERNEL_SOURCES = ("collide.hip", "collide.h", "qgbe_common.h", "api.hip")
+KERNEL_SOURCES = ("collide_f32.hip", "collide_device.h", "collide.h", "qgbe_common.h", "api.hip")
 
 
 def kernel_sources_digest() -> str:

@@ -1,4 +1,4 @@
-"""Coefficients of the FP64 polynomials in collide.hip (exp64, log64,
+"""Coefficients of the FP64 polynomials in collide_device.h (exp64, log64,
 sincos_2pi): Chebyshev-node fits (mpmath.chebyfit, near-minimax) of the
 smooth part of each function on its reduced range, at 60 digits, rounded to
 FP64.  Prints each list highest degree first with the fit's error bound.
