@@ -133,12 +133,13 @@ void make_grid(const qgbe_grid_desc* d, Grid& G) {
 void plan_groups(qgbe_ctx* c) {
   const size_t acc_b = (size_t)c->G.nodes * sizeof(double);
   const size_t tile_b = (size_t)c->G.nodes * sizeof(float);
+  const bool f32 = c->d.precision == QGBE_FP32;  // FP64 reads f from the FP64 field
   c->group_index.clear();
   c->groups.clear();
   for (int nslot = 1; nslot <= 3; ++nslot) {
     Group g{(int)c->group_index.size(), 0, nslot, {0, 0}, {0, 0}, {c->G.nodes, c->G.nodes}, false};
     for (int l = 0; l < 2; ++l) {
-      const size_t budget = c->lds_budget[l];
+      const size_t budget = l ? c->lds.learned : c->lds.plain;
       if (c->d.symmetric && budget < acc_b) {
         // one slot's FP64 accumulators exceed LDS: node windows, one launch
         // per window holding every slot's accumulators for that window, the
@@ -151,16 +152,16 @@ void plan_groups(qgbe_ctx* c) {
         continue;
       }
       g.lds_acc[l] = c->d.symmetric ? (int)std::min<size_t>(nslot, budget / acc_b) : 0;
-      g.lds_tiles[l] = (int)std::min<size_t>(nslot, (budget - g.lds_acc[l] * acc_b) / tile_b);
+      g.lds_tiles[l] = f32 ? (int)std::min<size_t>(nslot, (budget - g.lds_acc[l] * acc_b) / tile_b) : 0;
     }
-    g.queue = c->d.symmetric && g.lds_acc[0] == nslot && nslot * acc_b <= c->lds_budget_queue;
+    g.queue = c->d.symmetric && g.lds_acc[0] == nslot && nslot * acc_b <= c->lds.queue;
     for (int i = 0; i < c->nch; ++i)
       if (c->chans[i].nslot == nslot) c->group_index.push_back(i);
     g.count = (int)c->group_index.size() - g.start;
     if (g.count) {
       c->groups.push_back(g);
-      for (int l = 0; l < 2; ++l) c->need_quads[l] = c->need_quads[l] || g.lds_tiles[l] < nslot;
-      c->need_quads[0] = c->need_quads[0] || g.queue;
+      for (int l = 0; l < 2; ++l) c->need_quads[l] = f32 && (c->need_quads[l] || g.lds_tiles[l] < nslot);
+      c->need_quads[0] = f32 && (c->need_quads[0] || g.queue);
     }
   }
 }
@@ -170,9 +171,9 @@ struct Chunking {
   int split;  // waves that share a node
 };
 
-// Observed nodes per workgroup of the FP32 kernel.
+// Observed nodes per workgroup.
 Chunking plan_chunks(const qgbe_ctx* c, const Group& g, int l, int n_samples, bool queue, bool learned) {
-  const int waves = collide_f32_waves(queue), nb = collide_f32_node_block(queue, learned);
+  const int waves = collide_waves(queue), nb = collide_node_block(queue, learned);
   const long long nodes = c->G.nodes, pairs = (long long)c->G.cells * g.count;
   if (pairs >= c->n_cu) {
     // Enough (cell, channel) pairs to give every compute unit one: the nodes
@@ -192,34 +193,42 @@ Chunking plan_chunks(const qgbe_ctx* c, const Group& g, int l, int n_samples, bo
     return {(int)chunk, 1};
   }
   // Fewer pairs than compute units.  A workgroup has its compute unit to
-  // itself (LDS and registers), so the workgroups number a multiple of the
-  // compute units, rounded down: one round while the samples of a workgroup
-  // are few beside the accumulators it zeroes and flushes, up to eight where
-  // they outweigh them, so that heavier and lighter nodes balance (20^3 nodes
-  // of one gluon cell, 512 samples: 167 workgroups 156 us, 256 shared ones 120).
+  // itself (LDS and registers), so their number is chosen near a multiple of
+  // the compute units (up to eight rounds), and with few nodes per workgroup
+  // several waves share a node.  The estimate, in sample iterations of a lone
+  // wave (1.7 us): turns of the waves times (iterations per node plus one for
+  // the node's constants, sums and partly filled batches), a turn 1.3 or 1.75
+  // times as long with two or three waves at work on a SIMD, plus the
+  // workgroup's start and the accumulators it zeroes and flushes (450 take
+  // about an iteration), in every round; nodes differ in how many samples
+  // they accept, which unbalances one round by about a tenth.  (20^3 nodes of one gluon cell,
+  // 512 samples: 167 workgroups without sharing 156 us, 256 with it 120.)
   const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
-  const long long samples = pairs * nodes * n_samples / c->n_cu;
-  const long long rounds = acc > 0 ? std::max(1LL, std::min(8LL, samples / (4 * acc))) : 8;
-  const long long per_pair = std::max(1LL, rounds * c->n_cu / pairs);
-  const int chunk = (int)std::max(1LL, (nodes + per_pair - 1) / per_pair);
-  // Waves per node: the one that leaves a wave the fewest sample iterations,
-  // counting per node about two more for its constants, sums and partly
-  // filled batches.
+  const auto turn = [](long long active) { return active <= 0 ? 0.0 : active <= 4 ? 1.0 : active <= 8 ? 1.3 : 1.75; };
   Chunking best{0, 1};
-  long long least = 0;
-  for (int split = 1; split <= waves; ++split) {
-    if (waves % split || (split > 1 && chunk > kSplitNodes)) continue;
-    // split 1: chunks start on node blocks and waves take whole blocks
-    const int blk = split == 1 ? std::max(nb, collide_f32_node_block(true, true)) : 1;
-    const long long ch = std::min((chunk + blk - 1) / blk * (long long)blk, (nodes + blk - 1) / blk * blk);
-    const long long wgs = pairs * ((nodes + ch - 1) / ch);
-    const int step = split == 1 ? nb : 1;
-    const long long turns = (ch + (long long)step * (waves / split) - 1) / ((long long)step * (waves / split)) * step;
-    const long long iters = (n_samples + 64LL * split - 1) / (64LL * split) + 2;
-    const long long cost = (wgs + c->n_cu - 1) / c->n_cu * turns * iters;
-    if (!best.chunk || cost < least) {
-      best = {(int)ch, split};
-      least = cost;
+  double least = 0.0;
+  for (int rounds = 1; rounds <= 8; ++rounds) {
+    const long long want = std::max(1LL, rounds * c->n_cu / pairs);
+    const long long even = (nodes + want - 1) / want;
+    for (int split = 1; split <= waves; ++split) {
+      if (waves % split) continue;
+      const long long unit = split > 1 ? 1 : nb;       // one wave per node: whole node blocks
+      const long long group = unit * (waves / split);  // nodes the workgroup takes at a time
+      for (const long long step : {unit, group}) {
+        const long long chunk = std::min((even + step - 1) / step * step, (nodes + unit - 1) / unit * unit);
+        if (split > 1 && chunk > kSplitNodes) continue;
+        const long long iters = (n_samples + 64LL * split - 1) / (64LL * split) + 1;
+        const long long units = (chunk + unit - 1) / unit, per_turn = waves / split;
+        const double busy = (double)(unit * iters) * ((double)(units / per_turn) * turn(per_turn * split) +
+                                                      turn(units % per_turn * split));
+        const long long wgs = pairs * ((nodes + chunk - 1) / chunk);
+        const double r = (double)((wgs + c->n_cu - 1) / c->n_cu);
+        const double cost = r * (busy * (1.0 + 0.1 / r) + 3.0 + (double)acc / 450.0);
+        if (!best.chunk || cost < least) {
+          best = {(int)chunk, split};
+          least = cost;
+        }
+      }
     }
   }
   return best;
@@ -247,13 +256,6 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
     return QGBE_OK;
   }
   const bool f64_path = c->d.precision == QGBE_FP64;
-  if (f64_path) {
-    a.group = c->d_all;
-    a.n_group = c->nch;
-    HIP_TRY(launch_collide_f64(a, c->stream), "collide (fp64)");
-    ++c->n_launches;
-    return QGBE_OK;
-  }
   const int l = learned ? 1 : 0;
   if (c->need_quads[l]) HIP_TRY(launch_f32_quads(c->G, c->d_f32, c->d_f32q, c->stream), "f32 quads");
   a.f32q = c->d_f32q;
@@ -287,10 +289,12 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
         a.lds_tiles = g.lds_tiles[l];
         if (n_pass > 1 && n_win == 1) {
           const size_t used = (size_t)(a.slot_hi - a.slot_lo) * acc_b;
-          a.lds_tiles = (int)std::min<size_t>(g.nslot, (c->lds_budget[l] - used) / tile_b);
+          a.lds_tiles = f64_path ? 0 : (int)std::min<size_t>(g.nslot, ((l ? c->lds.learned : c->lds.plain) - used) / tile_b);
         }
         if (queue) a.lds_tiles = 0;  // the compacting variant reads f from the node quads
-        HIP_TRY(launch_collide_f32(a, g.nslot, queue && n_pass == 1 && n_win == 1, c->stream), "collide (fp32)");
+        const bool q = queue && n_pass == 1 && n_win == 1;
+        if (f64_path) HIP_TRY(launch_collide_f64(a, g.nslot, q, c->stream), "collide (fp64)");
+        else HIP_TRY(launch_collide_f32(a, g.nslot, q, c->stream), "collide (fp32)");
         ++c->n_launches;
       }
     }
@@ -406,8 +410,9 @@ qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out) {
   int lds_max = 0;
   HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, desc->device),
           "query LDS size");
-  size_t lds_budget[3] = {0, 0, 0};
-  HIP_TRY(set_collide_lds_limit((size_t)std::max(lds_max, 0), &lds_budget[0], &lds_budget[1], &lds_budget[2]),
+  LdsBudget lds;
+  const size_t lds_bytes = (size_t)std::max(lds_max, 0);
+  HIP_TRY(desc->precision == QGBE_FP64 ? collide_f64_lds_limit(lds_bytes, &lds) : collide_f32_lds_limit(lds_bytes, &lds),
           "raise the dynamic LDS limit");
   qgbe_ctx* c = new qgbe_ctx();
   c->d = *desc;
@@ -416,9 +421,7 @@ qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out) {
   c->chans.resize(kMaxChannels);
   c->nch = build_channels(desc->species_mask, desc->row_mask, c->chans.data(), kMaxChannels);
   c->chans.resize(c->nch);
-  c->lds_budget[0] = lds_budget[0];
-  c->lds_budget[1] = lds_budget[1];
-  c->lds_budget_queue = lds_budget[2];
+  c->lds = lds;
   int n_cu = 0;
   if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, desc->device) == hipSuccess && n_cu > 0)
     c->n_cu = n_cu;

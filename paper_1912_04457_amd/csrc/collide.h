@@ -22,15 +22,15 @@ struct CollideArgs {
   const int* group;       // channel indices processed by this launch
   int n_group;
   int n_channels;         // total channels (layout of items)
-  int n_chunks;           // workgroups per (cell, channel) (FP32 kernel)
-  int chunk_items;        // observed nodes per workgroup (FP32 kernel)
-  int split;              // waves that share a node, each a part of its samples (FP32 kernel): divides
+  int n_chunks;           // workgroups per (cell, channel)
+  int chunk_items;        // observed nodes per workgroup
+  int split;              // waves that share a node, each a part of its samples: divides
                           // the workgroup's waves; > 1 only with chunk_items <= kSplitNodes
-  int lds_tiles;          // f tiles staged in LDS (FP32 kernel)
-  int lds_acc;            // FP64 deposit accumulators in LDS (FP32 kernel)
-  int slot_lo, slot_hi;   // deposit slots [lo, hi) written by this launch (FP32 kernel); the
+  int lds_tiles;          // f tiles staged in LDS
+  int lds_acc;            // FP64 deposit accumulators in LDS
+  int slot_lo, slot_hi;   // deposit slots [lo, hi) written by this launch; the
                           // first lds_acc of them accumulate in LDS, the rest in global memory
-  int win_lo, win_n;      // LDS accumulators cover nodes [win_lo, win_lo + win_n) (FP32 kernel);
+  int win_lo, win_n;      // LDS accumulators cover nodes [win_lo, win_lo + win_n);
                           // deposit corners outside belong to another launch
   int direct;             // this launch also writes the direct sums, items, scale and counts
   int n_samples;
@@ -58,21 +58,26 @@ struct CollideArgs {
   const uint8_t* mix_on;     // [channels] 0: the channel falls back to the uniform sampler; NULL: all 1
 };
 
-hipError_t launch_collide_f64(const CollideArgs& a, hipStream_t stream);
+// Dynamic LDS of one precision's kernel variants.
+struct LdsBudget {
+  size_t plain = 0, learned = 0, queue = 0;  // uniform sampler, learned sampler, the compacting variant
+};
+
 // The paper's root parameterisation (FP64; alt: the alternative elimination).
 hipError_t launch_collide_roots(const CollideArgs& a, bool alt, hipStream_t stream);
 // queue: use the compacting variant if the launch qualifies (uniform sampler,
-// symmetric, every tile and accumulator in LDS within the queue budget).
+// symmetric, every accumulator in LDS within the queue budget).
 hipError_t launch_collide_f32(const CollideArgs& a, int nslot, bool queue, hipStream_t stream);
-// Raise the FP32 kernels' dynamic LDS limit to what their static LDS leaves
-// of lds_max; returns the dynamic budget of the uniform-sampler, the
-// learned-sampler and the compacting variants.
-hipError_t set_collide_lds_limit(size_t lds_max, size_t* budget_plain, size_t* budget_learned, size_t* budget_queue);
-// Waves per workgroup of the FP32 kernel (chunks are multiples of it).
-int collide_f32_waves(bool queue);
-// Consecutive observed nodes a wave of the FP32 kernel takes at a time
-// (chunks must be multiples of it; multiples of the waves are).
-int collide_f32_node_block(bool queue, bool learned);
+hipError_t launch_collide_f64(const CollideArgs& a, int nslot, bool queue, hipStream_t stream);
+// Raise the kernels' dynamic LDS limit to what their static LDS leaves of
+// lds_max; returns the dynamic budgets.
+hipError_t collide_f32_lds_limit(size_t lds_max, LdsBudget* out);
+hipError_t collide_f64_lds_limit(size_t lds_max, LdsBudget* out);
+// Waves per workgroup of the kernel (chunks are multiples of it).
+int collide_waves(bool queue);
+// Consecutive observed nodes a wave of the kernel takes at a time (chunks
+// must be multiples of it; multiples of the waves are).
+int collide_node_block(bool queue, bool learned);
 hipError_t launch_record(const CollideArgs& a, int n_per_item, long long item_stride, long long n_sel, float* rows,
                          hipStream_t stream);
 

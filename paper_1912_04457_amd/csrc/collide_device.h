@@ -18,8 +18,7 @@
 // precisions reject exactly the samples an FP64 evaluation rejects; on CDNA4
 // FP64 add/mul/FMA issue at the rate of unpacked FP32.  The integrand
 // (|M|^2, interpolation, bracket, value) is FP32 in QGBE_FP32 mode.  Direct
-// sums are FP64; in FP32 mode the deposits go to FP32 LDS accumulators per
-// workgroup and are flushed into the FP64 output.
+// sums and deposits are FP64 in both modes.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -425,34 +424,6 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 constexpr double kTwo32 = 4294967296.0;
 constexpr double kHalfLog2Pi = 0.91893853320467274178;
 
-// Draw u (and y = logit u) for one sample from the 8 words of two Philox blocks.
-__device__ __forceinline__ void mix_draw(const uint32_t x[8], const uint32_t* __restrict__ thr,
-                                         const float* __restrict__ mu, const float* __restrict__ sg, int K,
-                                         double u[5], double y[5]) {
-  if (x[0] < thr[0]) {
-    for (int d = 0; d < 5; ++d) {
-      u[d] = unif23(x[1 + d] >> 9);
-      y[d] = log64(u[d] * rcp64(1.0 - u[d]));
-    }
-    return;
-  }
-  int k = 0;
-  for (int j = 1; j < K; ++j) k = x[0] >= thr[j] ? j : k;
-  double z[6];
-  for (int pr = 0; pr < 3; ++pr) {
-    const double a1 = unif23(x[1 + 2 * pr] >> 9), a2 = unif23(x[2 + 2 * pr] >> 9);
-    const double r = sqrt64(-2.0 * log64(a1));
-    double sn, cs;
-    sincos_2pi(a2, sn, cs);
-    z[2 * pr] = r * cs;
-    z[2 * pr + 1] = r * sn;
-  }
-  for (int d = 0; d < 5; ++d) {
-    y[d] = (double)mu[k * 5 + d] + (double)sg[k * 5 + d] * z[d];
-    u[d] = rcp64(1.0 + exp64(-y[d]));
-  }
-}
-
 // Per-item constants of the FP32 sampler, one row per wave in LDS: mu (40),
 // 1/sigma (40), log pi_k - sum_d log sigma_kd - 5/2 log 2 pi (8), alpha,
 // sigma (40).
@@ -498,38 +469,92 @@ __device__ __forceinline__ void mix_draw_row(const uint32_t x[8], const uint32_t
   }
 }
 
-// log of u(1-u) from y = logit(u), written stably
-template <typename R>
-__device__ __forceinline__ R log_u1mu(R y) {
-  const R a = y < R(0) ? -y : y;
-  return -a - R(2) * log1p(exp(-a));
+// Per-item constants of the FP64 sampler (up to 16 components), one row per
+// wave in LDS: mu (80), 1/sigma (80), sigma (80), log pi_k - sum_d log
+// sigma_kd - 5/2 log 2 pi (16), alpha.
+constexpr int kMixMaxK = 16;
+constexpr int kMixRowF64 = 16 * kMixMaxK + 1;
+
+__device__ __forceinline__ void mix_prepare_f64(const uint32_t* thr, const float* mu, const float* sg, int K,
+                                                double* row, int lane) {
+  for (int i = lane; i < K * 5; i += kWave) {
+    row[i] = (double)mu[i];
+    row[80 + i] = 1.0 / (double)sg[i];
+    row[160 + i] = (double)sg[i];
+  }
+  if (lane < K) {
+    const double hi = lane + 1 < K ? (double)thr[lane + 1] : kTwo32;
+    const double pk = (hi - (double)thr[lane]) / kTwo32;
+    double c = -1e300;
+    if (pk > 0.0) {
+      c = log(pk) - 5.0 * kHalfLog2Pi;
+      for (int d = 0; d < 5; ++d) c -= log((double)sg[lane * 5 + d]);
+    }
+    row[240 + lane] = c;
+  }
+  if (lane == 0) row[256] = (double)thr[0] / kTwo32;
 }
 
-// q(u) in FP64 straight from the table row (reference-precision path)
-__device__ __forceinline__ double mix_density_f64(const uint32_t* thr, const float* mu, const float* sg, int K,
-                                                  const double y[5]) {
-  double lk[16];
+// Draw u (and y = logit u) for one sample from the 8 words of two Philox blocks.
+__device__ __forceinline__ void mix_draw_row_f64(const uint32_t x[8], const uint32_t* __restrict__ thr,
+                                                 const double* row, int K, double u[5], double y[5]) {
+  if (x[0] < thr[0]) {
+    for (int d = 0; d < 5; ++d) {
+      u[d] = unif23(x[1 + d] >> 9);
+      y[d] = log64(u[d] * rcp64(1.0 - u[d]));
+    }
+    return;
+  }
+  int k = 0;
+  for (int j = 1; j < K; ++j) k = x[0] >= thr[j] ? j : k;
+  double z[6];
+  for (int pr = 0; pr < 3; ++pr) {
+    const double a1 = unif23(x[1 + 2 * pr] >> 9), a2 = unif23(x[2 + 2 * pr] >> 9);
+    const double r = sqrt64(-2.0 * log64(a1));
+    double sn, cs;
+    sincos_2pi(a2, sn, cs);
+    z[2 * pr] = r * cs;
+    z[2 * pr + 1] = r * sn;
+  }
+  for (int d = 0; d < 5; ++d) {
+    y[d] = row[k * 5 + d] + row[160 + k * 5 + d] * z[d];
+    u[d] = rcp64(1.0 + exp64(-y[d]));
+  }
+}
+
+// q(u) in FP64 from the row, the largest component scaled out; arguments
+// below -800 (an exponential of 0) and above 1000 (inf) are clamped, as
+// exp64 takes finite powers of two.
+__device__ __forceinline__ double mix_density_f64(const double* row, int K, const double y[5]) {
   double mx = -1e300;
   for (int k = 0; k < K; ++k) {
-    const double hi = k + 1 < K ? (double)thr[k + 1] : kTwo32;
-    const double pk = (hi - (double)thr[k]) / kTwo32;
-    if (!(pk > 0.0)) { lk[k] = -1e300; continue; }
-    double l = log(pk);
+    double l = row[240 + k];
     for (int d = 0; d < 5; ++d) {
-      const double s = (double)sg[k * 5 + d];
-      const double z = (y[d] - (double)mu[k * 5 + d]) / s;
-      l += -0.5 * z * z - log(s) - kHalfLog2Pi;
+      const double z = (y[d] - row[k * 5 + d]) * row[80 + k * 5 + d];
+      l = fma(-0.5 * z, z, l);
     }
-    lk[k] = l;
     mx = fmax(mx, l);
   }
   double acc = 0.0;
-  for (int k = 0; k < K; ++k) acc += exp(lk[k] - mx);
-  double lq = mx + log(acc);
-  for (int d = 0; d < 5; ++d) lq -= log_u1mu<double>(y[d]);
-  return (double)thr[0] / kTwo32 + exp(lq);
+  for (int k = 0; k < K; ++k) {
+    double l = row[240 + k];
+    for (int d = 0; d < 5; ++d) {
+      const double z = (y[d] - row[k * 5 + d]) * row[80 + k * 5 + d];
+      l = fma(-0.5 * z, z, l);
+    }
+    acc += exp64(fmax(l - mx, -800.0));
+  }
+  double lq = mx + log64(acc);  // acc >= 1
+  // log(u (1 - u)) = -|y| - 2 log(1 + e^-|y|); the five factors lie in [1, 2]
+  double prod = 1.0;
+  for (int d = 0; d < 5; ++d) {
+    const double a = fabs(y[d]);
+    lq += a;
+    prod *= 1.0 + exp64(-fmin(a, 800.0));
+  }
+  lq += 2.0 * log64(prod);
+  return row[256] + exp64(fmin(fmax(lq, -800.0), 1000.0));
 }
-
 
 __device__ __forceinline__ void mix_prepare_f32(const uint32_t* thr, const float* mu, const float* sg, int K,
                                                 float* row, int lane) {

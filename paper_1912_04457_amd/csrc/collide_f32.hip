@@ -1,551 +1,15 @@
-// The FP32 collision kernel.
-#include <algorithm>
-
-#include "collide_device.h"
+// The collision kernel of the CM-angle samplers, FP32 integrand.
+#include "collide_slots.h"
 
 namespace qgbe {
 
-// ---------------------------------------------------------------------------
-// FP32 kernel.  A workgroup owns (cell, channel, a chunk of observed nodes).
-// LDS holds FP64 accumulators for the first `lds_acc` deposit slots of the
-// channel and FP32 f tiles for the first `lds_tiles` slots; slots beyond those
-// deposit with FP64 atomics into the output / read f from global memory.  The
-// accumulators are flushed into the FP64 output once per workgroup.
-// ---------------------------------------------------------------------------
-// Trilinear read from the node quads: the same corners and the same
-// arithmetic as interpolate, in two 16-byte loads.
-template <typename R>
-__device__ __forceinline__ R interpolate_quads(const float4* __restrict__ q4, const Stencil<R>& st, int ox) {
-  typedef float V4 __attribute__((ext_vector_type(4)));
-  typedef __attribute__((address_space(1))) const V4 GlobalV4;
-  const V4 lo = ((GlobalV4*)q4)[st.base];
-  const V4 hi = ((GlobalV4*)q4)[st.base + ox];
-  const R a00 = (R)lo.x + st.wz * ((R)lo.y - (R)lo.x);
-  const R a01 = (R)lo.z + st.wz * ((R)lo.w - (R)lo.z);
-  const R a10 = (R)hi.x + st.wz * ((R)hi.y - (R)hi.x);
-  const R a11 = (R)hi.z + st.wz * ((R)hi.w - (R)hi.z);
-  const R b0 = a00 + st.wy * (a01 - a00);
-  const R b1 = a10 + st.wy * (a11 - a10);
-  return b0 + st.wx * (b1 - b0);
-}
-
-template <bool kAllLds, typename R>
-__device__ __forceinline__ R interp_slot(int k, int n_tiles, const float* tiles, const float4* __restrict__ f32q,
-                                         size_t off, const Stencil<R>& st, int nodes, int ox, int oy) {
-  // an address-space-qualified view keeps the LDS reads ds_read instructions
-  // instead of generic flat loads
-  typedef __attribute__((address_space(3))) const float LdsF32;
-  if (kAllLds || k < n_tiles) return interpolate<R>((LdsF32*)(tiles + k * nodes), st, ox, oy);
-  return interpolate_quads<R>(f32q + off, st, ox);
-}
-
-// The corner values are split in FP64 from the FP32 value and weights (both
-// convert exactly), so the deposits of a sample cancel to FP64 rounding.
-__device__ __forceinline__ Stencil<double> widen(const Stencil<float>& st) {
-  return Stencil<double>{st.base, (double)st.wx, (double)st.wy, (double)st.wz};
-}
-
-template <bool kAllLds, bool kWin = true>
-__device__ __forceinline__ void deposit_slot(int k, int slot_lo, int slot_hi, int n_acc, double* acc,
-                                             double* __restrict__ out, size_t off, const Stencil<float>& st,
-                                             float v, int nodes, int ox, int oy, int win_lo, int win_n) {
-  if (k < slot_lo || k >= slot_hi) return;  // deposited by another launch
-  const int j = k - slot_lo;
-  if (kAllLds || j < n_acc) {
-    if (!kWin || win_n == nodes)  // (wave-uniform) the whole grid in LDS
-      deposit<double, double, __HIP_MEMORY_SCOPE_WORKGROUP>(acc + j * win_n, widen(st), (double)v, ox, oy);
-    else
-      deposit_window(acc + j * win_n, widen(st), (double)v, ox, oy, win_lo, win_n);
-  } else {
-    deposit<double, double>(out + off, widen(st), (double)v, ox, oy);
-  }
-}
-
-// Workgroups are dispatched to the 8 XCDs in turn (workgroup b to XCD b mod
-// 8), and each XCD has its own L2.  The logical index hands each XCD a
-// contiguous range of (cell, channel, chunk) work, so the workgroups that
-// read a cell's f quads and flush into its output rows share one L2.
-__device__ __forceinline__ int xcd_local_block(int b, int n) {
-  constexpr int kXcd = 8;
-  const int q = n / kXcd, r = n % kXcd, x = b % kXcd;
-  return x * q + min(x, r) + b / kXcd;
-}
-
-// Workgroup size: 12 waves, 3 per SIMD (the register budget is then 168
-// VGPRs; the learned variant spills a few to scratch and still runs faster
-// than with 8 waves), for both samplers.
-constexpr int kF32Threads = 768;
-// The compacting variant (below) keeps a sample queue per wave in LDS (52 B
-// per entry) next to the accumulators and reads f from the global node quads.
-constexpr int kQueueWaves = 12;
-constexpr int kQueueLen = 128;  // ring entries per wave (>= 63 pending + 64 new)
-constexpr int f32_block(bool queue) { return queue ? kQueueWaves * 64 : kF32Threads; }
-// Compacting and learned variants: observed nodes go to the waves of a
-// workgroup in blocks of 4 consecutive nodes; a wave stages the direct sums
-// of its block in LDS and adds them to the output with one atomic
-// instruction over one 32-byte sector, instead of one single-lane atomic
-// (counted as a whole sector) per node.  The other variants keep one node
-// per wave in turn and one atomic per node: there the block order cost 5%
-// (the three-slot variant's sample loop compiled to more instructions).
-constexpr int kNodeBlock = 4;
-
-// kQueue (uniform sampler, every deposit slot in LDS, f from the global node
-// quads): each wave first runs the sample geometry for 64 samples, appends
-// the accepted ones (the three 23-bit uniforms of p2, p3 in FP64, s, t, u and
-// the prefactor in FP32) to its ring in LDS, and evaluates |M|^2, f, bracket
-// and deposits 64 queued samples at a time, so that long path runs on full
-// wavefronts.  The deposits of one such batch are issued while the geometry
-// of the next 64 samples runs, a third before, between and after it, so the
-// LDS works off the atomics behind VALU work.  Same arithmetic per sample as
-// the direct loop.
-// kUser: some row of the matrix-element table is replaced by user terms; the
-// variants without them carry no code for the user-term evaluation (which
-// otherwise holds registers across the sample loop: 6% of the 7-species term).
-// kShort: short items.  The (cell, channel) constants are computed once per
-// workgroup, the item's sums reduce through DPP without LDS round trips, and
-// several waves may share a node (A.split).  The learned sampler is always
-// in this form; a long uniform item is not: those constants held across its
-// item loop cost more spilled registers in the sample loop than they save.
-// Short items are bound by latency (three wavefronts per SIMD, an item's
-// constants, sums and partial batch each a serial chain); one gluon cell,
-// collision term: 10^3 nodes x 1000 samples 255 -> 46 us, 16^3 x 2048 547 ->
-// 203 us, 20^3 x 256 98 -> 78 us; 7 species, 30^3 x 128 20.9 -> 19.5 ms.
-template <bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kUser, bool kShort>
-__global__ __launch_bounds__(f32_block(kQueue)) void collide_f32_kernel(CollideArgs A) {
-  static_assert(!kLearned || kShort, "the learned sampler's items are short");
-  static_assert(!kQueue || (kSym && kAllLds && !kLearned), "the queue serves the uniform sampler, slots in LDS");
-  // kAllLds: every f tile and accumulator in LDS (the queue variant: every
-  // accumulator; f from the quads)
-  constexpr bool kTilesLds = kAllLds && !kQueue;
-  constexpr bool kAccLds = kAllLds;
-  extern __shared__ double lds[];
-  __shared__ float mix_rows[kLearned ? kF32Threads / kWave : 1][kLearned ? kMixRow : 1];
-  __shared__ uint32_t q_v[kQueue ? kQueueWaves : 1][3][kQueue ? kQueueLen : 1];  // 23-bit uniforms of p2
-  __shared__ double q_p3[kQueue ? kQueueWaves : 1][3][kQueue ? kQueueLen : 1];
-  __shared__ float q_f[kQueue ? kQueueWaves : 1][4][kQueue ? kQueueLen : 1];    // s, t, u, prefactor
-  __shared__ double mc_wg[2];  // this workgroup's item variances and squared item sums
-  __shared__ unsigned long long ok_wg;  // and its accepted samples
-  constexpr int kNB = kQueue || kLearned ? kNodeBlock : 1;  // nodes per block (as collide_f32_node_block)
-  __shared__ double d_stage[kNB > 1 ? kF32Threads / kWave : 1][kNB];  // direct sums of a wave's current block
-  static_assert(f32_block(kQueue) % (kWave * kNB) == 0, "a multiple of the waves is one of the block");
-  __shared__ double it_sum[3][kShort ? kSplitNodes : 1];  // A.split > 1: S_i, sum v^2 and the gain+loss sum of the chunk's items
-  const Grid& G = A.G;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wid = threadIdx.x / kWave;
-  const int nw = blockDim.x / kWave;
-  const int lb = xcd_local_block(blockIdx.x, gridDim.x);
-  const int chunk = lb % A.n_chunks;
-  // Uniform sampler: the chunks and channels of one cell follow each other
-  // (they share its f quads and output rows in the XCD's L2).  Learned
-  // sampler: blocks of 32 cells (the workgroups one XCD holds at a time),
-  // and within a block the cells of one channel follow each other, so the
-  // channel's proposal rows, shared by all cells, are read from HBM about
-  // once per block instead of once per cell, and the block's f rows serve
-  // every channel.
-  int gi, cell;
-  if (kLearned) {
-    constexpr int kCellBlock = 32;
-    const int u = lb / A.n_chunks;
-    const int per = A.n_group * kCellBlock;
-    const int cb = u / per;
-    const int S = min(kCellBlock, G.cells - cb * kCellBlock);  // the last block may be short
-    const int r = u - cb * per;
-    gi = r / S;
-    cell = cb * kCellBlock + r % S;
-  } else {
-    gi = (lb / A.n_chunks) % A.n_group;
-    cell = lb / (A.n_chunks * A.n_group);
-  }
-  const int ci = A.group[gi];
-  const Channel ch = A.chans[ci];
-  const int nslot = ch.nslot;
-  const int nodes = G.nodes;
-  const int n_acc = kSym ? min(A.slot_hi - A.slot_lo, A.lds_acc) : 0;
-  const int n_tiles = min(nslot, A.lds_tiles);
-  const int win_lo = A.win_lo, win_n = A.win_n;
-  double* acc = lds;                                          // [n_acc][win_n], slots slot_lo..
-  float* tiles = reinterpret_cast<float*>(lds + (size_t)n_acc * win_n);  // [n_tiles][nodes]
-  size_t goff[3];  // offsets of the slots' (species, cell) rows in f32 and A
-  for (int k = 0; k < 3; ++k) {
-    const int sp = k < nslot ? ch.slot_sp[k] : ch.slot_sp[0];
-    goff[k] = ((size_t)sp * G.cells + cell) * nodes;
-  }
-  for (int i = threadIdx.x; i < n_acc * win_n; i += blockDim.x) acc[i] = 0.0;
-  if (threadIdx.x < 2) mc_wg[threadIdx.x] = 0.0;
-  if (threadIdx.x == 0) ok_wg = 0ull;
-  if (kNB > 1 && lane < kNB) d_stage[wid][lane] = 0.0;
-  const int split = kShort ? A.split : 1;
-  if (kShort && split > 1)
-    for (int i = threadIdx.x; i < 3 * kSplitNodes; i += blockDim.x) it_sum[i / kSplitNodes][i % kSplitNodes] = 0.0;
-  for (int k = 0; k < n_tiles; ++k)
-    for (int i = threadIdx.x; i < nodes; i += blockDim.x) tiles[k * nodes + i] = A.f32[goff[k] + i];
-  __syncthreads();
-  const int k2 = ch.pos_slot[0], k3 = ch.pos_slot[1], k4 = ch.pos_slot[2];
-  // row offsets of positions 2, 3, 4 (scalars: no dynamically indexed array in the loop)
-  const size_t off2 = goff[k2], off3 = goff[k3], off4 = goff[k4];
-  const bool g1 = is_gluon(ch.sp[0]), g2 = is_gluon(ch.sp[1]);
-  const bool g3 = is_gluon(ch.sp[2]), g4 = is_gluon(ch.sp[3]);
-  const int first = chunk * A.chunk_items;
-  const int last = min(first + A.chunk_items, nodes);
-  Item pair;
-  if (kShort) item_pair(pair, A, ch, cell);
-  // After the item at node p, the last of its node block (or of the chunk):
-  // the wave adds the block's staged direct sums to the output, the lanes of
-  // one atomic instruction covering consecutive nodes.
-  auto flush_block = [&](int p) {
-    if (kNB == 1 || !A.direct || ((p & (kNB - 1)) != kNB - 1 && p + 1 < last)) return;
-    wave_lds_sync();
-    if (lane < kNB) {
-      const double d = d_stage[wid][lane];
-      if (d != 0.0) atomicAdd(A.A + ((size_t)ch.sp[0] * G.cells + cell) * nodes + (p & ~(kNB - 1)) + lane, d);
-      d_stage[wid][lane] = 0.0;
-    }
-    wave_lds_sync();
-  };
-  // Wave w takes the node blocks w, w + nw, w + 2 nw, ... of the chunk (the
-  // chunk starts on a block boundary), the nodes of a block in turn.  With
-  // few items (A.split > 1) `split` waves share a node, each its part of the
-  // samples, and the groups of waves take the chunk's nodes in turn.
-  const int s_first = split > 1 ? (wid % split) * kWave : 0, s_step = split * kWave;
-  const int n_grp = nw / split;
-  for (int p1_lin = first + (split > 1 ? wid / split : kNB * wid); p1_lin < last;
-       p1_lin += split > 1 ? n_grp : ((p1_lin & (kNB - 1)) == kNB - 1 ? kNB * (nw - 1) + 1 : 1)) {
-    Item it;
-    if (kShort) {
-      it = pair;
-      item_node(it, A, ch, p1_lin);
-    } else {
-      load_item(it, A, ch, cell, p1_lin);
-    }
-    if (!(it.E1 > 0.0)) {  // massless p = 0 node: zero measure
-      if (lane == 0 && A.items && A.direct) A.items[((size_t)cell * A.n_channels + ci) * nodes + p1_lin] = 0.0;
-      if (split == 1) flush_block(p1_lin);
-      continue;
-    }
-    const float f1 = (float)it.f1;
-    const float F1 = g1 ? 1.0f + f1 : 1.0f - f1;
-    double dsum = 0.0, ssum = 0.0, dsq = 0.0;
-    int n_ok = 0;
-    const size_t mrow = (size_t)ci * nodes + p1_lin;
-    const bool mix = kLearned && (!A.mix_on || A.mix_on[ci]);
-    if (mix) {
-      mix_prepare_f32(A.mix_thr + mrow * A.mix_K, A.mix_mu + mrow * A.mix_K * 5, A.mix_sigma + mrow * A.mix_K * 5,
-                      A.mix_K, mix_rows[wid], lane);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    // Queue mode: the deposits of the last evaluated batch, issued while the
-    // next samples' geometry runs.
-    Stencil<float> pd2{}, pd3{}, pd4{};
-    float pdv = 0.0f;
-    bool pending = false;
-    // Integrand, direct sum and deposits of an accepted sample (wnb = value
-    // without the bracket).
-    auto finish = [&](const Geo& g, float wnb) {
-      ++n_ok;
-      const Stencil<float> s2 = make_stencil<float>(g.p2, G);
-      const Stencil<float> s3 = make_stencil<float>(g.p3, G);
-      const Stencil<float> s4 = make_stencil<float>(g.p4, G);
-      const float f2 = interp_slot<kTilesLds, float>(k2, n_tiles, tiles, A.f32q, off2, s2, nodes, G.ox, G.oy);
-      const float f3 = interp_slot<kTilesLds, float>(k3, n_tiles, tiles, A.f32q, off3, s3, nodes, G.ox, G.oy);
-      const float f4 = interp_slot<kTilesLds, float>(k4, n_tiles, tiles, A.f32q, off4, s4, nodes, G.ox, G.oy);
-      const float F2 = g2 ? 1.0f + f2 : 1.0f - f2;
-      const float F3 = g3 ? 1.0f + f3 : 1.0f - f3;
-      const float F4 = g4 ? 1.0f + f4 : 1.0f - f4;
-      const float gain = f3 * f4 * F1 * F2, loss = f1 * f2 * F3 * F4;
-      const float v = wnb * (gain - loss);
-      dsum += (double)v;
-      dsq = fma((double)v, (double)v, dsq);
-      if (kScale) ssum += (double)(fabsf(wnb) * (gain + loss));
-      if (kSym) {
-        if (kQueue) {
-          pd2 = s2; pd3 = s3; pd4 = s4; pdv = v;
-        } else {
-          deposit_slot<kAccLds>(k2, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off2, s2, v,
-                                nodes, G.ox, G.oy, win_lo, win_n);
-          deposit_slot<kAccLds>(k3, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off3, s3, -v,
-                                nodes, G.ox, G.oy, win_lo, win_n);
-          deposit_slot<kAccLds>(k4, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off4, s4, -v,
-                                nodes, G.ox, G.oy, win_lo, win_n);
-        }
-        if (kScale && A.direct) {
-          const float vs = fabsf(wnb) * (gain + loss);
-          deposit<double, double>(A.scale + ((size_t)ch.sp[1] * G.cells + cell) * nodes, widen(s2), (double)vs, G.ox, G.oy);
-          deposit<double, double>(A.scale + ((size_t)ch.sp[2] * G.cells + cell) * nodes, widen(s3), (double)vs, G.ox, G.oy);
-          deposit<double, double>(A.scale + ((size_t)ch.sp[3] * G.cells + cell) * nodes, widen(s4), (double)vs, G.ox, G.oy);
-        }
-      }
-    };
-    auto evaluate = [&](const double u[5], float inv_q) {
-      Geo g;
-      if (!geometry(it, G, u, g)) return;
-      finish(g, weight_no_bracket<float, kUser>(A, it, g, ch.row) * inv_q);
-    };
-    if (kQueue) {
-      // queued record -> the accepted sample's geometry, as geometry() left it
-      auto finish_queued = [&](int slot) {
-        Geo g;
-        const uint32_t v0 = q_v[wid][0][slot], v1 = q_v[wid][1][slot], v2 = q_v[wid][2][slot];
-        const double uu[3] = {unif23(v0), unif23(v1), unif23(v2)};
-        for (int a = 0; a < 3; ++a) {
-          g.p2[a] = fma(2.0 * G.ph[a], uu[a], -G.ph[a]);
-          g.p3[a] = q_p3[wid][a][slot];
-          g.p4[a] = (it.p1[a] + g.p2[a]) - g.p3[a];
-        }
-        const float m = msq_row<float, kUser>(A.msq_mask, A.msq, ch.row, q_f[wid][0][slot], q_f[wid][1][slot],
-                                       q_f[wid][2][slot], (float)it.mu);
-        finish(g, m * q_f[wid][3][slot]);
-      };
-      unsigned head = 0, tail = 0;  // ring positions (wave-uniform)
-      for (int base = s_first; base < A.n_samples; base += s_step) {
-        const int s = base + lane;
-        uint32_t x0 = (uint32_t)s, x1 = (uint32_t)p1_lin, x2 = (uint32_t)cell, x3 = ((uint32_t)ch.code << 8);
-        philox4x32_10(x0, x1, x2, x3, A.key0, A.key1);
-        if (pending) deposit_slot<true, false>(k2, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off2, pd2, pdv,
-                                        nodes, G.ox, G.oy, win_lo, win_n);
-        double u[5];
-        five_uniforms(x0, x1, x2, x3, u);
-        Geo g;
-        const bool ok = s < A.n_samples && geometry(it, G, u, g);
-        if (pending) deposit_slot<true, false>(k3, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off3, pd3, -pdv,
-                                        nodes, G.ox, G.oy, win_lo, win_n);
-        const unsigned long long mask = __ballot(ok);
-        if (ok) {
-          const unsigned slot = (tail + (unsigned)__popcll(mask & ((1ull << lane) - 1ull))) & (kQueueLen - 1);
-          q_v[wid][0][slot] = x0 >> 9;
-          q_v[wid][1][slot] = x1 >> 9;
-          q_v[wid][2][slot] = x2 >> 9;
-          for (int a = 0; a < 3; ++a) q_p3[wid][a][slot] = g.p3[a];
-          q_f[wid][0][slot] = (float)g.s;
-          q_f[wid][1][slot] = (float)g.t;
-          q_f[wid][2][slot] = (float)g.u;
-          q_f[wid][3][slot] = prefactor<float>(it, g);
-        }
-        if (pending) deposit_slot<true, false>(k4, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off4, pd4, -pdv,
-                                        nodes, G.ox, G.oy, win_lo, win_n);
-        pending = false;
-        tail += (unsigned)__popcll(mask);
-        if (tail - head >= (unsigned)kWave) {
-          wave_lds_sync();
-          finish_queued((head + lane) & (kQueueLen - 1));
-          pending = true;
-          head += kWave;
-          wave_lds_sync();
-        }
-      }
-      auto flush = [&]() {
-        deposit_slot<true, false>(k2, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off2, pd2, pdv,
-                           nodes, G.ox, G.oy, win_lo, win_n);
-        deposit_slot<true, false>(k3, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off3, pd3, -pdv,
-                           nodes, G.ox, G.oy, win_lo, win_n);
-        deposit_slot<true, false>(k4, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off4, pd4, -pdv,
-                           nodes, G.ox, G.oy, win_lo, win_n);
-      };
-      if (pending) flush();  // the last full batch
-      // the last, partial batch: only the lanes that hold a sample deposit (zeros
-      // of the idle lanes, all at one address, took 60 us of an 88 us launch of
-      // 7722 items x 100 samples)
-      if (tail != head) {
-        wave_lds_sync();
-        if ((unsigned)lane < tail - head) {
-          finish_queued((head + lane) & (kQueueLen - 1));
-          flush();
-        }
-        wave_lds_sync();
-      }
-      pending = false;
-    } else
-    for (int s = s_first + lane; s < A.n_samples; s += s_step) {
-      uint32_t x0 = (uint32_t)s, x1 = (uint32_t)p1_lin, x2 = (uint32_t)cell, x3 = ((uint32_t)ch.code << 8);
-      philox4x32_10(x0, x1, x2, x3, A.key0, A.key1);
-      double u[5];
-      float inv_q = 1.0f;
-      if (mix) {
-        uint32_t y0 = (uint32_t)s, y1 = (uint32_t)p1_lin, y2 = (uint32_t)cell, y3 = ((uint32_t)ch.code << 8) | 1u;
-        philox4x32_10(y0, y1, y2, y3, A.key0, A.key1);
-        const uint32_t xw[8] = {x0, x1, x2, x3, y0, y1, y2, y3};
-        float yl[5];
-        mix_draw_row(xw, A.mix_thr + mrow * A.mix_K, mix_rows[wid], A.mix_K, u, yl);
-        inv_q = __builtin_amdgcn_rcpf(mix_density_f32(mix_rows[wid], A.mix_K, yl));  // about 1 ulp; q >= alpha
-      } else {
-        five_uniforms(x0, x1, x2, x3, u);
-      }
-      evaluate(u, inv_q);
-    }
-    if (!A.direct) continue;
-    int ok_total;
-    if (kShort) {
-      dsum = wave_sum_dpp(dsum);
-      if (kScale) ssum = wave_sum_dpp(ssum);
-      dsq = wave_sum_dpp(dsq);
-      ok_total = wave_count_dpp(n_ok);
-    } else {
-      dsum = wave_sum(dsum);
-      if (kScale) ssum = wave_sum(ssum);
-      dsq = wave_sum(dsq);
-      ok_total = wave_count(n_ok);
-    }
-    if (kShort && split > 1) {  // this wave's part of the item
-      if (lane == 0) {
-        const int i = p1_lin - first;
-        __hip_atomic_fetch_add(&ok_wg, (unsigned long long)ok_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(&it_sum[0][i], dsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(&it_sum[1][i], dsq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (kScale) __hip_atomic_fetch_add(&it_sum[2][i], ssum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-      continue;
-    }
-    if (lane == 0) {
-      __hip_atomic_fetch_add(&ok_wg, (unsigned long long)ok_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      __hip_atomic_fetch_add(&mc_wg[0], item_variance(dsum, dsq, A.n_samples), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
-      __hip_atomic_fetch_add(&mc_wg[1], dsum * dsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if (kNB > 1)
-        d_stage[wid][p1_lin & (kNB - 1)] = dsum;
-      else
-        atomicAdd(A.A + ((size_t)ch.sp[0] * G.cells + cell) * nodes + p1_lin, dsum);
-      if (kScale) atomicAdd(A.scale + ((size_t)ch.sp[0] * G.cells + cell) * nodes + p1_lin, ssum);
-      if (A.items) A.items[((size_t)cell * A.n_channels + ci) * nodes + p1_lin] = dsum;
-    }
-    flush_block(p1_lin);
-  }
-  __syncthreads();
-  if (kShort && split > 1 && A.direct) {  // the chunk's items from their waves' parts, a node per lane
-    const int i = threadIdx.x, p1_lin = first + i;
-    if (p1_lin < last) {
-      const double dsum = it_sum[0][i];
-      __hip_atomic_fetch_add(&mc_wg[0], item_variance(dsum, it_sum[1][i], A.n_samples), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
-      __hip_atomic_fetch_add(&mc_wg[1], dsum * dsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      const size_t at = ((size_t)ch.sp[0] * G.cells + cell) * nodes + p1_lin;
-      if (dsum != 0.0) atomicAdd(A.A + at, dsum);
-      if (kScale) atomicAdd(A.scale + at, it_sum[2][i]);
-      if (A.items) A.items[((size_t)cell * A.n_channels + ci) * nodes + p1_lin] = dsum;
-    }
-    __syncthreads();
-  }
-  const int stripe = blockIdx.x % kStripes;
-  if (threadIdx.x < 2 && A.mc_acc && A.direct) atomicAdd(&A.mc_acc[2 * stripe + threadIdx.x], mc_wg[threadIdx.x]);
-  if (threadIdx.x == 0 && A.n_accepted && A.direct) atomicAdd(A.n_accepted + stripe, ok_wg);
-  if (threadIdx.x == 0 && A.chan_var && A.direct)  // one channel per workgroup
-    atomicAdd(&A.chan_var[(size_t)stripe * A.n_channels + ci], mc_wg[0]);
-  if (n_acc > 0) {
-    for (int i = threadIdx.x; i < n_acc * win_n; i += blockDim.x) {
-      const double v = acc[i];
-      if (v != 0.0) {
-        const int j = i / win_n;
-        atomicAdd(A.A + goff[A.slot_lo + j] + win_lo + (i - j * win_n), v);
-      }
-    }
-  }
-}
-
-// Uniform sampler: the short-item form when waves share nodes, and below
-// kShortSamples samples per item (at 2048 samples on 256 cells of gluons the
-// compiled long form is 1.8% faster, 65.8 against 67.0 ms; at 128 samples on
-// the 70 channels of a 30^3 cell the short one 3.5%, 20.2 against 19.5 ms).
-constexpr int kShortSamples = 1024;
-bool f32_short(const CollideArgs& a) { return a.split > 1 || a.n_samples < kShortSamples; }
-
-template <bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kShort>
-void launch_f32_user(const CollideArgs& a, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
-  if (a.msq_mask)
-    hipLaunchKernelGGL((collide_f32_kernel<kSym, kScale, kAllLds, kLearned, kQueue, true, kShort>), grid, block, lds, st, a);
-  else
-    hipLaunchKernelGGL((collide_f32_kernel<kSym, kScale, kAllLds, kLearned, kQueue, false, kShort>), grid, block, lds, st, a);
-}
-
-template <bool kSym, bool kScale, bool kLearned, bool kShort>
-void launch_f32_variant(const CollideArgs& a, bool all_lds, bool queue, dim3 grid, dim3 block, size_t lds,
-                        hipStream_t st) {
-  if constexpr (kSym && !kLearned) {
-    if (queue) {
-      launch_f32_user<true, kScale, true, false, true, kShort>(a, grid, block, lds, st);
-      return;
-    }
-  }
-  if (all_lds) launch_f32_user<kSym, kScale, true, kLearned, false, kShort>(a, grid, block, lds, st);
-  else launch_f32_user<kSym, kScale, false, kLearned, false, kShort>(a, grid, block, lds, st);
-}
-
-template <bool kSym, bool kScale>
-void launch_f32_sampler(const CollideArgs& a, bool all_lds, bool queue, dim3 grid, dim3 block, size_t lds,
-                        hipStream_t st) {
-  if (a.learned) launch_f32_variant<kSym, kScale, true, true>(a, all_lds, false, grid, block, lds, st);
-  else if (f32_short(a)) launch_f32_variant<kSym, kScale, false, true>(a, all_lds, queue, grid, block, lds, st);
-  else launch_f32_variant<kSym, kScale, false, false>(a, all_lds, queue, grid, block, lds, st);
-}
-
-int collide_f32_waves(bool queue) { return f32_block(queue) / kWave; }
-int collide_f32_node_block(bool queue, bool learned) { return queue || learned ? kNodeBlock : 1; }
+int collide_waves(bool queue) { return slots_block(queue) / kWave; }
+int collide_node_block(bool queue, bool learned) { return queue || learned ? kNodeBlock : 1; }
 
 hipError_t launch_collide_f32(const CollideArgs& a, int nslot, bool queue, hipStream_t stream) {
-  const int n_acc = a.symmetric ? std::min(a.slot_hi - a.slot_lo, a.lds_acc) : 0;
-  const int n_tiles = std::min(nslot, a.lds_tiles);
-  // every tile and every accumulator of this launch's slots in LDS: the
-  // variant without global-memory paths
-  const bool all_acc = !a.symmetric || n_acc == a.slot_hi - a.slot_lo;
-  const bool all_lds = n_tiles == nslot && all_acc;
-  queue = queue && all_acc && a.symmetric && !a.learned && a.win_n == a.G.nodes;
-  const int threads = f32_block(queue);
-  const size_t lds = (size_t)n_acc * a.win_n * sizeof(double) + (size_t)n_tiles * a.G.nodes * sizeof(float);
-  const long long blocks = (long long)a.G.cells * a.n_group * a.n_chunks;
-  if (blocks <= 0) return hipSuccess;
-  if (a.split < 1 || (threads / kWave) % a.split) return hipErrorInvalidValue;  // whole groups of waves
-  if (a.split > 1 ? a.chunk_items > kSplitNodes : a.chunk_items % kNodeBlock != 0)
-    return hipErrorInvalidValue;  // a shared chunk's sums fit in it_sum; other chunks start on node blocks
-  const dim3 grid((unsigned)blocks), block(threads);
-  if (a.symmetric) {
-    if (a.scale) launch_f32_sampler<true, true>(a, all_lds, queue, grid, block, lds, stream);
-    else launch_f32_sampler<true, false>(a, all_lds, queue, grid, block, lds, stream);
-  } else {
-    if (a.scale) launch_f32_sampler<false, true>(a, all_lds, false, grid, block, lds, stream);
-    else launch_f32_sampler<false, false>(a, all_lds, false, grid, block, lds, stream);
-  }
-  return hipGetLastError();
+  return launch_slots<float>(a, nslot, queue, stream);
 }
 
-hipError_t set_collide_lds_limit(size_t lds_max, size_t* budget_plain, size_t* budget_learned, size_t* budget_queue) {
-  // Each FP32 variant may use what its static LDS leaves of lds_max.  Raising
-  // the per-kernel dynamic limit is only needed (and only accepted) above the
-  // runtime's default; after a refusal the budget is the limit in force.
-  // Groups: 0 uniform sampler, 1 learned sampler, 2 the compacting variant.
-  struct Fn { const void* fn; int group; };
-#define QGBE_F32_PAIR(S, Sc, L, Le, Q, Sh, G)                          \
-  {(const void*)collide_f32_kernel<S, Sc, L, Le, Q, false, Sh>, G},    \
-      {(const void*)collide_f32_kernel<S, Sc, L, Le, Q, true, Sh>, G}
-#define QGBE_F32_SYM(L, Le, Q, Sh, G)                                               \
-  QGBE_F32_PAIR(true, true, L, Le, Q, Sh, G), QGBE_F32_PAIR(true, false, L, Le, Q, Sh, G)
-#define QGBE_F32_ALL(L, Le, Sh, G)                                                   \
-  QGBE_F32_SYM(L, Le, false, Sh, G), QGBE_F32_PAIR(false, true, L, Le, false, Sh, G), \
-      QGBE_F32_PAIR(false, false, L, Le, false, Sh, G)
-  const Fn fns[] = {
-      QGBE_F32_ALL(true, false, false, 0), QGBE_F32_ALL(false, false, false, 0), QGBE_F32_ALL(true, false, true, 0),
-      QGBE_F32_ALL(false, false, true, 0), QGBE_F32_ALL(true, true, true, 1),    QGBE_F32_ALL(false, true, true, 1),
-      QGBE_F32_SYM(true, false, true, false, 2), QGBE_F32_SYM(true, false, true, true, 2)};
-#undef QGBE_F32_ALL
-#undef QGBE_F32_SYM
-#undef QGBE_F32_PAIR
-  size_t budget[3] = {lds_max, lds_max, lds_max};
-  for (const Fn& f : fns) {
-    hipFuncAttributes attr;
-    if (hipFuncGetAttributes(&attr, f.fn) != hipSuccess) return hipGetLastError();
-    const size_t stat = attr.sharedSizeBytes;
-    size_t want = lds_max > stat ? lds_max - stat : 0;
-    size_t have = attr.maxDynamicSharedSizeBytes > 0 ? (size_t)attr.maxDynamicSharedSizeBytes : 0;
-    if (have < want) {
-      if (hipFuncSetAttribute(f.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)want) == hipSuccess)
-        have = want;
-      else
-        (void)hipGetLastError();
-    }
-    budget[f.group] = std::min(budget[f.group], std::min(have, want));
-  }
-  *budget_plain = budget[0];
-  *budget_learned = budget[1];
-  *budget_queue = budget[2];
-  return hipSuccess;
-}
+hipError_t collide_f32_lds_limit(size_t lds_max, LdsBudget* out) { return slots_lds_limit<float>(lds_max, out); }
 
 }  // namespace qgbe

@@ -23,12 +23,12 @@ qgbe_status hip_fail(hipError_t e, const char* what);
     if (_e != hipSuccess) return ::qgbe::hip_fail(_e, what); \
   } while (0)
 
-// Channels of the FP32 kernel grouped by their number of deposit slots.
+// Channels grouped by their number of deposit slots.
 struct Group {
   int start, count;   // range in the group index array
   int nslot;          // distinct species at positions 2..4
   int lds_acc[2];     // FP64 accumulators staged in LDS  [uniform, learned sampler]
-  int lds_tiles[2];   // FP32 f tiles staged in LDS       [uniform, learned sampler]
+  int lds_tiles[2];   // FP32 f tiles staged in LDS       [uniform, learned sampler]; none in FP64
   int win[2];         // nodes per accumulator window (= nodes unless one slot's FP64
                       // accumulators exceed LDS; then one launch per window and slot)
   bool queue;         // the uniform sampler's compacting variant fits
@@ -59,7 +59,7 @@ struct qgbe_ctx {
   std::vector<qgbe::Group> groups;
   qgbe::Channel* d_chans = nullptr;
   int* d_groups = nullptr;
-  int* d_all = nullptr;            // identity channel list (FP64 kernel)
+  int* d_all = nullptr;            // identity channel list (root kernel)
   double* d_f = nullptr;
   double* d_f_next = nullptr;
   float* d_f32 = nullptr;
@@ -94,8 +94,7 @@ struct qgbe_ctx {
   qgbe::MlpState mlp;
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   size_t ws = 0;
-  size_t lds_budget[2] = {0, 0};   // dynamic LDS per workgroup [uniform, learned sampler]
-  size_t lds_budget_queue = 0;     // dynamic LDS of the compacting uniform-sampler variant
+  qgbe::LdsBudget lds;             // dynamic LDS per workgroup of the context's precision
   int n_cu = 256;                  // compute units of the device
 };
 
@@ -103,7 +102,7 @@ namespace qgbe {
 
 size_t field_len(const qgbe_ctx* c);
 // Descriptor checks (QGBE_EINVAL with a message), the grid it describes, and
-// the LDS plan of the FP32 channel groups (needs c->G, c->d, c->chans and the
+// the LDS plan of the channel groups (needs c->G, c->d, c->chans and the
 // LDS budgets).
 qgbe_status validate(const qgbe_grid_desc* d);
 void make_grid(const qgbe_grid_desc* d, Grid& G);

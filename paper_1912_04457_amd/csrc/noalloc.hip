@@ -26,7 +26,7 @@ __device__ __align__(256) unsigned char scratch[kScratchBytes];
 struct DeviceState {
   bool ready = false;
   unsigned char* ptr = nullptr;   // this device's copy of scratch
-  size_t lds[3] = {0, 0, 0};      // dynamic LDS budgets of the FP32 kernels
+  LdsBudget lds[2];               // dynamic LDS budgets [QGBE_FP64, QGBE_FP32]
   int n_cu = 256;
   // what the channel-table region holds (host copy of the last upload)
   std::vector<unsigned char> table;
@@ -46,8 +46,8 @@ qgbe_status setup(int device, DeviceState** out) {
     HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)), "scratch address");
     int lds_max = 0;
     HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, device), "query LDS size");
-    HIP_TRY(set_collide_lds_limit((size_t)std::max(lds_max, 0), &s.lds[0], &s.lds[1], &s.lds[2]),
-            "raise the dynamic LDS limit");
+    HIP_TRY(collide_f64_lds_limit((size_t)std::max(lds_max, 0), &s.lds[QGBE_FP64]), "raise the dynamic LDS limit");
+    HIP_TRY(collide_f32_lds_limit((size_t)std::max(lds_max, 0), &s.lds[QGBE_FP32]), "raise the dynamic LDS limit");
     int n_cu = 0;
     if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && n_cu > 0)
       s.n_cu = n_cu;
@@ -102,9 +102,7 @@ qgbe_status qgbe_collision_term_noalloc(const qgbe_grid_desc* desc, const double
   c.chans.resize(kMaxChannels);
   c.nch = build_channels(desc->species_mask, desc->row_mask, c.chans.data(), kMaxChannels);
   c.chans.resize(c.nch);
-  c.lds_budget[0] = dev->lds[0];
-  c.lds_budget[1] = dev->lds[1];
-  c.lds_budget_queue = dev->lds[2];
+  c.lds = dev->lds[desc->precision];
   c.n_cu = dev->n_cu;
   c.step = step;
   plan_groups(&c);

@@ -325,3 +325,21 @@ def test_waves_share_nodes_fp32(O, n_x, n_p, mask, N):
     assert st2.n_accepted == st.n_accepted == r["st"].n_accepted
     if np.isfinite(st.mc_err_est):
         assert st2.mc_err_est == pytest.approx(st.mc_err_est, rel=1e-2)
+
+
+@pytest.mark.parametrize("n_x,n_p,mask,N", [((1, 1, 1), (28, 29, 28), 1 << 6, 3), ((1, 1, 1), (20, 20, 20), 0x7F, 2),
+                                            ((2, 1, 1), (15, 16, 14), 0x49, 40), ((1, 1, 1), (9, 8, 7), 1 << 6, 1025)],
+                         ids=["windows", "slot_passes", "plain_and_queue", "shared_nodes"])
+def test_lds_plans_fp64(O, n_x, n_p, mask, N):
+    """The FP64 kernel's LDS plans: one slot over two node windows, three slots
+    over two launches, groups with and without the compacting variant, and
+    waves that share a node."""
+    _case(f"fp64 plans {n_x} {n_p} mask={mask:#x} N={N}")
+    wl = W.Workload("plans", n_x, n_p, (3.0, 3.0, 3.0), (2.0, 2.5, 1.5), mask, N, "f64", 1, 0.01)
+    f = W.random_f(26, wl.cells, wl.nodes, species_mask=mask)
+    r = _run_pair(O, wl, f, N, qgbe.FP64, step=2)
+    _compare(r["A"], r["A_ref"], r["S_ref"], TOL[qgbe.FP64], "A")
+    scale_items = np.abs(r["I_ref"]).max()
+    assert np.allclose(r["I"], r["I_ref"], rtol=TOL[qgbe.FP64], atol=TOL[qgbe.FP64] * scale_items)
+    for cell in range(wl.cells):
+        assert abs(r["A"][:, cell].sum()) <= 1e-13 * r["S_ref"][:, cell].sum()
