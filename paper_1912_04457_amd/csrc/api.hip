@@ -137,7 +137,7 @@ void plan_groups(qgbe_ctx* c) {
   c->group_index.clear();
   c->groups.clear();
   for (int nslot = 1; nslot <= 3; ++nslot) {
-    Group g{(int)c->group_index.size(), 0, nslot, {0, 0}, {0, 0}, {c->G.nodes, c->G.nodes}, false};
+    Group g{(int)c->group_index.size(), 0, nslot, {0, 0}, {0, 0}, {c->G.nodes, c->G.nodes}, {false, false}};
     for (int l = 0; l < 2; ++l) {
       const size_t budget = l ? c->lds.learned : c->lds.plain;
       if (c->d.symmetric && budget < acc_b) {
@@ -154,14 +154,15 @@ void plan_groups(qgbe_ctx* c) {
       g.lds_acc[l] = c->d.symmetric ? (int)std::min<size_t>(nslot, budget / acc_b) : 0;
       g.lds_tiles[l] = f32 ? (int)std::min<size_t>(nslot, (budget - g.lds_acc[l] * acc_b) / tile_b) : 0;
     }
-    g.queue = c->d.symmetric && g.lds_acc[0] == nslot && nslot * acc_b <= c->lds.queue;
+    for (int i = 0; i < 2; ++i)
+      g.queue[i] = c->d.symmetric && g.lds_acc[0] == nslot && g.win[0] == c->G.nodes && nslot * acc_b <= c->lds.queue[i];
     for (int i = 0; i < c->nch; ++i)
       if (c->chans[i].nslot == nslot) c->group_index.push_back(i);
     g.count = (int)c->group_index.size() - g.start;
     if (g.count) {
       c->groups.push_back(g);
       for (int l = 0; l < 2; ++l) c->need_quads[l] = f32 && (c->need_quads[l] || g.lds_tiles[l] < nslot);
-      c->need_quads[0] = f32 && (c->need_quads[0] || g.queue);
+      c->need_quads[0] = f32 && (c->need_quads[0] || g.queue[0] || g.queue[1]);
     }
   }
 }
@@ -169,11 +170,12 @@ void plan_groups(qgbe_ctx* c) {
 struct Chunking {
   int chunk;  // observed nodes per workgroup
   int split;  // waves that share a node
+  int block;  // nodes a wave takes at a time
 };
 
 // Observed nodes per workgroup.
 Chunking plan_chunks(const qgbe_ctx* c, const Group& g, int l, int n_samples, bool queue, bool learned) {
-  const int waves = collide_waves(queue), nb = collide_node_block(queue, learned);
+  const int waves = collide_waves(queue);
   const long long nodes = c->G.nodes, pairs = (long long)c->G.cells * g.count;
   if (pairs >= c->n_cu) {
     // Enough (cell, channel) pairs to give every compute unit one: the nodes
@@ -187,17 +189,21 @@ Chunking plan_chunks(const qgbe_ctx* c, const Group& g, int l, int n_samples, bo
     // 0.5% (compute units that ran two long ones).
     const long long per_pair = std::max(1LL, 2LL * c->n_cu / pairs);
     long long chunk = std::max<long long>(waves, (nodes + per_pair - 1) / per_pair);
+    int nb = collide_node_block(queue);
+    if (collide_short(c->d.precision, learned, 1, n_samples))  // the largest block that leaves every wave 4 turns
+      for (nb = kMaxNodeBlock; nb > 1 && chunk < 4LL * waves * nb; nb /= 2) {}
     const int unit = chunk < 16LL * waves * nb ? waves * nb : waves;
     chunk = (chunk + unit - 1) / unit * unit;
     chunk = std::min(chunk, (nodes + unit - 1) / unit * unit);
-    return {(int)chunk, 1};
+    return {(int)chunk, 1, nb};
   }
   // Fewer pairs than compute units.  A workgroup has its compute unit to
   // itself (LDS and registers), so their number is chosen near a multiple of
   // the compute units (up to eight rounds), and with few nodes per workgroup
   // several waves share a node.  The estimate, in sample iterations of a lone
-  // wave (1.7 us): turns of the waves times (iterations per node plus one for
-  // the node's constants, sums and partly filled batches), a turn 1.3 or 1.75
+  // wave (1.7 us): turns of the waves times (iterations per node plus 0.4
+  // for its sums and partly filled batches, plus 0.8 per block of nodes for
+  // their constants), a turn 1.3 or 1.75
   // times as long with two or three waves at work on a SIMD, plus the
   // workgroup's start and the accumulators it zeroes and flushes (450 take
   // about an iteration), in every round; nodes differ in how many samples
@@ -205,29 +211,33 @@ Chunking plan_chunks(const qgbe_ctx* c, const Group& g, int l, int n_samples, bo
   // 512 samples: 167 workgroups without sharing 156 us, 256 with it 120.)
   const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
   const auto turn = [](long long active) { return active <= 0 ? 0.0 : active <= 4 ? 1.0 : active <= 8 ? 1.3 : 1.75; };
-  Chunking best{0, 1};
+  Chunking best{0, 1, 1};
   double least = 0.0;
   for (int rounds = 1; rounds <= 8; ++rounds) {
     const long long want = std::max(1LL, rounds * c->n_cu / pairs);
     const long long even = (nodes + want - 1) / want;
     for (int split = 1; split <= waves; ++split) {
       if (waves % split) continue;
-      const long long unit = split > 1 ? 1 : nb;       // one wave per node: whole node blocks
-      const long long group = unit * (waves / split);  // nodes the workgroup takes at a time
-      for (const long long step : {unit, group}) {
-        const long long chunk = std::min((even + step - 1) / step * step, (nodes + unit - 1) / unit * unit);
-        if (split > 1 && chunk > kSplitNodes) continue;
-        const long long iters = (n_samples + 64LL * split - 1) / (64LL * split) + 1;
-        const long long units = (chunk + unit - 1) / unit, per_turn = waves / split;
-        const double busy = (double)(unit * iters) * ((double)(units / per_turn) * turn(per_turn * split) +
+      const bool is_short = collide_short(c->d.precision, learned, split, n_samples);
+      for (long long unit = is_short ? kMaxNodeBlock : collide_node_block(queue); unit >= 1; unit /= 2) {
+        const long long group = unit * (waves / split);  // nodes the workgroup takes at a time
+        for (const long long step : {is_short ? 1LL : unit, group}) {
+          const long long chunk = std::min((even + step - 1) / step * step,
+                                           is_short ? nodes : (nodes + unit - 1) / unit * unit);
+          if (split > 1 && chunk > kSplitNodes) continue;
+          const double iters = (double)((n_samples + 64LL * split - 1) / (64LL * split)) + 0.4 + 0.8 / (double)unit;
+          const long long units = (chunk + unit - 1) / unit, per_turn = waves / split;
+          const double busy = (double)unit * iters * ((double)(units / per_turn) * turn(per_turn * split) +
                                                       turn(units % per_turn * split));
-        const long long wgs = pairs * ((nodes + chunk - 1) / chunk);
-        const double r = (double)((wgs + c->n_cu - 1) / c->n_cu);
-        const double cost = r * (busy * (1.0 + 0.1 / r) + 3.0 + (double)acc / 450.0);
-        if (!best.chunk || cost < least) {
-          best = {(int)chunk, split};
-          least = cost;
+          const long long wgs = pairs * ((nodes + chunk - 1) / chunk);
+          const double r = (double)((wgs + c->n_cu - 1) / c->n_cu);
+          const double cost = r * (busy * (1.0 + 0.1 / r) + 3.0 + (double)acc / 450.0);
+          if (!best.chunk || cost < least) {
+            best = {(int)chunk, split, (int)unit};
+            least = cost;
+          }
         }
+        if (!is_short) break;
       }
     }
   }
@@ -263,9 +273,12 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
     a.group = c->d_groups + g.start;
     a.n_group = g.count;
     // the compacting variant when the whole group fits in LDS next to its queues
-    const bool queue = !learned && g.queue;
+    const bool is_short = collide_short(c->d.precision, learned, 1, n_samples);
+    bool queue = !learned && g.queue[is_short];
     const Chunking ck = plan_chunks(c, g, l, n_samples, queue, learned);
+    if (!is_short && ck.split > 1) queue = queue && g.queue[1];  // waves that share nodes take the short form
     a.split = ck.split;
+    a.node_block = ck.block;
     const int chunk = ck.chunk;
     a.chunk_items = chunk;
     a.n_chunks = (c->G.nodes + chunk - 1) / chunk;

@@ -15,6 +15,8 @@ constexpr int kMixKF32 = 8;
 
 // Most observed nodes of a workgroup whose waves share nodes (split > 1).
 constexpr int kSplitNodes = 64;
+// Most consecutive nodes a wave takes at a time.
+constexpr int kMaxNodeBlock = 8;
 
 struct CollideArgs {
   Grid G;
@@ -26,6 +28,7 @@ struct CollideArgs {
   int chunk_items;        // observed nodes per workgroup
   int split;              // waves that share a node, each a part of its samples: divides
                           // the workgroup's waves; > 1 only with chunk_items <= kSplitNodes
+  int node_block;         // consecutive nodes a wave takes at a time in the short-item form
   int lds_tiles;          // f tiles staged in LDS
   int lds_acc;            // FP64 deposit accumulators in LDS
   int slot_lo, slot_hi;   // deposit slots [lo, hi) written by this launch; the
@@ -60,7 +63,8 @@ struct CollideArgs {
 
 // Dynamic LDS of one precision's kernel variants.
 struct LdsBudget {
-  size_t plain = 0, learned = 0, queue = 0;  // uniform sampler, learned sampler, the compacting variant
+  size_t plain = 0, learned = 0;  // uniform sampler, learned sampler
+  size_t queue[2] = {0, 0};       // the compacting variant for long and short items
 };
 
 // The paper's root parameterisation (FP64; alt: the alternative elimination).
@@ -75,9 +79,11 @@ hipError_t collide_f32_lds_limit(size_t lds_max, LdsBudget* out);
 hipError_t collide_f64_lds_limit(size_t lds_max, LdsBudget* out);
 // Waves per workgroup of the kernel (chunks are multiples of it).
 int collide_waves(bool queue);
-// Consecutive observed nodes a wave of the kernel takes at a time (chunks
-// must be multiples of it; multiples of the waves are).
-int collide_node_block(bool queue, bool learned);
+// Consecutive observed nodes a wave of the long-item form takes at a time
+// (its chunks must be multiples of it; multiples of the waves are).
+int collide_node_block(bool queue);
+// Whether a launch takes the short-item form.
+bool collide_short(int precision, bool learned, int split, int n_samples);
 hipError_t launch_record(const CollideArgs& a, int n_per_item, long long item_stride, long long n_sel, float* rows,
                          hipStream_t stream);
 

@@ -1,10 +1,14 @@
 // The collision kernel of the CM-angle samplers, FP32 integrand.
 #include "collide_slots.h"
+#include "qgbe.h"
 
 namespace qgbe {
 
 int collide_waves(bool queue) { return slots_block(queue) / kWave; }
-int collide_node_block(bool queue, bool learned) { return queue || learned ? kNodeBlock : 1; }
+int collide_node_block(bool queue) { return queue ? kNodeBlock : 1; }
+bool collide_short(int precision, bool learned, int split, int n_samples) {
+  return precision == QGBE_FP64 || learned || short_items(split, n_samples);
+}
 
 hipError_t launch_collide_f32(const CollideArgs& a, int nslot, bool queue, hipStream_t stream) {
   return launch_slots<float>(a, nslot, queue, stream);

@@ -111,13 +111,13 @@ constexpr int kSlotThreads = 768;
 constexpr int kQueueWaves = 12;
 constexpr int kQueueLen = 128;  // ring entries per wave (>= 63 pending + 64 new)
 constexpr int slots_block(bool queue) { return queue ? kQueueWaves * 64 : kSlotThreads; }
-// Compacting and learned variants: observed nodes go to the waves of a
+// Long items, compacting variant: observed nodes go to the waves of a
 // workgroup in blocks of 4 consecutive nodes; a wave stages the direct sums
 // of its block in LDS and adds them to the output with one atomic
 // instruction over one 32-byte sector, instead of one single-lane atomic
-// (counted as a whole sector) per node.  The other variants keep one node
-// per wave in turn and one atomic per node: there the block order cost 5%
-// (the three-slot variant's sample loop compiled to more instructions).
+// (counted as a whole sector) per node.  The plain long variants keep one
+// node per wave in turn and one atomic per node: there the block order cost
+// 5% (the three-slot variant's sample loop compiled to more instructions).
 constexpr int kNodeBlock = 4;
 
 // kQueue (uniform sampler, every deposit slot in LDS, f from the global node
@@ -132,15 +132,17 @@ constexpr int kNodeBlock = 4;
 // kUser: some row of the matrix-element table is replaced by user terms; the
 // variants without them carry no code for the user-term evaluation (which
 // otherwise holds registers across the sample loop: 6% of the 7-species term).
-// kShort: short items.  The (cell, channel) constants are computed once per
-// workgroup, the item's sums reduce through DPP without LDS round trips, and
-// several waves may share a node (A.split).  The learned sampler is always
-// in this form; a long uniform item is not: those constants held across its
-// item loop cost more spilled registers in the sample loop than they save.
-// Short items are bound by latency (three wavefronts per SIMD, an item's
-// constants, sums and partial batch each a serial chain); one gluon cell,
+// kShort: short items, bound by the latency of an item's serial parts (three
+// wavefronts per SIMD): its constants, its sums, its partly filled batches.
+// The (cell, channel) constants are computed once per workgroup; a wave takes
+// A.node_block consecutive nodes at a time, computes their constants side by
+// side, a node per lane, and keeps them and the nodes' sums in LDS, so that
+// the variances and outputs of the block are side by side too; and several
+// waves may share a node (A.split).  The learned sampler is always in this
+// form; a long uniform item is not: what it holds across its item loop costs
+// more spilled registers in the sample loop than it saves.  One gluon cell,
 // collision term: 10^3 nodes x 1000 samples 255 -> 46 us, 16^3 x 2048 547 ->
-// 203 us, 20^3 x 256 98 -> 78 us; 7 species, 30^3 x 128 20.9 -> 19.5 ms.
+// 190 us, 20^3 x 256 98 -> 78 us; 7 species, 30^3 x 128 20.9 -> 19.5 ms.
 template <typename R, bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kUser, bool kShort>
 __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(CollideArgs A) {
   constexpr bool kF64 = std::is_same<R, double>::value;
@@ -157,9 +159,12 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   __shared__ R q_f[kQueue ? kQueueWaves : 1][4][kQueue ? kQueueLen : 1];    // s, t, u, prefactor
   __shared__ double mc_wg[2];  // this workgroup's item variances and squared item sums
   __shared__ unsigned long long ok_wg;  // and its accepted samples
-  constexpr int kNB = kQueue || kLearned ? kNodeBlock : 1;  // nodes per block (as collide_node_block)
+  constexpr int kNB = kQueue && !kShort ? kNodeBlock : 1;  // nodes per block (as collide_node_block)
   __shared__ double d_stage[kNB > 1 ? kSlotThreads / kWave : 1][kNB];  // direct sums of a wave's current block
   static_assert(slots_block(kQueue) % (kWave * kNB) == 0, "a multiple of the waves is one of the block");
+  // kShort: constants (p1, E1, f1, prefactor) of a wave's current nodes; a node that is done holds its sums (S_i,
+  // sum v^2, gain + loss) in the last three
+  __shared__ double node_tab[kShort ? kSlotThreads / kWave : 1][6][kShort ? kMaxNodeBlock : 1];
   __shared__ double it_sum[3][kShort ? kSplitNodes : 1];  // A.split > 1: S_i, sum v^2 and the gain+loss sum of the chunk's items
   const Grid& G = A.G;
   const int lane = threadIdx.x & (kWave - 1);
@@ -234,30 +239,36 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
     }
     wave_lds_sync();
   };
-  // Wave w takes the node blocks w, w + nw, w + 2 nw, ... of the chunk (the
-  // chunk starts on a block boundary), the nodes of a block in turn.  With
-  // few items (A.split > 1) `split` waves share a node, each its part of the
-  // samples, and the groups of waves take the chunk's nodes in turn.
+  int n_ok = 0;  // accepted samples: of the item, kShort of the wave
   const int s_first = split > 1 ? (wid % split) * kWave : 0, s_step = split * kWave;
-  const int n_grp = nw / split;
-  for (int p1_lin = first + (split > 1 ? wid / split : kNB * wid); p1_lin < last;
-       p1_lin += split > 1 ? n_grp : ((p1_lin & (kNB - 1)) == kNB - 1 ? kNB * (nw - 1) + 1 : 1)) {
+  const size_t row1 = ((size_t)ch.sp[0] * G.cells + cell) * nodes;  // the observed species' output row
+  // The samples of the observed node p1_lin; kShort: the j-th of the wave's
+  // block, its constants in node_tab, where it leaves its sums.
+  auto run_node = [&](const int p1_lin, const int j) __attribute__((always_inline)) {
     Item it;
     if (kShort) {
       it = pair;
-      item_node(it, A, ch, p1_lin);
+      it.p1_lin = p1_lin;
+      for (int a = 0; a < 3; ++a) it.p1[a] = node_tab[wid][a][j];
+      it.E1 = node_tab[wid][3][j];
+      it.f1 = node_tab[wid][4][j];
+      it.pref = node_tab[wid][5][j];
     } else {
       load_item(it, A, ch, cell, p1_lin);
     }
     if (!(it.E1 > 0.0)) {  // massless p = 0 node: zero measure
+      if (kShort) {
+        if (lane < 3) node_tab[wid][3 + lane][j] = 0.0;
+        return;
+      }
       if (lane == 0 && A.items && A.direct) A.items[((size_t)cell * A.n_channels + ci) * nodes + p1_lin] = 0.0;
-      if (split == 1) flush_block(p1_lin);
-      continue;
+      flush_block(p1_lin);
+      return;
     }
     const R f1 = (R)it.f1;
     const R F1 = g1 ? R(1) + f1 : R(1) - f1;
     double dsum = 0.0, ssum = 0.0, dsq = 0.0;
-    int n_ok = 0;
+    if (!kShort) n_ok = 0;
     const size_t mrow = (size_t)ci * nodes + p1_lin;
     const bool mix = kLearned && (!A.mix_on || A.mix_on[ci]);
     if (mix) {
@@ -419,29 +430,22 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       }
       evaluate(u, inv_q);
     }
-    if (!A.direct) continue;
-    int ok_total;
+    if (!A.direct) return;
     if (kShort) {
       dsum = wave_sum_dpp(dsum);
       if (kScale) ssum = wave_sum_dpp(ssum);
       dsq = wave_sum_dpp(dsq);
-      ok_total = wave_count_dpp(n_ok);
-    } else {
-      dsum = wave_sum(dsum);
-      if (kScale) ssum = wave_sum(ssum);
-      dsq = wave_sum(dsq);
-      ok_total = wave_count(n_ok);
-    }
-    if (kShort && split > 1) {  // this wave's part of the item
       if (lane == 0) {
-        const int i = p1_lin - first;
-        __hip_atomic_fetch_add(&ok_wg, (unsigned long long)ok_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(&it_sum[0][i], dsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(&it_sum[1][i], dsq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (kScale) __hip_atomic_fetch_add(&it_sum[2][i], ssum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        node_tab[wid][3][j] = dsum;
+        node_tab[wid][4][j] = dsq;
+        if (kScale) node_tab[wid][5][j] = ssum;
       }
-      continue;
+      return;
     }
+    dsum = wave_sum(dsum);
+    if (kScale) ssum = wave_sum(ssum);
+    dsq = wave_sum(dsq);
+    const int ok_total = wave_count(n_ok);
     if (lane == 0) {
       __hip_atomic_fetch_add(&ok_wg, (unsigned long long)ok_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       __hip_atomic_fetch_add(&mc_wg[0], item_variance(dsum, dsq, A.n_samples), __ATOMIC_RELAXED,
@@ -450,25 +454,64 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       if (kNB > 1)
         d_stage[wid][p1_lin & (kNB - 1)] = dsum;
       else
-        atomicAdd(A.A + ((size_t)ch.sp[0] * G.cells + cell) * nodes + p1_lin, dsum);
-      if (kScale) atomicAdd(A.scale + ((size_t)ch.sp[0] * G.cells + cell) * nodes + p1_lin, ssum);
+        atomicAdd(A.A + row1 + p1_lin, dsum);
+      if (kScale) atomicAdd(A.scale + row1 + p1_lin, ssum);
       if (A.items) A.items[((size_t)cell * A.n_channels + ci) * nodes + p1_lin] = dsum;
     }
     flush_block(p1_lin);
+  };
+  // An item's sums into the outputs and the workgroup's totals.
+  auto finish_item = [&](int p1_lin, double dsum, double dsq, double ssum) {
+    __hip_atomic_fetch_add(&mc_wg[0], item_variance(dsum, dsq, A.n_samples), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add(&mc_wg[1], dsum * dsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (dsum != 0.0) atomicAdd(A.A + row1 + p1_lin, dsum);
+    if (kScale) atomicAdd(A.scale + row1 + p1_lin, ssum);
+    if (A.items) A.items[((size_t)cell * A.n_channels + ci) * nodes + p1_lin] = dsum;
+  };
+  if (kShort) {
+    // The groups of `split` waves take blocks of node_block nodes in turn; the
+    // waves of a group share the samples of each node.
+    const int nb = A.node_block;
+    for (int u0 = first + nb * (wid / split); u0 < last; u0 += nb * (nw / split)) {
+      const int cnt = min(nb, last - u0);
+      if (lane < cnt) {
+        Item t = pair;
+        item_node(t, A, ch, u0 + lane);
+        for (int a = 0; a < 3; ++a) node_tab[wid][a][lane] = t.p1[a];
+        node_tab[wid][3][lane] = t.E1;
+        node_tab[wid][4][lane] = t.f1;
+        node_tab[wid][5][lane] = t.pref;
+      }
+      wave_lds_sync();
+      for (int j = 0; j < cnt; ++j) run_node(u0 + j, j);
+      wave_lds_sync();
+      if (A.direct && lane < cnt) {
+        const double dsum = node_tab[wid][3][lane], dsq = node_tab[wid][4][lane];
+        const double ssum = kScale ? node_tab[wid][5][lane] : 0.0;
+        if (split == 1) {
+          finish_item(u0 + lane, dsum, dsq, ssum);
+        } else {  // this wave's part of the items
+          const int i = u0 + lane - first;
+          __hip_atomic_fetch_add(&it_sum[0][i], dsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_add(&it_sum[1][i], dsq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (kScale) __hip_atomic_fetch_add(&it_sum[2][i], ssum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+      }
+      wave_lds_sync();
+    }
+    n_ok = wave_count_dpp(n_ok);
+    if (lane == 0)
+      __hip_atomic_fetch_add(&ok_wg, (unsigned long long)n_ok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  } else {
+    // Wave w takes the node blocks w, w + nw, w + 2 nw, ... of the chunk (the
+    // chunk starts on a block boundary), the nodes of a block in turn.
+    for (int p = first + kNB * wid; p < last; p += (p & (kNB - 1)) == kNB - 1 ? kNB * (nw - 1) + 1 : 1) run_node(p, 0);
   }
   __syncthreads();
   if (kShort && split > 1 && A.direct) {  // the chunk's items from their waves' parts, a node per lane
-    const int i = threadIdx.x, p1_lin = first + i;
-    if (p1_lin < last) {
-      const double dsum = it_sum[0][i];
-      __hip_atomic_fetch_add(&mc_wg[0], item_variance(dsum, it_sum[1][i], A.n_samples), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
-      __hip_atomic_fetch_add(&mc_wg[1], dsum * dsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      const size_t at = ((size_t)ch.sp[0] * G.cells + cell) * nodes + p1_lin;
-      if (dsum != 0.0) atomicAdd(A.A + at, dsum);
-      if (kScale) atomicAdd(A.scale + at, it_sum[2][i]);
-      if (A.items) A.items[((size_t)cell * A.n_channels + ci) * nodes + p1_lin] = dsum;
-    }
+    const int i = threadIdx.x;
+    if (first + i < last) finish_item(first + i, it_sum[0][i], it_sum[1][i], it_sum[2][i]);
     __syncthreads();
   }
   const int stripe = blockIdx.x % kStripes;
@@ -492,11 +535,11 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
 // compiled long form is 1.8% faster, 65.8 against 67.0 ms; at 128 samples on
 // the 70 channels of a 30^3 cell the short one 3.5%, 20.2 against 19.5 ms).
 constexpr int kShortSamples = 1024;
-inline bool short_items(const CollideArgs& a) { return a.split > 1 || a.n_samples < kShortSamples; }
+inline bool short_items(int split, int n_samples) { return split > 1 || n_samples < kShortSamples; }
 
 // One precision's kernel variants: the launch of one, and all of them with
-// their LDS budget group (0 uniform sampler, 1 learned sampler, 2 the
-// compacting variant).
+// their LDS budget group (0 uniform sampler, 1 learned sampler, 2 and 3 the
+// compacting variant for long and short items).
 template <typename R>
 struct SlotsVariants {
   // the reference precision keeps one form of an item
@@ -529,7 +572,7 @@ struct SlotsVariants {
   static void launch_sampler(const CollideArgs& a, bool all_lds, bool queue, dim3 grid, dim3 block, size_t lds,
                              hipStream_t st) {
     if (a.learned) launch_variant<kSym, kScale, true, true>(a, all_lds, false, grid, block, lds, st);
-    else if (kF64 || short_items(a)) launch_variant<kSym, kScale, false, true>(a, all_lds, queue, grid, block, lds, st);
+    else if (kF64 || short_items(a.split, a.n_samples)) launch_variant<kSym, kScale, false, true>(a, all_lds, queue, grid, block, lds, st);
     else if constexpr (!kF64) launch_variant<kSym, kScale, false, false>(a, all_lds, queue, grid, block, lds, st);
   }
 
@@ -549,8 +592,8 @@ struct SlotsVariants {
   }
   template <bool kShort>
   static void add_queue(std::vector<Fn>& out) {
-    add<true, true, true, false, true, kShort>(out, 2);
-    add<true, false, true, false, true, kShort>(out, 2);
+    add<true, true, true, false, true, kShort>(out, kShort ? 3 : 2);
+    add<true, false, true, false, true, kShort>(out, kShort ? 3 : 2);
   }
   static std::vector<Fn> all() {
     std::vector<Fn> fns;
@@ -584,9 +627,10 @@ hipError_t launch_slots(const CollideArgs& a, int nslot, bool queue, hipStream_t
   const long long blocks = (long long)a.G.cells * a.n_group * a.n_chunks;
   if (blocks <= 0) return hipSuccess;
   if (a.split < 1 || (threads / kWave) % a.split) return hipErrorInvalidValue;  // whole groups of waves
-  const int unit = queue || a.learned ? kNodeBlock : 1;
-  if (a.split > 1 ? a.chunk_items > kSplitNodes : a.chunk_items % unit != 0)
-    return hipErrorInvalidValue;  // a shared chunk's sums fit in it_sum; other chunks start on node blocks
+  if (a.split > 1 && a.chunk_items > kSplitNodes) return hipErrorInvalidValue;  // a shared chunk's sums fit in it_sum
+  if (a.node_block < 1 || a.node_block > kMaxNodeBlock) return hipErrorInvalidValue;  // a block fits in node_tab
+  if (a.chunk_items % kNodeBlock != 0 && queue && !kF64 && !a.learned && !short_items(a.split, a.n_samples))
+    return hipErrorInvalidValue;  // the long form's chunks start on node blocks
   const dim3 grid((unsigned)blocks), block(threads);
   using V = SlotsVariants<R>;
   if (a.symmetric) {
@@ -604,7 +648,7 @@ hipError_t launch_slots(const CollideArgs& a, int nslot, bool queue, hipStream_t
 // runtime's default; after a refusal the budget is the limit in force.
 template <typename R>
 hipError_t slots_lds_limit(size_t lds_max, LdsBudget* out) {
-  size_t budget[3] = {lds_max, lds_max, lds_max};
+  size_t budget[4] = {lds_max, lds_max, lds_max, lds_max};
   for (const auto& f : SlotsVariants<R>::all()) {
     hipFuncAttributes attr;
     if (hipFuncGetAttributes(&attr, f.fn) != hipSuccess) return hipGetLastError();
@@ -621,7 +665,8 @@ hipError_t slots_lds_limit(size_t lds_max, LdsBudget* out) {
   }
   out->plain = budget[0];
   out->learned = budget[1];
-  out->queue = budget[2];
+  out->queue[0] = std::is_same<R, double>::value ? 0 : budget[2];  // FP64 has the short form only
+  out->queue[1] = budget[3];
   return hipSuccess;
 }
 

@@ -31,7 +31,7 @@ struct Group {
   int lds_tiles[2];   // FP32 f tiles staged in LDS       [uniform, learned sampler]; none in FP64
   int win[2];         // nodes per accumulator window (= nodes unless one slot's FP64
                       // accumulators exceed LDS; then one launch per window and slot)
-  bool queue;         // the uniform sampler's compacting variant fits
+  bool queue[2];      // the uniform sampler's compacting variant fits [long, short items]
 };
 
 // Device buffers of the proposal network (allocated on first use).
