@@ -5,7 +5,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "context.h"
@@ -127,6 +129,11 @@ void make_grid(const qgbe_grid_desc* d, Grid& G) {
   G.species_mask = d->species_mask;
 }
 
+// Whether a group's accumulators take more than one launch (slots or windows).
+bool several_launches(const qgbe_ctx* c, const Group& g, int l) {
+  return c->d.symmetric && (g.lds_acc[l] < g.nslot || g.win[l] < c->G.nodes);
+}
+
 // LDS plan per sampler: FP64 accumulators first (they replace global
 // atomics), then FP32 f tiles in what is left; slots that do not fit use
 // global memory.
@@ -165,6 +172,26 @@ void plan_groups(qgbe_ctx* c) {
       c->need_quads[0] = f32 && (c->need_quads[0] || g.queue[0] || g.queue[1]);
     }
   }
+  for (int l = 0; l < 2; ++l) {
+    Replay& r = c->replay[l];
+    r.start = (int)c->group_index.size();
+    for (const Group& g : c->groups)
+      if (several_launches(c, g, l))
+        for (int i = 0; i < g.count; ++i) {
+          const int gi = (int)c->group_index.size() - r.start, ci = c->group_index[g.start + i];
+          for (int p = 1; p < 4; ++p) r.match[c->chans[ci].sp[p]].push_back(4 * gi + p);
+          c->group_index.push_back(ci);
+        }
+    r.count = (int)c->group_index.size() - r.start;
+  }
+  for (Replay& r : c->replay) {
+    if (!r.count) continue;
+    r.match_at = (int)c->group_index.size();
+    for (int y = 0; y < kSpecies; ++y) {
+      c->group_index.insert(c->group_index.end(), r.match[y].begin(), r.match[y].end());
+      c->group_index.resize(r.match_at + (size_t)(y + 1) * kMaxMatches, 0);
+    }
+  }
 }
 
 struct Chunking {
@@ -173,10 +200,10 @@ struct Chunking {
   int block;  // nodes a wave takes at a time
 };
 
-// Observed nodes per workgroup.
-Chunking plan_chunks(const qgbe_ctx* c, const Group& g, int l, int n_samples, bool queue, bool learned) {
+// Observed nodes per workgroup; acc: entries a workgroup zeroes and flushes.
+Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long long acc, int n_samples, bool queue,
+                     bool learned) {
   const int waves = collide_waves(queue);
-  const long long nodes = c->G.nodes, pairs = (long long)c->G.cells * g.count;
   if (pairs >= c->n_cu) {
     // Enough (cell, channel) pairs to give every compute unit one: the nodes
     // of a pair are split over at most two workgroups per compute unit in all,
@@ -209,7 +236,6 @@ Chunking plan_chunks(const qgbe_ctx* c, const Group& g, int l, int n_samples, bo
   // about an iteration), in every round; nodes differ in how many samples
   // they accept, which unbalances one round by about a tenth.  (20^3 nodes of one gluon cell,
   // 512 samples: 167 workgroups without sharing 156 us, 256 with it 120.)
-  const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
   const auto turn = [](long long active) { return active <= 0 ? 0.0 : active <= 4 ? 1.0 : active <= 8 ? 1.3 : 1.75; };
   Chunking best{0, 1, 1};
   double least = 0.0;
@@ -244,6 +270,70 @@ Chunking plan_chunks(const qgbe_ctx* c, const Group& g, int l, int n_samples, bo
   return best;
 }
 
+// Whether the channels of more than one launch record their deposits in this call.
+bool records(const qgbe_ctx* c, int l, int n_samples, const double* scale) {
+  return c->d_rec && c->replay[l].count && !scale && n_samples <= c->rec.capacity;
+}
+
+// Their samples and deposits, in batches that fit the record buffers.
+qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l) {
+  const Replay& rp = c->replay[l];
+  const bool f64 = c->d.precision == QGBE_FP64;
+  const long long nodes = c->G.nodes, all_pairs = (long long)c->G.cells * rp.count;
+  const long long fit = c->rec.capacity / a.n_samples;  // items a batch holds
+  const Chunking ck = plan_chunks(c, std::min(nodes, fit), std::max(1LL, std::min(all_pairs, fit / nodes)), 0,
+                                  a.n_samples, l == 0, l == 1);
+  a.group = c->d_groups + rp.start;
+  a.n_group = rp.count;
+  a.split = ck.split;
+  a.node_block = ck.block;
+  a.chunk_items = (int)std::min<long long>(ck.chunk, fit);
+  a.n_chunks = (int)((nodes + a.chunk_items - 1) / a.chunk_items);
+  a.rec = c->rec;
+  a.rec.region = (long long)a.chunk_items * a.n_samples;
+  const long long wgs = all_pairs * a.n_chunks;
+  long long per = std::min(c->rec_wgs, c->rec.capacity / a.rec.region);
+  if (per > c->n_cu) per = per / c->n_cu * c->n_cu;
+  ReplayArgs r{};
+  r.G = c->G;
+  r.match = c->d_groups + rp.match_at;
+  r.n_group = rp.count;
+  r.n_chunks = a.n_chunks;
+  r.A = a.A;
+  const long long lds_nodes = (long long)(c->lds.replay / sizeof(double));
+  r.n_win = (int)((nodes + lds_nodes - 1) / lds_nodes);
+  r.win_n = (int)((nodes + r.n_win - 1) / r.n_win);
+  // workgroups of a replay launch: two to a compute unit where their windows fit
+  const double target = (double)c->n_cu * (2 * (size_t)r.win_n * sizeof(double) <= c->lds.replay ? 2 : 1);
+  for (long long wg = 0; wg < wgs; wg += per) {
+    const int n = (int)std::min(per, wgs - wg);
+    a.rec.wg_base = (int)wg;
+    HIP_TRY(f64 ? launch_record_f64(a, n, c->stream) : launch_record_f32(a, n, c->stream), "collide (record)");
+    r.rec = a.rec;
+    r.n_wg = n;
+    const long long per_cell = (long long)rp.count * a.n_chunks;
+    r.cell_lo = (int)(wg / per_cell);
+    r.n_cells = (int)((wg + n - 1) / per_cell) - r.cell_lo + 1;
+    const int gi_lo = r.n_cells > 1 ? 0 : (int)(wg % per_cell / a.n_chunks);
+    const int gi_hi = r.n_cells > 1 ? rp.count - 1 : (int)((wg + n - 1) % per_cell / a.n_chunks);
+    long long total = 0;
+    for (int y = 0; y < kSpecies; ++y) {
+      const std::vector<int>& m = rp.match[y];
+      r.m_lo[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * gi_lo) - m.begin());
+      r.m_hi[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * (gi_hi + 1)) - m.begin());
+      total += r.m_hi[y] - r.m_lo[y];
+    }
+    for (int y = 0; y < kSpecies; ++y) {
+      const int m = r.m_hi[y] - r.m_lo[y];
+      const double share = target * m / (double)std::max(1LL, total) / ((double)r.n_win * r.n_cells);
+      r.parts[y] = m ? (int)std::max(1LL, std::min<long long>((long long)m * a.n_chunks, (long long)(share + 0.5))) : 0;
+    }
+    HIP_TRY(f64 ? launch_replay_f64(r, c->stream) : launch_replay_f32(r, c->stream), "collide (replay)");
+    c->n_launches += 2;
+  }
+  return QGBE_OK;
+}
+
 // Enqueue the collision kernels accumulating into A (zeroed by the caller).
 qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, double* scale, double* items) {
   const bool learned = sampler == QGBE_SAMPLER_LEARNED;
@@ -267,15 +357,22 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
   }
   const bool f64_path = c->d.precision == QGBE_FP64;
   const int l = learned ? 1 : 0;
+  const bool recorded = records(c, l, n_samples, scale);
   if (c->need_quads[l]) HIP_TRY(launch_f32_quads(c->G, c->d_f32, c->d_f32q, c->stream), "f32 quads");
   a.f32q = c->d_f32q;
+  if (recorded) {
+    const qgbe_status s = run_replay(c, a, l);
+    if (s) return s;
+  }
   for (const Group& g : c->groups) {
+    if (recorded && several_launches(c, g, l)) continue;
     a.group = c->d_groups + g.start;
     a.n_group = g.count;
     // the compacting variant when the whole group fits in LDS next to its queues
     const bool is_short = collide_short(c->d.precision, learned, 1, n_samples);
     bool queue = !learned && g.queue[is_short];
-    const Chunking ck = plan_chunks(c, g, l, n_samples, queue, learned);
+    const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
+    const Chunking ck = plan_chunks(c, c->G.nodes, (long long)c->G.cells * g.count, acc, n_samples, queue, learned);
     if (!is_short && ck.split > 1) queue = queue && g.queue[1];  // waves that share nodes take the short form
     a.split = ck.split;
     a.node_block = ck.block;
@@ -313,6 +410,26 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
     }
   }
   return QGBE_OK;
+}
+
+// Record buffers: for 128 samples per item (and an eighth more, as whole
+// chunks of nodes count), between kRecMin and kRecMax samples (7 species at 30^3 x 128: 2 M samples 13.3 ms, 4 M 12.1, 8 M
+// 9.6, 16 M 9.2, 64 M 8.8; 52 B a sample, 92 B in FP64).  Without the memory
+// for them every launch draws its samples again.
+constexpr long long kRecMin = 1LL << 21, kRecMax = 1LL << 23;
+
+void alloc_records(qgbe_ctx* c) {
+  const size_t tile = c->d.precision == QGBE_FP64 ? collide_f64_record_tile() : collide_f32_record_tile();
+  const long long items = (long long)c->G.cells * std::max(c->replay[0].count, c->replay[1].count) * c->G.nodes;
+  const size_t tiles = (size_t)(std::max(kRecMin, std::min(kRecMax, items * 144)) + 63) / 64, wgs = 1 << 16;
+  if (dev_alloc(c, &c->d_rec, tiles * tile + wgs * sizeof(uint32_t), "records")) {
+    (void)hipGetLastError();
+    return;
+  }
+  c->rec.tiles = c->d_rec;
+  c->rec.count = (uint32_t*)(c->d_rec + tiles * tile);
+  c->rec.capacity = 64 * (long long)tiles;
+  c->rec_wgs = (long long)wgs;
 }
 
 }  // namespace qgbe
@@ -376,6 +493,25 @@ qgbe_status read_stats(qgbe_ctx* c, qgbe_stats* st, bool energy = false) {
   return QGBE_OK;
 }
 
+// The kernels' dynamic LDS limits, raised once per GPU and precision: each of
+// the some 50 kernel variants takes a query and a call of the runtime.
+hipError_t lds_budget(int device, int precision, size_t lds_max, LdsBudget* out) {
+  constexpr int kMaxDevices = 64;
+  static std::mutex mu;
+  static struct { bool ready; LdsBudget lds; } known[kMaxDevices][2];
+  const auto raise = precision == QGBE_FP64 ? collide_f64_lds_limit : collide_f32_lds_limit;
+  if (device >= kMaxDevices) return raise(lds_max, out);
+  std::lock_guard<std::mutex> lock(mu);
+  auto& k = known[device][precision];
+  if (!k.ready) {
+    const hipError_t e = raise(lds_max, &k.lds);
+    if (e != hipSuccess) return e;
+    k.ready = true;
+  }
+  *out = k.lds;
+  return hipSuccess;
+}
+
 bool species_ok(int s) { return s >= -1 && s < kSpecies; }
 
 }  // namespace
@@ -425,8 +561,7 @@ qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out) {
           "query LDS size");
   LdsBudget lds;
   const size_t lds_bytes = (size_t)std::max(lds_max, 0);
-  HIP_TRY(desc->precision == QGBE_FP64 ? collide_f64_lds_limit(lds_bytes, &lds) : collide_f32_lds_limit(lds_bytes, &lds),
-          "raise the dynamic LDS limit");
+  HIP_TRY(lds_budget(desc->device, desc->precision, lds_bytes, &lds), "raise the dynamic LDS limit");
   qgbe_ctx* c = new qgbe_ctx();
   c->d = *desc;
   c->stream = (hipStream_t)desc->stream;
@@ -442,52 +577,58 @@ qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out) {
   const size_t n = field_len(c);
   std::vector<int> all(std::max(1, c->nch));
   for (int i = 0; i < c->nch; ++i) all[i] = i;
-#define ALLOC(p, cnt, what)                       \
-  do {                                            \
-    qgbe_status _s = dev_alloc(c, &(p), (cnt), what); \
-    if (_s) { qgbe_destroy(c); return _s; }       \
-  } while (0)
-  ALLOC(c->d_chans, std::max(1, c->nch), "channel table");
-  ALLOC(c->d_groups, std::max<size_t>(1, c->group_index.size()), "channel groups");
-  ALLOC(c->d_all, all.size(), "channel list");
-  ALLOC(c->d_f, n, "f");
-  ALLOC(c->d_f_next, n, "f (next)");
-  ALLOC(c->d_f32, n, "f (fp32)");
-  if (c->d.precision == QGBE_FP32 && (c->need_quads[0] || c->need_quads[1])) ALLOC(c->d_f32q, n, "f (fp32 quads)");
-  ALLOC(c->d_A, n, "collision term");
-  ALLOC(c->d_mass2, (size_t)kSpecies * c->G.cells, "masses");
-  ALLOC(c->d_lag, (size_t)kSpecies * c->G.cells, "lagged masses");
-  ALLOC(c->d_obs_scratch, observables_scratch(c->G), "observables scratch");
-  ALLOC(c->d_obs, (size_t)observables_len, "observables");
-  ALLOC(c->d_energy, 2, "energy budget");
-  ALLOC(c->d_msq, 1, "matrix element table");
-  ALLOC(c->d_mass_part, mass_scratch(c->G), "mass partial sums");
-  ALLOC(c->d_count, kStripes, "accepted counter");
-  ALLOC(c->d_mc, 2 * kStripes, "error accumulators");
-  ALLOC(c->d_chan_var, kStripes * std::max(1, c->nch), "channel variances");
-#undef ALLOC
-  const char* what = "copy channel table";
-  hipError_t e = hipSuccess;
-  if (c->nch) e = hipMemcpy(c->d_chans, c->chans.data(), c->nch * sizeof(Channel), hipMemcpyHostToDevice);
-  if (e == hipSuccess && !c->group_index.empty()) {
-    what = "copy channel groups";
-    e = hipMemcpy(c->d_groups, c->group_index.data(), c->group_index.size() * sizeof(int), hipMemcpyHostToDevice);
+  // One allocation, carved: twice, first for its size.
+  char* arena = nullptr;
+  size_t used = 0;
+  const auto take = [&](auto** p, size_t cnt) {
+    using T = std::remove_reference_t<decltype(**p)>;
+    if (arena) *p = reinterpret_cast<T*>(arena + used);
+    used += (cnt * sizeof(T) + 255) & ~size_t(255);
+  };
+  const auto carve = [&]() {
+    used = 0;
+    take(&c->d_chans, std::max(1, c->nch));  // the channel tables side by side: one upload
+    take(&c->d_groups, std::max<size_t>(1, c->group_index.size()));
+    take(&c->d_all, all.size());
+    take(&c->d_f, n);                        // the zeroed fields side by side: one fill
+    take(&c->d_f_next, n);
+    take(&c->d_f32, n);
+    if (c->d.precision == QGBE_FP32 && (c->need_quads[0] || c->need_quads[1])) take(&c->d_f32q, n);
+    take(&c->d_A, n);
+    take(&c->d_mass2, (size_t)kSpecies * c->G.cells);
+    take(&c->d_lag, (size_t)kSpecies * c->G.cells);
+    take(&c->d_obs_scratch, observables_scratch(c->G));
+    take(&c->d_obs, (size_t)observables_len);
+    take(&c->d_energy, 2);
+    take(&c->d_msq, 1);
+    take(&c->d_mass_part, mass_scratch(c->G));
+    take(&c->d_count, kStripes);
+    take(&c->d_mc, 2 * kStripes);
+    take(&c->d_chan_var, kStripes * std::max(1, c->nch));
+  };
+  carve();
+  if (const qgbe_status s = dev_alloc(c, &c->d_arena, used, "context")) {
+    qgbe_destroy(c);
+    return s;
   }
-  if (e == hipSuccess) {
-    what = "copy channel list";
-    e = hipMemcpy(c->d_all, all.data(), all.size() * sizeof(int), hipMemcpyHostToDevice);
-  }
+  arena = c->d_arena;
+  carve();
+  if (c->replay[0].count || c->replay[1].count) alloc_records(c);
+  std::vector<char> tables((char*)c->d_f - arena);
+  std::memcpy(tables.data(), c->chans.data(), c->nch * sizeof(Channel));
+  std::memcpy(tables.data() + ((char*)c->d_groups - arena), c->group_index.data(), c->group_index.size() * sizeof(int));
+  std::memcpy(tables.data() + ((char*)c->d_all - arena), all.data(), all.size() * sizeof(int));
+  const char* what = "copy channel tables";
+  hipError_t e = hipMemcpy(arena, tables.data(), tables.size(), hipMemcpyHostToDevice);
   for (int i = 0; i < 4 && e == hipSuccess; ++i) {
     what = "create events";
     e = hipEventCreate(&c->ev[i]);
   }
   if (e == hipSuccess) {
     what = "zero f";
-    e = launch_fill(c->d_f, 0.0, n, c->stream);
-    // both buffers: the step updates only the evolving species
-    if (e == hipSuccess) e = launch_fill(c->d_f_next, 0.0, n, c->stream);
+    // both buffers, as a step updates only the evolving species, and the FP32 shadow
+    e = launch_fill(c->d_f, 0.0, ((char*)(c->d_f32 + n) - (char*)c->d_f + 7) / sizeof(double), c->stream);
   }
-  if (e == hipSuccess) e = launch_to_f32(c->d_f, c->d_f32, n, c->stream);
   if (e == hipSuccess) {
     what = "synchronise";
     e = hipStreamSynchronize(c->stream);
@@ -506,24 +647,8 @@ void qgbe_destroy(qgbe_ctx* c) {
   if (!c) return;
   (void)hipSetDevice(c->d.device);
   (void)hipStreamSynchronize(c->stream);
-  (void)hipFree(c->d_chans);
-  (void)hipFree(c->d_groups);
-  (void)hipFree(c->d_all);
-  (void)hipFree(c->d_f);
-  (void)hipFree(c->d_f_next);
-  (void)hipFree(c->d_f32);
-  (void)hipFree(c->d_f32q);
-  (void)hipFree(c->d_A);
-  (void)hipFree(c->d_mass2);
-  (void)hipFree(c->d_lag);
-  (void)hipFree(c->d_obs_scratch);
-  (void)hipFree(c->d_energy);
-  (void)hipFree(c->d_msq);
-  (void)hipFree(c->d_mass_part);
-  (void)hipFree(c->d_obs);
-  (void)hipFree(c->d_count);
-  (void)hipFree(c->d_mc);
-  (void)hipFree(c->d_chan_var);
+  (void)hipFree(c->d_arena);
+  (void)hipFree(c->d_rec);
   (void)hipFree(c->d_thr);
   (void)hipFree(c->d_mu);
   (void)hipFree(c->d_sigma);

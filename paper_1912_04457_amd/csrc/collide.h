@@ -18,6 +18,21 @@ constexpr int kSplitNodes = 64;
 // Most consecutive nodes a wave takes at a time.
 constexpr int kMaxNodeBlock = 8;
 
+// Deposits of a launch's accepted samples, kept for replay_kernel: per sample
+// the stencils of positions 2, 3, 4 (base node and weights) and the value, in
+// the integrand's precision.  A workgroup of the sampling kernel owns `region`
+// consecutive records (its nodes times the samples per node, all it can
+// accept) and leaves their number in count.  Records lie in tiles of 64, field
+// after field (see Record), so that a field of 64 consecutive records is one
+// wide access and the fields of a record are constant offsets apart.
+struct RecordArgs {
+  unsigned char* tiles;
+  uint32_t* count;    // [workgroups of the batch]
+  long long capacity; // records the tiles hold, a multiple of 64
+  long long region;   // records of a workgroup
+  int wg_base;       // first workgroup of the batch; workgroups run over (cell, channel, chunk)
+};
+
 struct CollideArgs {
   Grid G;
   const Channel* chans;   // device channel table (all channels)
@@ -59,12 +74,29 @@ struct CollideArgs {
   const float* mix_mu;       // [channels*nodes][K][5]
   const float* mix_sigma;    // [channels*nodes][K][5]
   const uint8_t* mix_on;     // [channels] 0: the channel falls back to the uniform sampler; NULL: all 1
+  RecordArgs rec;            // launch_record_deposits only
+};
+
+// The (channel, position) pairs of a channel list that deposit into a species.
+constexpr int kMaxMatches = 3 * kMaxChannels;
+struct ReplayArgs {
+  Grid G;
+  RecordArgs rec;
+  const int* match;       // [7][kMaxMatches]: 4 * (index in the channel list) + position (1..3), ascending
+  int n_group, n_chunks;  // as the sampling launch
+  int n_wg;               // workgroups of the batch
+  int cell_lo, n_cells;   // cells of the batch
+  int win_n, n_win;       // nodes per LDS window, windows
+  int m_lo[kSpecies], m_hi[kSpecies];  // matches of each species within the batch
+  int parts[kSpecies];                 // workgroups per (cell, species, window)
+  double* A;
 };
 
 // Dynamic LDS of one precision's kernel variants.
 struct LdsBudget {
   size_t plain = 0, learned = 0;  // uniform sampler, learned sampler
   size_t queue[2] = {0, 0};       // the compacting variant for long and short items
+  size_t replay = 0;              // replay_kernel
 };
 
 // The paper's root parameterisation (FP64; alt: the alternative elimination).
@@ -73,6 +105,17 @@ hipError_t launch_collide_roots(const CollideArgs& a, bool alt, hipStream_t stre
 // symmetric, every accumulator in LDS within the queue budget).
 hipError_t launch_collide_f32(const CollideArgs& a, int nslot, bool queue, hipStream_t stream);
 hipError_t launch_collide_f64(const CollideArgs& a, int nslot, bool queue, hipStream_t stream);
+// Sample a batch of n_wg workgroups (a.rec.wg_base onwards) and record the
+// deposits instead of adding them: symmetric sampling without the scale
+// output, short-item form.
+hipError_t launch_record_f32(const CollideArgs& a, int n_wg, hipStream_t stream);
+hipError_t launch_record_f64(const CollideArgs& a, int n_wg, hipStream_t stream);
+// Bytes of 64 records.
+size_t collide_f32_record_tile();
+size_t collide_f64_record_tile();
+// Add the recorded deposits of a batch to A.
+hipError_t launch_replay_f32(const ReplayArgs& a, hipStream_t stream);
+hipError_t launch_replay_f64(const ReplayArgs& a, hipStream_t stream);
 // Raise the kernels' dynamic LDS limit to what their static LDS leaves of
 // lds_max; returns the dynamic budgets.
 hipError_t collide_f32_lds_limit(size_t lds_max, LdsBudget* out);

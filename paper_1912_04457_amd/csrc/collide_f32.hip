@@ -14,6 +14,14 @@ hipError_t launch_collide_f32(const CollideArgs& a, int nslot, bool queue, hipSt
   return launch_slots<float>(a, nslot, queue, stream);
 }
 
+hipError_t launch_record_f32(const CollideArgs& a, int n_wg, hipStream_t stream) {
+  return launch_rec<float>(a, n_wg, stream);
+}
+
+size_t collide_f32_record_tile() { return record_tile_bytes<float>(); }
+
+hipError_t launch_replay_f32(const ReplayArgs& a, hipStream_t stream) { return launch_replay<float>(a, stream); }
+
 hipError_t collide_f32_lds_limit(size_t lds_max, LdsBudget* out) { return slots_lds_limit<float>(lds_max, out); }
 
 }  // namespace qgbe

@@ -143,14 +143,40 @@ constexpr int kNodeBlock = 4;
 // more spilled registers in the sample loop than it saves.  One gluon cell,
 // collision term: 10^3 nodes x 1000 samples 255 -> 46 us, 16^3 x 2048 547 ->
 // 190 us, 20^3 x 256 98 -> 78 us; 7 species, 30^3 x 128 20.9 -> 19.5 ms.
-template <typename R, bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kUser, bool kShort>
+// One record of RecordArgs: three weights per position and the value, then
+// the three base nodes.
+template <typename R>
+struct Record {
+  static constexpr size_t kTileBytes = 64 * (10 * sizeof(R) + 3 * sizeof(uint32_t));
+  R* w;            // [10][64]
+  uint32_t* base;  // [3][64]
+  __device__ __forceinline__ Record(unsigned char* tiles, long long i) {
+    unsigned char* t = tiles + (i >> 6) * (long long)kTileBytes;
+    w = (R*)t + (i & 63);
+    base = (uint32_t*)(t + 640 * sizeof(R)) + (i & 63);
+  }
+  __device__ __forceinline__ void store(int pos, const Stencil<R>& st) const {
+    base[pos * 64] = (uint32_t)st.base;
+    w[(3 * pos) * 64] = st.wx;
+    w[(3 * pos + 1) * 64] = st.wy;
+    w[(3 * pos + 2) * 64] = st.wz;
+  }
+  __device__ __forceinline__ Stencil<R> load(int pos) const {
+    return Stencil<R>{(int)base[pos * 64], w[(3 * pos) * 64], w[(3 * pos + 1) * 64], w[(3 * pos + 2) * 64]};
+  }
+};
+
+// kRec: the deposits go to A.rec instead of accumulators (see replay_kernel).
+template <typename R, bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kUser, bool kShort,
+          bool kRec = false>
 __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(CollideArgs A) {
   constexpr bool kF64 = std::is_same<R, double>::value;
   static_assert(!kLearned || kShort, "the learned sampler's items are short");
   static_assert(!kQueue || (kSym && kAllLds && !kLearned), "the queue serves the uniform sampler, slots in LDS");
+  static_assert(!kRec || (kSym && !kScale && kShort), "deposits are recorded in the short form");
   // kAllLds: every f tile and accumulator in LDS (the queue variant: every
   // accumulator; f from the quads)
-  constexpr bool kTilesLds = kAllLds && !kQueue && !kF64;
+  constexpr bool kTilesLds = kAllLds && !kQueue && !kF64 && !kRec;
   constexpr bool kAccLds = kAllLds;
   extern __shared__ double lds[];
   __shared__ R mix_rows[kLearned ? kSlotThreads / kWave : 1][kLearned ? (kF64 ? kMixRowF64 : kMixRow) : 1];
@@ -159,6 +185,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   __shared__ R q_f[kQueue ? kQueueWaves : 1][4][kQueue ? kQueueLen : 1];    // s, t, u, prefactor
   __shared__ double mc_wg[2];  // this workgroup's item variances and squared item sums
   __shared__ unsigned long long ok_wg;  // and its accepted samples
+  __shared__ unsigned rec_n;            // kRec: records of this workgroup
   constexpr int kNB = kQueue && !kShort ? kNodeBlock : 1;  // nodes per block (as collide_node_block)
   __shared__ double d_stage[kNB > 1 ? kSlotThreads / kWave : 1][kNB];  // direct sums of a wave's current block
   static_assert(slots_block(kQueue) % (kWave * kNB) == 0, "a multiple of the waves is one of the block");
@@ -170,7 +197,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = threadIdx.x / kWave;
   const int nw = blockDim.x / kWave;
-  const int lb = xcd_local_block(blockIdx.x, gridDim.x);
+  const int lb = (kRec ? A.rec.wg_base : 0) + xcd_local_block(blockIdx.x, gridDim.x);
   const int chunk = lb % A.n_chunks;
   // Uniform sampler: the chunks and channels of one cell follow each other
   // (they share its f quads and output rows in the XCD's L2).  Learned
@@ -180,7 +207,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   // once per block instead of once per cell, and the block's f rows serve
   // every channel.
   int gi, cell;
-  if (kLearned) {
+  if (kLearned && !kRec) {
     constexpr int kCellBlock = 32;
     const int u = lb / A.n_chunks;
     const int per = A.n_group * kCellBlock;
@@ -197,8 +224,8 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   const Channel ch = A.chans[ci];
   const int nslot = ch.nslot;
   const int nodes = G.nodes;
-  const int n_acc = kSym ? min(A.slot_hi - A.slot_lo, A.lds_acc) : 0;
-  const int n_tiles = min(nslot, A.lds_tiles);
+  const int n_acc = kSym && !kRec ? min(A.slot_hi - A.slot_lo, A.lds_acc) : 0;
+  const int n_tiles = kRec ? 0 : min(nslot, A.lds_tiles);
   const int win_lo = A.win_lo, win_n = A.win_n;
   double* acc = lds;                                          // [n_acc][win_n], slots slot_lo..
   float* tiles = reinterpret_cast<float*>(lds + (size_t)n_acc * win_n);  // [n_tiles][nodes]
@@ -209,7 +236,10 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   }
   for (int i = threadIdx.x; i < n_acc * win_n; i += blockDim.x) acc[i] = 0.0;
   if (threadIdx.x < 2) mc_wg[threadIdx.x] = 0.0;
-  if (threadIdx.x == 0) ok_wg = 0ull;
+  if (threadIdx.x == 0) {
+    ok_wg = 0ull;
+    rec_n = 0u;
+  }
   if (kNB > 1 && lane < kNB) d_stage[wid][lane] = 0.0;
   const int split = kShort ? A.split : 1;
   if (kShort && split > 1)
@@ -238,6 +268,20 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       d_stage[wid][lane] = 0.0;
     }
     wave_lds_sync();
+  };
+  const long long rec0 = kRec ? (long long)(lb - A.rec.wg_base) * A.rec.region : 0;
+  // kRec: the active lanes append their samples' deposits to the workgroup's records.
+  auto record = [&](const Stencil<R>& s2, const Stencil<R>& s3, const Stencil<R>& s4, R v) {
+    const unsigned long long m = __ballot(1);
+    const int rank = __popcll(m & ((1ull << lane) - 1ull));
+    unsigned at = 0;
+    if (rank == 0) at = __hip_atomic_fetch_add(&rec_n, (unsigned)__popcll(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
+    const Record<R> r(A.rec.tiles, rec0 + at + rank);
+    r.store(0, s2);
+    r.store(1, s3);
+    r.store(2, s4);
+    r.w[9 * 64] = v;
   };
   int n_ok = 0;  // accepted samples: of the item, kShort of the wave
   const int s_first = split > 1 ? (wid % split) * kWave : 0, s_step = split * kWave;
@@ -312,7 +356,9 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       const R vs = (wnb < R(0) ? -wnb : wnb) * (gain + loss);
       if (kScale) ssum += (double)vs;
       if (kSym) {
-        if (kQueue) {
+        if (kRec) {
+          record(s2, s3, s4, v);
+        } else if (kQueue) {
           pd2 = s2; pd3 = s3; pd4 = s4; pdv = v;
         } else {
           deposit_slot<kAccLds, true, R>(k2, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off2, s2, v,
@@ -381,7 +427,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         if (tail - head >= (unsigned)kWave) {
           wave_lds_sync();
           finish_queued((head + lane) & (kQueueLen - 1));
-          pending = true;
+          pending = !kRec;
           head += kWave;
           wave_lds_sync();
         }
@@ -402,7 +448,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         wave_lds_sync();
         if ((unsigned)lane < tail - head) {
           finish_queued((head + lane) & (kQueueLen - 1));
-          flush();
+          if (!kRec) flush();
         }
         wave_lds_sync();
       }
@@ -519,6 +565,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   if (threadIdx.x == 0 && A.n_accepted && A.direct) atomicAdd(A.n_accepted + stripe, ok_wg);
   if (threadIdx.x == 0 && A.chan_var && A.direct)  // one channel per workgroup
     atomicAdd(&A.chan_var[(size_t)stripe * A.n_channels + ci], mc_wg[0]);
+  if (kRec && threadIdx.x == 0) A.rec.count[lb - A.rec.wg_base] = rec_n;
   if (n_acc > 0) {
     for (int i = threadIdx.x; i < n_acc * win_n; i += blockDim.x) {
       const double v = acc[i];
@@ -530,6 +577,65 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   }
 }
 
+// ---------------------------------------------------------------------------
+// Replay.  A workgroup owns (cell, species, node window, part): it adds its
+// part of the deposits that the batch's samples recorded for the species to
+// LDS accumulators of the window and flushes them.  For grids whose deposit
+// accumulators do not fit in LDS at once: drawing every sample again for each
+// window or slot costs about 800 VALU instructions per 64 samples and launch,
+// a record 52 B written once (92 B in FP64) and 20 B (36 B) read per deposit
+// and window, and the sampling kernel then runs with its compacting queue.
+// Bound: the sampling launch by VALU issue (576 instructions per 64 samples,
+// 63% of the issue cycles), the replay by the LDS atomics (56% busy) and, with
+// few records per workgroup, by the flush (13500 entries x 256 workgroups, 34
+// us).  7 species at 30^3, 128 samples: 9 launches 18.8 ms -> 35 batches 9.4
+// ms; gluons at 30^3, 128 samples: 2 x 110 us -> 94 + 58 us; 7 species at 20^3
+// (15 channels of three slots): learned, 256 samples 9.0 -> 7.8 ms, plain, 4096
+// samples 51.5 -> 49.9 ms.
+// ---------------------------------------------------------------------------
+constexpr int kReplayThreads = 1024;
+
+template <typename R>
+__global__ __launch_bounds__(kReplayThreads) void replay_kernel(ReplayArgs a) {
+  extern __shared__ double lds[];
+  const Grid& G = a.G;
+  int per_cell = 0;
+  for (int y = 0; y < kSpecies; ++y) per_cell += a.parts[y] * a.n_win;
+  const int cell = a.cell_lo + blockIdx.x / per_cell;
+  int r = blockIdx.x % per_cell, sp = 0;
+  while (r >= a.parts[sp] * a.n_win) {
+    r -= a.parts[sp] * a.n_win;
+    ++sp;
+  }
+  const int part = r / a.n_win, lo = r % a.n_win * a.win_n;
+  const int n = min(a.win_n, G.nodes - lo);
+  for (int i = threadIdx.x; i < n; i += blockDim.x) lds[i] = 0.0;
+  __syncthreads();
+  const int jobs = (a.m_hi[sp] - a.m_lo[sp]) * a.n_chunks;
+  for (int j = part; j < jobs; j += a.parts[sp]) {
+    const int m = a.match[sp * kMaxMatches + a.m_lo[sp] + j / a.n_chunks];
+    const int pos = (m & 3) - 1;  // 0, 1, 2: positions 2, 3, 4
+    const long long wg = ((long long)cell * a.n_group + (m >> 2)) * a.n_chunks + j % a.n_chunks - a.rec.wg_base;
+    if (wg < 0 || wg >= a.n_wg) continue;
+    const int cnt = (int)a.rec.count[wg];
+    const long long i0 = wg * a.rec.region;
+    for (int i = threadIdx.x; i < cnt; i += blockDim.x) {
+      const Record<R> rec(a.rec.tiles, i0 + i);
+      const Stencil<R> st = rec.load(pos);
+      const R x = rec.w[9 * 64];
+      const double v = (double)(pos == 0 ? x : -x);
+      if (a.n_win == 1)
+        deposit<double, double, __HIP_MEMORY_SCOPE_WORKGROUP>(lds, widen(st), v, G.ox, G.oy);
+      else
+        deposit_window(lds, widen(st), v, G.ox, G.oy, lo, n);
+    }
+  }
+  __syncthreads();
+  double* out = a.A + ((size_t)sp * G.cells + cell) * G.nodes + lo;
+  for (int i = threadIdx.x; i < n; i += blockDim.x)
+    if (lds[i] != 0.0) atomicAdd(out + i, lds[i]);
+}
+
 // Uniform sampler: the short-item form when waves share nodes, and below
 // kShortSamples samples per item (at 2048 samples on 256 cells of gluons the
 // compiled long form is 1.8% faster, 65.8 against 67.0 ms; at 128 samples on
@@ -539,7 +645,7 @@ inline bool short_items(int split, int n_samples) { return split > 1 || n_sample
 
 // One precision's kernel variants: the launch of one, and all of them with
 // their LDS budget group (0 uniform sampler, 1 learned sampler, 2 and 3 the
-// compacting variant for long and short items).
+// compacting variant for long and short items, 4 the replay kernel).
 template <typename R>
 struct SlotsVariants {
   // the reference precision keeps one form of an item
@@ -595,8 +701,19 @@ struct SlotsVariants {
     add<true, true, true, false, true, kShort>(out, kShort ? 3 : 2);
     add<true, false, true, false, true, kShort>(out, kShort ? 3 : 2);
   }
+  template <bool kLearned>
+  static void launch_rec(const CollideArgs& a, dim3 grid, hipStream_t st) {
+    const dim3 block(slots_block(!kLearned));
+    if (a.msq_mask)
+      hipLaunchKernelGGL((collide_slots_kernel<R, true, false, true, kLearned, !kLearned, true, true, true>), grid,
+                         block, 0, st, a);
+    else
+      hipLaunchKernelGGL((collide_slots_kernel<R, true, false, true, kLearned, !kLearned, false, true, true>), grid,
+                         block, 0, st, a);
+  }
   static std::vector<Fn> all() {
     std::vector<Fn> fns;
+    fns.push_back({(const void*)replay_kernel<R>, 4});
     add_all<true, false, true>(fns, 0);
     add_all<true, true, true>(fns, 1);
     add_queue<true>(fns);
@@ -643,12 +760,44 @@ hipError_t launch_slots(const CollideArgs& a, int nslot, bool queue, hipStream_t
   return hipGetLastError();
 }
 
+template <typename R>
+size_t record_tile_bytes() {
+  return Record<R>::kTileBytes;
+}
+
+template <typename R>
+hipError_t launch_rec(const CollideArgs& a, int n_wg, hipStream_t stream) {
+  if (n_wg <= 0) return hipSuccess;
+  const int waves = slots_block(true) / kWave;
+  if (!a.symmetric || a.scale || a.split < 1 || waves % a.split) return hipErrorInvalidValue;
+  if (a.split > 1 && a.chunk_items > kSplitNodes) return hipErrorInvalidValue;
+  if (a.node_block < 1 || a.node_block > kMaxNodeBlock) return hipErrorInvalidValue;
+  // every workgroup's samples fit in its region and the regions in the buffers
+  if ((long long)a.chunk_items * a.n_samples > a.rec.region || a.rec.region * n_wg > a.rec.capacity)
+    return hipErrorInvalidValue;
+  if (a.rec.wg_base + (long long)n_wg > (long long)a.G.cells * a.n_group * a.n_chunks) return hipErrorInvalidValue;
+  if (a.learned) SlotsVariants<R>::template launch_rec<true>(a, dim3((unsigned)n_wg), stream);
+  else SlotsVariants<R>::template launch_rec<false>(a, dim3((unsigned)n_wg), stream);
+  return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_replay(const ReplayArgs& a, hipStream_t stream) {
+  long long per_cell = 0;
+  for (int y = 0; y < kSpecies; ++y) per_cell += (long long)a.parts[y] * a.n_win;
+  if (per_cell * a.n_cells <= 0) return hipSuccess;
+  if ((long long)a.n_win * a.win_n < a.G.nodes) return hipErrorInvalidValue;  // the windows cover the grid
+  hipLaunchKernelGGL(replay_kernel<R>, dim3((unsigned)(per_cell * a.n_cells)), dim3(kReplayThreads),
+                     a.win_n * sizeof(double), stream, a);
+  return hipGetLastError();
+}
+
 // Each variant may use what its static LDS leaves of lds_max.  Raising the
 // per-kernel dynamic limit is only needed (and only accepted) above the
 // runtime's default; after a refusal the budget is the limit in force.
 template <typename R>
 hipError_t slots_lds_limit(size_t lds_max, LdsBudget* out) {
-  size_t budget[4] = {lds_max, lds_max, lds_max, lds_max};
+  size_t budget[5] = {lds_max, lds_max, lds_max, lds_max, lds_max};
   for (const auto& f : SlotsVariants<R>::all()) {
     hipFuncAttributes attr;
     if (hipFuncGetAttributes(&attr, f.fn) != hipSuccess) return hipGetLastError();
@@ -667,6 +816,7 @@ hipError_t slots_lds_limit(size_t lds_max, LdsBudget* out) {
   out->learned = budget[1];
   out->queue[0] = std::is_same<R, double>::value ? 0 : budget[2];  // FP64 has the short form only
   out->queue[1] = budget[3];
+  out->replay = budget[4];
   return hipSuccess;
 }
 

@@ -34,6 +34,15 @@ struct Group {
   bool queue[2];      // the uniform sampler's compacting variant fits [long, short items]
 };
 
+// Channels whose deposit accumulators need more than one launch (slots or node
+// windows): their samples are drawn once and their deposits recorded, then
+// replayed per (species, window).
+struct Replay {
+  int start = 0, count = 0;        // range in the group index array
+  std::vector<int> match[kSpecies];  // as ReplayArgs::match
+  int match_at = 0;                // the lists in the group index array, kMaxMatches apart
+};
+
 // Device buffers of the proposal network (allocated on first use).
 struct MlpState {
   bool ready = false;
@@ -57,6 +66,11 @@ struct qgbe_ctx {
   std::vector<qgbe::Channel> chans;
   std::vector<int> group_index;
   std::vector<qgbe::Group> groups;
+  qgbe::Replay replay[2];          // [uniform, learned sampler]
+  unsigned char* d_rec = nullptr;  // record buffers, an allocation of their own (NULL: none, every launch draws its samples again)
+  qgbe::RecordArgs rec{};          // their parts
+  long long rec_wgs = 0;           // counters in rec.count
+  char* d_arena = nullptr;         // the allocation that holds the buffers below unless noted
   qgbe::Channel* d_chans = nullptr;
   int* d_groups = nullptr;
   int* d_all = nullptr;            // identity channel list (root kernel)
@@ -82,6 +96,7 @@ struct qgbe_ctx {
   double* d_mc = nullptr;          // [2] MC error accumulators of the last collision term
   double* d_chan_var = nullptr;    // [kStripes][channels] per-channel variance sums of the last collision term
   uint32_t step = 0;
+  // allocated on first use
   int K = 0;                       // proposal table components (0 = none)
   uint32_t* d_thr = nullptr;
   float* d_mu = nullptr;

@@ -112,6 +112,7 @@ qgbe_status qgbe_collision_term_noalloc(const qgbe_grid_desc* desc, const double
   const bool fp32 = desc->precision == QGBE_FP32 && sampler == QGBE_SAMPLER_UNIFORM;
   Carve cv{dev->ptr};
   c.d_chans = cv.take<Channel>(kMaxChannels);
+  c.group_index.resize(std::min<size_t>(c.group_index.size(), kMaxChannels));  // no record buffers, no replay lists
   c.d_groups = cv.take<int>(kMaxChannels);
   c.d_all = cv.take<int>(kMaxChannels);
   const size_t table_bytes = cv.used;

@@ -343,3 +343,43 @@ def test_lds_plans_fp64(O, n_x, n_p, mask, N):
     assert np.allclose(r["I"], r["I_ref"], rtol=TOL[qgbe.FP64], atol=TOL[qgbe.FP64] * scale_items)
     for cell in range(wl.cells):
         assert abs(r["A"][:, cell].sum()) <= 1e-13 * r["S_ref"][:, cell].sum()
+
+
+@pytest.mark.parametrize("n_x,n_p,mask,N,precision,learned",
+                         [((1, 1, 1), (20, 20, 20), 0x7F, 80, qgbe.FP32, False),
+                          ((2, 1, 1), (18, 19, 20), 0x49, 40, qgbe.FP64, False),
+                          ((1, 1, 1), (40, 39, 41), 1 << 6, 5, qgbe.FP32, False),
+                          ((2, 1, 1), (28, 27, 29), 1 << 6, 70, qgbe.FP32, True),
+                          ((1, 1, 1), (19, 20, 21), 0x43, 30, qgbe.FP64, True),
+                          ((1, 1, 1), (28, 28, 28), 1 << 6, 1500, qgbe.FP32, False)],
+                         ids=["batches", "cells_f64", "four_windows", "learned_cells", "learned_f64", "long_items"])
+def test_recorded_deposits(O, n_x, n_p, mask, N, precision, learned):
+    """Grids whose deposit accumulators take more than one launch: the samples
+    are drawn once and their deposits recorded and replayed, in one batch or
+    several, over one node window or several, for every sampler and precision;
+    with the scale output the same term draws its samples in every launch."""
+    _case(f"recorded deposits {n_x} {n_p} mask={mask:#x} N={N} precision={precision} learned={learned}")
+    wl = W.Workload("recorded", n_x, n_p, (3.0, 3.0, 3.0), (2.0, 2.5, 1.5), mask, N, "f32", 1, 0.01)
+    f = W.random_f(27, wl.cells, wl.nodes, species_mask=mask)
+    g = O.Grid(n_x=n_x, n_p=n_p, x_half=wl.x_half, p_half=wl.p_half, species_mask=mask, alpha_s=wl.alpha_s)
+    with qgbe.Solver(**_grid_kw(wl), precision=precision, seed=SEED) as s:
+        s.set_f(f)
+        qgbe.qgbe_set_step_index(s.ctx, 4)
+        if learned:
+            table = W.random_mog_table(5, s.n_channels * wl.nodes)
+            qgbe.qgbe_set_proposal_table(s.ctx, *table)
+        sampler = qgbe.SAMPLER_LEARNED if learned else qgbe.SAMPLER_UNIFORM
+        A, _, I, st = s.collision(N, sampler=sampler, items=True)
+        A2, S2, I2, st2 = s.collision(N, sampler=sampler, scale=True, items=True)
+        m = s.masses()
+    if learned:
+        A_ref, S_ref, I_ref = O.collision_learned(g, f, m, SEED, 4, N, *table, want_items=True)
+    else:
+        A_ref, S_ref, I_ref = O.collision(g, f, m, SEED, 4, N, want_items=True)
+    for a, i in ((A, I), (A2, I2)):
+        _compare(a, A_ref, S_ref, TOL[precision], "A")
+        assert np.allclose(i, I_ref, rtol=TOL[precision], atol=TOL[precision] * np.abs(I_ref).max())
+    for cell in range(wl.cells):
+        assert abs(A[:, cell].sum()) <= 1e-13 * S_ref[:, cell].sum()
+    assert st.n_accepted == st2.n_accepted
+    assert st.mc_err_est == pytest.approx(st2.mc_err_est, rel=1e-9)
