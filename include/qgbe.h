@@ -290,8 +290,8 @@ qgbe_status qgbe_observables(qgbe_ctx* ctx, qgbe_stats* st);
  * sampler: QGBE_SAMPLER_UNIFORM (in desc->precision) or one of the root
  * samplers (FP64); QGBE_SAMPLER_LEARNED is refused (no proposal table).
  * Everything else the kernels need (channel table, masses, per-launch totals,
- * the FP32 copy of f and its node quads) lives in one device array of
- * QGBE_NOALLOC_SCRATCH_MIB MiB per GPU; a grid that needs more returns
+ * the FP32 copy of f and its node quads, records of deposits in what is left)
+ * lives in one device array of QGBE_NOALLOC_SCRATCH_MIB MiB per GPU; a grid that needs more returns
  * QGBE_EINVAL before any device work.  Every call on a GPU shares that GPU's
  * array, so calls that overlap on one GPU (other streams, other threads)
  * race; calls in sequence on one stream do not.  Asynchronous on desc->stream

@@ -144,9 +144,9 @@ void plan_groups(qgbe_ctx* c) {
   c->group_index.clear();
   c->groups.clear();
   for (int nslot = 1; nslot <= 3; ++nslot) {
-    Group g{(int)c->group_index.size(), 0, nslot, {0, 0}, {0, 0}, {c->G.nodes, c->G.nodes}, {false, false}};
-    for (int l = 0; l < 2; ++l) {
-      const size_t budget = l ? c->lds.learned : c->lds.plain;
+    Group g{(int)c->group_index.size(), 0, nslot, {}, {}, {c->G.nodes, c->G.nodes, c->G.nodes}, {false, false}};
+    for (int l = 0; l < 3; ++l) {
+      const size_t budget = l == 0 ? c->lds.plain : l == 1 ? c->lds.learned : c->lds.roots;
       if (c->d.symmetric && budget < acc_b) {
         // one slot's FP64 accumulators exceed LDS: node windows, one launch
         // per window holding every slot's accumulators for that window, the
@@ -159,7 +159,7 @@ void plan_groups(qgbe_ctx* c) {
         continue;
       }
       g.lds_acc[l] = c->d.symmetric ? (int)std::min<size_t>(nslot, budget / acc_b) : 0;
-      g.lds_tiles[l] = f32 ? (int)std::min<size_t>(nslot, (budget - g.lds_acc[l] * acc_b) / tile_b) : 0;
+      g.lds_tiles[l] = f32 && l < 2 ? (int)std::min<size_t>(nslot, (budget - g.lds_acc[l] * acc_b) / tile_b) : 0;
     }
     for (int i = 0; i < 2; ++i)
       g.queue[i] = c->d.symmetric && g.lds_acc[0] == nslot && g.win[0] == c->G.nodes && nslot * acc_b <= c->lds.queue[i];
@@ -172,7 +172,7 @@ void plan_groups(qgbe_ctx* c) {
       c->need_quads[0] = f32 && (c->need_quads[0] || g.queue[0] || g.queue[1]);
     }
   }
-  for (int l = 0; l < 2; ++l) {
+  for (int l = 0; l < 3; ++l) {
     Replay& r = c->replay[l];
     r.start = (int)c->group_index.size();
     for (const Group& g : c->groups)
@@ -270,19 +270,82 @@ Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long l
   return best;
 }
 
+// Record buffers: for 128 samples per item (and an eighth more, as whole
+// chunks of nodes count), between kRecMin and kRecMax samples (7 species at 30^3 x 128: 2 M samples 13.3 ms, 4 M 12.1, 8 M
+// 9.6, 16 M 9.2, 64 M 8.8; 52 B a sample, 92 B in FP64).  Without the memory
+// for them every launch draws its samples again.
+constexpr long long kRecMin = 1LL << 21, kRecMax = 1LL << 23, kRecLeast = 1LL << 19;
+
+size_t record_tile(const qgbe_ctx* c, bool roots) {
+  return roots || c->d.precision == QGBE_FP64 ? collide_f64_record_tile() : collide_f32_record_tile();
+}
+
+void carve_records(qgbe_ctx* c, unsigned char* p, size_t bytes) {
+  const size_t wgs = 1 << 16, counts = wgs * sizeof(uint32_t);
+  if (bytes < counts + (kRecLeast / 64) * record_tile(c, false)) return;
+  c->d_rec = p;
+  c->rec.count = (uint32_t*)p;
+  c->rec.tiles = p + counts;
+  c->rec_wgs = (long long)wgs;
+  c->rec_bytes = bytes - counts;
+}
+
+void alloc_records(qgbe_ctx* c) {
+  const long long items = (long long)c->G.cells * c->G.nodes *
+                          std::max({c->replay[0].count, c->replay[1].count, c->replay[2].count});
+  const size_t tiles = (size_t)(std::max(kRecMin, std::min(kRecMax, items * 144)) + 63) / 64;
+  const size_t bytes = tiles * record_tile(c, false) + ((size_t)sizeof(uint32_t) << 16);
+  unsigned char* p = nullptr;
+  if (dev_alloc(c, &p, bytes, "records")) (void)hipGetLastError();
+  else carve_records(c, p, bytes);
+}
+
+// Records the buffers hold for a sampler (the root samplers' are FP64).
+long long record_capacity(const qgbe_ctx* c, int l) {
+  return 64 * (long long)(c->rec_bytes / record_tile(c, l == 2));
+}
+
 // Whether the channels of more than one launch record their deposits in this call.
-bool records(const qgbe_ctx* c, int l, int n_samples, const double* scale) {
-  return c->d_rec && c->replay[l].count && !scale && n_samples <= c->rec.capacity;
+// (The buffers are there from the start where the CM-angle samplers need them;
+// for the root samplers alone they are made by the first call that uses them,
+// unless its stream is being captured.)
+bool records(qgbe_ctx* c, int l, int n_samples, const double* scale) {
+  if (!c->replay[l].count || scale) return false;
+  if (!c->d_rec && l == 2 && c->d_arena) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) alloc_records(c);
+  }
+  const long long capacity = record_capacity(c, l) / (l == 2 ? 2 : 1);
+  if (!c->d_rec || n_samples > capacity) return false;
+  // Microseconds: 26 per million samples drawn (whole iterations of 64, and
+  // half a one for the item), 14 per million replayed, 45 per launch that
+  // draws and flushes, 40 per batch.  With the buffers of a context recording
+  // wins from two launches on (gluons at 30^3: 94 against 142 us with one
+  // sample, 184 against 250 with 128, 2.3 against 2.6 ms with 2048); in the few
+  // MB of the call without allocation, 1000 samples there take 25 batches and
+  // 2.1 ms instead of 1.3.
+  const double per_sample = 1e-6 * (double)c->G.cells * c->G.nodes;
+  const double drawn = per_sample * (64.0 * ((n_samples + 63) / 64) + 32.0);
+  double again = 0.0;
+  for (const Group& g : c->groups)
+    if (several_launches(c, g, l)) {
+      const int passes = (g.nslot + g.lds_acc[l] - 1) / g.lds_acc[l];
+      const int windows = (c->G.nodes + g.win[l] - 1) / g.win[l];
+      again += passes * windows * (26.0 * drawn * g.count + 45.0);
+    }
+  const double n = c->replay[l].count, replayed = per_sample * n_samples * n;
+  return 26.0 * drawn * n + 14.0 * replayed + 40.0 * std::ceil(1e6 * replayed / (double)capacity) < again;
 }
 
 // Their samples and deposits, in batches that fit the record buffers.
-qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l) {
+qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
   const Replay& rp = c->replay[l];
-  const bool f64 = c->d.precision == QGBE_FP64;
+  const bool roots = l == 2, f64 = roots || c->d.precision == QGBE_FP64;
+  const int per_sample = roots ? 2 : 1;
   const long long nodes = c->G.nodes, all_pairs = (long long)c->G.cells * rp.count;
-  const long long fit = c->rec.capacity / a.n_samples;  // items a batch holds
+  const long long fit = record_capacity(c, l) / (per_sample * a.n_samples);  // items a batch holds
   const Chunking ck = plan_chunks(c, std::min(nodes, fit), std::max(1LL, std::min(all_pairs, fit / nodes)), 0,
-                                  a.n_samples, l == 0, l == 1);
+                                  a.n_samples, l == 0, l != 0);
   a.group = c->d_groups + rp.start;
   a.n_group = rp.count;
   a.split = ck.split;
@@ -290,9 +353,10 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l) {
   a.chunk_items = (int)std::min<long long>(ck.chunk, fit);
   a.n_chunks = (int)((nodes + a.chunk_items - 1) / a.chunk_items);
   a.rec = c->rec;
-  a.rec.region = (long long)a.chunk_items * a.n_samples;
+  a.rec.capacity = record_capacity(c, l);
+  a.rec.region = (long long)a.chunk_items * a.n_samples * per_sample;
   const long long wgs = all_pairs * a.n_chunks;
-  long long per = std::min(c->rec_wgs, c->rec.capacity / a.rec.region);
+  long long per = std::min(c->rec_wgs, a.rec.capacity / a.rec.region);
   if (per > c->n_cu) per = per / c->n_cu * c->n_cu;
   ReplayArgs r{};
   r.G = c->G;
@@ -308,7 +372,8 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l) {
   for (long long wg = 0; wg < wgs; wg += per) {
     const int n = (int)std::min(per, wgs - wg);
     a.rec.wg_base = (int)wg;
-    HIP_TRY(f64 ? launch_record_f64(a, n, c->stream) : launch_record_f32(a, n, c->stream), "collide (record)");
+    HIP_TRY(roots ? launch_record_roots(a, alt, n, c->stream)
+                  : f64 ? launch_record_f64(a, n, c->stream) : launch_record_f32(a, n, c->stream), "collide (record)");
     r.rec = a.rec;
     r.n_wg = n;
     const long long per_cell = (long long)rp.count * a.n_chunks;
@@ -347,21 +412,14 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
   a.slot_lo = 0;
   a.slot_hi = 3;
   a.direct = 1;
-  if (sampler == QGBE_SAMPLER_ROOTS || sampler == QGBE_SAMPLER_ROOTS_ALT) {
-    a.learned = 0;
-    a.group = c->d_all;
-    a.n_group = c->nch;
-    HIP_TRY(launch_collide_roots(a, sampler == QGBE_SAMPLER_ROOTS_ALT, c->stream), "collide (roots)");
-    ++c->n_launches;
-    return QGBE_OK;
-  }
+  const bool roots = sampler == QGBE_SAMPLER_ROOTS || sampler == QGBE_SAMPLER_ROOTS_ALT;
   const bool f64_path = c->d.precision == QGBE_FP64;
-  const int l = learned ? 1 : 0;
+  const int l = roots ? 2 : learned ? 1 : 0;
   const bool recorded = records(c, l, n_samples, scale);
-  if (c->need_quads[l]) HIP_TRY(launch_f32_quads(c->G, c->d_f32, c->d_f32q, c->stream), "f32 quads");
+  if (!roots && c->need_quads[l]) HIP_TRY(launch_f32_quads(c->G, c->d_f32, c->d_f32q, c->stream), "f32 quads");
   a.f32q = c->d_f32q;
   if (recorded) {
-    const qgbe_status s = run_replay(c, a, l);
+    const qgbe_status s = run_replay(c, a, l, sampler == QGBE_SAMPLER_ROOTS_ALT);
     if (s) return s;
   }
   for (const Group& g : c->groups) {
@@ -369,10 +427,10 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
     a.group = c->d_groups + g.start;
     a.n_group = g.count;
     // the compacting variant when the whole group fits in LDS next to its queues
-    const bool is_short = collide_short(c->d.precision, learned, 1, n_samples);
-    bool queue = !learned && g.queue[is_short];
+    const bool is_short = roots || collide_short(c->d.precision, learned, 1, n_samples);
+    bool queue = l == 0 && g.queue[is_short];
     const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
-    const Chunking ck = plan_chunks(c, c->G.nodes, (long long)c->G.cells * g.count, acc, n_samples, queue, learned);
+    const Chunking ck = plan_chunks(c, c->G.nodes, (long long)c->G.cells * g.count, acc, n_samples, queue, learned || roots);
     if (!is_short && ck.split > 1) queue = queue && g.queue[1];  // waves that share nodes take the short form
     a.split = ck.split;
     a.node_block = ck.block;
@@ -399,37 +457,18 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
         a.lds_tiles = g.lds_tiles[l];
         if (n_pass > 1 && n_win == 1) {
           const size_t used = (size_t)(a.slot_hi - a.slot_lo) * acc_b;
-          a.lds_tiles = f64_path ? 0 : (int)std::min<size_t>(g.nslot, ((l ? c->lds.learned : c->lds.plain) - used) / tile_b);
+          a.lds_tiles = f64_path || roots ? 0 : (int)std::min<size_t>(g.nslot, ((l ? c->lds.learned : c->lds.plain) - used) / tile_b);
         }
         if (queue) a.lds_tiles = 0;  // the compacting variant reads f from the node quads
         const bool q = queue && n_pass == 1 && n_win == 1;
-        if (f64_path) HIP_TRY(launch_collide_f64(a, g.nslot, q, c->stream), "collide (fp64)");
+        if (roots) HIP_TRY(launch_collide_roots(a, sampler == QGBE_SAMPLER_ROOTS_ALT, c->stream), "collide (roots)");
+        else if (f64_path) HIP_TRY(launch_collide_f64(a, g.nslot, q, c->stream), "collide (fp64)");
         else HIP_TRY(launch_collide_f32(a, g.nslot, q, c->stream), "collide (fp32)");
         ++c->n_launches;
       }
     }
   }
   return QGBE_OK;
-}
-
-// Record buffers: for 128 samples per item (and an eighth more, as whole
-// chunks of nodes count), between kRecMin and kRecMax samples (7 species at 30^3 x 128: 2 M samples 13.3 ms, 4 M 12.1, 8 M
-// 9.6, 16 M 9.2, 64 M 8.8; 52 B a sample, 92 B in FP64).  Without the memory
-// for them every launch draws its samples again.
-constexpr long long kRecMin = 1LL << 21, kRecMax = 1LL << 23;
-
-void alloc_records(qgbe_ctx* c) {
-  const size_t tile = c->d.precision == QGBE_FP64 ? collide_f64_record_tile() : collide_f32_record_tile();
-  const long long items = (long long)c->G.cells * std::max(c->replay[0].count, c->replay[1].count) * c->G.nodes;
-  const size_t tiles = (size_t)(std::max(kRecMin, std::min(kRecMax, items * 144)) + 63) / 64, wgs = 1 << 16;
-  if (dev_alloc(c, &c->d_rec, tiles * tile + wgs * sizeof(uint32_t), "records")) {
-    (void)hipGetLastError();
-    return;
-  }
-  c->rec.tiles = c->d_rec;
-  c->rec.count = (uint32_t*)(c->d_rec + tiles * tile);
-  c->rec.capacity = 64 * (long long)tiles;
-  c->rec_wgs = (long long)wgs;
 }
 
 }  // namespace qgbe
@@ -500,11 +539,15 @@ hipError_t lds_budget(int device, int precision, size_t lds_max, LdsBudget* out)
   static std::mutex mu;
   static struct { bool ready; LdsBudget lds; } known[kMaxDevices][2];
   const auto raise = precision == QGBE_FP64 ? collide_f64_lds_limit : collide_f32_lds_limit;
-  if (device >= kMaxDevices) return raise(lds_max, out);
+  if (device >= kMaxDevices) {
+    const hipError_t e = raise(lds_max, out);
+    return e != hipSuccess ? e : collide_roots_lds_limit(lds_max, &out->roots);
+  }
   std::lock_guard<std::mutex> lock(mu);
   auto& k = known[device][precision];
   if (!k.ready) {
-    const hipError_t e = raise(lds_max, &k.lds);
+    hipError_t e = raise(lds_max, &k.lds);
+    if (e == hipSuccess) e = collide_roots_lds_limit(lds_max, &k.lds.roots);
     if (e != hipSuccess) return e;
     k.ready = true;
   }
@@ -575,8 +618,6 @@ qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out) {
     c->n_cu = n_cu;
   plan_groups(c);
   const size_t n = field_len(c);
-  std::vector<int> all(std::max(1, c->nch));
-  for (int i = 0; i < c->nch; ++i) all[i] = i;
   // One allocation, carved: twice, first for its size.
   char* arena = nullptr;
   size_t used = 0;
@@ -589,7 +630,6 @@ qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out) {
     used = 0;
     take(&c->d_chans, std::max(1, c->nch));  // the channel tables side by side: one upload
     take(&c->d_groups, std::max<size_t>(1, c->group_index.size()));
-    take(&c->d_all, all.size());
     take(&c->d_f, n);                        // the zeroed fields side by side: one fill
     take(&c->d_f_next, n);
     take(&c->d_f32, n);
@@ -617,7 +657,6 @@ qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out) {
   std::vector<char> tables((char*)c->d_f - arena);
   std::memcpy(tables.data(), c->chans.data(), c->nch * sizeof(Channel));
   std::memcpy(tables.data() + ((char*)c->d_groups - arena), c->group_index.data(), c->group_index.size() * sizeof(int));
-  std::memcpy(tables.data() + ((char*)c->d_all - arena), all.data(), all.size() * sizeof(int));
   const char* what = "copy channel tables";
   hipError_t e = hipMemcpy(arena, tables.data(), tables.size(), hipMemcpyHostToDevice);
   for (int i = 0; i < 4 && e == hipSuccess; ++i) {

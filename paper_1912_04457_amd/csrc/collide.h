@@ -22,7 +22,7 @@ constexpr int kMaxNodeBlock = 8;
 // the stencils of positions 2, 3, 4 (base node and weights) and the value, in
 // the integrand's precision.  A workgroup of the sampling kernel owns `region`
 // consecutive records (its nodes times the samples per node, all it can
-// accept) and leaves their number in count.  Records lie in tiles of 64, field
+// accept; twice that for the root samplers) and leaves their number in count.  Records lie in tiles of 64, field
 // after field (see Record), so that a field of 64 consecutive records is one
 // wide access and the fields of a record are constant offsets apart.
 struct RecordArgs {
@@ -97,9 +97,11 @@ struct LdsBudget {
   size_t plain = 0, learned = 0;  // uniform sampler, learned sampler
   size_t queue[2] = {0, 0};       // the compacting variant for long and short items
   size_t replay = 0;              // replay_kernel
+  size_t roots = 0;               // the root samplers
 };
 
-// The paper's root parameterisation (FP64; alt: the alternative elimination).
+// The paper's root parameterisation (FP64; alt: the alternative elimination);
+// a launch's slots and window as for the CM-angle samplers.
 hipError_t launch_collide_roots(const CollideArgs& a, bool alt, hipStream_t stream);
 // queue: use the compacting variant if the launch qualifies (uniform sampler,
 // symmetric, every accumulator in LDS within the queue budget).
@@ -110,6 +112,8 @@ hipError_t launch_collide_f64(const CollideArgs& a, int nslot, bool queue, hipSt
 // output, short-item form.
 hipError_t launch_record_f32(const CollideArgs& a, int n_wg, hipStream_t stream);
 hipError_t launch_record_f64(const CollideArgs& a, int n_wg, hipStream_t stream);
+// The root samplers record up to two deposits per sample, in FP64.
+hipError_t launch_record_roots(const CollideArgs& a, bool alt, int n_wg, hipStream_t stream);
 // Bytes of 64 records.
 size_t collide_f32_record_tile();
 size_t collide_f64_record_tile();
@@ -118,6 +122,7 @@ hipError_t launch_replay_f32(const ReplayArgs& a, hipStream_t stream);
 hipError_t launch_replay_f64(const ReplayArgs& a, hipStream_t stream);
 // Raise the kernels' dynamic LDS limit to what their static LDS leaves of
 // lds_max; returns the dynamic budgets.
+hipError_t collide_roots_lds_limit(size_t lds_max, size_t* out);
 hipError_t collide_f32_lds_limit(size_t lds_max, LdsBudget* out);
 hipError_t collide_f64_lds_limit(size_t lds_max, LdsBudget* out);
 // Waves per workgroup of the kernel (chunks are multiples of it).

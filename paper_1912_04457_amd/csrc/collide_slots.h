@@ -143,6 +143,132 @@ constexpr int kNodeBlock = 4;
 // more spilled registers in the sample loop than it saves.  One gluon cell,
 // collision term: 10^3 nodes x 1000 samples 255 -> 46 us, 16^3 x 2048 547 ->
 // 190 us, 20^3 x 256 98 -> 78 us; 7 species, 30^3 x 128 20.9 -> 19.5 ms.
+// ---------------------------------------------------------------------------
+// The paper's own parameterisation (Eq. work out delta E, Eq. delta replace):
+// momentum conservation eliminates one momentum, energy conservation fixes
+// one z component at the two roots of a quadratic, and each root carries
+// 1/|J|.  In channel order k1 + k2 <-> k3 + k4 with k1 observed (the
+// paper's p):
+//   kAlt = false, the paper's choice: k2 uniform in the box, k3x and k3y
+//     uniform, k4 = k1 + k2 - k3; E1 + E2 = E3 + E4 has the roots
+//     z = (c Qz +- W sqrt(c^2 - 4 a (W^2 - Qz^2))) / (2 (W^2 - Qz^2)) with
+//     W = E1 + E2 > 0, Q = k1 + k2, a = k3x^2 + k3y^2 + m3^2,
+//     c = W^2 + a - (Qx - k3x)^2 - (Qy - k3y)^2 - m4^2 - Qz^2; a root holds
+//     when c + 2 Qz z > 0 and E3 < W;
+//   kAlt = true, the alternative the paper tests (Sec. IV A): k4 uniform in
+//     the box, k3x and k3y uniform, k2 = k3 + k4 - k1; E3 - E2 = D = E1 - E4
+//     gives z = (-C Qz +- |D| sqrt(C^2 + 4 a (Qz^2 - D^2))) / (2 (Qz^2 - D^2))
+//     with Q = k4 - k1, C = 2 (k3x Qx + k3y Qy) + Q^2 + m2^2 - m3^2 - D^2; a
+//     root holds when (C + 2 Qz z) D < 0 and E3 > D.  Its leading
+//     coefficient has no fixed sign: the instability the paper reports.
+// The value of a root is w V5 / N |M|^2 B / ((2 pi)^5 16 E1 E2 E3 E4 |J|),
+// V5 = (2 P)^3 (2 Px) (2 Py), J the z derivative of the energy sum.  FP64
+// throughout (f from the FP64 field, FP64 atomics): the reference method.
+// Every lane draws a sample and solves for its roots; samples with a valid
+// root go to a per-wavefront queue in LDS (five 23-bit uniforms, both roots and
+// which hold: 36 B), and whenever 64 are queued (and at the end of the item)
+// the wavefront evaluates them on full lanes, the first valid root of every
+// sample and then the second of those that have two.
+// Deposits and launches as for the CM-angle samplers.  Bound by VALU issue
+// (three wavefronts per SIMD; with workgroups of four and two per SIMD, and
+// global FP64 atomics beyond 1170 points, before): 64000 gluon nodes x 100
+// samples, direct, 262 -> 195 us a call; 7 species at 15^3 x 100, symmetric,
+// 10.6 ms -> 0.78 ms, at 20^3 23.5 -> 2.7 ms, at 30^3 x 20 14.9 -> 5.7 ms.
+// ---------------------------------------------------------------------------
+constexpr double kRootNorm = 1.0 / (32.0 * kPi * kPi * kPi * kPi * kPi * 16.0);
+
+// A sample's two root candidates: z and whether each holds (bits 0 and 1).
+template <bool kAlt>
+__device__ __forceinline__ uint32_t solve_roots(const Item& it, const Grid& G, const double u[5], double zr[2]) {
+  double q[3];
+  for (int a = 0; a < 3; ++a) q[a] = fma(2.0 * G.ph[a], u[a], -G.ph[a]);
+  const double k3x = fma(2.0 * G.ph[0], u[3], -G.ph[0]);
+  const double k3y = fma(2.0 * G.ph[1], u[4], -G.ph[1]);
+  const double a3 = k3x * k3x + k3y * k3y + it.m3sq;
+  const double Eq = sqrt64(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + (kAlt ? it.m4sq : it.m2sq));
+  double Q[3], lin, half, den, W = 0.0, D = 0.0, C = 0.0;
+  bool any;
+  if (!kAlt) {
+    W = it.E1 + Eq;
+    for (int a = 0; a < 3; ++a) Q[a] = it.p1[a] + q[a];
+    const double b = (Q[0] - k3x) * (Q[0] - k3x) + (Q[1] - k3y) * (Q[1] - k3y) + it.m4sq;
+    C = W * W + a3 - b - Q[2] * Q[2];
+    den = W * W - Q[2] * Q[2];
+    const double H = C * C - 4.0 * a3 * den;
+    any = H >= 0.0 && den > 0.0;
+    lin = C * Q[2];
+    half = any ? W * sqrt64(H) : 0.0;
+  } else {
+    D = it.E1 - Eq;
+    for (int a = 0; a < 3; ++a) Q[a] = q[a] - it.p1[a];
+    C = 2.0 * (k3x * Q[0] + k3y * Q[1]) + (Q[0] * Q[0] + Q[1] * Q[1] + Q[2] * Q[2]) + it.m2sq - it.m3sq - D * D;
+    den = Q[2] * Q[2] - D * D;
+    const double H = C * C + 4.0 * a3 * den;
+    any = H >= 0.0 && den != 0.0 && D != 0.0;
+    lin = -C * Q[2];
+    half = any ? fabs(D) * sqrt64(H) : 0.0;
+  }
+  const double inv_2den = any ? rcp64(2.0 * den) : 0.0;
+  uint32_t roots = 0;
+  for (int r = 0; r < 2; ++r) {
+    const double z = (lin + (r == 0 ? half : -half)) * inv_2den;
+    const double E3 = sqrt64(a3 + z * z);
+    bool ok = any;
+    if (!kAlt) ok = ok && (C + 2.0 * Q[2] * z > 0.0) && (E3 < W);
+    else ok = ok && ((C + 2.0 * Q[2] * z) * D < 0.0) && (E3 - D > 0.0);
+    const double p3[3] = {k3x, k3y, z};
+    for (int a = 0; a < 3; ++a) {
+      const double other = kAlt ? p3[a] + Q[a] : Q[a] - p3[a];  // p2 or p4
+      ok = ok && fabs(p3[a]) <= G.ph[a] && fabs(other) <= G.ph[a];
+    }
+    zr[r] = z;
+    if (ok) roots |= 1u << r;
+  }
+  return roots;
+}
+
+// Momenta of the root z of a sample, and 1 / (E2 E3 E4 |J|) in place of the
+// prefactor's p*/(sqrt s E2); s, t, u.
+template <bool kAlt>
+__device__ __forceinline__ double root_geometry(const Item& it, const Grid& G, const double u[5], double z, Geo& g) {
+  double q[3];
+  for (int a = 0; a < 3; ++a) q[a] = fma(2.0 * G.ph[a], u[a], -G.ph[a]);
+  g.p3[0] = fma(2.0 * G.ph[0], u[3], -G.ph[0]);
+  g.p3[1] = fma(2.0 * G.ph[1], u[4], -G.ph[1]);
+  g.p3[2] = z;
+  const double Eq = sqrt64(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + (kAlt ? it.m4sq : it.m2sq));
+  const double E3 = sqrt64(g.p3[0] * g.p3[0] + g.p3[1] * g.p3[1] + it.m3sq + z * z);
+  double E2, E4, J;
+  if (!kAlt) {
+    for (int a = 0; a < 3; ++a) {
+      g.p2[a] = q[a];
+      g.p4[a] = it.p1[a] + q[a] - g.p3[a];
+    }
+    E2 = Eq;
+    E4 = sqrt64(g.p4[0] * g.p4[0] + g.p4[1] * g.p4[1] + g.p4[2] * g.p4[2] + it.m4sq);
+    J = fabs(z * rcp64(E3) - g.p4[2] * rcp64(E4));
+  } else {
+    for (int a = 0; a < 3; ++a) {
+      g.p4[a] = q[a];
+      g.p2[a] = g.p3[a] + (q[a] - it.p1[a]);
+    }
+    E4 = Eq;
+    E2 = sqrt64(g.p2[0] * g.p2[0] + g.p2[1] * g.p2[1] + g.p2[2] * g.p2[2] + it.m2sq);
+    J = fabs(g.p2[2] * rcp64(E2) - z * rcp64(E3));
+  }
+  double Pq[3], d13[3], d14[3];
+  for (int a = 0; a < 3; ++a) {
+    Pq[a] = it.p1[a] + g.p2[a];
+    d13[a] = it.p1[a] - g.p3[a];
+    d14[a] = it.p1[a] - g.p4[a];
+  }
+  const double E12 = it.E1 + E2, E13 = it.E1 - E3, E14 = it.E1 - E4;
+  g.s = E12 * E12 - (Pq[0] * Pq[0] + Pq[1] * Pq[1] + Pq[2] * Pq[2]);
+  g.t = E13 * E13 - (d13[0] * d13[0] + d13[1] * d13[1] + d13[2] * d13[2]);
+  g.u = E14 * E14 - (d14[0] * d14[0] + d14[1] * d14[1] + d14[2] * d14[2]);
+  return rcp64(E2 * E3 * E4 * J);
+}
+
 // One record of RecordArgs: three weights per position and the value, then
 // the three base nodes.
 template <typename R>
@@ -167,11 +293,14 @@ struct Record {
 };
 
 // kRec: the deposits go to A.rec instead of accumulators (see replay_kernel).
+// kRoot: 0 the CM-angle samplers, 1 the root parameterisation, 2 its
+// alternative (FP64, short form, their own queue; deposits issued at once).
 template <typename R, bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kUser, bool kShort,
-          bool kRec = false>
+          bool kRec = false, int kRoot = 0>
 __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(CollideArgs A) {
   constexpr bool kF64 = std::is_same<R, double>::value;
   static_assert(!kLearned || kShort, "the learned sampler's items are short");
+  static_assert(!kRoot || (kF64 && kShort && !kLearned && !kQueue), "the root samplers: FP64, short form");
   static_assert(!kQueue || (kSym && kAllLds && !kLearned), "the queue serves the uniform sampler, slots in LDS");
   static_assert(!kRec || (kSym && !kScale && kShort), "deposits are recorded in the short form");
   // kAllLds: every f tile and accumulator in LDS (the queue variant: every
@@ -183,6 +312,8 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   __shared__ uint32_t q_v[kQueue ? kQueueWaves : 1][3][kQueue ? kQueueLen : 1];  // 23-bit uniforms of p2
   __shared__ double q_p3[kQueue ? kQueueWaves : 1][3][kQueue ? kQueueLen : 1];
   __shared__ R q_f[kQueue ? kQueueWaves : 1][4][kQueue ? kQueueLen : 1];    // s, t, u, prefactor
+  __shared__ uint32_t r_v[kRoot ? kQueueWaves : 1][5][kRoot ? kQueueLen : 1];  // 23-bit uniforms; which roots hold
+  __shared__ double r_z[kRoot ? kQueueWaves : 1][2][kRoot ? kQueueLen : 1];    // the roots
   __shared__ double mc_wg[2];  // this workgroup's item variances and squared item sums
   __shared__ unsigned long long ok_wg;  // and its accepted samples
   __shared__ unsigned rec_n;            // kRec: records of this workgroup
@@ -256,6 +387,9 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   const int last = min(first + A.chunk_items, nodes);
   Item pair;
   if (kShort) item_pair(pair, A, ch, cell);
+  if (kRoot)  // V5 and the norm of a root's value in place of the CM form's
+    pair.coef = (A.symmetric ? ch.w : ch.sigma) * (G.Vp * (2.0 * G.ph[0]) * (2.0 * G.ph[1])) / (double)A.n_samples *
+                (kRootNorm / kNorm);
   // After the item at node p, the last of its node block (or of the chunk):
   // the wave adds the block's staged direct sums to the output, the lanes of
   // one atomic instruction covering consecutive nodes.
@@ -352,7 +486,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       const R gain = f3 * f4 * F1 * F2, loss = f1 * f2 * F3 * F4;
       const R v = wnb * (gain - loss);
       dsum += (double)v;
-      dsq = fma((double)v, (double)v, dsq);
+      if (!kRoot) dsq = fma((double)v, (double)v, dsq);  // a root sample's value is the sum over its roots
       const R vs = (wnb < R(0) ? -wnb : wnb) * (gain + loss);
       if (kScale) ssum += (double)vs;
       if (kSym) {
@@ -375,6 +509,65 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         }
       }
     };
+    if constexpr (kRoot != 0) {
+      constexpr bool kAlt = kRoot == 2;
+      // The value of one queued sample: the sum over its valid roots, with
+      // their deposits.
+      auto finish_roots = [&](int slot) {
+        const uint32_t v0 = r_v[wid][0][slot];
+        double u[5];
+        u[0] = unif23(v0 & 0x7FFFFFu);
+        for (int a = 1; a < 5; ++a) u[a] = unif23(r_v[wid][a][slot]);
+        const uint32_t roots = v0 >> 23;
+        const double z0 = r_z[wid][0][slot], z1 = r_z[wid][1][slot];
+        const double d0 = dsum;
+        double vs2 = 0.0;
+#pragma unroll 1
+        for (int r = 0; r < 2; ++r) {
+          if (r == 1 && roots != 3u) continue;
+          const double z = r == 0 && (roots & 1u) ? z0 : z1;
+          Geo g;
+          const double w = root_geometry<kAlt>(it, G, u, z, g);
+          const double m = msq_row<double, kUser>(A.msq_mask, A.msq, ch.row, g.s, g.t, g.u, it.mu);
+          finish(g, it.pref * m * w);
+        }
+        vs2 = dsum - d0;
+        dsq = fma(vs2, vs2, dsq);
+      };
+      unsigned head = 0, tail = 0;  // ring positions (wave-uniform)
+      for (int base = s_first; base < A.n_samples; base += s_step) {
+        const int s = base + lane;
+        uint32_t x0 = (uint32_t)s, x1 = (uint32_t)p1_lin, x2 = (uint32_t)cell, x3 = ((uint32_t)ch.code << 8) | 2u;
+        philox4x32_10(x0, x1, x2, x3, A.key0, A.key1);
+        double u[5], zr[2];
+        five_uniforms(x0, x1, x2, x3, u);
+        uint32_t roots = 0;
+        if (s < A.n_samples) roots = solve_roots<kAlt>(it, G, u, zr);
+        const unsigned long long mask = __ballot(roots != 0u);
+        if (roots) {
+          const unsigned slot = (tail + (unsigned)__popcll(mask & ((1ull << lane) - 1ull))) & (kQueueLen - 1);
+          r_v[wid][0][slot] = (x0 >> 9) | (roots << 23);
+          r_v[wid][1][slot] = x1 >> 9;
+          r_v[wid][2][slot] = x2 >> 9;
+          r_v[wid][3][slot] = x3 >> 9;
+          r_v[wid][4][slot] = ((x0 & 0x1FFu) << 14) | ((x1 & 0x1FFu) << 5) | ((x2 & 0x1FFu) >> 4);
+          r_z[wid][0][slot] = zr[0];
+          r_z[wid][1][slot] = zr[1];
+        }
+        tail += (unsigned)__popcll(mask);
+        if (tail - head >= (unsigned)kWave) {
+          wave_lds_sync();
+          finish_roots((head + lane) & (kQueueLen - 1));
+          head += kWave;
+          wave_lds_sync();
+        }
+      }
+      if (tail != head) {  // the last, partial batch
+        wave_lds_sync();
+        if ((unsigned)lane < tail - head) finish_roots((head + lane) & (kQueueLen - 1));
+        wave_lds_sync();
+      }
+    } else {
     auto evaluate = [&](const double u[5], R inv_q) {
       Geo g;
       if (!geometry(it, G, u, g)) return;
@@ -476,6 +669,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       }
       evaluate(u, inv_q);
     }
+    }  // CM-angle samplers
     if (!A.direct) return;
     if (kShort) {
       dsum = wave_sum_dpp(dsum);
@@ -765,17 +959,22 @@ size_t record_tile_bytes() {
   return Record<R>::kTileBytes;
 }
 
+// The launch plan of a recording launch: every workgroup's samples (per_sample
+// records each) fit in its region, and the regions in the buffers.
+inline bool record_fits(const CollideArgs& a, int n_wg, int per_sample) {
+  const int waves = slots_block(true) / kWave;
+  if (!a.symmetric || a.scale || a.split < 1 || waves % a.split) return false;
+  if (a.split > 1 && a.chunk_items > kSplitNodes) return false;
+  if (a.node_block < 1 || a.node_block > kMaxNodeBlock) return false;
+  if ((long long)a.chunk_items * a.n_samples * per_sample > a.rec.region || a.rec.region * n_wg > a.rec.capacity)
+    return false;
+  return a.rec.wg_base + (long long)n_wg <= (long long)a.G.cells * a.n_group * a.n_chunks;
+}
+
 template <typename R>
 hipError_t launch_rec(const CollideArgs& a, int n_wg, hipStream_t stream) {
   if (n_wg <= 0) return hipSuccess;
-  const int waves = slots_block(true) / kWave;
-  if (!a.symmetric || a.scale || a.split < 1 || waves % a.split) return hipErrorInvalidValue;
-  if (a.split > 1 && a.chunk_items > kSplitNodes) return hipErrorInvalidValue;
-  if (a.node_block < 1 || a.node_block > kMaxNodeBlock) return hipErrorInvalidValue;
-  // every workgroup's samples fit in its region and the regions in the buffers
-  if ((long long)a.chunk_items * a.n_samples > a.rec.region || a.rec.region * n_wg > a.rec.capacity)
-    return hipErrorInvalidValue;
-  if (a.rec.wg_base + (long long)n_wg > (long long)a.G.cells * a.n_group * a.n_chunks) return hipErrorInvalidValue;
+  if (!record_fits(a, n_wg, 1)) return hipErrorInvalidValue;
   if (a.learned) SlotsVariants<R>::template launch_rec<true>(a, dim3((unsigned)n_wg), stream);
   else SlotsVariants<R>::template launch_rec<false>(a, dim3((unsigned)n_wg), stream);
   return hipGetLastError();
@@ -792,32 +991,96 @@ hipError_t launch_replay(const ReplayArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Each variant may use what its static LDS leaves of lds_max.  Raising the
+// A kernel may use what its static LDS leaves of lds_max.  Raising the
 // per-kernel dynamic limit is only needed (and only accepted) above the
 // runtime's default; after a refusal the budget is the limit in force.
+inline hipError_t raise_lds_limit(const void* fn, size_t lds_max, size_t* budget) {
+  hipFuncAttributes attr;
+  if (hipFuncGetAttributes(&attr, fn) != hipSuccess) return hipGetLastError();
+  const size_t stat = attr.sharedSizeBytes;
+  size_t want = lds_max > stat ? lds_max - stat : 0;
+  size_t have = attr.maxDynamicSharedSizeBytes > 0 ? (size_t)attr.maxDynamicSharedSizeBytes : 0;
+  if (have < want) {
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)want) == hipSuccess)
+      have = want;
+    else
+      (void)hipGetLastError();
+  }
+  *budget = std::min(*budget, std::min(have, want));
+  return hipSuccess;
+}
+
 template <typename R>
 hipError_t slots_lds_limit(size_t lds_max, LdsBudget* out) {
   size_t budget[5] = {lds_max, lds_max, lds_max, lds_max, lds_max};
-  for (const auto& f : SlotsVariants<R>::all()) {
-    hipFuncAttributes attr;
-    if (hipFuncGetAttributes(&attr, f.fn) != hipSuccess) return hipGetLastError();
-    const size_t stat = attr.sharedSizeBytes;
-    size_t want = lds_max > stat ? lds_max - stat : 0;
-    size_t have = attr.maxDynamicSharedSizeBytes > 0 ? (size_t)attr.maxDynamicSharedSizeBytes : 0;
-    if (have < want) {
-      if (hipFuncSetAttribute(f.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)want) == hipSuccess)
-        have = want;
-      else
-        (void)hipGetLastError();
-    }
-    budget[f.group] = std::min(budget[f.group], std::min(have, want));
-  }
+  for (const auto& f : SlotsVariants<R>::all())
+    if (const hipError_t e = raise_lds_limit(f.fn, lds_max, &budget[f.group])) return e;
   out->plain = budget[0];
   out->learned = budget[1];
   out->queue[0] = std::is_same<R, double>::value ? 0 : budget[2];  // FP64 has the short form only
   out->queue[1] = budget[3];
   out->replay = budget[4];
   return hipSuccess;
+}
+
+// The root samplers' kernel variants: [symmetric][scale][user terms].
+template <int kRoot>
+using RootFn = void (*)(CollideArgs);
+template <int kRoot>
+void root_variants(RootFn<kRoot> out[2][2][2]) {
+  out[0][0][0] = collide_slots_kernel<double, false, false, true, false, false, false, true, false, kRoot>;
+  out[0][0][1] = collide_slots_kernel<double, false, false, true, false, false, true, true, false, kRoot>;
+  out[0][1][0] = collide_slots_kernel<double, false, true, true, false, false, false, true, false, kRoot>;
+  out[0][1][1] = collide_slots_kernel<double, false, true, true, false, false, true, true, false, kRoot>;
+  out[1][0][0] = collide_slots_kernel<double, true, false, true, false, false, false, true, false, kRoot>;
+  out[1][0][1] = collide_slots_kernel<double, true, false, true, false, false, true, true, false, kRoot>;
+  out[1][1][0] = collide_slots_kernel<double, true, true, true, false, false, false, true, false, kRoot>;
+  out[1][1][1] = collide_slots_kernel<double, true, true, true, false, false, true, true, false, kRoot>;
+}
+
+template <int kRoot>
+hipError_t launch_roots(const CollideArgs& a, hipStream_t stream) {
+  const int n_acc = a.symmetric ? std::min(a.slot_hi - a.slot_lo, a.lds_acc) : 0;
+  if (a.symmetric && n_acc != a.slot_hi - a.slot_lo) return hipErrorInvalidValue;
+  const int waves = kSlotThreads / kWave;
+  if (a.split < 1 || waves % a.split || (a.split > 1 && a.chunk_items > kSplitNodes)) return hipErrorInvalidValue;
+  if (a.node_block < 1 || a.node_block > kMaxNodeBlock) return hipErrorInvalidValue;
+  const long long blocks = (long long)a.G.cells * a.n_group * a.n_chunks;
+  if (blocks <= 0) return hipSuccess;
+  RootFn<kRoot> fns[2][2][2];
+  root_variants<kRoot>(fns);
+  hipLaunchKernelGGL(fns[a.symmetric ? 1 : 0][a.scale ? 1 : 0][a.msq_mask ? 1 : 0], dim3((unsigned)blocks),
+                     dim3(kSlotThreads), (size_t)n_acc * a.win_n * sizeof(double), stream, a);
+  return hipGetLastError();
+}
+
+template <int kRoot>
+hipError_t launch_roots_rec(const CollideArgs& a, int n_wg, hipStream_t stream) {
+  if (n_wg <= 0) return hipSuccess;
+  if (!record_fits(a, n_wg, 2)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)n_wg), block(kSlotThreads);
+  if (a.msq_mask)
+    hipLaunchKernelGGL((collide_slots_kernel<double, true, false, true, false, false, true, true, true, kRoot>), grid,
+                       block, 0, stream, a);
+  else
+    hipLaunchKernelGGL((collide_slots_kernel<double, true, false, true, false, false, false, true, true, kRoot>), grid,
+                       block, 0, stream, a);
+  return hipGetLastError();
+}
+
+template <int kRoot>
+hipError_t roots_lds_limit_of(size_t lds_max, size_t* out) {
+  RootFn<kRoot> fns[2][2][2];
+  root_variants<kRoot>(fns);
+  for (int i = 0; i < 8; ++i)
+    if (const hipError_t e = raise_lds_limit((const void*)fns[i >> 2][(i >> 1) & 1][i & 1], lds_max, out)) return e;
+  return hipSuccess;
+}
+
+inline hipError_t roots_lds_limit(size_t lds_max, size_t* out) {
+  *out = lds_max;
+  const hipError_t e = roots_lds_limit_of<1>(lds_max, out);
+  return e != hipSuccess ? e : roots_lds_limit_of<2>(lds_max, out);
 }
 
 }  // namespace

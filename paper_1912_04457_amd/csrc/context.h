@@ -27,9 +27,9 @@ qgbe_status hip_fail(hipError_t e, const char* what);
 struct Group {
   int start, count;   // range in the group index array
   int nslot;          // distinct species at positions 2..4
-  int lds_acc[2];     // FP64 accumulators staged in LDS  [uniform, learned sampler]
-  int lds_tiles[2];   // FP32 f tiles staged in LDS       [uniform, learned sampler]; none in FP64
-  int win[2];         // nodes per accumulator window (= nodes unless one slot's FP64
+  int lds_acc[3];     // FP64 accumulators staged in LDS  [uniform, learned, root samplers]
+  int lds_tiles[3];   // FP32 f tiles staged in LDS; none in FP64 and for the root samplers
+  int win[3];         // nodes per accumulator window (= nodes unless one slot's FP64
                       // accumulators exceed LDS; then one launch per window and slot)
   bool queue[2];      // the uniform sampler's compacting variant fits [long, short items]
 };
@@ -66,14 +66,14 @@ struct qgbe_ctx {
   std::vector<qgbe::Channel> chans;
   std::vector<int> group_index;
   std::vector<qgbe::Group> groups;
-  qgbe::Replay replay[2];          // [uniform, learned sampler]
+  qgbe::Replay replay[3];          // [uniform, learned, root samplers]
   unsigned char* d_rec = nullptr;  // record buffers, an allocation of their own (NULL: none, every launch draws its samples again)
   qgbe::RecordArgs rec{};          // their parts
   long long rec_wgs = 0;           // counters in rec.count
+  size_t rec_bytes = 0;            // of the tiles
   char* d_arena = nullptr;         // the allocation that holds the buffers below unless noted
   qgbe::Channel* d_chans = nullptr;
   int* d_groups = nullptr;
-  int* d_all = nullptr;            // identity channel list (root kernel)
   double* d_f = nullptr;
   double* d_f_next = nullptr;
   float* d_f32 = nullptr;
@@ -122,6 +122,11 @@ size_t field_len(const qgbe_ctx* c);
 qgbe_status validate(const qgbe_grid_desc* d);
 void make_grid(const qgbe_grid_desc* d, Grid& G);
 void plan_groups(qgbe_ctx* c);
+// Entries of the group index array: the groups, the replay lists and their
+// matches.
+constexpr size_t kMaxGroupIndex = 4 * (size_t)kMaxChannels + 3 * (size_t)kSpecies * kMaxMatches;
+// Record buffers in given memory (none if they would be too small to pay).
+void carve_records(qgbe_ctx* c, unsigned char* p, size_t bytes);
 // Enqueue the collision kernels of one collision term, accumulating into A
 // (zeroed by the caller); zeroes the per-launch totals first.
 qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, double* scale, double* items);

@@ -51,6 +51,8 @@ qgbe_status setup(int device, DeviceState** out) {
     int n_cu = 0;
     if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && n_cu > 0)
       s.n_cu = n_cu;
+    for (LdsBudget& b : s.lds)
+      HIP_TRY(collide_roots_lds_limit((size_t)std::max(lds_max, 0), &b.roots), "raise the dynamic LDS limit");
     s.ptr = static_cast<unsigned char*>(p);
     s.ready = true;
   }
@@ -112,9 +114,7 @@ qgbe_status qgbe_collision_term_noalloc(const qgbe_grid_desc* desc, const double
   const bool fp32 = desc->precision == QGBE_FP32 && sampler == QGBE_SAMPLER_UNIFORM;
   Carve cv{dev->ptr};
   c.d_chans = cv.take<Channel>(kMaxChannels);
-  c.group_index.resize(std::min<size_t>(c.group_index.size(), kMaxChannels));  // no record buffers, no replay lists
-  c.d_groups = cv.take<int>(kMaxChannels);
-  c.d_all = cv.take<int>(kMaxChannels);
+  c.d_groups = cv.take<int>(kMaxGroupIndex);
   const size_t table_bytes = cv.used;
   c.d_mass2 = cv.take<double>((size_t)kSpecies * c.G.cells);
   c.d_mass_part = cv.take<double>(mass_scratch(c.G));
@@ -128,9 +128,10 @@ qgbe_status qgbe_collision_term_noalloc(const qgbe_grid_desc* desc, const double
   if (cv.used > kScratchBytes)
     return fail(QGBE_EINVAL, "grid needs " + std::to_string(cv.used) + " bytes of scratch, more than the " +
                                  std::to_string(kScratchBytes) + " of qgbe_collision_term_noalloc");
+  carve_records(&c, dev->ptr + cv.used, kScratchBytes - cv.used);  // what is left
   c.d_f = const_cast<double*>(f);  // read only: masses and the collision kernels
 
-  // Channel table, group lists and identity list, uploaded when they differ
+  // Channel table and group lists, uploaded when they differ
   // from what this device's scratch holds and waited for; the host record of
   // what the scratch holds changes only after the upload has completed, so a
   // failed upload is retried by the next call.
@@ -138,8 +139,6 @@ qgbe_status qgbe_collision_term_noalloc(const qgbe_grid_desc* desc, const double
   std::memcpy(tab.data(), c.chans.data(), c.chans.size() * sizeof(Channel));
   std::memcpy(tab.data() + ((unsigned char*)c.d_groups - dev->ptr), c.group_index.data(),
               c.group_index.size() * sizeof(int));
-  int* all = reinterpret_cast<int*>(tab.data() + ((unsigned char*)c.d_all - dev->ptr));
-  for (int i = 0; i < c.nch; ++i) all[i] = i;
   {
     std::lock_guard<std::mutex> lock(g_mu);
     if (dev->table != tab) {

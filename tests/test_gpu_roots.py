@@ -113,3 +113,30 @@ def test_stability_spread_of_the_two_eliminations():
     # the three estimate the same step
     for k in (qgbe.SAMPLER_ROOTS, qgbe.SAMPLER_ROOTS_ALT):
         assert abs(mean[k] - mean[0]) < 5.0 * (spread[k] + spread[0]) / np.sqrt(24)
+
+
+@pytest.mark.parametrize("sampler", [qgbe.SAMPLER_ROOTS, qgbe.SAMPLER_ROOTS_ALT])
+@pytest.mark.parametrize("n_x,n_p,mask,N,precision", [((1, 1, 1), (24, 25, 24), 1 << 6, 70, qgbe.FP64),
+                                                      ((2, 1, 1), (16, 17, 18), 0x49, 20, qgbe.FP32),
+                                                      ((1, 1, 1), (9, 8, 7), 1 << 6, 600, qgbe.FP64)],
+                         ids=["windows", "slots_f32_context", "shared_nodes"])
+def test_roots_lds_plans(O, sampler, n_x, n_p, mask, N, precision):
+    """Symmetric deposits in LDS accumulators: grids that take several launches
+    (deposits recorded and replayed; with the scale output, the samples drawn
+    again in every launch) and waves that share a node."""
+    _case(f"roots plans sampler={sampler} {n_x} {n_p} mask={mask:#x} N={N}")
+    g = _grid(O, n_x, n_p, mask)
+    f = W.random_f(33, g.cells, g.nodes, species_mask=mask) * 0.6
+    with _solver(g, precision) as s:
+        s.set_f(f)
+        A, _, I, st = s.collision(N, sampler=sampler, items=True)
+        A2, _, I2, st2 = s.collision(N, sampler=sampler, scale=True, items=True)
+        m = s.masses()
+    A_ref, S_ref, I_ref = O.collision(g, f, m, SEED, 0, N, estimator=EST[sampler], want_items=True)
+    for a in (A, A2):
+        assert np.all(np.abs(a - A_ref) <= 1e-10 * S_ref + 1e-300)
+    # the same samples by two routes: sums in another order
+    assert np.abs(I - I2).max() <= 1e-12 * np.abs(I_ref).max()
+    assert st.n_accepted == st2.n_accepted > 0
+    for cell in range(g.cells):
+        assert abs(A[:, cell].sum()) <= 1e-13 * S_ref[:, cell].sum()
