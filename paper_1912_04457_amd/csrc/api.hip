@@ -694,12 +694,7 @@ void qgbe_destroy(qgbe_ctx* c) {
   (void)hipFree(c->d_feat);
   (void)hipFree(c->d_mix_on);
   (void)hipFree(c->d_mass7);
-  {
-    MlpState& m = c->mlp;
-    void* bufs[] = {m.params, m.m, m.v, m.grad, m.pb, m.X, m.Xb, m.Z1, m.H1b, m.Z2, m.H2b, m.Y, m.dY, m.dYb,
-                    m.dH, m.dZ, m.dZb, m.yw, m.scalars};
-    for (void* b : bufs) (void)hipFree(b);
-  }
+  (void)hipFree(c->mlp.arena);
   for (auto& e : c->ev)
     if (e) (void)hipEventDestroy(e);
   delete c;

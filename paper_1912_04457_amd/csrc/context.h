@@ -43,17 +43,18 @@ struct Replay {
   int match_at = 0;                // the lists in the group index array, kMaxMatches apart
 };
 
-// Device buffers of the proposal network (allocated on first use).
+// Device buffers of the proposal network (one allocation, on first use).
 struct MlpState {
   bool ready = false;
   bool has_weights = false;
   int adam_t = 0;
+  char* arena = nullptr;
   float *params = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
-  __bf16* pb = nullptr;
-  float *X = nullptr, *Z1 = nullptr, *Z2 = nullptr, *Y = nullptr, *dY = nullptr, *dH = nullptr, *dZ = nullptr;
-  float* yw = nullptr;
-  __bf16 *Xb = nullptr, *H1b = nullptr, *H2b = nullptr, *dYb = nullptr, *dZb = nullptr;
-  double* scalars = nullptr;   // [0] loss, [1] weight sum
+  __bf16 *pb = nullptr, *pbt = nullptr;   // BF16 weights, row-major and transposed
+  float *X = nullptr, *yw = nullptr, *Y = nullptr;  // staging of host buffers
+  float* part = nullptr;                  // gradient slices
+  double* loss_part = nullptr;
+  double* scalars = nullptr;              // [0] loss, [1] weight sum
 };
 
 }  // namespace qgbe

@@ -1,5 +1,5 @@
-// Launch interface of the proposal network kernels (BF16 MFMA GEMMs and the
-// mixture head).
+// Launch interface of the proposal network kernels (BF16 matrix products and
+// the mixture head).
 #pragma once
 
 #include "qgbe_common.h"
@@ -22,33 +22,52 @@ constexpr int kOffW3 = kOffB2 + kMlpHidden;
 constexpr int kOffB3 = kOffW3 + kMlpHidden * kMlpOut;
 constexpr int kMlpParams = kOffB3 + kMlpOut;
 
-struct GemmArgs {
-  int M, N, K;
-  const __bf16* A;
-  long long ars, acs;      // A(m,k) = A[m*ars + k*acs]
-  const __bf16* B;
-  long long brs, bcs;      // B(k,n) = B[k*brs + n*bcs]
-  const float* bias;       // [N] or null
-  int silu;                // apply SiLU in the epilogue
-  int accumulate;          // add the existing Cf
-  float* Cz;               // pre-activation (FP32) or null
-  float* Cf;               // activation (FP32) or null
-  __bf16* Cb;              // activation (BF16) or null
-  long long ldc;
-  int k_chunk;             // > 0: split K into chunks of this many (a multiple of 32), one
-                           // workgroup per (tile, chunk), partial products added into Cf with
-                           // FP32 atomics (Cf zeroed or holding what to add to; no epilogue)
+// BF16 weights transposed to [out][in], the head's 88 rows padded to 96
+constexpr int kOffT1 = 0;
+constexpr int kOffT2 = kOffT1 + kMlpHidden * kMlpIn;
+constexpr int kOffT3 = kOffT2 + kMlpHidden * kMlpHidden;
+constexpr int kMlpParamsT = kOffT3 + 96 * kMlpHidden;
+
+constexpr int kMlpTileRows = 64;    // rows a workgroup takes at a time
+constexpr int kMlpMaxSlices = 256;  // gradient slices of a batch, one per workgroup
+
+struct MlpTileArgs {
+  long long rows;
+  const float* X;          // row r: X[i * xs ..+7], i = idx ? idx[r] : r
+  long long xs;
+  const float* yw;         // gradient: row r: logits (5) and weight at yw[i * ys ..+5]
+  long long ys;
+  const int* idx;          // optional row order
+  const __bf16* pb;        // weights, row-major
+  const __bf16* pbt;       // weights, transposed
+  const float* P;          // FP32 parameters (biases)
+  float* Y;                // forward: head [rows][88]
+  const double* wsum;      // gradient: sum of the rows' weights
+  float* part;             // gradient: [slices][kMlpParams]
+  double* loss_part;       // gradient: [slices]
 };
 
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t st);
-hipError_t launch_f32_to_bf16(const float* src, __bf16* dst, size_t n, hipStream_t st);
-hipError_t launch_silu_backward(const float* dH, const float* Z, float* dZ, __bf16* dZb, size_t n, hipStream_t st);
-hipError_t launch_colsum(const float* M, int rows, int cols, float* out, hipStream_t st);
-hipError_t launch_sum(const float* w, int stride, int rows, double* out, hipStream_t st);
-hipError_t launch_nll(const float* Y, const float* yw, int yws, int rows, const double* wsum, float* dY, __bf16* dYb,
-                      double* loss, hipStream_t st);
-hipError_t launch_adam(float* p, const float* g, float* m, float* v, __bf16* pb, int n, float lr, float b1, float b2,
-                       float eps, int t, hipStream_t st);
+struct MlpReduceArgs {
+  const float* part;
+  const double* loss_part;
+  int n_part;
+  double* loss;            // the batch's loss is added
+  float* grad;             // without adam: the gradient
+  int adam;                // an Adam step in place of it
+  float *p, *m, *v;
+  __bf16 *pb, *pbt;
+  float lr, b1, b2, eps, c1, c2;  // c1 = 1 - b1^t, c2 = 1 - b2^t
+};
+
+size_t mlp_grad_slices(long long rows);
+hipError_t raise_mlp_lds_limit();
+hipError_t launch_mlp_forward(const MlpTileArgs& g, hipStream_t st);
+hipError_t launch_mlp_grad(const MlpTileArgs& g, hipStream_t st);
+hipError_t launch_reduce_grad(const MlpReduceArgs& a, hipStream_t st);
+hipError_t launch_refresh_weights(const float* p, __bf16* pb, __bf16* pbt, hipStream_t st);
+// out[b] = sum of w[i * stride] over the rows of batch b
+hipError_t launch_weight_sums(const float* w, long long stride, const int* idx, long long n, int batch, double* out,
+                              hipStream_t st);
 // Conditioning features of every (channel, node) row from the cell-averaged
 // masses; mass7 receives those 7 averages.
 hipError_t launch_features(const Grid& G, const Channel* chans, int nch, const double* mass2, double* mass7, float* X,
@@ -57,6 +76,5 @@ hipError_t launch_features(const Grid& G, const Channel* chans, int nch, const d
 // sigma in the layout of qgbe_set_proposal_table), activations kept on chip.
 hipError_t launch_mlp_table(const float* X, int rows, const __bf16* pb, const float* P, float alpha, uint32_t* thr,
                             float* mu, float* sigma, hipStream_t st);
-hipError_t launch_gather(const float* rows, const int* idx, int n, float* X, __bf16* Xb, float* yw, hipStream_t st);
 
 }  // namespace qgbe

@@ -2,10 +2,11 @@
 //
 // x (8) -> Linear 8x128 -> SiLU -> Linear 128x128 -> SiLU -> Linear 128x88
 // (head: 8 mixture logits, 8x5 locations, 8x5 log scales in logit space).
-// Every product, forward and backward, is a BF16 x BF16 -> FP32 MFMA GEMM
-// (v_mfma_f32_16x16x32_bf16) with strided operands, so transposed operands of
-// the backward pass need no copies.  Master weights and Adam moments are FP32.
+// Every product, forward and backward, is BF16 x BF16 -> FP32 on the matrix
+// cores (v_mfma_f32_16x16x32_bf16).  Master weights and Adam moments are FP32.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "mlp.h"
 
@@ -15,9 +16,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-constexpr int kTile = 64;    // block tile (M and N)
 constexpr int kKStep = 32;   // K per MFMA
-constexpr int kThreads = 256;
 
 __device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 __device__ __forceinline__ float dsilu_f(float z) {
@@ -25,181 +24,374 @@ __device__ __forceinline__ float dsilu_f(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// C[M x N] = A[M x K] B[K x N] (+ bias[N]); A(m,k) = A[m*ars + k*acs],
-// B(k,n) = B[k*brs + n*bcs].  Epilogue: z -> Cz (FP32, optional),
-// act(z) -> Cb (BF16, optional) and/or Cf (FP32, optional), all with ldc.
-// Wave w of the block owns the 32x32 sub-tile (w/2, w%2): 2x2 MFMA tiles.
-__global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs g) {
-  __shared__ __bf16 As[kTile][kKStep];   // [m][k]
-  __shared__ __bf16 Bs[kTile][kKStep];   // [n][k] (transposed for k-contiguous reads)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = blockIdx.y * kTile, n0 = blockIdx.x * kTile;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const bool split = g.k_chunk > 0;
-  const int k_begin = split ? blockIdx.z * g.k_chunk : 0;
-  const int k_end = split ? min(g.K, k_begin + g.k_chunk) : g.K;
-  floatx4 acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = k_begin; k0 < k_end; k0 += kKStep) {
-    // stage the tiles (zero outside the matrices)
-    for (int e = tid; e < kTile * kKStep; e += kThreads) {
-      const int r = e / kKStep, k = e % kKStep;
-      const int gm = m0 + r, gn = n0 + r, gk = k0 + k;
-      As[r][k] = (gm < g.M && gk < k_end) ? g.A[(size_t)gm * g.ars + (size_t)gk * g.acs] : (__bf16)0.0f;
-      Bs[r][k] = (gn < g.N && gk < k_end) ? g.B[(size_t)gk * g.brs + (size_t)gn * g.bcs] : (__bf16)0.0f;
+// ---------------------------------------------------------------------------
+// The network on tiles of 64 rows: forward, and with kGrad the mixture head's
+// weighted NLL and the backward pass, one kernel for what are 14 products and
+// elementwise passes.  A workgroup of 16 waves takes a tile through every
+// layer; the activations and their gradients stay in LDS (150 of the 160 KB),
+// row-major where they are the left operand of a product over features and
+// transposed where they enter a product over rows, so that every MFMA operand
+// is one 16-byte read.  Wave w owns rows 16 (w % 4).. and the feature tiles 2
+// (w / 4) and 2 (w / 4) + 1 of each layer and keeps their pre-activations in
+// registers for the backward pass; the weight gradients accumulate in
+// registers over the workgroup's tiles and go to its own slice of `part`,
+// which reduce_grad_kernel sums in a fixed order.  Weights are read from L2:
+// pb is row-major [in][out] (left factor of the backward products), pbt its
+// transpose [out][in].  A batch of 4096 rows is 64 workgroups and bound by the
+// chain of its phases: 196 us in 21 launches before, see the figures at
+// reduce_grad_kernel.
+// Per row the arithmetic is that of the separate products: BF16 operands, FP32
+// accumulation over K in steps of 32, FP32 bias, activations and head.
+// ---------------------------------------------------------------------------
+constexpr int kRows = kMlpTileRows;
+constexpr int kHidPad = kMlpHidden + 8;   // row strides that spread the LDS banks
+constexpr int kRowPad = kRows + 8;
+constexpr int kOut16 = 96;                // head columns rounded up to MFMA tiles
+constexpr int kOutPad16 = kOut16 + 8;
+constexpr int kHeadPad = kMlpOut + 4;
+
+struct TileLds {
+  __bf16 Xb[kRows][kKStep + 8];           // inputs, k >= 8 zero
+  __bf16 H1[kRows][kHidPad];              // in the backward pass dZ2
+  __bf16 H2[kRows][kHidPad];
+};
+struct GradLds {
+  __bf16 XT[16][kRowPad];                 // rows >= 8 zero
+  __bf16 H1T[kMlpHidden][kRowPad];
+  __bf16 H2T[kMlpHidden][kRowPad];
+  __bf16 dYb[kRows][kOutPad16];           // columns >= 88 zero
+  __bf16 dYT[kOut16][kRowPad];
+  __bf16 dZ2T[kMlpHidden][kRowPad];
+  float Y[kRows][kHeadPad];               // head, then its gradient
+  float yw[kRows][kMixD + 1];
+  float colsum[2][4][kMlpHidden];         // per 16 rows: dZ2, dZ1
+  float colsum3[8][kMlpOut];              // per 8 rows: dY
+  double loss[8];
+};
+static_assert(sizeof(TileLds) + sizeof(GradLds) <= 160 * 1024, "one workgroup's LDS");
+
+// A fragment: lane l holds row l % 16, k = 8 (l / 16)..+7 of a row-major tile.
+template <typename T>
+__device__ __forceinline__ bf16x8 frag(const T* row, int k) { return *(const bf16x8*)(row + k); }
+
+__device__ __forceinline__ floatx4 mfma(bf16x8 a, bf16x8 b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+template <bool kGrad>
+__global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  TileLds& L = *reinterpret_cast<TileLds*>(lds_raw);
+  GradLds& D = *reinterpret_cast<GradLds*>(lds_raw + sizeof(TileLds));  // kGrad only
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int r16 = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
+  const int m0 = 16 * (w & 3), n0 = 32 * (w >> 2);  // this wave's rows and first feature column of a layer
+  const bf16x8 zero8 = {};
+  const floatx4 zero4 = floatx4{0.f, 0.f, 0.f, 0.f};
+  const __bf16 *T1 = g.pbt + kOffT1, *T2 = g.pbt + kOffT2, *T3 = g.pbt + kOffT3;
+  floatx4 dw1 = zero4, dw2[4] = {zero4, zero4, zero4, zero4}, dw3[3] = {zero4, zero4, zero4};
+  float db = 0.f, db3 = 0.f;  // thread n < 128: bias gradient 2, n in 128..255: bias gradient 1; n < 88: head
+  double loss = 0.0;
+  // the paddings that no tile writes
+  for (int e = tid; e < kRows * kKStep; e += 1024) L.Xb[e / kKStep][e % kKStep] = (__bf16)0.0f;
+  if (kGrad) {
+    for (int e = tid; e < 8 * kRows; e += 1024) D.XT[8 + e / kRows][e % kRows] = (__bf16)0.0f;
+    for (int e = tid; e < 8 * kRows; e += 1024) {
+      D.dYb[e % kRows][kMlpOut + e / kRows] = (__bf16)0.0f;
+      D.dYT[kMlpOut + e / kRows][e % kRows] = (__bf16)0.0f;
+    }
+  }
+  __syncthreads();
+  const long long n_tiles = (g.rows + kRows - 1) / kRows;
+  for (long long tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    const long long row0 = tile * kRows;
+    // inputs; rows beyond the last are zero with weight zero
+    for (int e = tid; e < kRows * kMlpIn; e += 1024) {
+      const int r = e / kMlpIn, c = e % kMlpIn;
+      float x = 0.f;
+      if (row0 + r < g.rows) x = g.X[(g.idx ? (long long)g.idx[row0 + r] : row0 + r) * g.xs + c];
+      L.Xb[r][c] = (__bf16)x;
+      if (kGrad) D.XT[c][r] = (__bf16)x;
+    }
+    if (kGrad)
+      for (int e = tid; e < kRows * (kMixD + 1); e += 1024) {
+        const int r = e / (kMixD + 1), c = e % (kMixD + 1);
+        float x = 0.f;
+        if (row0 + r < g.rows) x = g.yw[(g.idx ? (long long)g.idx[row0 + r] : row0 + r) * g.ys + c];
+        D.yw[r][c] = x;
+      }
+    __syncthreads();
+    // layer 1 (K = 8 in one step, zeros beyond)
+    floatx4 z1[2], z2[2];
+    {
+      const bf16x8 a = frag(L.Xb[m0 + r16], kq);
+      for (int j = 0; j < 2; ++j) {
+        const int n = n0 + 16 * j + r16;
+        z1[j] = mfma(a, kq == 0 ? frag(T1 + n * kMlpIn, 0) : zero8, zero4);
+        const float bias = g.P[kOffB1 + n];
+        for (int q = 0; q < 4; ++q) {
+          z1[j][q] += bias;
+          const __bf16 h = (__bf16)silu_f(z1[j][q]);
+          L.H1[m0 + rq + q][n] = h;
+          if (kGrad) D.H1T[n][m0 + rq + q] = h;
+        }
+      }
     }
     __syncthreads();
-    // operand fragments: lane l holds row (l%16) and k = 8*(l/16) .. +7
-    const int r = lane & 15, kq = (lane >> 4) * 8;
-    bf16x8 a[2], b[2];
-    for (int i = 0; i < 2; ++i)
-      for (int q = 0; q < 8; ++q) {
-        a[i][q] = As[wm + i * 16 + r][kq + q];
-        b[i][q] = Bs[wn + i * 16 + r][kq + q];
+    // layer 2
+    {
+      bf16x8 a[4];
+      for (int ks = 0; ks < 4; ++ks) a[ks] = frag(L.H1[m0 + r16], ks * kKStep + kq);
+      for (int j = 0; j < 2; ++j) {
+        const int n = n0 + 16 * j + r16;
+        z2[j] = zero4;
+        for (int ks = 0; ks < 4; ++ks) z2[j] = mfma(a[ks], frag(T2 + n * kMlpHidden, ks * kKStep + kq), z2[j]);
+        const float bias = g.P[kOffB2 + n];
+        for (int q = 0; q < 4; ++q) {
+          z2[j][q] += bias;
+          const __bf16 h = (__bf16)silu_f(z2[j][q]);
+          L.H2[m0 + rq + q][n] = h;
+          if (kGrad) D.H2T[n][m0 + rq + q] = h;
+        }
       }
-    for (int i = 0; i < 2; ++i)
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+    // head: six column tiles, the last one half used
+    if (n0 < kOut16) {
+      bf16x8 a[4];
+      for (int ks = 0; ks < 4; ++ks) a[ks] = frag(L.H2[m0 + r16], ks * kKStep + kq);
+      for (int j = 0; j < 2; ++j) {
+        const int n = n0 + 16 * j + r16;
+        floatx4 y = zero4;
+        for (int ks = 0; ks < 4; ++ks) y = mfma(a[ks], frag(T3 + n * kMlpHidden, ks * kKStep + kq), y);
+        if (n < kMlpOut) {
+          const float bias = g.P[kOffB3 + n];
+          for (int q = 0; q < 4; ++q) {
+            const int r = m0 + rq + q;
+            if (kGrad) D.Y[r][n] = y[q] + bias;
+            else if (row0 + r < g.rows) g.Y[(row0 + r) * kMlpOut + n] = y[q] + bias;
+          }
+        }
+      }
+    }
+    if (!kGrad) {
+      __syncthreads();  // the next tile's inputs
+      continue;
+    }
+    __syncthreads();
+    // NLL of the mixture head and its gradient: eight lanes per row, one per
+    // component; the sums over components in component order
+    if (w < 8) {
+      const int r = tid >> 3, k = tid & 7;
+      float* h = D.Y[r];
+      const float s = row0 + r < g.rows ? (float)((double)D.yw[r][kMixD] / *g.wsum) : 0.f;
+      const float hk = h[k];
+      float mx = -INFINITY;
+      for (int j = 0; j < kMixK; ++j) mx = fmaxf(mx, __shfl(hk, j, 8));
+      const float ea = __expf(hk - mx);
+      float se = 0.f;
+      for (int j = 0; j < kMixK; ++j) se += __shfl(ea, j, 8);
+      const float lse_a = mx + __logf(se);
+      float l = hk - lse_a, z[kMixD], lr[kMixD];
+      for (int e = 0; e < kMixD; ++e) {
+        lr[e] = h[kMixK + kMixK * kMixD + k * kMixD + e];
+        const float ls = fminf(fmaxf(lr[e], kLsMin), kLsMax);
+        const float zz = (D.yw[r][e] - h[kMixK + k * kMixD + e]) * __expf(-ls);
+        z[e] = zz;
+        l += -0.5f * zz * zz - ls - 0.91893853320467274f;
+      }
+      float m2 = -INFINITY;
+      for (int j = 0; j < kMixK; ++j) m2 = fmaxf(m2, __shfl(l, j, 8));
+      const float eb = __expf(l - m2);
+      float se2 = 0.f;
+      for (int j = 0; j < kMixK; ++j) se2 += __shfl(eb, j, 8);
+      const float lm = m2 + __logf(se2);
+      double part = k == 0 ? -(double)s * (double)lm : 0.0;
+      const float resp = __expf(l - lm), pi = __expf(hk - lse_a);
+      const auto put = [&](int c, float v) {
+        h[c] = v;
+        D.dYb[r][c] = (__bf16)v;
+        D.dYT[c][r] = (__bf16)v;
+      };
+      put(k, -s * (resp - pi));
+      for (int e = 0; e < kMixD; ++e) {
+        const float ls = fminf(fmaxf(lr[e], kLsMin), kLsMax);
+        const float gmu = -s * resp * z[e] * __expf(-ls);
+        float gls = -s * resp * (z[e] * z[e] - 1.0f);
+        if (lr[e] < kLsMin || lr[e] > kLsMax) gls = 0.f;
+        put(kMixK + k * kMixD + e, gmu);
+        put(kMixK + kMixK * kMixD + k * kMixD + e, gls);
+      }
+      for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
+      if (lane == 0) D.loss[w] = part;
+    }
+    __syncthreads();
+    // dZ2 = (dY W3^T) silu'(Z2); dW3 = H2^T dY; column sums of dY
+    {
+      bf16x8 a[3];
+      for (int ks = 0; ks < 3; ++ks) a[ks] = frag(D.dYb[m0 + r16], ks * kKStep + kq);
+      for (int j = 0; j < 2; ++j) {
+        const int n = n0 + 16 * j + r16;
+        const __bf16* wr = g.pb + kOffW3 + n * kMlpOut;
+        floatx4 dh = zero4;
+        for (int ks = 0; ks < 3; ++ks)
+          dh = mfma(a[ks], ks * kKStep + kq < kMlpOut ? frag(wr, ks * kKStep + kq) : zero8, dh);
+        float cs = 0.f;
+        for (int q = 0; q < 4; ++q) {
+          const float v = dh[q] * dsilu_f(z2[j][q]);
+          cs += v;
+          L.H1[m0 + rq + q][n] = (__bf16)v;
+          D.dZ2T[n][m0 + rq + q] = (__bf16)v;
+        }
+        cs += __shfl_xor(cs, 16, 64);
+        cs += __shfl_xor(cs, 32, 64);
+        if (lane < 16) D.colsum[0][w & 3][n] = cs;
+      }
+      for (int i = 0; i < 3; ++i) {
+        const int t = 3 * w + i, m = t / 6, n = t % 6;
+        for (int ks = 0; ks < kRows / kKStep; ++ks)
+          dw3[i] = mfma(frag(D.H2T[16 * m + r16], ks * kKStep + kq), frag(D.dYT[16 * n + r16], ks * kKStep + kq), dw3[i]);
+      }
+      if (tid < 8 * kMlpOut) {
+        const int c = tid % kMlpOut, r8 = tid / kMlpOut * 8;
+        float cs = 0.f;
+        for (int r = 0; r < 8; ++r) cs += D.Y[r8 + r][c];
+        D.colsum3[r8 / 8][c] = cs;
+      }
+    }
+    __syncthreads();
+    // dZ1 = (dZ2 W2^T) silu'(Z1), transposed into H2T's place; dW2 = H1^T dZ2
+    {
+      bf16x8 a[4];
+      for (int ks = 0; ks < 4; ++ks) a[ks] = frag(L.H1[m0 + r16], ks * kKStep + kq);
+      for (int j = 0; j < 2; ++j) {
+        const int n = n0 + 16 * j + r16;
+        floatx4 dh = zero4;
+        for (int ks = 0; ks < 4; ++ks) dh = mfma(a[ks], frag(g.pb + kOffW2 + n * kMlpHidden, ks * kKStep + kq), dh);
+        float cs = 0.f;
+        for (int q = 0; q < 4; ++q) {
+          const float v = dh[q] * dsilu_f(z1[j][q]);
+          cs += v;
+          D.H2T[n][m0 + rq + q] = (__bf16)v;
+        }
+        cs += __shfl_xor(cs, 16, 64);
+        cs += __shfl_xor(cs, 32, 64);
+        if (lane < 16) D.colsum[1][w & 3][n] = cs;
+      }
+      for (int ks = 0; ks < kRows / kKStep; ++ks) {
+        const bf16x8 h = frag(D.H1T[16 * (w >> 1) + r16], ks * kKStep + kq);
+        for (int i = 0; i < 4; ++i)
+          dw2[i] = mfma(h, frag(D.dZ2T[16 * (4 * (w & 1) + i) + r16], ks * kKStep + kq), dw2[i]);
+      }
+    }
+    __syncthreads();
+    // dW1 = X^T dZ1 and the bias gradients
+    if (w < 8)
+      for (int ks = 0; ks < kRows / kKStep; ++ks)
+        dw1 = mfma(frag(D.XT[r16], ks * kKStep + kq), frag(D.H2T[16 * w + r16], ks * kKStep + kq), dw1);
+    if (tid < 2 * kMlpHidden) {
+      const auto& c = D.colsum[tid / kMlpHidden];
+      const int n = tid % kMlpHidden;
+      db += (c[0][n] + c[1][n]) + (c[2][n] + c[3][n]);
+    }
+    if (tid < kMlpOut)
+      for (int i = 0; i < 8; ++i) db3 += D.colsum3[i][tid];
+    if (tid == 0)
+      for (int i = 0; i < 8; ++i) loss += D.loss[i];
     __syncthreads();
   }
-  // result fragment: lane l holds column (l%16), rows 4*(l/16) .. +3
-  const int c = lane & 15, rq = (lane >> 4) * 4;
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j)
-      for (int q = 0; q < 4; ++q) {
-        const int gm = m0 + wm + i * 16 + rq + q, gn = n0 + wn + j * 16 + c;
-        if (gm >= g.M || gn >= g.N) continue;
-        if (split) {  // a partial product over this workgroup's K chunk
-          atomicAdd(&g.Cf[(size_t)gm * g.ldc + gn], acc[i][j][q]);
-          continue;
-        }
-        float z = acc[i][j][q];
-        if (g.bias) z += g.bias[gn];
-        if (g.accumulate) z += g.Cf[(size_t)gm * g.ldc + gn];
-        if (g.Cz) g.Cz[(size_t)gm * g.ldc + gn] = z;
-        const float h = g.silu ? silu_f(z) : z;
-        if (g.Cf) g.Cf[(size_t)gm * g.ldc + gn] = h;
-        if (g.Cb) g.Cb[(size_t)gm * g.ldc + gn] = (__bf16)h;
-      }
-}
-
-__global__ void f32_to_bf16_kernel(const float* __restrict__ src, __bf16* __restrict__ dst, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    dst[i] = (__bf16)src[i];
-}
-
-// dZ = dH * silu'(Z), FP32 and BF16 copies
-__global__ void silu_backward_kernel(const float* __restrict__ dH, const float* __restrict__ Z,
-                                     float* __restrict__ dZ, __bf16* __restrict__ dZb, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const float v = dH[i] * dsilu_f(Z[i]);
-    dZ[i] = v;
-    dZb[i] = (__bf16)v;
+  if (!kGrad) return;
+  float* out = g.part + (size_t)blockIdx.x * kMlpParams;
+  for (int q = 0; q < 4; ++q) {
+    for (int i = 0; i < 3; ++i) {
+      const int t = 3 * w + i, n = 16 * (t % 6) + r16;
+      if (n < kMlpOut) out[kOffW3 + (16 * (t / 6) + rq + q) * kMlpOut + n] = dw3[i][q];
+    }
+    for (int i = 0; i < 4; ++i)
+      out[kOffW2 + (16 * (w >> 1) + rq + q) * kMlpHidden + 16 * (4 * (w & 1) + i) + r16] = dw2[i][q];
+    if (w < 8 && rq + q < kMlpIn) out[kOffW1 + (rq + q) * kMlpHidden + 16 * w + r16] = dw1[q];
   }
+  if (tid < kMlpHidden) out[kOffB2 + tid] = db;
+  else if (tid < 2 * kMlpHidden) out[kOffB1 + tid - kMlpHidden] = db;
+  if (tid < kMlpOut) out[kOffB3 + tid] = db3;
+  if (tid == 0) g.loss_part[blockIdx.x] = loss;
 }
 
-// out[n] += sum over rows of M[row][n] (column sums for the bias gradients).
-// A workgroup sums a chunk of kColsumRows rows of 64 columns: four row phases
-// of 64 lanes, combined in LDS, one atomic per column.
-constexpr int kColsumRows = 64;
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ M, int rows, int cols,
-                                                     float* __restrict__ out) {
-  __shared__ float part[4][64];
-  const int lane = threadIdx.x & 63, ph = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + lane;
-  const int r0 = blockIdx.y * kColsumRows, r1 = min(rows, r0 + kColsumRows);
+// Position of parameter i in the transposed BF16 weights, -1 for a bias.
+__device__ __forceinline__ int transposed_at(int i) {
+  if (i < kOffB1) return kOffT1 + i % kMlpHidden * kMlpIn + i / kMlpHidden;
+  if (i < kOffW2) return -1;
+  if (i < kOffB2) return kOffT2 + (i - kOffW2) % kMlpHidden * kMlpHidden + (i - kOffW2) / kMlpHidden;
+  if (i < kOffW3) return -1;
+  if (i < kOffB3) return kOffT3 + (i - kOffW3) % kMlpOut * kMlpHidden + (i - kOffW3) / kMlpOut;
+  return -1;
+}
+
+__device__ __forceinline__ void put_weight(__bf16* pb, __bf16* pbt, int i, float w) {
+  pb[i] = (__bf16)w;
+  const int t = transposed_at(i);
+  if (t >= 0) pbt[t] = (__bf16)w;
+}
+
+// BF16 copies of the master weights, row-major and transposed (head rows
+// beyond 88 zero).
+__global__ void refresh_weights_kernel(const float* __restrict__ p, __bf16* __restrict__ pb, __bf16* __restrict__ pbt) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < kMlpParams) put_weight(pb, pbt, i, p[i]);
+  if (i < (kOut16 - kMlpOut) * kMlpHidden) pbt[kOffT3 + kMlpOut * kMlpHidden + i] = (__bf16)0.0f;
+}
+
+// The workgroups' gradient slices summed (four threads per parameter, each a
+// quarter of the slices in order), and with adam the bias-corrected Adam step
+// on the FP32 master weights and their BF16 copies; block 0 adds the batch's
+// loss.  Gradient and step of a batch of 4096 rows are two launches: 196 ->
+// 35 us.
+constexpr int kReduceParams = 64;
+__global__ __launch_bounds__(4 * kReduceParams) void reduce_grad_kernel(MlpReduceArgs a) {
+  __shared__ float sh[4][kReduceParams];
+  const int j = threadIdx.x % kReduceParams, grp = threadIdx.x / kReduceParams;
+  const int i = blockIdx.x * kReduceParams + j;
+  const int lo = a.n_part * grp / 4, hi = a.n_part * (grp + 1) / 4;
   float s = 0.f;
-  if (n < cols)
-    for (int r = r0 + ph; r < r1; r += 4) s += M[(size_t)r * cols + n];
-  part[ph][lane] = s;
+  if (i < kMlpParams) {
+#pragma unroll 8
+    for (int k = lo; k < hi; ++k) s += a.part[(size_t)k * kMlpParams + i];
+  }
+  sh[grp][j] = s;
   __syncthreads();
-  if (ph == 0 && n < cols) atomicAdd(&out[n], (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    double l = 0.0;
+    for (int k = 0; k < a.n_part; ++k) l += a.loss_part[k];
+    *a.loss += l;
+  }
+  if (grp != 0 || i >= kMlpParams) return;
+  const float g = (sh[0][j] + sh[1][j]) + (sh[2][j] + sh[3][j]);
+  if (!a.adam) {
+    a.grad[i] = g;
+    return;
+  }
+  const float mi = a.b1 * a.m[i] + (1.f - a.b1) * g;
+  const float vi = a.b2 * a.v[i] + (1.f - a.b2) * g * g;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  const float w = a.p[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+  a.p[i] = w;
+  put_weight(a.pb, a.pbt, i, w);
 }
 
-__global__ void sum_kernel(const float* __restrict__ w, int stride, int rows, double* out) {
+// Weight sums of the batches: block b sums the weights of rows b * batch.. of
+// the order idx (or of the rows themselves).
+__global__ __launch_bounds__(256) void weight_sum_kernel(const float* __restrict__ w, long long stride,
+                                                         const int* __restrict__ idx, long long n, int batch,
+                                                         double* __restrict__ out) {
   __shared__ double sh[4];
+  const long long lo = (long long)blockIdx.x * batch, hi = lo + batch < n ? lo + batch : n;
   double s = 0.0;
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < rows; r += gridDim.x * blockDim.x) s += w[(size_t)r * stride];
+  for (long long r = lo + threadIdx.x; r < hi; r += blockDim.x) s += w[(idx ? (long long)idx[r] : r) * stride];
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) atomicAdd(out, sh[0] + sh[1] + sh[2] + sh[3]);
-}
-
-// Weighted NLL of the mixture head per row: loss += -w L / W, dY.
-// y and w are read from `yw` with row stride `yws` (y at 0..4, w at 5).
-__global__ void nll_kernel(const float* __restrict__ Y, const float* __restrict__ yw, int yws, int rows,
-                           const double* __restrict__ wsum, float* __restrict__ dY, __bf16* __restrict__ dYb,
-                           double* loss) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  double part = 0.0;  // this row's loss term; summed over the wave before the atomic
-  if (r < rows) {
-    const float* h = Y + (size_t)r * kMlpOut;
-    const float* yr = yw + (size_t)r * yws;
-    const float s = (float)((double)yr[kMixD] / *wsum);
-    float mx = -INFINITY;
-    for (int k = 0; k < kMixK; ++k) mx = fmaxf(mx, h[k]);
-    float se = 0.f;
-    for (int k = 0; k < kMixK; ++k) se += __expf(h[k] - mx);
-    const float lse_a = mx + __logf(se);
-    float lk[kMixK];
-    float z[kMixK][kMixD];
-    float m2 = -INFINITY;
-    for (int k = 0; k < kMixK; ++k) {
-      float l = h[k] - lse_a;
-      for (int d = 0; d < kMixD; ++d) {
-        const float lr = h[kMixK + kMixK * kMixD + k * kMixD + d];
-        const float ls = fminf(fmaxf(lr, kLsMin), kLsMax);
-        const float zz = (yr[d] - h[kMixK + k * kMixD + d]) * __expf(-ls);
-        z[k][d] = zz;
-        l += -0.5f * zz * zz - ls - 0.91893853320467274f;
-      }
-      lk[k] = l;
-      m2 = fmaxf(m2, l);
-    }
-    float se2 = 0.f;
-    for (int k = 0; k < kMixK; ++k) se2 += __expf(lk[k] - m2);
-    const float L = m2 + __logf(se2);
-    part = -(double)s * (double)L;
-    float* g = dY + (size_t)r * kMlpOut;
-    __bf16* gb = dYb + (size_t)r * kMlpOut;
-    for (int k = 0; k < kMixK; ++k) {
-      const float resp = __expf(lk[k] - L);
-      const float pi = __expf(h[k] - lse_a);
-      const float ga = -s * (resp - pi);
-      g[k] = ga;
-      gb[k] = (__bf16)ga;
-      for (int d = 0; d < kMixD; ++d) {
-        const float lr = h[kMixK + kMixK * kMixD + k * kMixD + d];
-        const float ls = fminf(fmaxf(lr, kLsMin), kLsMax);
-        const float gmu = -s * resp * z[k][d] * __expf(-ls);
-        float gls = -s * resp * (z[k][d] * z[k][d] - 1.0f);
-        if (lr < kLsMin || lr > kLsMax) gls = 0.f;
-        const int im = kMixK + k * kMixD + d, il = kMixK + kMixK * kMixD + k * kMixD + d;
-        g[im] = gmu;
-        gb[im] = (__bf16)gmu;
-        g[il] = gls;
-        gb[il] = (__bf16)gls;
-      }
-    }
-  }
-  for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
-  if ((threadIdx.x & 63) == 0) atomicAdd(loss, part);
-}
-
-// Adam (bias-corrected) on the FP32 master weights; refresh the BF16 copies.
-__global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                            float* __restrict__ v, __bf16* __restrict__ pb, int n, float lr, float b1, float b2,
-                            float eps, float c1, float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float mi = b1 * m[i] + (1.f - b1) * g[i];
-  const float vi = b2 * v[i] + (1.f - b2) * g[i] * g[i];
-  m[i] = mi;
-  v[i] = vi;
-  const float w = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  p[i] = w;
-  pb[i] = (__bf16)w;
+  if (threadIdx.x == 0) out[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
 // Inference straight to the proposal table: each wave takes 16-row blocks of
@@ -370,69 +562,50 @@ __global__ void features_kernel(Grid G, const Channel* __restrict__ chans, int n
   x[7] = nch > 1 ? (float)(2.0 * ci / (nch - 1) - 1.0) : 0.0f;
 }
 
-// Gather rows idx[i] of the recorded samples into a minibatch: X (FP32 and
-// BF16) and the (y, w) block.
-__global__ void gather_kernel(const float* __restrict__ rows, const int* __restrict__ idx, int n, float* __restrict__ X,
-                              __bf16* __restrict__ Xb, float* __restrict__ yw) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float* src = rows + (size_t)idx[i] * kRecordWidth;
-  for (int c = 0; c < kMlpIn; ++c) {
-    X[(size_t)i * kMlpIn + c] = src[c];
-    Xb[(size_t)i * kMlpIn + c] = (__bf16)src[c];
-  }
-  for (int c = 0; c < kMixD + 1; ++c) yw[(size_t)i * (kMixD + 1) + c] = src[kMlpIn + c];
-}
-
-unsigned blocks_for(size_t n, int t = 256) {
-  size_t b = (n + t - 1) / t;
-  return (unsigned)(b > 65535 ? 65535 : (b ? b : 1));
-}
-
 }  // namespace
 
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
-  if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  if (g.k_chunk < 0 || g.k_chunk % kKStep) return hipErrorInvalidValue;
-  if (g.k_chunk > 0 && (!g.Cf || g.bias || g.silu || g.Cz || g.Cb)) return hipErrorInvalidValue;
-  const int chunks = g.k_chunk > 0 ? (g.K + g.k_chunk - 1) / g.k_chunk : 1;
-  dim3 grid((g.N + kTile - 1) / kTile, (g.M + kTile - 1) / kTile, chunks);
-  hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(kThreads), 0, st, g);
+size_t mlp_grad_slices(long long rows) {
+  return (size_t)std::min<long long>(kMlpMaxSlices, (rows + kRows - 1) / kRows);
+}
+
+// The gradient kernel's LDS exceeds the runtime's default dynamic limit: it is
+// raised once per GPU.
+hipError_t raise_mlp_lds_limit() {
+  return hipFuncSetAttribute((const void*)mlp_tile_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)(sizeof(TileLds) + sizeof(GradLds)));
+}
+
+hipError_t launch_mlp_forward(const MlpTileArgs& g, hipStream_t st) {
+  if (g.rows <= 0) return hipSuccess;
+  const long long tiles = (g.rows + kRows - 1) / kRows;
+  hipLaunchKernelGGL(mlp_tile_kernel<false>, dim3((unsigned)std::min<long long>(tiles, 4096)), dim3(1024),
+                     sizeof(TileLds), st, g);
   return hipGetLastError();
 }
 
-hipError_t launch_f32_to_bf16(const float* src, __bf16* dst, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(f32_to_bf16_kernel, dim3(blocks_for(n)), dim3(256), 0, st, src, dst, n);
+hipError_t launch_mlp_grad(const MlpTileArgs& g, hipStream_t st) {
+  if (g.rows <= 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(mlp_tile_kernel<true>, dim3((unsigned)mlp_grad_slices(g.rows)), dim3(1024),
+                     sizeof(TileLds) + sizeof(GradLds), st, g);
   return hipGetLastError();
 }
 
-hipError_t launch_silu_backward(const float* dH, const float* Z, float* dZ, __bf16* dZb, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(silu_backward_kernel, dim3(blocks_for(n)), dim3(256), 0, st, dH, Z, dZ, dZb, n);
+hipError_t launch_reduce_grad(const MlpReduceArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(reduce_grad_kernel, dim3((kMlpParams + kReduceParams - 1) / kReduceParams), dim3(4 * kReduceParams),
+                     0, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_colsum(const float* M, int rows, int cols, float* out, hipStream_t st) {
-  dim3 grid((cols + 63) / 64, (rows + kColsumRows - 1) / kColsumRows);
-  hipLaunchKernelGGL(colsum_kernel, grid, dim3(256), 0, st, M, rows, cols, out);
+hipError_t launch_refresh_weights(const float* p, __bf16* pb, __bf16* pbt, hipStream_t st) {
+  hipLaunchKernelGGL(refresh_weights_kernel, dim3((kMlpParams + 255) / 256), dim3(256), 0, st, p, pb, pbt);
   return hipGetLastError();
 }
 
-hipError_t launch_sum(const float* w, int stride, int rows, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(sum_kernel, dim3(blocks_for(rows) > 256 ? 256 : blocks_for(rows)), dim3(256), 0, st, w, stride,
-                     rows, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_nll(const float* Y, const float* yw, int yws, int rows, const double* wsum, float* dY, __bf16* dYb,
-                      double* loss, hipStream_t st) {
-  hipLaunchKernelGGL(nll_kernel, dim3((rows + 127) / 128), dim3(128), 0, st, Y, yw, yws, rows, wsum, dY, dYb, loss);
-  return hipGetLastError();
-}
-
-hipError_t launch_adam(float* p, const float* g, float* m, float* v, __bf16* pb, int n, float lr, float b1, float b2,
-                       float eps, int t, hipStream_t st) {
-  const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
-  hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, g, m, v, pb, n, lr, b1, b2, eps, c1, c2);
+hipError_t launch_weight_sums(const float* w, long long stride, const int* idx, long long n, int batch, double* out,
+                              hipStream_t st) {
+  const long long blocks = (n + batch - 1) / batch;
+  if (blocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL(weight_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, st, w, stride, idx, n, batch, out);
   return hipGetLastError();
 }
 
@@ -452,11 +625,6 @@ hipError_t launch_mlp_table(const float* X, int rows, const __bf16* pb, const fl
   int grid = (n_blocks + kInfWaves - 1) / kInfWaves;
   grid = grid > 512 ? 512 : grid;
   hipLaunchKernelGGL(mlp_table_kernel, dim3(grid), dim3(kInfWaves * 64), 0, st, X, rows, pb, P, alpha, thr, mu, sigma);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather(const float* rows, const int* idx, int n, float* X, __bf16* Xb, float* yw, hipStream_t st) {
-  hipLaunchKernelGGL(gather_kernel, dim3((n + 127) / 128), dim3(128), 0, st, rows, idx, n, X, Xb, yw);
   return hipGetLastError();
 }
 

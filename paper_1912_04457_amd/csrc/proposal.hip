@@ -7,6 +7,7 @@
 #include <cstring>
 #include <numeric>
 #include <random>
+#include <type_traits>
 #include <vector>
 
 #include "context.h"
@@ -21,98 +22,62 @@ static_assert(QGBE_MLP_PARAMS == kMlpParams, "header and kernels disagree on the
 qgbe_status mlp_ensure(qgbe_ctx* c) {
   MlpState& m = c->mlp;
   if (m.ready) return QGBE_OK;
-  qgbe_status s = QGBE_OK;
-#define MA(p, n, what) \
-  if (!s) s = dev_alloc(c, &(p), (size_t)(n), what)
-  MA(m.params, kMlpParams, "mlp params");
-  MA(m.m, kMlpParams, "adam m");
-  MA(m.v, kMlpParams, "adam v");
-  MA(m.grad, kMlpParams, "mlp grad");
-  MA(m.pb, kMlpParams, "mlp bf16 params");
-  MA(m.X, (size_t)kBatch * kMlpIn, "mlp X");
-  MA(m.Xb, (size_t)kBatch * kMlpIn, "mlp X bf16");
-  MA(m.Z1, (size_t)kBatch * kMlpHidden, "mlp Z1");
-  MA(m.H1b, (size_t)kBatch * kMlpHidden, "mlp H1");
-  MA(m.Z2, (size_t)kBatch * kMlpHidden, "mlp Z2");
-  MA(m.H2b, (size_t)kBatch * kMlpHidden, "mlp H2");
-  MA(m.Y, (size_t)kBatch * kMlpOut, "mlp Y");
-  MA(m.dY, (size_t)kBatch * kMlpOut, "mlp dY");
-  MA(m.dYb, (size_t)kBatch * kMlpOut, "mlp dY bf16");
-  MA(m.dH, (size_t)kBatch * kMlpHidden, "mlp dH");
-  MA(m.dZ, (size_t)kBatch * kMlpHidden, "mlp dZ");
-  MA(m.dZb, (size_t)kBatch * kMlpHidden, "mlp dZ bf16");
-  MA(m.yw, (size_t)kBatch * (kMixD + 1), "mlp yw");
-  MA(m.scalars, 2, "mlp scalars");
-#undef MA
-  if (s) return s;
+  HIP_TRY(raise_mlp_lds_limit(), "raise the dynamic LDS limit");
+  char* base = nullptr;
+  size_t used = 0;
+  const auto take = [&](auto** p, size_t n) {
+    using T = std::remove_reference_t<decltype(**p)>;
+    if (base) *p = reinterpret_cast<T*>(base + used);
+    used += (n * sizeof(T) + 255) & ~size_t(255);
+  };
+  for (int pass = 0; pass < 2; ++pass) {  // first for the size
+    used = 0;
+    take(&m.params, kMlpParams);
+    take(&m.m, kMlpParams);
+    take(&m.v, kMlpParams);
+    take(&m.grad, kMlpParams);
+    take(&m.pb, kMlpParams);
+    take(&m.pbt, kMlpParamsT);
+    take(&m.X, (size_t)kBatch * kMlpIn);
+    take(&m.yw, (size_t)kBatch * (kMixD + 1));
+    take(&m.Y, (size_t)kBatch * kMlpOut);
+    take(&m.part, (size_t)kMlpMaxSlices * kMlpParams);
+    take(&m.loss_part, kMlpMaxSlices);
+    take(&m.scalars, 2);
+    if (pass == 0) {
+      const qgbe_status s = dev_alloc(c, &m.arena, used, "proposal network");
+      if (s) return s;
+      base = m.arena;
+    }
+  }
   m.ready = true;
   return QGBE_OK;
 }
 
-GemmArgs gemm(int M, int N, int K, const __bf16* A, long long ars, long long acs, const __bf16* B, long long brs,
-              long long bcs) {
-  GemmArgs g{};
-  g.M = M; g.N = N; g.K = K;
-  g.A = A; g.ars = ars; g.acs = acs;
-  g.B = B; g.brs = brs; g.bcs = bcs;
-  g.ldc = N;
+// Tile arguments of rows in place: X (stride xs), and yw (stride ys) or NULL.
+MlpTileArgs tile_args(const qgbe_ctx* c, long long rows, const float* X, long long xs, const float* yw, long long ys,
+                      const int* idx) {
+  const MlpState& m = c->mlp;
+  MlpTileArgs g{};
+  g.rows = rows;
+  g.X = X; g.xs = xs;
+  g.yw = yw; g.ys = ys;
+  g.idx = idx;
+  g.pb = m.pb; g.pbt = m.pbt; g.P = m.params;
+  g.part = m.part; g.loss_part = m.loss_part;
   return g;
 }
 
-// Forward pass on rows already staged in m.Xb (BF16); head in m.Y (FP32).
-qgbe_status forward_staged(qgbe_ctx* c, int rows) {
-  MlpState& m = c->mlp;
-  const float* P = m.params;
-  GemmArgs g1 = gemm(rows, kMlpHidden, kMlpIn, m.Xb, kMlpIn, 1, m.pb + kOffW1, kMlpHidden, 1);
-  g1.bias = P + kOffB1; g1.silu = 1; g1.Cz = m.Z1; g1.Cb = m.H1b;
-  HIP_TRY(launch_gemm(g1, c->stream), "layer 1");
-  GemmArgs g2 = gemm(rows, kMlpHidden, kMlpHidden, m.H1b, kMlpHidden, 1, m.pb + kOffW2, kMlpHidden, 1);
-  g2.bias = P + kOffB2; g2.silu = 1; g2.Cz = m.Z2; g2.Cb = m.H2b;
-  HIP_TRY(launch_gemm(g2, c->stream), "layer 2");
-  GemmArgs g3 = gemm(rows, kMlpOut, kMlpHidden, m.H2b, kMlpHidden, 1, m.pb + kOffW3, kMlpOut, 1);
-  g3.bias = P + kOffB3; g3.Cf = m.Y;
-  HIP_TRY(launch_gemm(g3, c->stream), "layer 3");
-  return QGBE_OK;
-}
-
-// The weight gradients reduce over the rows (K = rows, M x N <= 128 x 128):
-// their K is split so that rows / 256 workgroups per tile share it.
-constexpr int kGradChunk = 256;
-
-// Loss and gradient for rows staged in m.Xb / m.yw; gradient in m.grad,
-// loss in m.scalars[0] (accumulated).
-qgbe_status loss_grad_staged(qgbe_ctx* c, int rows) {
-  MlpState& m = c->mlp;
-  qgbe_status s = forward_staged(c, rows);
-  if (s) return s;
-  HIP_TRY(hipMemsetAsync(m.scalars + 1, 0, sizeof(double), c->stream), "zero weight sum");
-  HIP_TRY(launch_sum(m.yw + kMixD, kMixD + 1, rows, m.scalars + 1, c->stream), "weight sum");
-  HIP_TRY(launch_nll(m.Y, m.yw, kMixD + 1, rows, m.scalars + 1, m.dY, m.dYb, m.scalars, c->stream), "nll");
-  HIP_TRY(hipMemsetAsync(m.grad, 0, kMlpParams * sizeof(float), c->stream), "zero grad");
-  // layer 3: dW3 = H2^T dY, db3 = colsum dY, dH2 = dY W3^T
-  GemmArgs w3 = gemm(kMlpHidden, kMlpOut, rows, m.H2b, 1, kMlpHidden, m.dYb, kMlpOut, 1);
-  w3.Cf = m.grad + kOffW3; w3.k_chunk = kGradChunk;
-  HIP_TRY(launch_gemm(w3, c->stream), "dW3");
-  HIP_TRY(launch_colsum(m.dY, rows, kMlpOut, m.grad + kOffB3, c->stream), "db3");
-  GemmArgs h2 = gemm(rows, kMlpHidden, kMlpOut, m.dYb, kMlpOut, 1, m.pb + kOffW3, 1, kMlpOut);
-  h2.Cf = m.dH;
-  HIP_TRY(launch_gemm(h2, c->stream), "dH2");
-  HIP_TRY(launch_silu_backward(m.dH, m.Z2, m.dZ, m.dZb, (size_t)rows * kMlpHidden, c->stream), "dZ2");
-  // layer 2
-  GemmArgs w2 = gemm(kMlpHidden, kMlpHidden, rows, m.H1b, 1, kMlpHidden, m.dZb, kMlpHidden, 1);
-  w2.Cf = m.grad + kOffW2; w2.k_chunk = kGradChunk;
-  HIP_TRY(launch_gemm(w2, c->stream), "dW2");
-  HIP_TRY(launch_colsum(m.dZ, rows, kMlpHidden, m.grad + kOffB2, c->stream), "db2");
-  GemmArgs h1 = gemm(rows, kMlpHidden, kMlpHidden, m.dZb, kMlpHidden, 1, m.pb + kOffW2, 1, kMlpHidden);
-  h1.Cf = m.dH;
-  HIP_TRY(launch_gemm(h1, c->stream), "dH1");
-  HIP_TRY(launch_silu_backward(m.dH, m.Z1, m.dZ, m.dZb, (size_t)rows * kMlpHidden, c->stream), "dZ1");
-  // layer 1
-  GemmArgs w1 = gemm(kMlpIn, kMlpHidden, rows, m.Xb, 1, kMlpIn, m.dZb, kMlpHidden, 1);
-  w1.Cf = m.grad + kOffW1; w1.k_chunk = kGradChunk;
-  HIP_TRY(launch_gemm(w1, c->stream), "dW1");
-  HIP_TRY(launch_colsum(m.dZ, rows, kMlpHidden, m.grad + kOffB1, c->stream), "db1");
-  return QGBE_OK;
+MlpReduceArgs reduce_args(const qgbe_ctx* c, long long rows, double* loss) {
+  const MlpState& m = c->mlp;
+  MlpReduceArgs r{};
+  r.part = m.part; r.loss_part = m.loss_part;
+  r.n_part = (int)mlp_grad_slices(rows);
+  r.loss = loss;
+  r.grad = m.grad;
+  r.p = m.params; r.m = m.m; r.v = m.v;
+  r.pb = m.pb; r.pbt = m.pbt;
+  return r;
 }
 
 qgbe_status check_weights(qgbe_ctx* c) {
@@ -209,7 +174,7 @@ qgbe_status qgbe_proposal_set_weights(qgbe_ctx* c, const float* w, int64_t n) {
   if (s) return s;
   MlpState& m = c->mlp;
   HIP_TRY(hipMemcpyAsync(m.params, w, kMlpParams * sizeof(float), hipMemcpyHostToDevice, c->stream), "copy weights");
-  HIP_TRY(launch_f32_to_bf16(m.params, m.pb, kMlpParams, c->stream), "bf16 weights");
+  HIP_TRY(launch_refresh_weights(m.params, m.pb, m.pbt, c->stream), "bf16 weights");
   HIP_TRY(hipMemsetAsync(m.m, 0, kMlpParams * sizeof(float), c->stream), "zero m");
   HIP_TRY(hipMemsetAsync(m.v, 0, kMlpParams * sizeof(float), c->stream), "zero v");
   HIP_TRY(hipStreamSynchronize(c->stream), "synchronise");
@@ -236,15 +201,20 @@ qgbe_status qgbe_mlp_forward(qgbe_ctx* c, const float* X, int64_t rows, float* Y
   if (s) return s;
   HIP_TRY(hipSetDevice(c->d.device), "hipSetDevice");
   MlpState& m = c->mlp;
-  const hipMemcpyKind in = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-  const hipMemcpyKind out = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-  for (int64_t r0 = 0; r0 < rows; r0 += kBatch) {
+  if (on_device) {
+    MlpTileArgs g = tile_args(c, rows, X, kMlpIn, nullptr, 0, nullptr);
+    g.Y = Y;
+    HIP_TRY(launch_mlp_forward(g, c->stream), "forward");
+  }
+  for (int64_t r0 = 0; !on_device && r0 < rows; r0 += kBatch) {
     const int nr = (int)std::min<int64_t>(kBatch, rows - r0);
-    HIP_TRY(hipMemcpyAsync(m.X, X + r0 * kMlpIn, (size_t)nr * kMlpIn * sizeof(float), in, c->stream), "copy X");
-    HIP_TRY(launch_f32_to_bf16(m.X, m.Xb, (size_t)nr * kMlpIn, c->stream), "X to bf16");
-    s = forward_staged(c, nr);
-    if (s) return s;
-    HIP_TRY(hipMemcpyAsync(Y + r0 * kMlpOut, m.Y, (size_t)nr * kMlpOut * sizeof(float), out, c->stream), "copy Y");
+    HIP_TRY(hipMemcpyAsync(m.X, X + r0 * kMlpIn, (size_t)nr * kMlpIn * sizeof(float), hipMemcpyHostToDevice, c->stream),
+            "copy X");
+    MlpTileArgs g = tile_args(c, nr, m.X, kMlpIn, nullptr, 0, nullptr);
+    g.Y = m.Y;
+    HIP_TRY(launch_mlp_forward(g, c->stream), "forward");
+    HIP_TRY(hipMemcpyAsync(Y + r0 * kMlpOut, m.Y, (size_t)nr * kMlpOut * sizeof(float), hipMemcpyDeviceToHost, c->stream),
+            "copy Y");
   }
   HIP_TRY(hipStreamSynchronize(c->stream), "synchronise");
   return QGBE_OK;
@@ -258,15 +228,23 @@ qgbe_status qgbe_mlp_loss_grad(qgbe_ctx* c, const float* X, const float* yw, int
   if (s) return s;
   HIP_TRY(hipSetDevice(c->d.device), "hipSetDevice");
   MlpState& m = c->mlp;
-  const hipMemcpyKind in = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-  HIP_TRY(hipMemcpyAsync(m.X, X, (size_t)rows * kMlpIn * sizeof(float), in, c->stream), "copy X");
-  HIP_TRY(hipMemcpyAsync(m.yw, yw, (size_t)rows * (kMixD + 1) * sizeof(float), in, c->stream), "copy yw");
-  HIP_TRY(launch_f32_to_bf16(m.X, m.Xb, (size_t)rows * kMlpIn, c->stream), "X to bf16");
-  HIP_TRY(hipMemsetAsync(m.scalars, 0, sizeof(double), c->stream), "zero loss");
-  s = loss_grad_staged(c, (int)rows);
-  if (s) return s;
-  HIP_TRY(hipMemcpyAsync(grad, m.grad, kMlpParams * sizeof(float),
-                         on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, c->stream), "copy grad");
+  if (!on_device) {
+    HIP_TRY(hipMemcpyAsync(m.X, X, (size_t)rows * kMlpIn * sizeof(float), hipMemcpyHostToDevice, c->stream), "copy X");
+    HIP_TRY(hipMemcpyAsync(m.yw, yw, (size_t)rows * (kMixD + 1) * sizeof(float), hipMemcpyHostToDevice, c->stream),
+            "copy yw");
+    X = m.X;
+    yw = m.yw;
+  }
+  HIP_TRY(launch_fill(m.scalars, 0.0, 1, c->stream), "zero loss");
+  HIP_TRY(launch_weight_sums(yw + kMixD, kMixD + 1, nullptr, rows, (int)rows, m.scalars + 1, c->stream), "weight sum");
+  MlpTileArgs g = tile_args(c, rows, X, kMlpIn, yw, kMixD + 1, nullptr);
+  g.wsum = m.scalars + 1;
+  HIP_TRY(launch_mlp_grad(g, c->stream), "gradient");
+  MlpReduceArgs r = reduce_args(c, rows, m.scalars);
+  if (on_device) r.grad = grad;
+  HIP_TRY(launch_reduce_grad(r, c->stream), "gradient sum");
+  if (!on_device)
+    HIP_TRY(hipMemcpyAsync(grad, m.grad, kMlpParams * sizeof(float), hipMemcpyDeviceToHost, c->stream), "copy grad");
   HIP_TRY(hipMemcpyAsync(loss, m.scalars, sizeof(double), hipMemcpyDeviceToHost, c->stream), "copy loss");
   HIP_TRY(hipStreamSynchronize(c->stream), "synchronise");
   return QGBE_OK;
@@ -418,48 +396,66 @@ qgbe_status qgbe_train_proposal(qgbe_ctx* c, const float* rows, int64_t n, const
             "copy rows");
     d_rows = owned;
   }
-  // the epoch's row order goes to the device once per epoch (one copy, waited
-  // for before the host shuffles again); each batch gathers its slice of it
-  int* d_perm = nullptr;
-  if (hipMalloc(&d_perm, (size_t)n * sizeof(int)) != hipSuccess) {
+  // Per epoch on the device: the row order (the host draws the next one while
+  // the GPU works on this one), the weight sum of every batch, and the loss.
+  const int steps_per_epoch = (int)((n + cfg->batch - 1) / cfg->batch);
+  const size_t perm_b = ((size_t)n * sizeof(int) + 255) & ~size_t(255);
+  const size_t sums_b = ((size_t)steps_per_epoch * sizeof(double) + 255) & ~size_t(255);
+  char* scratch = nullptr;
+  if (hipMalloc(&scratch, 2 * (perm_b + sums_b) + (size_t)cfg->epochs * sizeof(double)) != hipSuccess) {
     if (owned) (void)hipFree(owned);
-    return fail(QGBE_ENOMEM, "row order scratch");
+    return fail(QGBE_ENOMEM, "training scratch");
   }
+  double* d_loss = (double*)(scratch + 2 * (perm_b + sums_b));
   std::mt19937_64 rng(cfg->seed);
   std::vector<int> perm((size_t)n);
   std::iota(perm.begin(), perm.end(), 0);
-  const int steps_per_epoch = (int)((n + cfg->batch - 1) / cfg->batch);
+  std::vector<int> sent[2];  // the orders on their way; one is written again when its copy has ended
+  hipEvent_t copied[2] = {nullptr, nullptr};
   const long long total_steps = (long long)steps_per_epoch * cfg->epochs;
   long long step = 0;
-  hipError_t e = hipSuccess;
-  for (int ep = 0; ep < cfg->epochs && !s && e == hipSuccess; ++ep) {
+  hipError_t e = launch_fill(d_loss, 0.0, cfg->epochs, c->stream);
+  for (int i = 0; i < 2 && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&copied[i], hipEventDisableTiming);
+  for (int ep = 0; ep < cfg->epochs && e == hipSuccess; ++ep) {
     std::shuffle(perm.begin(), perm.end(), rng);
-    e = hipMemcpyAsync(d_perm, perm.data(), (size_t)n * sizeof(int), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(m.scalars, 0, sizeof(double), c->stream);
-    for (int b = 0; b < steps_per_epoch && !s && e == hipSuccess; ++b, ++step) {
-      const int r0 = b * cfg->batch;
+    int* d_perm = (int*)(scratch + (ep & 1) * (perm_b + sums_b));
+    double* d_sums = (double*)(scratch + (ep & 1) * (perm_b + sums_b) + perm_b);
+    if (ep >= 2) e = hipEventSynchronize(copied[ep & 1]);
+    if (e != hipSuccess) break;
+    sent[ep & 1] = perm;
+    e = hipMemcpyAsync(d_perm, sent[ep & 1].data(), (size_t)n * sizeof(int), hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess) e = hipEventRecord(copied[ep & 1], c->stream);
+    if (e == hipSuccess)
+      e = launch_weight_sums(d_rows + kMlpIn + kMixD, kRecordWidth, d_perm, n, cfg->batch, d_sums, c->stream);
+    for (int b = 0; b < steps_per_epoch && e == hipSuccess; ++b, ++step) {
+      const long long r0 = (long long)b * cfg->batch;
       const int nr = (int)std::min<int64_t>(cfg->batch, n - r0);
-      e = launch_gather(d_rows, d_perm + r0, nr, m.X, m.Xb, m.yw, c->stream);
+      MlpTileArgs g = tile_args(c, nr, d_rows, kRecordWidth, d_rows + kMlpIn, kRecordWidth, d_perm + r0);
+      g.wsum = d_sums + b;
+      e = launch_mlp_grad(g, c->stream);
       if (e != hipSuccess) break;
-      s = loss_grad_staged(c, nr);
-      if (s) break;
       const double frac = total_steps > 1 ? (double)step / (double)(total_steps - 1) : 1.0;
-      const float lr = (float)(cfg->lr_final + 0.5 * (cfg->lr - cfg->lr_final) * (1.0 + std::cos(kPi * frac)));
       m.adam_t += 1;
-      e = launch_adam(m.params, m.grad, m.m, m.v, m.pb, kMlpParams, lr, 0.9f, 0.999f, 1e-8f, m.adam_t, c->stream);
+      MlpReduceArgs r = reduce_args(c, nr, d_loss + ep);
+      r.adam = 1;
+      r.lr = (float)(cfg->lr_final + 0.5 * (cfg->lr - cfg->lr_final) * (1.0 + std::cos(kPi * frac)));
+      r.b1 = 0.9f; r.b2 = 0.999f; r.eps = 1e-8f;
+      r.c1 = 1.f - powf(r.b1, (float)m.adam_t);
+      r.c2 = 1.f - powf(r.b2, (float)m.adam_t);
+      e = launch_reduce_grad(r, c->stream);
     }
-    if (!s && e == hipSuccess && epoch_loss) {
-      double tot = 0.0;
-      e = hipMemcpyAsync(&tot, m.scalars, sizeof(double), hipMemcpyDeviceToHost, c->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-      epoch_loss[ep] = tot / steps_per_epoch;
-    }
+  }
+  if (e == hipSuccess && epoch_loss) {
+    e = hipMemcpyAsync(epoch_loss, d_loss, (size_t)cfg->epochs * sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    for (int ep = 0; ep < cfg->epochs; ++ep) epoch_loss[ep] /= steps_per_epoch;
   }
   // wait for the queued work before the scratch buffers go (also after an error)
   const hipError_t e_sync = hipStreamSynchronize(c->stream);
   if (e == hipSuccess) e = e_sync;
-  (void)hipFree(d_perm);
+  for (hipEvent_t ev : copied)
+    if (ev) (void)hipEventDestroy(ev);
+  (void)hipFree(scratch);
   if (owned) (void)hipFree(owned);
   if (s) return s;
   if (e != hipSuccess) return hip_fail(e, "train proposal");
