@@ -35,15 +35,43 @@ size_t field_len(const qgbe_ctx* c) { return (size_t)kSpecies * c->G.cells * c->
 
 namespace qgbe {
 
+namespace {
+
+TermStart mass_args(qgbe_ctx* c) {
+  TermStart t{};
+  t.G = c->G;
+  t.f = c->d_f;
+  t.lag = c->has_lag ? c->d_lag : nullptr;
+  if (c->d.mass_mode == QGBE_MASS_CONSTANT)
+    for (int s = 0; s < kSpecies; ++s) t.constant.v[s] = c->d.const_mass2[s];
+  else
+    t.part = c->d_mass_part;
+  t.mass2 = c->d_mass2;
+  t.done = c->d_done;
+  return t;
+}
+
+}  // namespace
+
 qgbe_status compute_masses(qgbe_ctx* c) {
-  if (c->d.mass_mode == QGBE_MASS_CONSTANT) {
-    Mass7 m;
-    for (int s = 0; s < kSpecies; ++s) m.v[s] = c->d.const_mass2[s];
-    HIP_TRY(launch_const_masses(c->G, m, c->d_mass2, c->stream), "constant masses");
-  } else {
-    HIP_TRY(launch_masses(c->G, c->d_f, c->has_lag ? c->d_lag : nullptr, c->d_mass_part, c->d_mass2, c->stream),
-            "masses");
+  HIP_TRY(launch_term_start(mass_args(c), c->stream), "masses");
+  c->masses_valid = true;
+  return QGBE_OK;
+}
+
+qgbe_status start_term(qgbe_ctx* c, int sampler, double* A, bool f32) {
+  TermStart t = mass_args(c);
+  t.A = A;
+  t.count = c->d_count;
+  t.n_count = kStripes;
+  t.totals = c->d_mc;  // and the channel variances behind it
+  t.n_totals = kStripes * (2 + std::max(1, c->nch));
+  const bool cm = sampler == QGBE_SAMPLER_UNIFORM || sampler == QGBE_SAMPLER_LEARNED;
+  if (c->d.precision == QGBE_FP32 && cm) {
+    if (f32) t.f32 = c->d_f32;
+    if (c->need_quads[sampler == QGBE_SAMPLER_LEARNED ? 1 : 0]) t.quads = c->d_f32q;
   }
+  HIP_TRY(launch_term_start(t, c->stream), "start of the collision term");
   c->masses_valid = true;
   return QGBE_OK;
 }
@@ -399,12 +427,9 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
   return QGBE_OK;
 }
 
-// Enqueue the collision kernels accumulating into A (zeroed by the caller).
+// Enqueue the collision kernels accumulating into A.
 qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, double* scale, double* items) {
   const bool learned = sampler == QGBE_SAMPLER_LEARNED;
-  HIP_TRY(launch_zero_u64(c->d_count, kStripes, c->stream), "zero counter");
-  HIP_TRY(launch_fill(c->d_mc, 0.0, 2 * kStripes, c->stream), "zero error accumulators");
-  HIP_TRY(launch_fill(c->d_chan_var, 0.0, kStripes * std::max(1, c->nch), c->stream), "zero channel variances");
   c->n_launches = 0;
   if (c->nch == 0) return QGBE_OK;
   CollideArgs a = base_args(c, n_samples, A, scale, items);
@@ -416,7 +441,6 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
   const bool f64_path = c->d.precision == QGBE_FP64;
   const int l = roots ? 2 : learned ? 1 : 0;
   const bool recorded = records(c, l, n_samples, scale);
-  if (!roots && c->need_quads[l]) HIP_TRY(launch_f32_quads(c->G, c->d_f32, c->d_f32q, c->stream), "f32 quads");
   a.f32q = c->d_f32q;
   if (recorded) {
     const qgbe_status s = run_replay(c, a, l, sampler == QGBE_SAMPLER_ROOTS_ALT);
@@ -502,19 +526,17 @@ void fill_stats(qgbe_ctx* c, const double* obs, const double* mass2_host, qgbe_s
 
 qgbe_status read_stats(qgbe_ctx* c, qgbe_stats* st, bool energy = false) {
   HIP_TRY(launch_observables(c->G, c->d_f, c->d_mass2, c->d_obs_scratch, c->d_obs, c->stream), "observables");
-  double obs[observables_len];
-  unsigned long long counts[kStripes];
-  HIP_TRY(hipMemcpyAsync(counts, c->d_count, sizeof counts, hipMemcpyDeviceToHost, c->stream), "copy counter");
-  double mcs[2 * kStripes];
-  HIP_TRY(hipMemcpyAsync(mcs, c->d_mc, sizeof mcs, hipMemcpyDeviceToHost, c->stream), "copy error accumulators");
-  std::vector<double> m2((size_t)kSpecies * c->G.cells);
-  HIP_TRY(hipMemcpyAsync(obs, c->d_obs, sizeof obs, hipMemcpyDeviceToHost, c->stream), "copy observables");
-  HIP_TRY(hipMemcpyAsync(m2.data(), c->d_mass2, m2.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream),
-          "copy masses");
-  double budget[2] = {0.0, 0.0};
-  if (energy)
-    HIP_TRY(hipMemcpyAsync(budget, c->d_energy, sizeof budget, hipMemcpyDeviceToHost, c->stream), "copy energy budget");
+  // the totals, the energy budget, the observables and the masses lie side by side: one copy
+  const char* base = (const char*)c->d_count;
+  std::vector<char> host((const char*)(c->d_mass2 + (size_t)kSpecies * c->G.cells) - base);
+  HIP_TRY(hipMemcpyAsync(host.data(), base, host.size(), hipMemcpyDeviceToHost, c->stream), "copy statistics");
   HIP_TRY(hipStreamSynchronize(c->stream), "synchronise");
+  const auto at = [&](const void* d) { return host.data() + ((const char*)d - base); };
+  const unsigned long long* counts = (const unsigned long long*)at(c->d_count);
+  const double *mcs = (const double*)at(c->d_mc), *obs = (const double*)at(c->d_obs);
+  const double* m2 = (const double*)at(c->d_mass2);
+  double budget[2] = {0.0, 0.0};
+  if (energy) std::memcpy(budget, at(c->d_energy), sizeof budget);
   unsigned long long accepted = 0;
   double mc[2] = {0.0, 0.0};
   for (int i = 0; i < kStripes; ++i) {  // in stripe order: the same sum for the same stripes
@@ -522,7 +544,7 @@ qgbe_status read_stats(qgbe_ctx* c, qgbe_stats* st, bool energy = false) {
     mc[0] += mcs[2 * i];
     mc[1] += mcs[2 * i + 1];
   }
-  fill_stats(c, obs, m2.data(), st);
+  fill_stats(c, obs, m2, st);
   st->E_source = budget[0];
   st->E_collide = budget[1];
   st->n_accepted = (double)accepted;
@@ -633,18 +655,19 @@ qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out) {
     take(&c->d_f, n);                        // the zeroed fields side by side: one fill
     take(&c->d_f_next, n);
     take(&c->d_f32, n);
+    take(&c->d_done, c->G.cells);            // zeroed with them
     if (c->d.precision == QGBE_FP32 && (c->need_quads[0] || c->need_quads[1])) take(&c->d_f32q, n);
     take(&c->d_A, n);
-    take(&c->d_mass2, (size_t)kSpecies * c->G.cells);
     take(&c->d_lag, (size_t)kSpecies * c->G.cells);
     take(&c->d_obs_scratch, observables_scratch(c->G));
-    take(&c->d_obs, (size_t)observables_len);
-    take(&c->d_energy, 2);
     take(&c->d_msq, 1);
     take(&c->d_mass_part, mass_scratch(c->G));
-    take(&c->d_count, kStripes);
-    take(&c->d_mc, 2 * kStripes);
-    take(&c->d_chan_var, kStripes * std::max(1, c->nch));
+    take(&c->d_count, kStripes);             // what the statistics read, side by side: one copy
+    take(&c->d_mc, kStripes * (2 + std::max(1, c->nch)));  // and the channel variances
+    c->d_chan_var = c->d_mc + 2 * kStripes;
+    take(&c->d_energy, 2);
+    take(&c->d_obs, (size_t)observables_len);
+    take(&c->d_mass2, (size_t)kSpecies * c->G.cells);
   };
   carve();
   if (const qgbe_status s = dev_alloc(c, &c->d_arena, used, "context")) {
@@ -666,7 +689,7 @@ qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out) {
   if (e == hipSuccess) {
     what = "zero f";
     // both buffers, as a step updates only the evolving species, and the FP32 shadow
-    e = launch_fill(c->d_f, 0.0, ((char*)(c->d_f32 + n) - (char*)c->d_f + 7) / sizeof(double), c->stream);
+    e = launch_fill(c->d_f, 0.0, ((char*)(c->d_done + c->G.cells) - (char*)c->d_f + 7) / sizeof(double), c->stream);
   }
   if (e == hipSuccess) {
     what = "synchronise";
@@ -707,12 +730,11 @@ qgbe_status qgbe_set_distribution(qgbe_ctx* c, int32_t species, const double* f,
   const size_t per = (size_t)c->G.cells * c->G.nodes;
   double* dst = species < 0 ? c->d_f : c->d_f + (size_t)species * per;
   const size_t cnt = species < 0 ? field_len(c) : per;
-  HIP_TRY(hipMemcpyAsync(dst, f, cnt * sizeof(double), on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
-                         c->stream), "copy f in");
+  if (!on_device)
+    HIP_TRY(hipMemcpyAsync(dst, f, cnt * sizeof(double), hipMemcpyHostToDevice, c->stream), "copy f in");
   // the second buffer of f too: a step updates only the evolving species
-  HIP_TRY(hipMemcpyAsync(c->d_f_next + (dst - c->d_f), dst, cnt * sizeof(double), hipMemcpyDeviceToDevice, c->stream),
-          "copy f to the second buffer");
-  HIP_TRY(launch_to_f32(c->d_f, c->d_f32, field_len(c), c->stream), "f to fp32");
+  const size_t at = dst - c->d_f;
+  HIP_TRY(launch_set_field(on_device ? f : dst, dst, c->d_f_next + at, c->d_f32 + at, cnt, c->stream), "set f");
   if (!on_device) HIP_TRY(hipStreamSynchronize(c->stream), "synchronise");
   c->has_lag = false;
   c->masses_valid = false;
@@ -776,17 +798,16 @@ qgbe_status qgbe_collision_term_ex(qgbe_ctx* c, int32_t n_samples, int32_t sampl
     if (ex_host) HIP_TRY(hipMalloc(&items, n_items * sizeof(double)), "item scratch");
     else items = ex->item_sums;
   }
-  qgbe_status s = compute_masses(c);
+  qgbe_status s = start_term(c, sampler, A, false);
   if (!s && sampler == QGBE_SAMPLER_LEARNED && c->table_net) s = refresh_proposal_table(c);
   if (!s) {
-    hipError_t e = launch_fill(A, 0.0, n, c->stream);
-    if (e == hipSuccess && scale) e = launch_fill(scale, 0.0, n, c->stream);
-    if (e == hipSuccess) e = hipEventRecord(c->ev[0], c->stream);
+    hipError_t e = scale ? launch_fill(scale, 0.0, n, c->stream) : hipSuccess;
+    if (e == hipSuccess && st) e = hipEventRecord(c->ev[0], c->stream);
     if (e != hipSuccess) s = hip_fail(e, "zero outputs");
   }
   if (!s) s = run_collide(c, n_samples, sampler, A, scale, items);
   if (!s) {
-    hipError_t e = hipEventRecord(c->ev[1], c->stream);
+    hipError_t e = st ? hipEventRecord(c->ev[1], c->stream) : hipSuccess;
     if (e == hipSuccess && !on_device)
       e = hipMemcpyAsync(A_out, A, n * sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess && ex_host && scale)
@@ -855,30 +876,26 @@ qgbe_status qgbe_step(qgbe_ctx* c, double dt_fm, int32_t n_samples, int32_t samp
   if (sampler == QGBE_SAMPLER_LEARNED && c->d.precision == QGBE_FP32 && c->K > kMixKF32)
     return fail(QGBE_EUNSUPPORTED, "the FP32 learned sampler takes at most 8 mixture components (FP64 takes 16)");
   HIP_TRY(hipSetDevice(c->d.device), "hipSetDevice");
-  const size_t n = field_len(c);
   qgbe_status result = QGBE_OK;
   for (int k = 0; k < n_steps; ++k) {
-    HIP_TRY(hipEventRecord(c->ev[2], c->stream), "event");
-    qgbe_status s = compute_masses(c);
+    if (per_step) HIP_TRY(hipEventRecord(c->ev[2], c->stream), "event");
+    qgbe_status s = start_term(c, sampler, c->d_A, false);
     if (!s && sampler == QGBE_SAMPLER_LEARNED && c->table_net) s = refresh_proposal_table(c);
     if (s) return s;
-    HIP_TRY(launch_fill(c->d_A, 0.0, n, c->stream), "zero A");
-    HIP_TRY(hipEventRecord(c->ev[0], c->stream), "event");
+    if (per_step) HIP_TRY(hipEventRecord(c->ev[0], c->stream), "event");
     s = run_collide(c, n_samples, sampler, c->d_A, nullptr, nullptr);
     if (s) return s;
-    HIP_TRY(hipEventRecord(c->ev[1], c->stream), "event");
+    if (per_step) HIP_TRY(hipEventRecord(c->ev[1], c->stream), "event");
     if (per_step)  // before the update: f_k, its masses, the step before's masses
       HIP_TRY(launch_energy_budget(c->G, c->d_f, c->d_A, c->d_mass2, c->has_lag ? c->d_lag : nullptr, dt_fm,
                                    c->d_obs_scratch, c->d_energy, c->stream),
               "energy budget");
-    HIP_TRY(launch_update(c->G, c->d_f, c->d_A, c->d_mass2, dt_fm, c->d.drift, c->d_f_next, c->d_f32, c->stream),
-            "update");
+    HIP_TRY(launch_update(c->G, c->d_f, c->d_A, c->d_mass2, dt_fm, c->d.drift, c->d_f_next, c->d_f32, c->d_lag,
+                          c->stream), "update");
     std::swap(c->d_f, c->d_f_next);
     c->masses_valid = false;
-    HIP_TRY(hipMemcpyAsync(c->d_lag, c->d_mass2, (size_t)kSpecies * c->G.cells * sizeof(double),
-                           hipMemcpyDeviceToDevice, c->stream), "lag masses");
     c->has_lag = c->d.mass_mode == QGBE_MASS_DYNAMIC;
-    HIP_TRY(hipEventRecord(c->ev[3], c->stream), "event");
+    if (per_step) HIP_TRY(hipEventRecord(c->ev[3], c->stream), "event");
     c->step += 1;
     if (per_step) {
       s = read_stats(c, &per_step[k], true);

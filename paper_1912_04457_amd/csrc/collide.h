@@ -56,7 +56,7 @@ struct CollideArgs {
   uint32_t key0, key1;    // Philox key
   const double* f64;      // [7][cells][nodes]
   const float* f32;       // FP32 shadow of f64
-  const float4* f32q;     // node quads of f32 (global-memory tiles), see launch_f32_quads
+  const float4* f32q;     // node quads of f32 (global-memory tiles), see TermStart
   const double* mass2;    // [7][cells]
   double* A;              // [7][cells][nodes], accumulated into
   double* scale;          // optional, same shape

@@ -91,6 +91,7 @@ struct qgbe_ctx {
   qgbe::MsqTable msq{};          // user matrix elements (host copy)
   uint32_t msq_mask = 0;         // rows replaced by them
   qgbe::MsqTable* d_msq = nullptr;  // device copy
+  unsigned* d_done = nullptr;     // per cell: chunk sums that are in (zero between launches)
   double* d_mass_part = nullptr;  // per (cell, chunk, species) partial mass integrals
   double* d_obs = nullptr;
   unsigned long long* d_count = nullptr;
@@ -128,8 +129,11 @@ void plan_groups(qgbe_ctx* c);
 constexpr size_t kMaxGroupIndex = 4 * (size_t)kMaxChannels + 3 * (size_t)kSpecies * kMaxMatches;
 // Record buffers in given memory (none if they would be too small to pay).
 void carve_records(qgbe_ctx* c, unsigned char* p, size_t bytes);
-// Enqueue the collision kernels of one collision term, accumulating into A
-// (zeroed by the caller); zeroes the per-launch totals first.
+// Masses, and the start of a collision term into A: A and the totals zeroed,
+// the node quads of the sampler's kernels (f32: also the FP32 copy of f).
+qgbe_status start_term(qgbe_ctx* c, int sampler, double* A, bool f32);
+// Enqueue the collision kernels of one collision term, accumulating into A;
+// start_term comes before.
 qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, double* scale, double* items);
 qgbe_status compute_masses(qgbe_ctx* c);
 CollideArgs base_args(qgbe_ctx* c, int n_samples, double* A, double* scale, double* items);

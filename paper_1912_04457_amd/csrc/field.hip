@@ -32,47 +32,49 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return t;  // valid in thread 0
 }
 
-// I_Y = sum_p dV/(2pi)^3 f_Y / (2 E_Y) per cell, E_Y from the lagged masses
-// (or |p| when there are none; a node at p = 0 then adds 0).  Stage 1: block
-// (cell, chunk) sums kMassChunk nodes of every species; stage 2: one block
-// per cell adds its chunks in a fixed order (deterministic) and applies
-// Eq. mg / mq.
-constexpr int kMassChunk = 256;  // nodes per block: a single cell of 30^3 nodes still fills 100+ CUs
+// The start of a collision term, one pass over f: the thermal masses, the
+// output and the term's totals zeroed, and for the FP32 kernels the FP32 shadow
+// and the node quads.  (Apart, these were seven launches of 2 to 9 us, most of
+// them latency: a step of 30^3 gluons spent 60 of 283 us in them.)
+//
+// Masses: I_Y = sum_p dV/(2pi)^3 f_Y / (2 E_Y) per cell, E_Y from the lagged
+// masses (or |p| when there are none; a node at p = 0 then adds 0).  Block
+// (cell, chunk) sums kMassChunk nodes of every species; the last block of a
+// cell to finish adds the cell's chunks in a fixed order (deterministic) and
+// applies Eq. mg / mq.  Without counters (`done`) a second kernel does that.
+constexpr int kMassChunk = kBlock;  // a node per thread: a single cell of 30^3 nodes fills 100+ CUs
 
 __host__ __device__ inline int mass_chunks(const Grid& G) { return (G.nodes + kMassChunk - 1) / kMassChunk; }
 
-__global__ __launch_bounds__(kBlock) void mass_partial(Grid G, const double* __restrict__ f,
-                                                       const double* __restrict__ lag, double* part) {
-  __shared__ double sh[kBlock / 64];
-  const int chunks = mass_chunks(G);
-  const int chunk = blockIdx.x % chunks, cell = blockIdx.x / chunks;
-  const int lo = chunk * kMassChunk, hi = min(G.nodes, lo + kMassChunk);
+// Sums of seven values over the block, in the order of block_sum: valid in
+// thread sp < 7 for value sp.
+__device__ __forceinline__ double block_sum7(const double v[kSpecies], double (*sh)[kSpecies]) {
+  const int w = threadIdx.x / 64, lane = threadIdx.x & 63;
+#pragma unroll
   for (int sp = 0; sp < kSpecies; ++sp) {
-    const double m2 = lag ? lag[sp * G.cells + cell] : 0.0;
-    const double* fc = f + ((size_t)sp * G.cells + cell) * G.nodes;
-    double acc = 0.0;
-    for (int node = lo + threadIdx.x; node < hi; node += blockDim.x) {
-      double p[3];
-      node_p(G, node, p);
-      const double E = sqrt(p[0] * p[0] + p[1] * p[1] + p[2] * p[2] + m2);
-      if (E > 0.0) acc += fc[node] / (2.0 * E);
-    }
-    const double t = block_sum(acc, sh);
-    if (threadIdx.x == 0) part[((size_t)cell * chunks + chunk) * kSpecies + sp] = t;
+    double t = v[sp];
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    if (lane == 0) sh[w][sp] = t;
   }
+  __syncthreads();
+  double t = 0.0;
+  if (threadIdx.x < kSpecies)
+    for (int i = 0; i < (int)(blockDim.x / 64); ++i) t += sh[i][threadIdx.x];
+  __syncthreads();
+  return t;
 }
 
-__global__ __launch_bounds__(kBlock) void mass_final(Grid G, const double* __restrict__ part, int chunks,
-                                                     double* mass2) {
-  __shared__ double sh[kBlock / 64];
-  const int cell = blockIdx.x;  // one block per cell; its threads stride over the chunks
+// The masses of a cell from its chunk sums, by one block.
+__device__ __forceinline__ void masses_of_cell(const Grid& G, const double* part, int chunks, int cell, double* mass2,
+                                               double (*sh)[kSpecies]) {
+  __shared__ double I[kSpecies];
   const double meas = G.dp[0] * G.dp[1] * G.dp[2] / (8.0 * kPi * kPi * kPi);
-  double I[kSpecies];
-  for (int sp = 0; sp < kSpecies; ++sp) {
-    double t = 0.0;
-    for (int c = threadIdx.x; c < chunks; c += blockDim.x) t += part[((size_t)cell * chunks + c) * kSpecies + sp];
-    I[sp] = block_sum(t, sh) * meas;  // fixed order: deterministic
-  }
+  double v[kSpecies] = {};
+  for (int c = threadIdx.x; c < chunks; c += blockDim.x)
+    for (int sp = 0; sp < kSpecies; ++sp) v[sp] += part[((size_t)cell * chunks + c) * kSpecies + sp];
+  const double t = block_sum7(v, sh);
+  if (threadIdx.x < kSpecies) I[threadIdx.x] = t * meas;
+  __syncthreads();
   if (threadIdx.x != 0) return;
   // SU(3): dA = 8, CA = 3, CF = 4/3; N_g = 16, N_q = 6
   const double CF = 4.0 / 3.0;
@@ -86,9 +88,64 @@ __global__ __launch_bounds__(kBlock) void mass_final(Grid G, const double* __res
   }
 }
 
-__global__ void const_mass_kernel(Grid G, Mass7 m, double* mass2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kSpecies * G.cells) mass2[i] = m.v[i / G.cells];
+__global__ __launch_bounds__(kBlock) void term_start_kernel(TermStart a) {
+  __shared__ double sh[kBlock / 64][kSpecies];
+  __shared__ bool last;
+  const Grid& G = a.G;
+  const int chunks = mass_chunks(G);
+  const int chunk = blockIdx.x % chunks, cell = blockIdx.x / chunks;
+  const int node = chunk * kMassChunk + threadIdx.x;
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < a.n_count; i += blockDim.x) a.count[i] = 0ull;
+    for (int i = threadIdx.x; i < a.n_totals; i += blockDim.x) a.totals[i] = 0.0;
+  }
+  double v[kSpecies] = {};
+  if (node < G.nodes) {
+    double p[3];
+    node_p(G, node, p);
+    const double p2 = p[0] * p[0] + p[1] * p[1] + p[2] * p[2];
+    const int iz = node % G.np[2], iy = (node / G.np[2]) % G.np[1];
+    const size_t dz = iz + 1 < G.np[2] ? 1 : 0;
+    const size_t dy = iy + 1 < G.np[1] ? (size_t)G.oy : 0;
+#pragma unroll
+    for (int sp = 0; sp < kSpecies; ++sp) {
+      const size_t i = ((size_t)sp * G.cells + cell) * G.nodes + node;
+      const double x = a.f[i];
+      if (a.A) a.A[i] = 0.0;
+      if (a.f32) a.f32[i] = (float)x;
+      if (a.quads) a.quads[i] = make_float4((float)x, (float)a.f[i + dz], (float)a.f[i + dy], (float)a.f[i + dy + dz]);
+      if (a.part) {
+        const double E = sqrt(p2 + (a.lag ? a.lag[sp * G.cells + cell] : 0.0));
+        if (E > 0.0) v[sp] = x / (2.0 * E);
+      }
+    }
+  }
+  if (!a.part) {  // constant masses
+    if (chunk == 0 && threadIdx.x < kSpecies) a.mass2[threadIdx.x * G.cells + cell] = a.constant.v[threadIdx.x];
+    return;
+  }
+  const double t = block_sum7(v, sh);
+  if (threadIdx.x < kSpecies) a.part[((size_t)cell * chunks + chunk) * kSpecies + threadIdx.x] = t;
+  if (!a.done) return;
+  if (chunks > 1) {
+    // release the partial sums, count this block in, and let the cell's last one read them all
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(&a.done[cell], 1u) == (unsigned)chunks - 1u;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    if (threadIdx.x == 0) a.done[cell] = 0u;
+  } else {
+    __syncthreads();
+  }
+  masses_of_cell(G, a.part, chunks, cell, a.mass2, sh);
+}
+
+__global__ __launch_bounds__(kBlock) void mass_final(Grid G, const double* __restrict__ part, int chunks,
+                                                     double* mass2) {
+  __shared__ double sh[kBlock / 64][kSpecies];
+  masses_of_cell(G, part, chunks, blockIdx.x, mass2, sh);
 }
 
 __device__ __forceinline__ int shift_cell(const Grid& G, int cell, int axis, int d) {
@@ -161,7 +218,10 @@ __global__ __launch_bounds__(kBlock) void update_kernel(Grid G, Evolving ev, con
                                                         const double* __restrict__ A,
                                                         const double* __restrict__ mass2, double dt,
                                                         int scheme, double* __restrict__ f_out,
-                                                        float* __restrict__ f32) {
+                                                        float* __restrict__ f32, double* __restrict__ lag) {
+  // the masses of this step are the lagged ones of the next
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kSpecies * G.cells; i += gridDim.x * blockDim.x)
+    lag[i] = mass2[i];
   const size_t per = (size_t)G.cells * G.nodes;
   const size_t total = (size_t)ev.n * per;
   for (size_t j = blockIdx.x * (size_t)blockDim.x + threadIdx.x; j < total; j += (size_t)gridDim.x * blockDim.x) {
@@ -185,65 +245,65 @@ __global__ __launch_bounds__(kBlock) void update_kernel(Grid G, Evolving ev, con
 // per-block partials; stage 2: one block.
 constexpr int kObs = kSpecies * kObsPer;
 
+constexpr int kObsRow = kObsPer + 3;  // partials of a (block, species): the values, min f, max fermion f, non-finite
+
+// Block (b, species): a block per species keeps the reductions of a block to
+// kObsRow instead of seven times that (30^3 nodes, one cell: 41 -> 11 us).
 __global__ __launch_bounds__(kBlock) void observables_partial(Grid G, const double* __restrict__ f,
                                                               const double* __restrict__ mass2,
                                                               double* partial) {
-  __shared__ double sh[kBlock / 64];
+  __shared__ double sh[kBlock / 64][kObsRow];
   const size_t per = (size_t)G.cells * G.nodes;
+  const int sp = blockIdx.y;
+  double v[kObsPer] = {};
   double minf = 1e300, maxq = -1e300, bad = 0.0;
-  for (int sp = 0; sp < kSpecies; ++sp) {
-    double N = 0.0, E = 0.0, P0 = 0.0, P1 = 0.0, P2 = 0.0, M = 0.0, S = 0.0, T0 = 0.0, T1 = 0.0, T2 = 0.0;
-    const bool evolve = (G.species_mask >> sp) & 1u;
-    const double sgn = sp == kGluon ? 1.0 : -1.0;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < per; i += (size_t)gridDim.x * blockDim.x) {
-      const int cell = (int)(i / G.nodes), node = (int)(i % G.nodes);
-      const double fv = f[(size_t)sp * per + i];
-      double p[3];
-      node_p(G, node, p);
-      const double m2 = mass2[sp * G.cells + cell];
-      const double En = sqrt(p[0] * p[0] + p[1] * p[1] + p[2] * p[2] + m2);
-      N += fv;
-      E += En * fv;
-      if (En > 0.0) {
-        const double w = fv / En;
-        M += m2 * w;
-        T0 += p[0] * p[0] * w;
-        T1 += p[1] * p[1] * w;
-        T2 += p[2] * p[2] * w;
-      }
-      const double one = 1.0 + sgn * fv;
-      if (fv > 0.0 && one > 0.0) S += one * log(one) * sgn - fv * log(fv);
-      P0 += p[0] * fv;
-      P1 += p[1] * fv;
-      P2 += p[2] * fv;
-      if (evolve) {
-        if (!isfinite(fv)) bad += 1.0;
-        minf = fmin(minf, fv);
-        if (sp != kGluon) maxq = fmax(maxq, fv);
-      }
+  const bool evolve = (G.species_mask >> sp) & 1u;
+  const double sgn = sp == kGluon ? 1.0 : -1.0;
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < per; i += (size_t)gridDim.x * blockDim.x) {
+    const int cell = (int)(i / G.nodes), node = (int)(i % G.nodes);
+    const double fv = f[(size_t)sp * per + i];
+    double p[3];
+    node_p(G, node, p);
+    const double m2 = mass2[sp * G.cells + cell];
+    const double En = sqrt(p[0] * p[0] + p[1] * p[1] + p[2] * p[2] + m2);
+    v[0] += fv;
+    v[1] += En * fv;
+    for (int k = 0; k < 3; ++k) v[2 + k] += p[k] * fv;
+    if (En > 0.0) {
+      const double w = fv / En;
+      v[5] += m2 * w;
+      for (int k = 0; k < 3; ++k) v[7 + k] += p[k] * p[k] * w;
     }
-    const double vals[kObsPer] = {N, E, P0, P1, P2, M, S, T0, T1, T2};
-    for (int k = 0; k < kObsPer; ++k) {
-      const double t = block_sum(vals[k], sh);
-      if (threadIdx.x == 0) partial[(size_t)blockIdx.x * (kObs + 3) + sp * kObsPer + k] = t;
+    const double one = 1.0 + sgn * fv;
+    if (fv > 0.0 && one > 0.0) v[6] += one * log(one) * sgn - fv * log(fv);
+    if (evolve) {
+      if (!isfinite(fv)) bad += 1.0;
+      minf = fmin(minf, fv);
+      if (sp != kGluon) maxq = fmax(maxq, fv);
     }
   }
-  // min / max over the block
   for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+    for (int k = 0; k < kObsPer; ++k) v[k] += __shfl_xor(v[k], off, 64);
     minf = fmin(minf, __shfl_xor(minf, off, 64));
     maxq = fmax(maxq, __shfl_xor(maxq, off, 64));
+    bad += __shfl_xor(bad, off, 64);
   }
-  const double nbad = block_sum(bad, sh);
-  __shared__ double shmin[kBlock / 64], shmax[kBlock / 64];
-  const int w = threadIdx.x / 64, lane = threadIdx.x & 63;
-  if (lane == 0) { shmin[w] = minf; shmax[w] = maxq; }
+  const int w = threadIdx.x / 64;
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int k = 0; k < kObsPer; ++k) sh[w][k] = v[k];
+    sh[w][kObsPer] = minf;
+    sh[w][kObsPer + 1] = maxq;
+    sh[w][kObsPer + 2] = bad;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < (int)(blockDim.x / 64); ++i) { minf = fmin(minf, shmin[i]); maxq = fmax(maxq, shmax[i]); }
-    double* o = partial + (size_t)blockIdx.x * (kObs + 3);
-    o[kObs] = minf;
-    o[kObs + 1] = maxq;
-    o[kObs + 2] = nbad;
+  if (threadIdx.x < kObsRow) {
+    const int k = threadIdx.x;
+    double t = k == kObsPer ? 1e300 : (k == kObsPer + 1 ? -1e300 : 0.0);
+    for (int i = 0; i < kBlock / 64; ++i)
+      t = k == kObsPer ? fmin(t, sh[i][k]) : (k == kObsPer + 1 ? fmax(t, sh[i][k]) : t + sh[i][k]);
+    partial[((size_t)blockIdx.x * kSpecies + sp) * kObsRow + k] = t;
   }
 }
 
@@ -256,9 +316,12 @@ __global__ __launch_bounds__(kFinalThreads) void observables_final(Grid G, const
   const int lane = threadIdx.x & 63, nw = blockDim.x / 64;
   for (int k = threadIdx.x / 64; k < kObs + 3; k += nw) {
     const bool is_min = k == kObs, is_max = k == kObs + 1;
+    const bool whole = k >= kObs;  // over every species
     double v = is_min ? 1e300 : (is_max ? -1e300 : 0.0);
-    for (int b = lane; b < nblocks; b += 64) {
-      const double x = partial[(size_t)b * (kObs + 3) + k];
+    const int n = whole ? nblocks * kSpecies : nblocks;
+    for (int b = lane; b < n; b += 64) {
+      const double x = whole ? partial[(size_t)b * kObsRow + kObsPer + (k - kObs)]
+                             : partial[((size_t)b * kSpecies + k / kObsPer) * kObsRow + k % kObsPer];
       v = is_min ? fmin(v, x) : (is_max ? fmax(v, x) : v + x);
     }
     for (int off = 32; off > 0; off >>= 1) {
@@ -319,29 +382,20 @@ __global__ __launch_bounds__(kBlock) void energy_final(Grid G, const double* par
   }
 }
 
-__global__ void to_f32_kernel(const double* __restrict__ src, float* __restrict__ dst, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    dst[i] = (float)src[i];
-}
-
-__global__ void quads_kernel(Grid G, const float* __restrict__ f, float4* __restrict__ q, size_t n) {
+// f into both buffers and the FP32 shadow (src may be f itself).
+__global__ void set_field_kernel(const double* src, double* f, double* __restrict__ f_next, float* __restrict__ f32,
+                                 size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int node = (int)(i % (size_t)G.nodes);
-    const int iz = node % G.np[2], iy = (node / G.np[2]) % G.np[1];
-    const size_t dz = iz + 1 < G.np[2] ? 1 : 0;
-    const size_t dy = iy + 1 < G.np[1] ? (size_t)G.oy : 0;
-    q[i] = make_float4(f[i], f[i + dz], f[i + dy], f[i + dy + dz]);
+    const double x = src[i];
+    f[i] = x;
+    f_next[i] = x;
+    f32[i] = (float)x;
   }
 }
 
 __global__ void fill_kernel(double* __restrict__ dst, double v, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
     dst[i] = v;
-}
-
-__global__ void zero_u64_kernel(unsigned long long* dst, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = 0ull;
 }
 
 unsigned grid_for(size_t n) {
@@ -354,29 +408,22 @@ unsigned grid_for(size_t n) {
 
 size_t mass_scratch(const Grid& G) { return (size_t)G.cells * mass_chunks(G) * kSpecies; }
 
-hipError_t launch_masses(const Grid& G, const double* f, const double* lag, double* scratch, double* mass2,
-                         hipStream_t st) {
-  const int chunks = mass_chunks(G);
-  hipLaunchKernelGGL(mass_partial, dim3(chunks * G.cells), dim3(kBlock), 0, st, G, f, lag, scratch);
-  hipLaunchKernelGGL(mass_final, dim3(G.cells), dim3(kBlock), 0, st, G, scratch, chunks, mass2);
-  return hipGetLastError();
-}
-
-hipError_t launch_const_masses(const Grid& G, const Mass7& m, double* mass2, hipStream_t st) {
-  const int n = kSpecies * G.cells;
-  hipLaunchKernelGGL(const_mass_kernel, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, G, m, mass2);
+hipError_t launch_term_start(const TermStart& a, hipStream_t st) {
+  const int chunks = mass_chunks(a.G);
+  hipLaunchKernelGGL(term_start_kernel, dim3(chunks * a.G.cells), dim3(kBlock), 0, st, a);
+  if (a.part && !a.done)
+    hipLaunchKernelGGL(mass_final, dim3(a.G.cells), dim3(kBlock), 0, st, a.G, a.part, chunks, a.mass2);
   return hipGetLastError();
 }
 
 hipError_t launch_update(const Grid& G, const double* f, const double* A, const double* mass2, double dt,
-                         int scheme, double* f_out, float* f32, hipStream_t st) {
+                         int scheme, double* f_out, float* f32, double* lag, hipStream_t st) {
   Evolving ev{};
   for (int sp = 0; sp < kSpecies; ++sp)
     if ((G.species_mask >> sp) & 1u) ev.sp[ev.n++] = sp;
   const size_t n = (size_t)ev.n * G.cells * G.nodes;
-  if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(update_kernel, dim3(grid_for(n)), dim3(kBlock), 0, st, G, ev, f, A, mass2, dt, scheme, f_out,
-                     f32);
+                     f32, lag);
   return hipGetLastError();
 }
 
@@ -386,12 +433,12 @@ int observables_blocks(const Grid& G) {
   return (int)(b > 512 ? 512 : (b ? b : 1));
 }
 
-size_t observables_scratch(const Grid& G) { return (size_t)observables_blocks(G) * (kObs + 3); }
+size_t observables_scratch(const Grid& G) { return (size_t)observables_blocks(G) * kSpecies * kObsRow; }
 
 hipError_t launch_observables(const Grid& G, const double* f, const double* mass2, double* scratch,
                               double* out, hipStream_t st) {
   const int nb = observables_blocks(G);
-  hipLaunchKernelGGL(observables_partial, dim3(nb), dim3(kBlock), 0, st, G, f, mass2, scratch);
+  hipLaunchKernelGGL(observables_partial, dim3(nb, kSpecies), dim3(kBlock), 0, st, G, f, mass2, scratch);
   hipLaunchKernelGGL(observables_final, dim3(1), dim3(kFinalThreads), 0, st, G, scratch, nb, out);
   return hipGetLastError();
 }
@@ -404,24 +451,13 @@ hipError_t launch_energy_budget(const Grid& G, const double* f, const double* A,
   return hipGetLastError();
 }
 
-hipError_t launch_to_f32(const double* src, float* dst, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(to_f32_kernel, dim3(grid_for(n)), dim3(kBlock), 0, st, src, dst, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_f32_quads(const Grid& G, const float* f32, float4* q, hipStream_t st) {
-  const size_t n = (size_t)kSpecies * G.cells * G.nodes;
-  hipLaunchKernelGGL(quads_kernel, dim3(grid_for(n)), dim3(kBlock), 0, st, G, f32, q, n);
+hipError_t launch_set_field(const double* src, double* f, double* f_next, float* f32, size_t n, hipStream_t st) {
+  hipLaunchKernelGGL(set_field_kernel, dim3(grid_for(n)), dim3(kBlock), 0, st, src, f, f_next, f32, n);
   return hipGetLastError();
 }
 
 hipError_t launch_fill(double* dst, double v, size_t n, hipStream_t st) {
   hipLaunchKernelGGL(fill_kernel, dim3(grid_for(n)), dim3(kBlock), 0, st, dst, v, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_zero_u64(unsigned long long* dst, int n, hipStream_t st) {
-  hipLaunchKernelGGL(zero_u64_kernel, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, dst, n);
   return hipGetLastError();
 }
 

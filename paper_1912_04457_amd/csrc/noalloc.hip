@@ -119,8 +119,8 @@ qgbe_status qgbe_collision_term_noalloc(const qgbe_grid_desc* desc, const double
   c.d_mass2 = cv.take<double>((size_t)kSpecies * c.G.cells);
   c.d_mass_part = cv.take<double>(mass_scratch(c.G));
   c.d_count = cv.take<unsigned long long>(kStripes);
-  c.d_mc = cv.take<double>(2 * kStripes);
-  c.d_chan_var = cv.take<double>((size_t)kStripes * nch1);
+  c.d_mc = cv.take<double>((size_t)kStripes * (2 + nch1));
+  c.d_chan_var = c.d_mc + 2 * kStripes;
   if (fp32) {
     c.d_f32 = cv.take<float>(n);
     if (c.need_quads[0]) c.d_f32q = cv.take<float4>(n);
@@ -150,10 +150,8 @@ qgbe_status qgbe_collision_term_noalloc(const qgbe_grid_desc* desc, const double
     }
   }
 
-  st = compute_masses(&c);
+  st = start_term(&c, sampler, A, true);
   if (st) return st;
-  if (fp32) HIP_TRY(launch_to_f32(c.d_f, c.d_f32, n, c.stream), "f to fp32");
-  HIP_TRY(launch_fill(A, 0.0, n, c.stream), "zero A");
   return run_collide(&c, n_samples, sampler, A, nullptr, nullptr);
 }
 
