@@ -41,7 +41,12 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
 // masses (or |p| when there are none; a node at p = 0 then adds 0).  Block
 // (cell, chunk) sums kMassChunk nodes of every species; the last block of a
 // cell to finish adds the cell's chunks in a fixed order (deterministic) and
-// applies Eq. mg / mq.  Without counters (`done`) a second kernel does that.
+// applies Eq. mg / mq.  Without counters (`done`), or with more than
+// kMaxFusedBlocks blocks, a second kernel does that: every block's release
+// writes its XCD's L2 back, 1.3 ms for the 8192 blocks of 256 cells of 20^3
+// against 0.2 ms with the second kernel (106 blocks of 30^3: the second kernel
+// is 6 us and a gap more).
+constexpr int kMaxFusedBlocks = 512;
 constexpr int kMassChunk = kBlock;  // a node per thread: a single cell of 30^3 nodes fills 100+ CUs
 
 __host__ __device__ inline int mass_chunks(const Grid& G) { return (G.nodes + kMassChunk - 1) / kMassChunk; }
@@ -408,8 +413,10 @@ unsigned grid_for(size_t n) {
 
 size_t mass_scratch(const Grid& G) { return (size_t)G.cells * mass_chunks(G) * kSpecies; }
 
-hipError_t launch_term_start(const TermStart& a, hipStream_t st) {
+hipError_t launch_term_start(const TermStart& args, hipStream_t st) {
+  TermStart a = args;
   const int chunks = mass_chunks(a.G);
+  if ((long long)chunks * a.G.cells > kMaxFusedBlocks) a.done = nullptr;
   hipLaunchKernelGGL(term_start_kernel, dim3(chunks * a.G.cells), dim3(kBlock), 0, st, a);
   if (a.part && !a.done)
     hipLaunchKernelGGL(mass_final, dim3(a.G.cells), dim3(kBlock), 0, st, a.G, a.part, chunks, a.mass2);
