@@ -52,38 +52,72 @@ __device__ __forceinline__ double rsqrt64(double x) {
 
 __device__ __forceinline__ double sqrt64(double x) { return x > 0.0 ? x * rsqrt64(x) : 0.0; }
 
-// sin and cos of 2 pi u for u in [0, 1).  With x = 2u = q/2 + r, q the
-// nearest multiple of 1/2 (exact: u has at most 24 significant bits) and
-// |r| <= 1/4, sin(pi r) = r S(r^2) and cos(pi r) = C(r^2) with S and C of
-// degree 6 (Chebyshev-node fits, gen_fp64_poly.py; fit errors 1e-17 and
-// 5e-17), and the quadrant q mod 4 permutes and negates them.  Measured on
-// the CPU over every 23-bit u: within 1.8e-16 of sin and cos (the Taylor
-// series to r^15 and r^16 it replaces: 1.9e-16).
-__device__ __forceinline__ void sincos_2pi(double u, double& sn, double& cs) {
-  const double x = 2.0 * u;
-  const double q = rint(2.0 * x);
-  const double r = fma(-0.5, q, x);
+// sqrt(x) for finite x > 0, refined as rsqrt64: g = x y, r = (1 - g y) / 2,
+// g (1 + r + 3/2 r^2).
+__device__ __forceinline__ double sqrt_pos(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double g = x * y;
+  const double r = fma(-0.5 * g, y, 0.5);
+  return fma(g, fma(1.5 * r, r, r), g);
+}
+
+// x with its sign flipped where bit 31 of m is set.
+__device__ __forceinline__ double flip_sign(double x, uint32_t m) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  return __longlong_as_double((long long)(b ^ ((unsigned long long)(m & 0x80000000u) << 32)));
+}
+
+// a b + c with a constant c.  Written out, the compiler keeps the coefficients
+// of the polynomials below in vector registers (26 to 64 of the 168) and copies
+// each before the accumulating form of the instruction overwrites it; in a
+// scalar pair c costs neither (scalar moves issue beside the vector unit).
+__device__ __forceinline__ double fma_k(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+
+// sin(pi r) and cos(pi r) for |r| <= 1/4, moved to the quadrant k (mod 4):
+// sin(pi r) = r S(r^2) and cos(pi r) = C(r^2) with S and C of degree 6
+// (Chebyshev-node fits, gen_fp64_poly.py; fit errors 1e-17 and 5e-17).
+// Measured on the CPU over every 23-bit u: within 1.8e-16 of sin and cos (the
+// Taylor series to r^15 and r^16 they replace: 1.9e-16).
+__device__ __forceinline__ void sincos_quadrant(double r, int k, double& sn, double& cs) {
   const double r2 = r * r;
   double ps = 0.0004615313805851339;
-  ps = fma(ps, r2, -0.0073700215052934955);
-  ps = fma(ps, r2, 0.08214586917478434);
-  ps = fma(ps, r2, -0.5992645289394928);
-  ps = fma(ps, r2, 2.550164039873374);
-  ps = fma(ps, r2, -5.167712780049954);
-  ps = fma(ps, r2, 3.141592653589793);
+  ps = fma_k(ps, r2, -0.0073700215052934955);
+  ps = fma_k(ps, r2, 0.08214586917478434);
+  ps = fma_k(ps, r2, -0.5992645289394928);
+  ps = fma_k(ps, r2, 2.550164039873374);
+  ps = fma_k(ps, r2, -5.167712780049954);
+  ps = fma_k(ps, r2, 3.141592653589793);
   ps *= r;
   double pc = 0.001906807054314109;
-  pc = fma(pc, r2, -0.025804938121446575);
-  pc = fma(pc, r2, 0.23533054718578558);
-  pc = fma(pc, r2, -1.3352627670358546);
-  pc = fma(pc, r2, 4.058712126397826);
-  pc = fma(pc, r2, -4.934802200544605);
+  pc = fma_k(pc, r2, -0.025804938121446575);
+  pc = fma_k(pc, r2, 0.23533054718578558);
+  pc = fma_k(pc, r2, -1.3352627670358546);
+  pc = fma_k(pc, r2, 4.058712126397826);
+  pc = fma_k(pc, r2, -4.934802200544605);
   pc = fma(pc, r2, 1.0);
-  const int k = (int)q;
   const double a = (k & 1) ? pc : ps;   // sin before the sign
   const double b = (k & 1) ? ps : pc;   // cos before the sign
-  sn = (k & 2) ? -a : a;
-  cs = ((k + 1) & 2) ? -b : b;
+  sn = flip_sign(a, (uint32_t)k << 30);
+  cs = flip_sign(b, (uint32_t)(k + 1) << 30);
+}
+
+// sin and cos of 2 pi u for u in [0, 1): 2u = k/2 + r, k the nearest integer
+// to 4u (exact: u has at most 24 significant bits, or r's rounding is below
+// the fits' errors).
+__device__ __forceinline__ void sincos_2pi(double u, double& sn, double& cs) {
+  const double q = rint(4.0 * u);
+  sincos_quadrant(fma(-0.5, q, 2.0 * u), (int)q, sn, cs);
+}
+
+// The same for u = (v + 1/2) 2^-23: the quadrant and the remainder are bit
+// fields of v.
+__device__ __forceinline__ void sincos_2pi_23(uint32_t v, double& sn, double& cs) {
+  const int rem = (int)(v << 11) >> 11;  // the low 21 bits, signed
+  sincos_quadrant(fma((double)rem, 0x1p-22, 0x1p-23), (int)((v + (1u << 20)) >> 21), sn, cs);
 }
 
 // e^x: x = k ln2 + r with |r| <= ln2/2 (ln2 split so k*ln2_hi is exact for
@@ -96,15 +130,15 @@ __device__ __forceinline__ double exp64(double x) {
   double r = fma(-k, 0.6931471805598903, x);
   r = fma(-k, 5.497923018708371e-14, r);
   double p = 2.510038549551032e-08;
-  p = fma(p, r, 2.7620088445409746e-07);
-  p = fma(p, r, 2.7557268459997064e-06);
-  p = fma(p, r, 2.4801521295954376e-05);
-  p = fma(p, r, 0.00019841269863053618);
-  p = fma(p, r, 0.0013888888917213717);
-  p = fma(p, r, 0.008333333333330062);
-  p = fma(p, r, 0.04166666666662413);
-  p = fma(p, r, 0.16666666666666669);
-  p = fma(p, r, 0.5000000000000001);
+  p = fma_k(p, r, 2.7620088445409746e-07);
+  p = fma_k(p, r, 2.7557268459997064e-06);
+  p = fma_k(p, r, 2.4801521295954376e-05);
+  p = fma_k(p, r, 0.00019841269863053618);
+  p = fma_k(p, r, 0.0013888888917213717);
+  p = fma_k(p, r, 0.008333333333330062);
+  p = fma_k(p, r, 0.04166666666662413);
+  p = fma_k(p, r, 0.16666666666666669);
+  p = fma_k(p, r, 0.5000000000000001);
   p = fma(p, r, 1.0);
   p = fma(p, r, 1.0);
   return ldexp(p, (int)k);
@@ -125,12 +159,12 @@ __device__ __forceinline__ double log64(double a) {
   const double s = (m - 1.0) * rcp64(m + 1.0);
   const double s2 = s * s;
   double p = 0.07404933786156531;
-  p = fma(p, s2, 0.0765625655736915);
-  p = fma(p, s2, 0.09091816120808513);
-  p = fma(p, s2, 0.11111098523202137);
-  p = fma(p, s2, 0.1428571438036914);
-  p = fma(p, s2, 0.19999999999650955);
-  p = fma(p, s2, 0.33333333333333826);
+  p = fma_k(p, s2, 0.0765625655736915);
+  p = fma_k(p, s2, 0.09091816120808513);
+  p = fma_k(p, s2, 0.11111098523202137);
+  p = fma_k(p, s2, 0.1428571438036914);
+  p = fma_k(p, s2, 0.19999999999650955);
+  p = fma_k(p, s2, 0.33333333333333826);
   p = fma(p, s2, 1.0);
   const double de = (double)e;
   return fma(de, 0.6931471805598903, fma(de, 5.497923018708371e-14, 2.0 * s * p));
@@ -192,8 +226,16 @@ struct Stencil {
 
 // The grid coordinate and its fraction are formed in FP64 so the weights carry
 // a relative (not an absolute 2^-24 * n) error when rounded to R.
+// (FP32 weights: the largest coordinate below n - 1 stands for n - 1, so the
+// whole part is at most n - 2 by itself, and the fraction rounds to 1.)
 template <typename R>
 __device__ __forceinline__ R clamp_axis(double p, double pc, double inv_dp, int n, int& i0) {
+  if constexpr (sizeof(R) == sizeof(float)) {
+    const double top = __longlong_as_double(__double_as_longlong((double)(n - 1)) - 1);
+    const double t = fmin(fmax(fma(p, inv_dp, pc), 0.0), top);
+    i0 = (int)t;
+    return (R)__builtin_amdgcn_fract(t);
+  }
   const double t = fmin(fmax(fma(p, inv_dp, pc), 0.0), (double)(n - 1));
   const int i = min((int)t, n - 2);
   i0 = i;
@@ -274,6 +316,7 @@ struct Item {
   double E1;
   double m1sq, m2sq, m3sq, m4sq;
   double dm34;              // m3^2 - m4^2
+  double dde, sde;          // m1^2 - m2^2 -+ dm34: E1* -+ ... of t and u, times 2 sqrt s
   double sum2, dif2;        // (m3 + m4)^2 (the threshold of s), (m3 - m4)^2
   double mu;                // regulator m_g^2
   double f1;
@@ -287,66 +330,114 @@ struct Geo {
   double E2, s, t, u, rs, pstar;
 };
 
-// Sample geometry from the five uniforms; false if below threshold or outside the box.
-__device__ __forceinline__ bool geometry(const Item& it, const Grid& G, const double u[5], Geo& g) {
-  for (int a = 0; a < 3; ++a) g.p2[a] = fma(2.0 * G.ph[a], u[a], -G.ph[a]);
-  g.E2 = sqrt64(g.p2[0] * g.p2[0] + g.p2[1] * g.p2[1] + g.p2[2] * g.p2[2] + it.m2sq);
+// Where a sample lies: p2 in the box, cos and sin of theta* (and 2 (1 -+ cos)
+// for t and u, without cancellation), cos and sin of phi*.
+struct SampleMap {
+  double p2[3], cth, sth, omc2, opc2, cphi, sphi;
+};
+
+// From the five unit-cube variables (the mixture's; any doubles in (0, 1)).
+__device__ __forceinline__ SampleMap map_unit(const Grid& G, const double u[5]) {
+  SampleMap m;
+  for (int a = 0; a < 3; ++a) m.p2[a] = fma(2.0 * G.ph[a], u[a], -G.ph[a]);
+  const double w = 1.0 - u[3];
+  m.cth = fma(2.0, u[3], -1.0);
+  m.sth = 2.0 * sqrt64(u[3] * w);
+  m.omc2 = 4.0 * w;
+  m.opc2 = 4.0 * u[3];
+  sincos_2pi(u[4], m.sphi, m.cphi);
+  return m;
+}
+
+// Five 23-bit uniforms (v + 1/2) 2^-23 from one Philox block: the top 23 bits
+// of each word, and for the fifth the low 9 bits of words 0 and 1 and bits
+// 4..8 of word 2.
+__device__ __forceinline__ uint32_t fifth_word(uint32_t x0, uint32_t x1, uint32_t x2) {
+  return ((x0 & 0x1FFu) << 14) | ((x1 & 0x1FFu) << 5) | ((x2 & 0x1FFu) >> 4);
+}
+
+__device__ __forceinline__ void five_uniforms(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, double u[5]) {
+  u[0] = unif23(x0 >> 9);
+  u[1] = unif23(x1 >> 9);
+  u[2] = unif23(x2 >> 9);
+  u[3] = unif23(x3 >> 9);
+  u[4] = unif23(fifth_word(x0, x1, x2));
+}
+
+// 2 (v + 1/2) 2^-23 - 1, exact.
+__device__ __forceinline__ double centred23(uint32_t v) { return fma((double)v, 0x1p-22, 0x1p-23 - 1.0); }
+
+// The uniform sampler's map, straight from the words.
+__device__ __forceinline__ SampleMap map_words(const Grid& G, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3) {
+  SampleMap m;
+  m.p2[0] = G.ph[0] * centred23(x0 >> 9);
+  m.p2[1] = G.ph[1] * centred23(x1 >> 9);
+  m.p2[2] = G.ph[2] * centred23(x2 >> 9);
+  m.cth = centred23(x3 >> 9);
+  m.sth = sqrt_pos(fma(-m.cth, m.cth, 1.0));
+  m.omc2 = fma(-2.0, m.cth, 2.0);
+  m.opc2 = fma(2.0, m.cth, 2.0);
+  sincos_2pi_23(fifth_word(x0, x1, x2), m.sphi, m.cphi);
+  return m;
+}
+
+// Sample geometry; false if below threshold or outside the box.  FP64 and the
+// bound of every sampler's loop (VALU issue), so written for few operations:
+// p3* = p* (sin cos phi e1 + sin sin phi e2 + cos n) with the frame of n
+// multiplied out, and t and u from the CM frame, t = (E1* - E3*)^2 - (p1* -
+// p*)^2 - 2 p1* p* (1 - cos), u likewise with E4* and 1 + cos: E1* - E3* and
+// E1* - E4* are mass differences over 2 sqrt s, and a small t or u keeps its
+// relative accuracy (differences of momenta lose it).  With the constants of
+// the polynomials in scalar registers, the three-way xors and map_words, a term
+// of 256 cells x 8000 nodes x 2048 samples takes 59.8 ms where the plain form
+// (frame vectors, t and u from the lab momenta) took 66.8; 7 species x 17
+// channels x 8000 x 4096 mixture samples 7.36 for 7.84.
+__device__ __forceinline__ bool geometry(const Item& it, const Grid& G, const SampleMap& m, Geo& g) {
+  for (int a = 0; a < 3; ++a) g.p2[a] = m.p2[a];
+  g.E2 = sqrt_pos(g.p2[0] * g.p2[0] + g.p2[1] * g.p2[1] + g.p2[2] * g.p2[2] + it.m2sq);  // p2 = 0, m2 = 0: NaN, rejected below
   const double E = it.E1 + g.E2;
   const double P[3] = {it.p1[0] + g.p2[0], it.p1[1] + g.p2[1], it.p1[2] + g.p2[2]};
   const double s = E * E - (P[0] * P[0] + P[1] * P[1] + P[2] * P[2]);
   g.s = s;
   if (!(s > it.sum2)) return false;  // threshold (m3 + m4)^2
   const double rs = rsqrt64(s);
-  const double sq = s * rs;
+  const double sq = s * rs, hrs = 0.5 * rs;
   g.rs = rs;
-  g.pstar = 0.5 * rs * sqrt64((s - it.sum2) * (s - it.dif2));
+  g.pstar = hrs * sqrt_pos((s - it.sum2) * (s - it.dif2));
   // k1 in the CM frame: p1* = p1 + P ((P.p1)/(sqrt s (E + sqrt s)) - E1/sqrt s)
   const double inv_E = rcp64(E + sq);
   const double Pp1 = P[0] * it.p1[0] + P[1] * it.p1[1] + P[2] * it.p1[2];
   const double c1 = (Pp1 * inv_E - it.E1) * rs;
   double n[3] = {it.p1[0] + P[0] * c1, it.p1[1] + P[1] * c1, it.p1[2] + P[2] * c1};
-  const double rn = rsqrt64(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
+  const double nn = n[0] * n[0] + n[1] * n[1] + n[2] * n[2];
+  const double rn = rsqrt64(nn);
   n[0] *= rn; n[1] *= rn; n[2] *= rn;
-  // orthonormal completion of n (Duff et al., JCGT 6(1), 2017)
-  const double sgn = copysign(1.0, n[2]);
-  const double a = -rcp64(sgn + n[2]);
-  const double b = n[0] * n[1] * a;
-  const double e1[3] = {1.0 + sgn * n[0] * n[0] * a, sgn * b, -sgn * n[0]};
-  const double e2[3] = {b, sgn + n[1] * n[1] * a, -n[1]};
-  const double cth = 2.0 * u[3] - 1.0;
-  const double sth = 2.0 * sqrt64(u[3] * (1.0 - u[3]));
-  double sphi, cphi;
-  sincos_2pi(u[4], sphi, cphi);
-  const double sc = sth * cphi, ss = sth * sphi;
-  double p3s[3];
-  for (int k = 0; k < 3; ++k) p3s[k] = g.pstar * (sc * e1[k] + ss * e2[k] + cth * n[k]);
-  const double E3s = 0.5 * (s + it.dm34) * rs;
+  // orthonormal completion of n (Duff et al., JCGT 6(1), 2017): with sg the
+  // sign of n_z, a = -1 / (sg + n_z), e1 = (1 + sg n_x^2 a, sg n_x n_y a, -sg n_x)
+  // and e2 = (n_x n_y a, sg + n_y^2 a, -n_y)
+  const uint32_t sgn = (uint32_t)((unsigned long long)__double_as_longlong(n[2]) >> 32);
+  const double ra = rcp64(flip_sign(1.0, sgn) + n[2]);
+  const double st = m.sth * g.pstar, ct = m.cth * g.pstar;
+  const double sc = st * m.cphi, ss = st * m.sphi;
+  const double w = fma(flip_sign(sc, sgn), n[0], ss * n[1]);
+  const double c2 = fma(-ra, w, ct);
+  const double p3s[3] = {fma(n[0], c2, sc), fma(n[1], c2, flip_sign(ss, sgn)), fma(n[2], ct, -w)};
+  const double E3s = (s + it.dm34) * hrs;
   const double Pp3 = P[0] * p3s[0] + P[1] * p3s[1] + P[2] * p3s[2];
   const double c3 = (Pp3 * inv_E + E3s) * rs;
   for (int k = 0; k < 3; ++k) {
     g.p3[k] = p3s[k] + P[k] * c3;
     g.p4[k] = P[k] - g.p3[k];
   }
-  const double E3 = (E * E3s + Pp3) * rs;
-  const double E4 = E - E3;
   for (int k = 0; k < 3; ++k) {
     if (!(fabs(g.p3[k]) <= G.ph[k]) || !(fabs(g.p4[k]) <= G.ph[k])) return false;
   }
-  const double d13[3] = {it.p1[0] - g.p3[0], it.p1[1] - g.p3[1], it.p1[2] - g.p3[2]};
-  const double d14[3] = {it.p1[0] - g.p4[0], it.p1[1] - g.p4[1], it.p1[2] - g.p4[2]};
-  g.t = (it.E1 - E3) * (it.E1 - E3) - (d13[0] * d13[0] + d13[1] * d13[1] + d13[2] * d13[2]);
-  g.u = (it.E1 - E4) * (it.E1 - E4) - (d14[0] * d14[0] + d14[1] * d14[1] + d14[2] * d14[2]);
+  const double p1s = nn * rn, pp = p1s * g.pstar;
+  const double dp = p1s - g.pstar, dp2 = dp * dp;
+  const double d3 = it.dde * hrs, d4 = it.sde * hrs;
+  g.t = fma(-pp, m.omc2, fma(d3, d3, -dp2));
+  g.u = fma(-pp, m.opc2, fma(d4, d4, -dp2));
   return true;
-}
-
-// Five 23-bit uniforms from one Philox block: the top 23 bits of each word,
-// and for the fifth the low 9 bits of words 0 and 1 and bits 4..8 of word 2.
-__device__ __forceinline__ void five_uniforms(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, double u[5]) {
-  u[0] = unif23(x0 >> 9);
-  u[1] = unif23(x1 >> 9);
-  u[2] = unif23(x2 >> 9);
-  u[3] = unif23(x3 >> 9);
-  u[4] = unif23(((x0 & 0x1FFu) << 14) | ((x1 & 0x1FFu) << 5) | ((x2 & 0x1FFu) >> 4));
 }
 
 // Order a wave's LDS accesses across its lanes (the LDS executes one wave's
@@ -638,6 +729,8 @@ __device__ __forceinline__ void item_pair(Item& it, const CollideArgs& A, const 
   it.sum2 = (m3 + m4) * (m3 + m4);
   it.dif2 = (m3 - m4) * (m3 - m4);
   it.dm34 = it.m3sq - it.m4sq;
+  it.dde = (it.m1sq - it.m2sq) - it.dm34;
+  it.sde = (it.m1sq - it.m2sq) + it.dm34;
   const double V5 = G.Vp * 4.0 * kPi;
   it.coef = (A.symmetric ? ch.w : ch.sigma) * V5 / (double)A.n_samples;
 }

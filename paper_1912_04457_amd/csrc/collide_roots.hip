@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void record_kernel(CollideArgs A, int n_per_it
     for (int d = 0; d < 5; ++d) out[8 + d] = (float)log(u[d] / (1.0 - u[d]));
     double v = 0.0;
     Geo g;
-    if (it.E1 > 0.0 && geometry(it, G, u, g)) {
+    if (it.E1 > 0.0 && geometry(it, G, map_words(G, x0, x1, x2, x3), g)) {
       const double wnb = weight_no_bracket<double>(A, it, g, ch.row);
       const Stencil<double> s2 = make_stencil<double>(g.p2, G);
       const Stencil<double> s3 = make_stencil<double>(g.p3, G);

@@ -550,7 +550,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
           r_v[wid][1][slot] = x1 >> 9;
           r_v[wid][2][slot] = x2 >> 9;
           r_v[wid][3][slot] = x3 >> 9;
-          r_v[wid][4][slot] = ((x0 & 0x1FFu) << 14) | ((x1 & 0x1FFu) << 5) | ((x2 & 0x1FFu) >> 4);
+          r_v[wid][4][slot] = fifth_word(x0, x1, x2);
           r_z[wid][0][slot] = zr[0];
           r_z[wid][1][slot] = zr[1];
         }
@@ -568,9 +568,9 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         wave_lds_sync();
       }
     } else {
-    auto evaluate = [&](const double u[5], R inv_q) {
+    auto evaluate = [&](const SampleMap& m, R inv_q) {
       Geo g;
-      if (!geometry(it, G, u, g)) return;
+      if (!geometry(it, G, m, g)) return;
       finish(g, weight_no_bracket<R, kUser>(A, it, g, ch.row) * inv_q);
     };
     if (kQueue) {
@@ -578,9 +578,9 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       auto finish_queued = [&](int slot) {
         Geo g;
         const uint32_t v0 = q_v[wid][0][slot], v1 = q_v[wid][1][slot], v2 = q_v[wid][2][slot];
-        const double uu[3] = {unif23(v0), unif23(v1), unif23(v2)};
+        const double c[3] = {centred23(v0), centred23(v1), centred23(v2)};
         for (int a = 0; a < 3; ++a) {
-          g.p2[a] = fma(2.0 * G.ph[a], uu[a], -G.ph[a]);
+          g.p2[a] = G.ph[a] * c[a];
           g.p3[a] = q_p3[wid][a][slot];
           g.p4[a] = (it.p1[a] + g.p2[a]) - g.p3[a];
         }
@@ -595,10 +595,9 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         philox4x32_10(x0, x1, x2, x3, A.key0, A.key1);
         if (pending) deposit_slot<true, false, R>(k2, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off2, pd2, pdv,
                                         nodes, G.ox, G.oy, win_lo, win_n);
-        double u[5];
-        five_uniforms(x0, x1, x2, x3, u);
+        const SampleMap map = map_words(G, x0, x1, x2, x3);
         Geo g;
-        const bool ok = s < A.n_samples && geometry(it, G, u, g);
+        const bool ok = s < A.n_samples && geometry(it, G, map, g);
         if (pending) deposit_slot<true, false, R>(k3, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off3, pd3, -pdv,
                                         nodes, G.ox, G.oy, win_lo, win_n);
         const unsigned long long mask = __ballot(ok);
@@ -650,9 +649,10 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
     for (int s = s_first + lane; s < A.n_samples; s += s_step) {
       uint32_t x0 = (uint32_t)s, x1 = (uint32_t)p1_lin, x2 = (uint32_t)cell, x3 = ((uint32_t)ch.code << 8);
       philox4x32_10(x0, x1, x2, x3, A.key0, A.key1);
-      double u[5];
+      SampleMap map;
       R inv_q = R(1);
       if (mix) {
+        double u[5];
         uint32_t y0 = (uint32_t)s, y1 = (uint32_t)p1_lin, y2 = (uint32_t)cell, y3 = ((uint32_t)ch.code << 8) | 1u;
         philox4x32_10(y0, y1, y2, y3, A.key0, A.key1);
         const uint32_t xw[8] = {x0, x1, x2, x3, y0, y1, y2, y3};
@@ -664,10 +664,11 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
           mix_draw_row(xw, A.mix_thr + mrow * A.mix_K, mix_rows[wid], A.mix_K, u, yl);
           inv_q = __builtin_amdgcn_rcpf(mix_density_f32(mix_rows[wid], A.mix_K, yl));  // about 1 ulp; q >= alpha
         }
+        map = map_unit(G, u);
       } else {
-        five_uniforms(x0, x1, x2, x3, u);
+        map = map_words(G, x0, x1, x2, x3);
       }
-      evaluate(u, inv_q);
+      evaluate(map, inv_q);
     }
     }  // CM-angle samplers
     if (!A.direct) return;

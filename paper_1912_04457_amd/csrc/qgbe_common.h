@@ -65,6 +65,15 @@ struct Grid {
   uint32_t species_mask;
 };
 
+// a ^ b ^ c: one instruction on the device.
+__host__ __device__ inline uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+  return a ^ b ^ c;
+#endif
+}
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
 // 32x32 -> 64 bit products with a Weyl key schedule.
 __host__ __device__ inline void philox4x32_10(uint32_t& x0, uint32_t& x1, uint32_t& x2, uint32_t& x3,
@@ -73,8 +82,8 @@ __host__ __device__ inline void philox4x32_10(uint32_t& x0, uint32_t& x1, uint32
   for (int r = 0; r < 10; ++r) {
     const uint64_t a = (uint64_t)0xD2511F53u * (uint64_t)x0;
     const uint64_t b = (uint64_t)0xCD9E8D57u * (uint64_t)x2;
-    const uint32_t n0 = (uint32_t)(b >> 32) ^ x1 ^ k0;
-    const uint32_t n2 = (uint32_t)(a >> 32) ^ x3 ^ k1;
+    const uint32_t n0 = xor3((uint32_t)(b >> 32), x1, k0);
+    const uint32_t n2 = xor3((uint32_t)(a >> 32), x3, k1);
     x1 = (uint32_t)b;
     x3 = (uint32_t)a;
     x0 = n0;
