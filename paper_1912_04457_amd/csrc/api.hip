@@ -172,7 +172,7 @@ void plan_groups(qgbe_ctx* c) {
   c->group_index.clear();
   c->groups.clear();
   for (int nslot = 1; nslot <= 3; ++nslot) {
-    Group g{(int)c->group_index.size(), 0, nslot, {}, {}, {c->G.nodes, c->G.nodes, c->G.nodes}, {false, false}};
+    Group g{(int)c->group_index.size(), 0, nslot, {}, {}, {c->G.nodes, c->G.nodes, c->G.nodes}, {0, 0}};
     for (int l = 0; l < 3; ++l) {
       const size_t budget = l == 0 ? c->lds.plain : l == 1 ? c->lds.learned : c->lds.roots;
       if (c->d.symmetric && budget < acc_b) {
@@ -190,7 +190,8 @@ void plan_groups(qgbe_ctx* c) {
       g.lds_tiles[l] = f32 && l < 2 ? (int)std::min<size_t>(nslot, (budget - g.lds_acc[l] * acc_b) / tile_b) : 0;
     }
     for (int i = 0; i < 2; ++i)
-      g.queue[i] = c->d.symmetric && g.lds_acc[0] == nslot && g.win[0] == c->G.nodes && nslot * acc_b <= c->lds.queue[i];
+      if (c->d.symmetric && g.lds_acc[0] == nslot && g.win[0] == c->G.nodes)
+        g.queue[i] = nslot * acc_b <= c->lds.queue[0][i] ? kRing : nslot * acc_b <= c->lds.queue[1][i] ? kTight : 0;
     for (int i = 0; i < c->nch; ++i)
       if (c->chans[i].nslot == nslot) c->group_index.push_back(i);
     g.count = (int)c->group_index.size() - g.start;
@@ -452,10 +453,10 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
     a.n_group = g.count;
     // the compacting variant when the whole group fits in LDS next to its queues
     const bool is_short = roots || collide_short(c->d.precision, learned, 1, n_samples);
-    bool queue = l == 0 && g.queue[is_short];
+    int queue = l == 0 ? g.queue[is_short] : 0;
     const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
     const Chunking ck = plan_chunks(c, c->G.nodes, (long long)c->G.cells * g.count, acc, n_samples, queue, learned || roots);
-    if (!is_short && ck.split > 1) queue = queue && g.queue[1];  // waves that share nodes take the short form
+    if (!is_short && ck.split > 1 && queue) queue = g.queue[1];  // waves that share nodes take the short form
     a.split = ck.split;
     a.node_block = ck.block;
     const int chunk = ck.chunk;
@@ -484,7 +485,7 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
           a.lds_tiles = f64_path || roots ? 0 : (int)std::min<size_t>(g.nslot, ((l ? c->lds.learned : c->lds.plain) - used) / tile_b);
         }
         if (queue) a.lds_tiles = 0;  // the compacting variant reads f from the node quads
-        const bool q = queue && n_pass == 1 && n_win == 1;
+        const int q = n_pass == 1 && n_win == 1 ? queue : 0;
         if (roots) HIP_TRY(launch_collide_roots(a, sampler == QGBE_SAMPLER_ROOTS_ALT, c->stream), "collide (roots)");
         else if (f64_path) HIP_TRY(launch_collide_f64(a, g.nslot, q, c->stream), "collide (fp64)");
         else HIP_TRY(launch_collide_f32(a, g.nslot, q, c->stream), "collide (fp32)");

@@ -95,7 +95,7 @@ struct ReplayArgs {
 // Dynamic LDS of one precision's kernel variants.
 struct LdsBudget {
   size_t plain = 0, learned = 0;  // uniform sampler, learned sampler
-  size_t queue[2] = {0, 0};       // the compacting variant for long and short items
+  size_t queue[2][2] = {};        // the compacting variant: [kRing, kTight][long, short items]
   size_t replay = 0;              // replay_kernel
   size_t roots = 0;               // the root samplers
 };
@@ -103,10 +103,12 @@ struct LdsBudget {
 // The paper's root parameterisation (FP64; alt: the alternative elimination);
 // a launch's slots and window as for the CM-angle samplers.
 hipError_t launch_collide_roots(const CollideArgs& a, bool alt, hipStream_t stream);
-// queue: use the compacting variant if the launch qualifies (uniform sampler,
-// symmetric, every accumulator in LDS within the queue budget).
-hipError_t launch_collide_f32(const CollideArgs& a, int nslot, bool queue, hipStream_t stream);
-hipError_t launch_collide_f64(const CollideArgs& a, int nslot, bool queue, hipStream_t stream);
+// queue: a form of the compacting variant (0: none), used if the launch
+// qualifies (uniform sampler, symmetric, every accumulator in LDS within the
+// queue's budget): with its queue as a ring in LDS, or in fewer bytes.
+constexpr int kRing = 1, kTight = 2;
+hipError_t launch_collide_f32(const CollideArgs& a, int nslot, int queue, hipStream_t stream);
+hipError_t launch_collide_f64(const CollideArgs& a, int nslot, int queue, hipStream_t stream);
 // Sample a batch of n_wg workgroups (a.rec.wg_base onwards) and record the
 // deposits instead of adding them: symmetric sampling without the scale
 // output, short-item form.

@@ -10,7 +10,7 @@ bool collide_short(int precision, bool learned, int split, int n_samples) {
   return precision == QGBE_FP64 || learned || short_items(split, n_samples);
 }
 
-hipError_t launch_collide_f32(const CollideArgs& a, int nslot, bool queue, hipStream_t stream) {
+hipError_t launch_collide_f32(const CollideArgs& a, int nslot, int queue, hipStream_t stream) {
   return launch_slots<float>(a, nslot, queue, stream);
 }
 

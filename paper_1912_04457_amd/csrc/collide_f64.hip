@@ -3,7 +3,7 @@
 
 namespace qgbe {
 
-hipError_t launch_collide_f64(const CollideArgs& a, int nslot, bool queue, hipStream_t stream) {
+hipError_t launch_collide_f64(const CollideArgs& a, int nslot, int queue, hipStream_t stream) {
   return launch_slots<double>(a, nslot, queue, stream);
 }
 

@@ -106,10 +106,17 @@ __device__ __forceinline__ int xcd_local_block(int b, int n) {
 // VGPRs; the learned variant spills a few to scratch and still runs faster
 // than with 8 waves), for both samplers.
 constexpr int kSlotThreads = 768;
-// The compacting variant (below) keeps a sample queue per wave in LDS (52 B
-// per entry) next to the accumulators and reads f from the global node quads.
+// The compacting variant (below) keeps a sample queue per wave in LDS next to
+// the accumulators and reads f from the global node quads.  Two forms: kRing
+// has room for a batch and 64 more (52 B x 128 per wave in FP32); kTight holds
+// one batch, its p2 words in registers (40 B x 64), for accumulators that fit
+// only so.  Where both fit the ring is faster (256 gluon cells of 20^3, 2048
+// samples: 60.0 and 62.0 ms); against no queue kTight gains what compaction
+// does (7 species at 20^3, 4096 samples, the two-slot channels: 29.8 -> 24.1
+// ms, the term 48.4 -> 42.7).
 constexpr int kQueueWaves = 12;
-constexpr int kQueueLen = 128;  // ring entries per wave (>= 63 pending + 64 new)
+constexpr int kQueueLen = 128;  // kRing: entries per wave (>= 63 pending + 64 new)
+constexpr int queue_len(int queue) { return queue == kRing ? kQueueLen : queue == kTight ? kWave : 1; }
 constexpr int slots_block(bool queue) { return queue ? kQueueWaves * 64 : kSlotThreads; }
 // Long items, compacting variant: observed nodes go to the waves of a
 // workgroup in blocks of 4 consecutive nodes; a wave stages the direct sums
@@ -123,7 +130,7 @@ constexpr int kNodeBlock = 4;
 // kQueue (uniform sampler, every deposit slot in LDS, f from the global node
 // quads): each wave first runs the sample geometry for 64 samples, appends
 // the accepted ones (the three 23-bit uniforms of p2, p3 in FP64, s, t, u and
-// the prefactor in FP32) to its ring in LDS, and evaluates |M|^2, f, bracket
+// the prefactor in FP32) to its queue, and evaluates |M|^2, f, bracket
 // and deposits 64 queued samples at a time, so that long path runs on full
 // wavefronts.  The deposits of one such batch are issued while the geometry
 // of the next 64 samples runs, a third before, between and after it, so the
@@ -295,7 +302,7 @@ struct Record {
 // kRec: the deposits go to A.rec instead of accumulators (see replay_kernel).
 // kRoot: 0 the CM-angle samplers, 1 the root parameterisation, 2 its
 // alternative (FP64, short form, their own queue; deposits issued at once).
-template <typename R, bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kUser, bool kShort,
+template <typename R, bool kSym, bool kScale, bool kAllLds, bool kLearned, int kQueue, bool kUser, bool kShort,
           bool kRec = false, int kRoot = 0>
 __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(CollideArgs A) {
   constexpr bool kF64 = std::is_same<R, double>::value;
@@ -309,9 +316,9 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   constexpr bool kAccLds = kAllLds;
   extern __shared__ double lds[];
   __shared__ R mix_rows[kLearned ? kSlotThreads / kWave : 1][kLearned ? (kF64 ? kMixRowF64 : kMixRow) : 1];
-  __shared__ uint32_t q_v[kQueue ? kQueueWaves : 1][3][kQueue ? kQueueLen : 1];  // 23-bit uniforms of p2
-  __shared__ double q_p3[kQueue ? kQueueWaves : 1][3][kQueue ? kQueueLen : 1];
-  __shared__ R q_f[kQueue ? kQueueWaves : 1][4][kQueue ? kQueueLen : 1];    // s, t, u, prefactor
+  __shared__ uint32_t q_v[kQueue == kRing ? kQueueWaves : 1][3][kQueue == kRing ? kQueueLen : 1];  // 23-bit uniforms of p2
+  __shared__ double q_p3[kQueue ? kQueueWaves : 1][3][queue_len(kQueue)];
+  __shared__ R q_f[kQueue ? kQueueWaves : 1][4][queue_len(kQueue)];    // s, t, u, prefactor
   __shared__ uint32_t r_v[kRoot ? kQueueWaves : 1][5][kRoot ? kQueueLen : 1];  // 23-bit uniforms; which roots hold
   __shared__ double r_z[kRoot ? kQueueWaves : 1][2][kRoot ? kQueueLen : 1];    // the roots
   __shared__ double mc_wg[2];  // this workgroup's item variances and squared item sums
@@ -574,21 +581,40 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       finish(g, weight_no_bracket<R, kUser>(A, it, g, ch.row) * inv_q);
     };
     if (kQueue) {
-      // queued record -> the accepted sample's geometry, as geometry() left it
-      auto finish_queued = [&](int slot) {
+      // A queued sample: the words of p2, p3, and s, t, u and the prefactor.
+      struct Queued {
+        uint32_t v[3];
+        double p3[3];
+        R f[4];
+      };
+      auto push = [&](unsigned i, const Geo& g) {
+        for (int a = 0; a < 3; ++a) q_p3[wid][a][i] = g.p3[a];
+        q_f[wid][0][i] = (R)g.s;
+        q_f[wid][1][i] = (R)g.t;
+        q_f[wid][2][i] = (R)g.u;
+        q_f[wid][3][i] = prefactor<R>(it, g);
+      };
+      auto pop = [&](unsigned i, uint32_t v0, uint32_t v1, uint32_t v2) {
+        return Queued{{v0, v1, v2},
+                      {q_p3[wid][0][i], q_p3[wid][1][i], q_p3[wid][2][i]},
+                      {q_f[wid][0][i], q_f[wid][1][i], q_f[wid][2][i], q_f[wid][3][i]}};
+      };
+      auto pop_ring = [&](unsigned i) {
+        i &= kQueueLen - 1;
+        return pop(i, q_v[wid][0][i], q_v[wid][1][i], q_v[wid][2][i]);
+      };
+      auto finish_queued = [&](const Queued& q) {
         Geo g;
-        const uint32_t v0 = q_v[wid][0][slot], v1 = q_v[wid][1][slot], v2 = q_v[wid][2][slot];
-        const double c[3] = {centred23(v0), centred23(v1), centred23(v2)};
         for (int a = 0; a < 3; ++a) {
-          g.p2[a] = G.ph[a] * c[a];
-          g.p3[a] = q_p3[wid][a][slot];
+          g.p2[a] = G.ph[a] * centred23(q.v[a]);  // as map_words formed it
+          g.p3[a] = q.p3[a];
           g.p4[a] = (it.p1[a] + g.p2[a]) - g.p3[a];
         }
-        const R m = msq_row<R, kUser>(A.msq_mask, A.msq, ch.row, q_f[wid][0][slot], q_f[wid][1][slot],
-                                      q_f[wid][2][slot], (R)it.mu);
-        finish(g, m * q_f[wid][3][slot]);
+        const R m = msq_row<R, kUser>(A.msq_mask, A.msq, ch.row, q.f[0], q.f[1], q.f[2], (R)it.mu);
+        finish(g, m * q.f[3]);
       };
-      unsigned head = 0, tail = 0;  // ring positions (wave-uniform)
+      unsigned head = 0, tail = 0;      // kRing: positions; kTight: tail samples are queued (wave-uniform)
+      uint32_t w0 = 0, w1 = 0, w2 = 0;  // kTight: lane i holds the words of queue entry i
       for (int base = s_first; base < A.n_samples; base += s_step) {
         const int s = base + lane;
         uint32_t x0 = (uint32_t)s, x1 = (uint32_t)p1_lin, x2 = (uint32_t)cell, x3 = ((uint32_t)ch.code << 8);
@@ -600,27 +626,56 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         const bool ok = s < A.n_samples && geometry(it, G, map, g);
         if (pending) deposit_slot<true, false, R>(k3, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off3, pd3, -pdv,
                                         nodes, G.ox, G.oy, win_lo, win_n);
+        // The accepted samples take the next places of the queue.
         const unsigned long long mask = __ballot(ok);
-        if (ok) {
-          const unsigned slot = (tail + (unsigned)__popcll(mask & ((1ull << lane) - 1ull))) & (kQueueLen - 1);
-          q_v[wid][0][slot] = x0 >> 9;
-          q_v[wid][1][slot] = x1 >> 9;
-          q_v[wid][2][slot] = x2 >> 9;
-          for (int a = 0; a < 3; ++a) q_p3[wid][a][slot] = g.p3[a];
-          q_f[wid][0][slot] = (R)g.s;
-          q_f[wid][1][slot] = (R)g.t;
-          q_f[wid][2][slot] = (R)g.u;
-          q_f[wid][3][slot] = prefactor<R>(it, g);
+        const unsigned cnt = (unsigned)__popcll(mask);
+        const unsigned rank = (unsigned)__popcll(mask & ((1ull << lane) - 1ull));
+        const unsigned at = tail + rank;
+        uint32_t m0 = x0 >> 9, m1 = x1 >> 9, m2 = x2 >> 9;
+        if constexpr (kQueue == kRing) {
+          if (ok) {
+            const unsigned slot = at & (kQueueLen - 1);
+            q_v[wid][0][slot] = m0;
+            q_v[wid][1][slot] = m1;
+            q_v[wid][2][slot] = m2;
+            push(slot, g);
+          }
+        } else {
+          // Places from 64 up are the first of the next batch: their entries
+          // wait in registers until this batch has been read.  The words go to
+          // their lanes by a permutation (place mod 64); the rejected samples'
+          // land on empty places.
+          if (ok && at < (unsigned)kWave) push(at, g);
+          const int to = (int)((ok ? at : tail + cnt + lane - rank) << 2);
+          m0 = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)m0);
+          m1 = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)m1);
+          m2 = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)m2);
+          if ((unsigned)lane >= tail) {
+            w0 = m0;
+            w1 = m1;
+            w2 = m2;
+          }
         }
         if (pending) deposit_slot<true, false, R>(k4, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off4, pd4, -pdv,
                                         nodes, G.ox, G.oy, win_lo, win_n);
         pending = false;
-        tail += (unsigned)__popcll(mask);
+        tail += cnt;
         if (tail - head >= (unsigned)kWave) {
           wave_lds_sync();
-          finish_queued((head + lane) & (kQueueLen - 1));
+          if constexpr (kQueue == kRing) {
+            finish_queued(pop_ring(head + lane));
+            head += kWave;
+          } else {
+            const Queued q = pop(lane, w0, w1, w2);
+            wave_lds_sync();
+            if (ok && at >= (unsigned)kWave) push(at - kWave, g);
+            w0 = m0;
+            w1 = m1;
+            w2 = m2;
+            tail -= kWave;
+            finish_queued(q);
+          }
           pending = !kRec;
-          head += kWave;
           wave_lds_sync();
         }
       }
@@ -639,7 +694,8 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       if (tail != head) {
         wave_lds_sync();
         if ((unsigned)lane < tail - head) {
-          finish_queued((head + lane) & (kQueueLen - 1));
+          if constexpr (kQueue == kRing) finish_queued(pop_ring(head + lane));
+          else finish_queued(pop(lane, w0, w1, w2));
           if (!kRec) flush();
         }
         wave_lds_sync();
@@ -839,14 +895,15 @@ constexpr int kShortSamples = 1024;
 inline bool short_items(int split, int n_samples) { return split > 1 || n_samples < kShortSamples; }
 
 // One precision's kernel variants: the launch of one, and all of them with
-// their LDS budget group (0 uniform sampler, 1 learned sampler, 2 and 3 the
-// compacting variant for long and short items, 4 the replay kernel).
+// their LDS budget group (0 uniform sampler, 1 learned sampler, 2 to 5 the
+// compacting variant: kRing and kTight, each for long and short items, 6 the
+// replay kernel).
 template <typename R>
 struct SlotsVariants {
   // the reference precision keeps one form of an item
   static constexpr bool kF64 = std::is_same<R, double>::value;
 
-  template <bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kShort>
+  template <bool kSym, bool kScale, bool kAllLds, bool kLearned, int kQueue, bool kShort>
   static void launch_user(const CollideArgs& a, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
     if (a.msq_mask)
       hipLaunchKernelGGL((collide_slots_kernel<R, kSym, kScale, kAllLds, kLearned, kQueue, true, kShort>), grid, block,
@@ -857,74 +914,81 @@ struct SlotsVariants {
   }
 
   template <bool kSym, bool kScale, bool kLearned, bool kShort>
-  static void launch_variant(const CollideArgs& a, bool all_lds, bool queue, dim3 grid, dim3 block, size_t lds,
+  static void launch_variant(const CollideArgs& a, bool all_lds, int queue, dim3 grid, dim3 block, size_t lds,
                              hipStream_t st) {
     if constexpr (kSym && !kLearned) {
-      if (queue) {
-        launch_user<true, kScale, true, false, true, kShort>(a, grid, block, lds, st);
+      if (queue == kRing) {
+        launch_user<true, kScale, true, false, kRing, kShort>(a, grid, block, lds, st);
+        return;
+      }
+      if (queue == kTight) {
+        launch_user<true, kScale, true, false, kTight, kShort>(a, grid, block, lds, st);
         return;
       }
     }
-    if (all_lds) launch_user<kSym, kScale, true, kLearned, false, kShort>(a, grid, block, lds, st);
-    else if constexpr (!kF64) launch_user<kSym, kScale, false, kLearned, false, kShort>(a, grid, block, lds, st);
+    if (all_lds) launch_user<kSym, kScale, true, kLearned, 0, kShort>(a, grid, block, lds, st);
+    else if constexpr (!kF64) launch_user<kSym, kScale, false, kLearned, 0, kShort>(a, grid, block, lds, st);
   }
 
   template <bool kSym, bool kScale>
-  static void launch_sampler(const CollideArgs& a, bool all_lds, bool queue, dim3 grid, dim3 block, size_t lds,
+  static void launch_sampler(const CollideArgs& a, bool all_lds, int queue, dim3 grid, dim3 block, size_t lds,
                              hipStream_t st) {
-    if (a.learned) launch_variant<kSym, kScale, true, true>(a, all_lds, false, grid, block, lds, st);
+    if (a.learned) launch_variant<kSym, kScale, true, true>(a, all_lds, 0, grid, block, lds, st);
     else if (kF64 || short_items(a.split, a.n_samples)) launch_variant<kSym, kScale, false, true>(a, all_lds, queue, grid, block, lds, st);
     else if constexpr (!kF64) launch_variant<kSym, kScale, false, false>(a, all_lds, queue, grid, block, lds, st);
   }
 
   struct Fn { const void* fn; int group; };
 
-  template <bool kSym, bool kScale, bool kAllLds, bool kLearned, bool kQueue, bool kShort>
+  template <bool kSym, bool kScale, bool kAllLds, bool kLearned, int kQueue, bool kShort>
   static void add(std::vector<Fn>& out, int group) {
     out.push_back({(const void*)collide_slots_kernel<R, kSym, kScale, kAllLds, kLearned, kQueue, false, kShort>, group});
     out.push_back({(const void*)collide_slots_kernel<R, kSym, kScale, kAllLds, kLearned, kQueue, true, kShort>, group});
   }
   template <bool kAllLds, bool kLearned, bool kShort>
   static void add_all(std::vector<Fn>& out, int group) {
-    add<true, true, kAllLds, kLearned, false, kShort>(out, group);
-    add<true, false, kAllLds, kLearned, false, kShort>(out, group);
-    add<false, true, kAllLds, kLearned, false, kShort>(out, group);
-    add<false, false, kAllLds, kLearned, false, kShort>(out, group);
+    add<true, true, kAllLds, kLearned, 0, kShort>(out, group);
+    add<true, false, kAllLds, kLearned, 0, kShort>(out, group);
+    add<false, true, kAllLds, kLearned, 0, kShort>(out, group);
+    add<false, false, kAllLds, kLearned, 0, kShort>(out, group);
   }
-  template <bool kShort>
+  template <int kQueue, bool kShort>
   static void add_queue(std::vector<Fn>& out) {
-    add<true, true, true, false, true, kShort>(out, kShort ? 3 : 2);
-    add<true, false, true, false, true, kShort>(out, kShort ? 3 : 2);
+    const int group = 2 * kQueue + (kShort ? 1 : 0);
+    add<true, true, true, false, kQueue, kShort>(out, group);
+    add<true, false, true, false, kQueue, kShort>(out, group);
   }
   template <bool kLearned>
   static void launch_rec(const CollideArgs& a, dim3 grid, hipStream_t st) {
     const dim3 block(slots_block(!kLearned));
     if (a.msq_mask)
-      hipLaunchKernelGGL((collide_slots_kernel<R, true, false, true, kLearned, !kLearned, true, true, true>), grid,
+      hipLaunchKernelGGL((collide_slots_kernel<R, true, false, true, kLearned, kLearned ? 0 : kRing, true, true, true>), grid,
                          block, 0, st, a);
     else
-      hipLaunchKernelGGL((collide_slots_kernel<R, true, false, true, kLearned, !kLearned, false, true, true>), grid,
+      hipLaunchKernelGGL((collide_slots_kernel<R, true, false, true, kLearned, kLearned ? 0 : kRing, false, true, true>), grid,
                          block, 0, st, a);
   }
   static std::vector<Fn> all() {
     std::vector<Fn> fns;
-    fns.push_back({(const void*)replay_kernel<R>, 4});
+    fns.push_back({(const void*)replay_kernel<R>, 6});
     add_all<true, false, true>(fns, 0);
     add_all<true, true, true>(fns, 1);
-    add_queue<true>(fns);
+    add_queue<kRing, true>(fns);
+    add_queue<kTight, true>(fns);
     if constexpr (!kF64) {
       add_all<false, false, true>(fns, 0);
       add_all<false, true, true>(fns, 1);
       add_all<true, false, false>(fns, 0);
       add_all<false, false, false>(fns, 0);
-      add_queue<false>(fns);
+      add_queue<kRing, false>(fns);
+      add_queue<kTight, false>(fns);
     }
     return fns;
   }
 };
 
 template <typename R>
-hipError_t launch_slots(const CollideArgs& a, int nslot, bool queue, hipStream_t stream) {
+hipError_t launch_slots(const CollideArgs& a, int nslot, int queue, hipStream_t stream) {
   constexpr bool kF64 = std::is_same<R, double>::value;
   const int n_acc = a.symmetric ? std::min(a.slot_hi - a.slot_lo, a.lds_acc) : 0;
   const int n_tiles = kF64 ? 0 : std::min(nslot, a.lds_tiles);
@@ -933,7 +997,7 @@ hipError_t launch_slots(const CollideArgs& a, int nslot, bool queue, hipStream_t
   const bool all_acc = !a.symmetric || n_acc == a.slot_hi - a.slot_lo;
   const bool all_lds = (kF64 || n_tiles == nslot) && all_acc;
   if (kF64 && !all_acc) return hipErrorInvalidValue;
-  queue = queue && all_acc && a.symmetric && !a.learned && a.win_n == a.G.nodes;
+  if (!all_acc || !a.symmetric || a.learned || a.win_n != a.G.nodes) queue = 0;
   const int threads = slots_block(queue);
   const size_t lds = (size_t)n_acc * a.win_n * sizeof(double) + (size_t)n_tiles * a.G.nodes * sizeof(float);
   const long long blocks = (long long)a.G.cells * a.n_group * a.n_chunks;
@@ -949,8 +1013,8 @@ hipError_t launch_slots(const CollideArgs& a, int nslot, bool queue, hipStream_t
     if (a.scale) V::template launch_sampler<true, true>(a, all_lds, queue, grid, block, lds, stream);
     else V::template launch_sampler<true, false>(a, all_lds, queue, grid, block, lds, stream);
   } else {
-    if (a.scale) V::template launch_sampler<false, true>(a, all_lds, false, grid, block, lds, stream);
-    else V::template launch_sampler<false, false>(a, all_lds, false, grid, block, lds, stream);
+    if (a.scale) V::template launch_sampler<false, true>(a, all_lds, 0, grid, block, lds, stream);
+    else V::template launch_sampler<false, false>(a, all_lds, 0, grid, block, lds, stream);
   }
   return hipGetLastError();
 }
@@ -1013,14 +1077,16 @@ inline hipError_t raise_lds_limit(const void* fn, size_t lds_max, size_t* budget
 
 template <typename R>
 hipError_t slots_lds_limit(size_t lds_max, LdsBudget* out) {
-  size_t budget[5] = {lds_max, lds_max, lds_max, lds_max, lds_max};
+  size_t budget[7] = {lds_max, lds_max, lds_max, lds_max, lds_max, lds_max, lds_max};
   for (const auto& f : SlotsVariants<R>::all())
     if (const hipError_t e = raise_lds_limit(f.fn, lds_max, &budget[f.group])) return e;
   out->plain = budget[0];
   out->learned = budget[1];
-  out->queue[0] = std::is_same<R, double>::value ? 0 : budget[2];  // FP64 has the short form only
-  out->queue[1] = budget[3];
-  out->replay = budget[4];
+  for (int f = 0; f < 2; ++f) {
+    out->queue[f][0] = std::is_same<R, double>::value ? 0 : budget[2 + 2 * f];  // FP64 has the short form only
+    out->queue[f][1] = budget[3 + 2 * f];
+  }
+  out->replay = budget[6];
   return hipSuccess;
 }
 
@@ -1029,14 +1095,14 @@ template <int kRoot>
 using RootFn = void (*)(CollideArgs);
 template <int kRoot>
 void root_variants(RootFn<kRoot> out[2][2][2]) {
-  out[0][0][0] = collide_slots_kernel<double, false, false, true, false, false, false, true, false, kRoot>;
-  out[0][0][1] = collide_slots_kernel<double, false, false, true, false, false, true, true, false, kRoot>;
-  out[0][1][0] = collide_slots_kernel<double, false, true, true, false, false, false, true, false, kRoot>;
-  out[0][1][1] = collide_slots_kernel<double, false, true, true, false, false, true, true, false, kRoot>;
-  out[1][0][0] = collide_slots_kernel<double, true, false, true, false, false, false, true, false, kRoot>;
-  out[1][0][1] = collide_slots_kernel<double, true, false, true, false, false, true, true, false, kRoot>;
-  out[1][1][0] = collide_slots_kernel<double, true, true, true, false, false, false, true, false, kRoot>;
-  out[1][1][1] = collide_slots_kernel<double, true, true, true, false, false, true, true, false, kRoot>;
+  out[0][0][0] = collide_slots_kernel<double, false, false, true, false, 0, false, true, false, kRoot>;
+  out[0][0][1] = collide_slots_kernel<double, false, false, true, false, 0, true, true, false, kRoot>;
+  out[0][1][0] = collide_slots_kernel<double, false, true, true, false, 0, false, true, false, kRoot>;
+  out[0][1][1] = collide_slots_kernel<double, false, true, true, false, 0, true, true, false, kRoot>;
+  out[1][0][0] = collide_slots_kernel<double, true, false, true, false, 0, false, true, false, kRoot>;
+  out[1][0][1] = collide_slots_kernel<double, true, false, true, false, 0, true, true, false, kRoot>;
+  out[1][1][0] = collide_slots_kernel<double, true, true, true, false, 0, false, true, false, kRoot>;
+  out[1][1][1] = collide_slots_kernel<double, true, true, true, false, 0, true, true, false, kRoot>;
 }
 
 template <int kRoot>
@@ -1061,10 +1127,10 @@ hipError_t launch_roots_rec(const CollideArgs& a, int n_wg, hipStream_t stream) 
   if (!record_fits(a, n_wg, 2)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)n_wg), block(kSlotThreads);
   if (a.msq_mask)
-    hipLaunchKernelGGL((collide_slots_kernel<double, true, false, true, false, false, true, true, true, kRoot>), grid,
+    hipLaunchKernelGGL((collide_slots_kernel<double, true, false, true, false, 0, true, true, true, kRoot>), grid,
                        block, 0, stream, a);
   else
-    hipLaunchKernelGGL((collide_slots_kernel<double, true, false, true, false, false, false, true, true, kRoot>), grid,
+    hipLaunchKernelGGL((collide_slots_kernel<double, true, false, true, false, 0, false, true, true, kRoot>), grid,
                        block, 0, stream, a);
   return hipGetLastError();
 }

@@ -31,7 +31,7 @@ struct Group {
   int lds_tiles[3];   // FP32 f tiles staged in LDS; none in FP64 and for the root samplers
   int win[3];         // nodes per accumulator window (= nodes unless one slot's FP64
                       // accumulators exceed LDS; then one launch per window and slot)
-  bool queue[2];      // the uniform sampler's compacting variant fits [long, short items]
+  int queue[2];       // the form of the uniform sampler's compacting variant that fits [long, short items]; 0: none
 };
 
 // Channels whose deposit accumulators need more than one launch (slots or node

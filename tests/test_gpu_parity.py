@@ -345,6 +345,20 @@ def test_lds_plans_fp64(O, n_x, n_p, mask, N):
         assert abs(r["A"][:, cell].sum()) <= 1e-13 * r["S_ref"][:, cell].sum()
 
 
+@pytest.mark.parametrize("N", [1, 64, 200, 1088], ids=["one", "one_batch", "short", "long"])
+def test_small_queue_fp32(O, N):
+    """Two slots whose accumulators leave room for the smaller of the sample
+    queues only: batches that fill exactly, overflow and end partly filled, in
+    the short and the long form of an item."""
+    _case(f"small queue N={N}")
+    wl = W.Workload("queue", (1, 1, 1), (17, 17, 17), (3.0, 3.0, 3.0), (2.0, 2.5, 1.5), 0x49, N, "f32", 1, 0.01)
+    r = _run_pair(O, wl, W.random_f(27, 1, wl.nodes, species_mask=0x49), N, qgbe.FP32, step=2)
+    _compare(r["A"], r["A_ref"], r["S_ref"], TOL[qgbe.FP32], "A")
+    scale_items = np.abs(r["I_ref"]).max()
+    assert np.allclose(r["I"], r["I_ref"], rtol=TOL[qgbe.FP32], atol=TOL[qgbe.FP32] * scale_items)
+    assert abs(r["A"].sum()) <= 1e-13 * r["S_ref"].sum()
+
+
 @pytest.mark.parametrize("n_x,n_p,mask,N,precision,learned",
                          [((1, 1, 1), (20, 20, 20), 0x7F, 80, qgbe.FP32, False),
                           ((2, 1, 1), (18, 19, 20), 0x49, 40, qgbe.FP64, False),
