@@ -388,8 +388,13 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   const int k2 = ch.pos_slot[0], k3 = ch.pos_slot[1], k4 = ch.pos_slot[2];
   // row offsets of positions 2, 3, 4 (scalars: no dynamically indexed array in the loop)
   const size_t off2 = goff[k2], off3 = goff[k3], off4 = goff[k4];
-  const bool g1 = is_gluon(ch.sp[0]), g2 = is_gluon(ch.sp[1]);
-  const bool g3 = is_gluon(ch.sp[2]), g4 = is_gluon(ch.sp[3]);
+  // 1 + f (gluons) or 1 - f, as one fma(+-1, f, 1): a select of the two is a
+  // branch per factor (256 gluon cells of 20^3, 2048 samples: 59.6 -> 59.0 ms).
+  // Not where the learned sampler records: there the signs' registers cost 0.6%.
+  auto occupied = [&](int sp, R f) {
+    if constexpr (kRec && kLearned) return is_gluon(sp) ? R(1) + f : R(1) - f;
+    else return fma(is_gluon(sp) ? R(1) : R(-1), f, R(1));
+  };
   const int first = chunk * A.chunk_items;
   const int last = min(first + A.chunk_items, nodes);
   Item pair;
@@ -451,7 +456,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       return;
     }
     const R f1 = (R)it.f1;
-    const R F1 = g1 ? R(1) + f1 : R(1) - f1;
+    const R F1 = occupied(ch.sp[0], f1);
     double dsum = 0.0, ssum = 0.0, dsq = 0.0;
     if (!kShort) n_ok = 0;
     const size_t mrow = (size_t)ci * nodes + p1_lin;
@@ -487,9 +492,9 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         f3 = interp_slot<kTilesLds, R>(k3, n_tiles, tiles, A.f32q, off3, s3, nodes, G.ox, G.oy);
         f4 = interp_slot<kTilesLds, R>(k4, n_tiles, tiles, A.f32q, off4, s4, nodes, G.ox, G.oy);
       }
-      const R F2 = g2 ? R(1) + f2 : R(1) - f2;
-      const R F3 = g3 ? R(1) + f3 : R(1) - f3;
-      const R F4 = g4 ? R(1) + f4 : R(1) - f4;
+      const R F2 = occupied(ch.sp[1], f2);
+      const R F3 = occupied(ch.sp[2], f3);
+      const R F4 = occupied(ch.sp[3], f4);
       const R gain = f3 * f4 * F1 * F2, loss = f1 * f2 * F3 * F4;
       const R v = wnb * (gain - loss);
       dsum += (double)v;
