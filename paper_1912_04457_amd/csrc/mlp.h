@@ -28,7 +28,7 @@ constexpr int kOffT2 = kOffT1 + kMlpHidden * kMlpIn;
 constexpr int kOffT3 = kOffT2 + kMlpHidden * kMlpHidden;
 constexpr int kMlpParamsT = kOffT3 + 96 * kMlpHidden;
 
-constexpr int kMlpTileRows = 64;    // rows a workgroup takes at a time
+constexpr int kMlpTileRows = 32;    // rows a workgroup takes at a time
 constexpr int kMlpMaxSlices = 256;  // gradient slices of a batch, one per workgroup
 
 struct MlpTileArgs {

@@ -25,25 +25,28 @@ __device__ __forceinline__ float dsilu_f(float z) {
 }
 
 // ---------------------------------------------------------------------------
-// The network on tiles of 64 rows: forward, and with kGrad the mixture head's
+// The network on tiles of 32 rows: forward, and with kGrad the mixture head's
 // weighted NLL and the backward pass, one kernel for what are 14 products and
 // elementwise passes.  A workgroup of 16 waves takes a tile through every
-// layer; the activations and their gradients stay in LDS (150 of the 160 KB),
-// row-major where they are the left operand of a product over features and
-// transposed where they enter a product over rows, so that every MFMA operand
-// is one 16-byte read.  Wave w owns rows 16 (w % 4).. and the feature tiles 2
-// (w / 4) and 2 (w / 4) + 1 of each layer and keeps their pre-activations in
-// registers for the backward pass; the weight gradients accumulate in
-// registers over the workgroup's tiles and go to its own slice of `part`,
-// which reduce_grad_kernel sums in a fixed order.  Weights are read from L2:
-// pb is row-major [in][out] (left factor of the backward products), pbt its
-// transpose [out][in].  A batch of 4096 rows is 64 workgroups and bound by the
-// chain of its phases: 196 us in 21 launches before, see the figures at
-// reduce_grad_kernel.
+// layer; the activations and their gradients stay in LDS (85 KB), row-major
+// where they are the left operand of a product over features and transposed
+// where they enter a product over rows, so that every MFMA operand is one
+// 16-byte read.  A wave owns 16 rows and one of the eight feature tiles of each
+// layer and keeps their pre-activations in registers for the backward pass; the
+// weight gradients accumulate in registers over the workgroup's tiles and go to
+// its own slice of `part`, which reduce_grad_kernel sums in a fixed order.
+// Weights are read from L2: pb is row-major [in][out] (left factor of the
+// backward products), pbt its transpose [out][in].
+// A batch is bound by the chain of its phases (4096 rows are 128 workgroups),
+// so a tile is as low as the products over rows allow, one MFMA's K: with 64
+// rows the gradient of 4096 rows took 36 us instead of 22.6, the forward pass of
+// 400,000 rows 262 us instead of 213 (two workgroups per compute unit).
 // Per row the arithmetic is that of the separate products: BF16 operands, FP32
 // accumulation over K in steps of 32, FP32 bias, activations and head.
 // ---------------------------------------------------------------------------
 constexpr int kRows = kMlpTileRows;
+constexpr int kBlocks = kRows / 16;       // row blocks of a tile; a wave owns one and one of 16 / kBlocks feature tiles
+static_assert(16 / kBlocks == kMlpHidden / 16, "16 waves cover a layer");
 constexpr int kHidPad = kMlpHidden + 8;   // row strides that spread the LDS banks
 constexpr int kRowPad = kRows + 8;
 constexpr int kOut16 = 96;                // head columns rounded up to MFMA tiles
@@ -64,9 +67,9 @@ struct GradLds {
   __bf16 dZ2T[kMlpHidden][kRowPad];
   float Y[kRows][kHeadPad];               // head, then its gradient
   float yw[kRows][kMixD + 1];
-  float colsum[2][4][kMlpHidden];         // per 16 rows: dZ2, dZ1
-  float colsum3[8][kMlpOut];              // per 8 rows: dY
-  double loss[8];
+  float colsum[2][kBlocks][kMlpHidden];   // per 16 rows: dZ2, dZ1
+  float colsum3[kRows / 8][kMlpOut];        // per 8 rows: dY
+  double loss[kRows / 8];
 };
 static_assert(sizeof(TileLds) + sizeof(GradLds) <= 160 * 1024, "one workgroup's LDS");
 
@@ -84,11 +87,11 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
   TileLds& L = *reinterpret_cast<TileLds*>(lds_raw);
   GradLds& D = *reinterpret_cast<GradLds*>(lds_raw + sizeof(TileLds));  // kGrad only
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int r16 = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
-  const int m0 = 16 * (w & 3), n0 = 32 * (w >> 2);  // this wave's rows and first feature column of a layer
+  int r16 = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
+  const int m0 = 16 * (w % kBlocks);             // this wave's rows
+  int n = 16 * (w / kBlocks) + r16;              // this lane's feature column of a layer
   const bf16x8 zero8 = {};
   const floatx4 zero4 = floatx4{0.f, 0.f, 0.f, 0.f};
-  const __bf16 *T1 = g.pbt + kOffT1, *T2 = g.pbt + kOffT2, *T3 = g.pbt + kOffT3;
   floatx4 dw1 = zero4, dw2[4] = {zero4, zero4, zero4, zero4}, dw3[3] = {zero4, zero4, zero4};
   float db = 0.f, db3 = 0.f;  // thread n < 128: bias gradient 2, n in 128..255: bias gradient 1; n < 88: head
   double loss = 0.0;
@@ -105,6 +108,12 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
   const long long n_tiles = (g.rows + kRows - 1) / kRows;
   for (long long tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     const long long row0 = tile * kRows;
+    const __bf16 *pb = g.pb, *pbt = g.pbt;
+    const float* P = g.P;
+    // (formed anew for each tile: kept over the loop, the weights' fragments and
+    // the addresses take the registers that the gradients need, 72 of them)
+    if (kGrad) asm volatile("" : "+s"(pb), "+s"(pbt), "+s"(P), "+v"(r16), "+v"(kq), "+v"(rq), "+v"(n));
+    const __bf16 *T1 = pbt + kOffT1, *T2 = pbt + kOffT2, *T3 = pbt + kOffT3;
     // inputs; rows beyond the last are zero with weight zero
     for (int e = tid; e < kRows * kMlpIn; e += 1024) {
       const int r = e / kMlpIn, c = e % kMlpIn;
@@ -122,19 +131,16 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
       }
     __syncthreads();
     // layer 1 (K = 8 in one step, zeros beyond)
-    floatx4 z1[2], z2[2];
+    floatx4 z1, z2;
     {
       const bf16x8 a = frag(L.Xb[m0 + r16], kq);
-      for (int j = 0; j < 2; ++j) {
-        const int n = n0 + 16 * j + r16;
-        z1[j] = mfma(a, kq == 0 ? frag(T1 + n * kMlpIn, 0) : zero8, zero4);
-        const float bias = g.P[kOffB1 + n];
-        for (int q = 0; q < 4; ++q) {
-          z1[j][q] += bias;
-          const __bf16 h = (__bf16)silu_f(z1[j][q]);
-          L.H1[m0 + rq + q][n] = h;
-          if (kGrad) D.H1T[n][m0 + rq + q] = h;
-        }
+      z1 = mfma(a, kq == 0 ? frag(T1 + n * kMlpIn, 0) : zero8, zero4);
+      const float bias = P[kOffB1 + n];
+      for (int q = 0; q < 4; ++q) {
+        z1[q] += bias;
+        const __bf16 h = (__bf16)silu_f(z1[q]);
+        L.H1[m0 + rq + q][n] = h;
+        if (kGrad) D.H1T[n][m0 + rq + q] = h;
       }
     }
     __syncthreads();
@@ -142,35 +148,29 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
     {
       bf16x8 a[4];
       for (int ks = 0; ks < 4; ++ks) a[ks] = frag(L.H1[m0 + r16], ks * kKStep + kq);
-      for (int j = 0; j < 2; ++j) {
-        const int n = n0 + 16 * j + r16;
-        z2[j] = zero4;
-        for (int ks = 0; ks < 4; ++ks) z2[j] = mfma(a[ks], frag(T2 + n * kMlpHidden, ks * kKStep + kq), z2[j]);
-        const float bias = g.P[kOffB2 + n];
-        for (int q = 0; q < 4; ++q) {
-          z2[j][q] += bias;
-          const __bf16 h = (__bf16)silu_f(z2[j][q]);
-          L.H2[m0 + rq + q][n] = h;
-          if (kGrad) D.H2T[n][m0 + rq + q] = h;
-        }
+      z2 = zero4;
+      for (int ks = 0; ks < 4; ++ks) z2 = mfma(a[ks], frag(T2 + n * kMlpHidden, ks * kKStep + kq), z2);
+      const float bias = P[kOffB2 + n];
+      for (int q = 0; q < 4; ++q) {
+        z2[q] += bias;
+        const __bf16 h = (__bf16)silu_f(z2[q]);
+        L.H2[m0 + rq + q][n] = h;
+        if (kGrad) D.H2T[n][m0 + rq + q] = h;
       }
     }
     __syncthreads();
     // head: six column tiles, the last one half used
-    if (n0 < kOut16) {
+    if (n < kOut16) {  // wave-uniform
       bf16x8 a[4];
       for (int ks = 0; ks < 4; ++ks) a[ks] = frag(L.H2[m0 + r16], ks * kKStep + kq);
-      for (int j = 0; j < 2; ++j) {
-        const int n = n0 + 16 * j + r16;
-        floatx4 y = zero4;
-        for (int ks = 0; ks < 4; ++ks) y = mfma(a[ks], frag(T3 + n * kMlpHidden, ks * kKStep + kq), y);
-        if (n < kMlpOut) {
-          const float bias = g.P[kOffB3 + n];
-          for (int q = 0; q < 4; ++q) {
-            const int r = m0 + rq + q;
-            if (kGrad) D.Y[r][n] = y[q] + bias;
-            else if (row0 + r < g.rows) g.Y[(row0 + r) * kMlpOut + n] = y[q] + bias;
-          }
+      floatx4 y = zero4;
+      for (int ks = 0; ks < 4; ++ks) y = mfma(a[ks], frag(T3 + n * kMlpHidden, ks * kKStep + kq), y);
+      if (n < kMlpOut) {
+        const float bias = P[kOffB3 + n];
+        for (int q = 0; q < 4; ++q) {
+          const int r = m0 + rq + q;
+          if (kGrad) D.Y[r][n] = y[q] + bias;
+          else if (row0 + r < g.rows) g.Y[(row0 + r) * kMlpOut + n] = y[q] + bias;
         }
       }
     }
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
     __syncthreads();
     // NLL of the mixture head and its gradient: eight lanes per row, one per
     // component; the sums over components in component order
-    if (w < 8) {
+    if (w < kRows / 8) {
       const int r = tid >> 3, k = tid & 7;
       float* h = D.Y[r];
       const float s = row0 + r < g.rows ? (float)((double)D.yw[r][kMixD] / *g.wsum) : 0.f;
@@ -230,29 +230,26 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
     {
       bf16x8 a[3];
       for (int ks = 0; ks < 3; ++ks) a[ks] = frag(D.dYb[m0 + r16], ks * kKStep + kq);
-      for (int j = 0; j < 2; ++j) {
-        const int n = n0 + 16 * j + r16;
-        const __bf16* wr = g.pb + kOffW3 + n * kMlpOut;
-        floatx4 dh = zero4;
-        for (int ks = 0; ks < 3; ++ks)
-          dh = mfma(a[ks], ks * kKStep + kq < kMlpOut ? frag(wr, ks * kKStep + kq) : zero8, dh);
-        float cs = 0.f;
-        for (int q = 0; q < 4; ++q) {
-          const float v = dh[q] * dsilu_f(z2[j][q]);
-          cs += v;
-          L.H1[m0 + rq + q][n] = (__bf16)v;
-          D.dZ2T[n][m0 + rq + q] = (__bf16)v;
-        }
-        cs += __shfl_xor(cs, 16, 64);
-        cs += __shfl_xor(cs, 32, 64);
-        if (lane < 16) D.colsum[0][w & 3][n] = cs;
+      const __bf16* wr = pb + kOffW3 + n * kMlpOut;
+      floatx4 dh = zero4;
+      for (int ks = 0; ks < 3; ++ks)
+        dh = mfma(a[ks], ks * kKStep + kq < kMlpOut ? frag(wr, ks * kKStep + kq) : zero8, dh);
+      float cs = 0.f;
+      for (int q = 0; q < 4; ++q) {
+        const float v = dh[q] * dsilu_f(z2[q]);
+        cs += v;
+        L.H1[m0 + rq + q][n] = (__bf16)v;
+        D.dZ2T[n][m0 + rq + q] = (__bf16)v;
       }
+      cs += __shfl_xor(cs, 16, 64);
+      cs += __shfl_xor(cs, 32, 64);
+      if (lane < 16) D.colsum[0][w % kBlocks][n] = cs;
       for (int i = 0; i < 3; ++i) {
         const int t = 3 * w + i, m = t / 6, n = t % 6;
         for (int ks = 0; ks < kRows / kKStep; ++ks)
           dw3[i] = mfma(frag(D.H2T[16 * m + r16], ks * kKStep + kq), frag(D.dYT[16 * n + r16], ks * kKStep + kq), dw3[i]);
       }
-      if (tid < 8 * kMlpOut) {
+      if (tid < kRows / 8 * kMlpOut) {
         const int c = tid % kMlpOut, r8 = tid / kMlpOut * 8;
         float cs = 0.f;
         for (int r = 0; r < 8; ++r) cs += D.Y[r8 + r][c];
@@ -264,20 +261,17 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
     {
       bf16x8 a[4];
       for (int ks = 0; ks < 4; ++ks) a[ks] = frag(L.H1[m0 + r16], ks * kKStep + kq);
-      for (int j = 0; j < 2; ++j) {
-        const int n = n0 + 16 * j + r16;
-        floatx4 dh = zero4;
-        for (int ks = 0; ks < 4; ++ks) dh = mfma(a[ks], frag(g.pb + kOffW2 + n * kMlpHidden, ks * kKStep + kq), dh);
-        float cs = 0.f;
-        for (int q = 0; q < 4; ++q) {
-          const float v = dh[q] * dsilu_f(z1[j][q]);
-          cs += v;
-          D.H2T[n][m0 + rq + q] = (__bf16)v;
-        }
-        cs += __shfl_xor(cs, 16, 64);
-        cs += __shfl_xor(cs, 32, 64);
-        if (lane < 16) D.colsum[1][w & 3][n] = cs;
+      floatx4 dh = zero4;
+      for (int ks = 0; ks < 4; ++ks) dh = mfma(a[ks], frag(pb + kOffW2 + n * kMlpHidden, ks * kKStep + kq), dh);
+      float cs = 0.f;
+      for (int q = 0; q < 4; ++q) {
+        const float v = dh[q] * dsilu_f(z1[q]);
+        cs += v;
+        D.H2T[n][m0 + rq + q] = (__bf16)v;
       }
+      cs += __shfl_xor(cs, 16, 64);
+      cs += __shfl_xor(cs, 32, 64);
+      if (lane < 16) D.colsum[1][w % kBlocks][n] = cs;
       for (int ks = 0; ks < kRows / kKStep; ++ks) {
         const bf16x8 h = frag(D.H1T[16 * (w >> 1) + r16], ks * kKStep + kq);
         for (int i = 0; i < 4; ++i)
@@ -292,12 +286,12 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
     if (tid < 2 * kMlpHidden) {
       const auto& c = D.colsum[tid / kMlpHidden];
       const int n = tid % kMlpHidden;
-      db += (c[0][n] + c[1][n]) + (c[2][n] + c[3][n]);
+      for (int i = 0; i < kBlocks; i += 2) db += c[i][n] + c[i + 1][n];
     }
     if (tid < kMlpOut)
-      for (int i = 0; i < 8; ++i) db3 += D.colsum3[i][tid];
+      for (int i = 0; i < kRows / 8; ++i) db3 += D.colsum3[i][tid];
     if (tid == 0)
-      for (int i = 0; i < 8; ++i) loss += D.loss[i];
+      for (int i = 0; i < kRows / 8; ++i) loss += D.loss[i];
     __syncthreads();
   }
   if (!kGrad) return;
@@ -341,20 +335,21 @@ __global__ void refresh_weights_kernel(const float* __restrict__ p, __bf16* __re
   if (i < (kOut16 - kMlpOut) * kMlpHidden) pbt[kOffT3 + kMlpOut * kMlpHidden + i] = (__bf16)0.0f;
 }
 
-// The workgroups' gradient slices summed (four threads per parameter, each a
-// quarter of the slices in order), and with adam the bias-corrected Adam step
+// The workgroups' gradient slices summed (eight threads per parameter, each an
+// eighth of the slices in order), and with adam the bias-corrected Adam step
 // on the FP32 master weights and their BF16 copies; block 0 adds the batch's
-// loss.  Gradient and step of a batch of 4096 rows are two launches: 196 ->
-// 35 us.
-constexpr int kReduceParams = 64;
-__global__ __launch_bounds__(4 * kReduceParams) void reduce_grad_kernel(MlpReduceArgs a) {
-  __shared__ float sh[4][kReduceParams];
+// loss.  Bound by the latency of a thread's loads (15 MB for 128 slices: 3 us
+// at the rate of a copy).  Gradient and step of a batch of 4096 rows are two
+// launches, 32 us together; as separate products they were 21 and 196 us.
+constexpr int kReduceParams = 64, kReduceParts = 8;
+__global__ __launch_bounds__(kReduceParts * kReduceParams) void reduce_grad_kernel(MlpReduceArgs a) {
+  __shared__ float sh[kReduceParts][kReduceParams];
   const int j = threadIdx.x % kReduceParams, grp = threadIdx.x / kReduceParams;
   const int i = blockIdx.x * kReduceParams + j;
-  const int lo = a.n_part * grp / 4, hi = a.n_part * (grp + 1) / 4;
+  const int lo = a.n_part * grp / kReduceParts, hi = a.n_part * (grp + 1) / kReduceParts;
   float s = 0.f;
   if (i < kMlpParams) {
-#pragma unroll 8
+#pragma unroll 16
     for (int k = lo; k < hi; ++k) s += a.part[(size_t)k * kMlpParams + i];
   }
   sh[grp][j] = s;
@@ -365,7 +360,8 @@ __global__ __launch_bounds__(4 * kReduceParams) void reduce_grad_kernel(MlpReduc
     *a.loss += l;
   }
   if (grp != 0 || i >= kMlpParams) return;
-  const float g = (sh[0][j] + sh[1][j]) + (sh[2][j] + sh[3][j]);
+  float g = 0.f;
+  for (int k = 0; k < kReduceParts; k += 2) g += sh[k][j] + sh[k + 1][j];
   if (!a.adam) {
     a.grad[i] = g;
     return;
@@ -591,7 +587,7 @@ hipError_t launch_mlp_grad(const MlpTileArgs& g, hipStream_t st) {
 }
 
 hipError_t launch_reduce_grad(const MlpReduceArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(reduce_grad_kernel, dim3((kMlpParams + kReduceParams - 1) / kReduceParams), dim3(4 * kReduceParams),
+  hipLaunchKernelGGL(reduce_grad_kernel, dim3((kMlpParams + kReduceParams - 1) / kReduceParams), dim3(kReduceParts * kReduceParams),
                      0, st, a);
   return hipGetLastError();
 }

@@ -345,6 +345,24 @@ def test_lds_plans_fp64(O, n_x, n_p, mask, N):
         assert abs(r["A"][:, cell].sum()) <= 1e-13 * r["S_ref"][:, cell].sum()
 
 
+@pytest.mark.parametrize("n_x,n_p", [((1, 1, 1), (24, 25, 23)), ((511, 1, 1), (2, 2, 3)), ((600, 1, 1), (3, 2, 2)),
+                                     ((3, 1, 1), (13, 14, 15))], ids=["one_cell", "511_cells", "600_cells", "parts"])
+@pytest.mark.parametrize("precision", [qgbe.FP64, qgbe.FP32])
+def test_masses_at_the_start_of_a_term(O, n_x, n_p, precision):
+    """The masses that a collision term forms in its first pass over f: cells
+    split over workgroups, and few and many cells (the sum over a cell's parts
+    by its last workgroup or by a second kernel)."""
+    _case(f"term start {n_x} {n_p} precision={precision}")
+    wl = W.Workload("start", n_x, n_p, (3.0, 3.0, 3.0), (2.0, 2.5, 1.5), 0x7F, 1, "f64", 1, 0.01)
+    f = W.random_f(29, wl.cells, wl.nodes)
+    g = O.Grid(n_x=wl.n_x, n_p=wl.n_p, x_half=wl.x_half, p_half=wl.p_half, species_mask=0x7F)
+    with qgbe.Solver(**_grid_kw(wl), precision=precision, seed=SEED) as s:
+        for scale in (1.0, 0.5):  # the second time on other values
+            s.set_f(scale * f)
+            s.collision(1)
+            assert np.allclose(s.masses(), O.masses(g, scale * f), rtol=1e-13, atol=0)
+
+
 @pytest.mark.parametrize("N", [1, 64, 200, 1088], ids=["one", "one_batch", "short", "long"])
 def test_small_queue_fp32(O, N):
     """Two slots whose accumulators leave room for the smaller of the sample

@@ -75,6 +75,30 @@ def test_mlp_loss_and_gradient_match_oracle():
         assert _rel(g[name], gref[name]) <= 1e-2, (name, _rel(g[name], gref[name]))
 
 
+@pytest.mark.parametrize("rows", [1, 31, 33, 64, 8192, 8193, 16384])
+def test_mlp_tiles(rows):
+    """Less than a tile of 32 rows, one row more or less than a tile, one tile per
+    gradient slice, one more, and the largest batch (two tiles per slice)."""
+    _case(f"mlp tiles {rows} rows")
+    w = W.random_mlp_params(7, head_scale=1.0)
+    X, yw = _mlp_inputs(rows, 8)
+    Y = np.zeros((rows, M.N_OUT), dtype=np.float32)
+    grad = np.zeros(qgbe.MLP_PARAMS, dtype=np.float32)
+    with qgbe.Solver(**_kw(SMALL_7)) as s:
+        qgbe.qgbe_proposal_set_weights(s.ctx, w)
+        qgbe.qgbe_mlp_forward(s.ctx, X, Y)
+        loss = qgbe.qgbe_mlp_loss_grad(s.ctx, X, yw, grad)
+    p = M.unflatten(w.astype(np.float64))
+    Yref, _ = M.forward(p, X.astype(np.float64), quantize=M.bf16)
+    lref, gref = M.loss_and_grad(p, X.astype(np.float64), yw[:, :5].astype(np.float64),
+                                 yw[:, 5].astype(np.float64), quantize=M.bf16)
+    assert _rel(Y, Yref) <= 1e-2
+    assert loss == pytest.approx(lref, rel=1e-3)
+    g = M.unflatten(grad.astype(np.float64))
+    for name, _ in M.PARAM_SHAPES:
+        assert _rel(g[name], gref[name]) <= 1e-2, (name, _rel(g[name], gref[name]))
+
+
 def test_features_match_oracle(O):
     _case("features")
     wl = SMALL_7
