@@ -74,7 +74,7 @@ def traffic_profile(workload: str) -> str:
     return os.path.join(ROOT, "profiles", f"collide_f32_{workload}_hbm_counters.md")
 
 
-KERNEL_SOURCES = ("collide_f32.hip", "collide_device.h", "collide.h", "qgbe_common.h", "api.hip")
+KERNEL_SOURCES = ("collide_f32.hip", "collide_slots.h", "collide_device.h", "collide.h", "qgbe_common.h", "api.hip")
 
 
 def kernel_sources_digest() -> str:
@@ -401,8 +401,7 @@ def run_workload(wl, N, steps, warmup, train_epochs, progress=False, proposal_in
     roof = dict(bound="alu", achieved=achieved, peak=ALU_PEAK_SLOTS, unit="lane-op slots/s",
                 frac=achieved / ALU_PEAK_SLOTS,
                 traffic=traffic,
-                kernel="collide_roots_kernel" if roots else
-                ("collide_f32_kernel" if prec == qgbe.FP32 else "collide_f64_kernel"),
+                kernel="collide_slots_kernel",
                 kernel_ms_avg=float(t_coll.sum() * 1e3 / launches),
                 launches_per_step=launches / len(stats),
                 hbm_frac=None if traffic is None else traffic * launches / float(t_coll.sum()) / HBM_PEAK)

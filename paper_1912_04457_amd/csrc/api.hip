@@ -349,8 +349,8 @@ bool records(qgbe_ctx* c, int l, int n_samples, const double* scale) {
   // Microseconds: 26 per million samples drawn (whole iterations of 64, and
   // half a one for the item), 14 per million replayed, 45 per launch that
   // draws and flushes, 40 per batch.  With the buffers of a context recording
-  // wins from two launches on (gluons at 30^3: 94 against 142 us with one
-  // sample, 184 against 250 with 128, 2.3 against 2.6 ms with 2048); in the few
+  // wins from two launches on (gluons at 30^3: 71 against 121 us with one
+  // sample, 156 against 216 with 128, 2.32 against 2.55 ms with 2048); in the few
   // MB of the call without allocation, 1000 samples there take 25 batches and
   // 2.1 ms instead of 1.3.
   const double per_sample = 1e-6 * (double)c->G.cells * c->G.nodes;

@@ -778,45 +778,5 @@ __device__ __forceinline__ double item_variance(double s, double sq, int n) {
   return fmax(0.0, (sq - s * s / n) * ((double)n / (n - 1)));
 }
 
-// Per-workgroup totals of the accepted count, the two error sums and the
-// per-channel variance sums: the waves add into LDS and the workgroup adds
-// its totals into global memory at the end, into stripe b mod kStripes (one
-// global atomic per workgroup and value instead of one per item on a single
-// address).
-struct BlockTotals {
-  unsigned long long* ok;
-  double* mc;   // [2]
-  double* var;  // [kMaxChannels]
-  __device__ void init() {
-    if (threadIdx.x == 0) {
-      *ok = 0ull;
-      mc[0] = 0.0;
-      mc[1] = 0.0;
-    }
-    for (int i = threadIdx.x; i < kMaxChannels; i += blockDim.x) var[i] = 0.0;
-    __syncthreads();
-  }
-  __device__ void add(int n_ok, double item_var, double sq, int ci) {
-    __hip_atomic_fetch_add(ok, (unsigned long long)n_ok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_fetch_add(&mc[0], item_var, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_fetch_add(&mc[1], sq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_fetch_add(&var[ci], item_var, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
-  __device__ void flush(const CollideArgs& A) {
-    __syncthreads();
-    const int stripe = blockIdx.x % kStripes;
-    if (threadIdx.x == 0) {
-      if (A.n_accepted) atomicAdd(A.n_accepted + stripe, *ok);
-      if (A.mc_acc) {
-        atomicAdd(&A.mc_acc[2 * stripe], mc[0]);
-        atomicAdd(&A.mc_acc[2 * stripe + 1], mc[1]);
-      }
-    }
-    if (A.chan_var)
-      for (int i = threadIdx.x; i < A.n_channels; i += blockDim.x)
-        if (var[i] != 0.0) atomicAdd(&A.chan_var[(size_t)stripe * A.n_channels + i], var[i]);
-  }
-};
-
 }  // namespace
 }  // namespace qgbe

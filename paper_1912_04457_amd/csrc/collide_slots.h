@@ -20,9 +20,9 @@ namespace {
 // R = double is the reference precision: the integrand in FP64 and f from the
 // FP64 field in global memory.  It is bound as FP32 is, by VALU issue and the
 // LDS atomics; with every deposit a global FP64 atomic, which the XCDs' shared
-// rows send past the L2 (20 G atomics/s), it took 38.3 instead of 3.0 ms on 7
-// species, 12 cells of 11x12x10 nodes, 64 samples; 1512 instead of 96 us on a
-// 20^3 gluon cell, 256 samples; 6.2 instead of 1.0 ms with the learned sampler
+// rows send past the L2 (20 G atomics/s), it took 38.3 instead of 2.3 ms on 7
+// species, 12 cells of 11x12x10 nodes, 64 samples; 1510 instead of 82 us on a
+// 20^3 gluon cell, 256 samples; 6.2 instead of 0.8 ms with the learned sampler
 // (7 species, 12^3, 64 samples).
 // ---------------------------------------------------------------------------
 // Trilinear read from the node quads: the same corners and the same
@@ -179,8 +179,8 @@ constexpr int kNodeBlock = 4;
 // Deposits and launches as for the CM-angle samplers.  Bound by VALU issue
 // (three wavefronts per SIMD; with workgroups of four and two per SIMD, and
 // global FP64 atomics beyond 1170 points, before): 64000 gluon nodes x 100
-// samples, direct, 262 -> 195 us a call; 7 species at 15^3 x 100, symmetric,
-// 10.6 ms -> 0.78 ms, at 20^3 23.5 -> 2.7 ms, at 30^3 x 20 14.9 -> 5.7 ms.
+// samples, direct, 262 -> 184 us a call; 7 species at 15^3 x 100, symmetric,
+// 10.6 ms -> 0.76 ms, at 20^3 23.5 -> 2.5 ms, at 30^3 x 20 15.0 -> 5.6 ms.
 // ---------------------------------------------------------------------------
 constexpr double kRootNorm = 1.0 / (32.0 * kPi * kPi * kPi * kPi * kPi * 16.0);
 
@@ -838,16 +838,16 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
 // part of the deposits that the batch's samples recorded for the species to
 // LDS accumulators of the window and flushes them.  For grids whose deposit
 // accumulators do not fit in LDS at once: drawing every sample again for each
-// window or slot costs about 800 VALU instructions per 64 samples and launch,
+// window or slot costs about 520 VALU instructions per 64 samples and launch,
 // a record 52 B written once (92 B in FP64) and 20 B (36 B) read per deposit
 // and window, and the sampling kernel then runs with its compacting queue.
-// Bound: the sampling launch by VALU issue (576 instructions per 64 samples,
-// 63% of the issue cycles), the replay by the LDS atomics (56% busy) and, with
+// Bound: the sampling launch by VALU issue (378 instructions per 64 samples,
+// 55% of the issue cycles), the replay by the LDS atomics (56% busy) and, with
 // few records per workgroup, by the flush (13500 entries x 256 workgroups, 34
-// us).  7 species at 30^3, 128 samples: 9 launches 18.8 ms -> 35 batches 9.4
-// ms; gluons at 30^3, 128 samples: 2 x 110 us -> 94 + 58 us; 7 species at 20^3
-// (15 channels of three slots): learned, 256 samples 9.0 -> 7.8 ms, plain, 4096
-// samples 51.5 -> 49.9 ms.
+// us).  Terms with every launch drawing again, and recorded: 7 species at 30^3,
+// 128 samples 18.8 and 9.0 ms (9 launches, 35 batches); gluons at 30^3, 128
+// samples 216 and 156 us; 7 species at 20^3 (15 channels of three slots)
+// learned, 256 samples 8.2 and 7.4 ms, plain, 4096 samples 44.0 and 42.7 ms.
 // ---------------------------------------------------------------------------
 constexpr int kReplayThreads = 1024;
 
@@ -894,8 +894,9 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(ReplayArgs a) {
 
 // Uniform sampler: the short-item form when waves share nodes, and below
 // kShortSamples samples per item (at 2048 samples on 256 cells of gluons the
-// compiled long form is 1.8% faster, 65.8 against 67.0 ms; at 128 samples on
-// the 70 channels of a 30^3 cell the short one 3.5%, 20.2 against 19.5 ms).
+// compiled long form is 0.9% faster, 59.75 against 60.3 ms; at 128 samples on
+// the 70 channels of a 30^3 cell, every launch drawing again, the short one was
+// 3.5%, 19.5 against 20.2 ms).
 constexpr int kShortSamples = 1024;
 inline bool short_items(int split, int n_samples) { return split > 1 || n_samples < kShortSamples; }
 
