@@ -19,9 +19,17 @@ namespace {
 constexpr size_t kScratchBytes = size_t(QGBE_NOALLOC_SCRATCH_MIB) << 20;
 constexpr int kMaxDevices = 64;
 
+constexpr size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
+
+// The group lists lie beyond the declared bytes, of which they count 1 KB (as
+// the two plain channel lists would): the grids that fit do not depend on
+// what the launch plan lists.
+constexpr size_t kListBytes = align256(kMaxGroupIndex * sizeof(int));
+constexpr size_t kListCounted = 2 * align256(kMaxChannels * sizeof(int));
+
 // One copy per GPU.  Host code never uses this name as an address: it takes
 // the device address from hipGetSymbolAddress once per device.
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kScratchBytes + kListBytes];
 
 struct DeviceState {
   bool ready = false;
@@ -34,8 +42,6 @@ struct DeviceState {
 
 std::mutex g_mu;
 DeviceState g_dev[kMaxDevices];
-
-size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 
 // Once per device, with that device current.
 qgbe_status setup(int device, DeviceState** out) {
@@ -121,14 +127,25 @@ qgbe_status qgbe_collision_term_noalloc(const qgbe_grid_desc* desc, const double
   c.d_count = cv.take<unsigned long long>(kStripes);
   c.d_mc = cv.take<double>((size_t)kStripes * (2 + nch1));
   c.d_chan_var = c.d_mc + 2 * kStripes;
+  const size_t limit = kScratchBytes + kListBytes - kListCounted;
   if (fp32) {
     c.d_f32 = cv.take<float>(n);
+    // Node quads that only the smaller sample queue would read (f tiles of every
+    // slot fit in LDS) give way where they do not fit.
+    bool tiles = true;
+    for (const Group& g : c.groups)
+      tiles = tiles && g.lds_tiles[0] == g.nslot && g.queue[0] != kRing && g.queue[1] != kRing;
+    if (c.need_quads[0] && tiles && cv.used + align256(n * sizeof(float4)) > limit) {
+      for (Group& g : c.groups) g.queue[0] = g.queue[1] = 0;
+      c.need_quads[0] = false;
+    }
     if (c.need_quads[0]) c.d_f32q = cv.take<float4>(n);
   }
-  if (cv.used > kScratchBytes)
-    return fail(QGBE_EINVAL, "grid needs " + std::to_string(cv.used) + " bytes of scratch, more than the " +
-                                 std::to_string(kScratchBytes) + " of qgbe_collision_term_noalloc");
-  carve_records(&c, dev->ptr + cv.used, kScratchBytes - cv.used);  // what is left
+  if (cv.used > limit)
+    return fail(QGBE_EINVAL, "grid needs " + std::to_string(cv.used - (limit - kScratchBytes)) +
+                                 " bytes of scratch, more than the " + std::to_string(kScratchBytes) +
+                                 " of qgbe_collision_term_noalloc");
+  carve_records(&c, dev->ptr + cv.used, limit - cv.used);  // what is left
   c.d_f = const_cast<double*>(f);  // read only: masses and the collision kernels
 
   // Channel table and group lists, uploaded when they differ

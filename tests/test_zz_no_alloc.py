@@ -67,6 +67,26 @@ def test_noalloc_matches_context_path(precision, sampler):
         assert np.all(np.abs(cell_sum) <= 1e-12 * S_ref.sum(axis=(0, 2)))
 
 
+@pytest.mark.parametrize("n_x,n_p", [((10, 6, 1), (22, 22, 22)), ((222, 1, 1), (22, 22, 22)), ((44, 1, 1), (22, 22, 22))],
+                         ids=["no_quads", "largest", "quads"])
+def test_noalloc_without_room_for_quads(n_x, n_p):
+    """Grids whose f tiles fit in LDS, but whose node quads (for the sample
+    queue) do not all fit in the scratch, are computed without the queue."""
+    torch = pytest.importorskip("torch")
+    print(f"\n[gpu case] noalloc quads n_x={n_x} n_p={n_p}", flush=True)
+    kw = dict(n_x=n_x, n_p=n_p, x_half=(3.0, 3.0, 3.0), p_half=(2.0, 2.0, 2.0), species_mask=1 << 6)
+    f = _f(kw, 11)
+    desc = qgbe.make_desc(**kw, precision=qgbe.FP32, seed=SEED, device=0)
+    fd = torch.from_numpy(f).cuda()
+    Ad = torch.full_like(fd, np.nan)
+    qgbe.qgbe_collision_term_noalloc(desc, fd, 2, 3, qgbe.SAMPLER_UNIFORM, Ad)
+    torch.cuda.synchronize()
+    A_ref, S_ref = _context_term(kw, f, qgbe.FP32, 2, 3, qgbe.SAMPLER_UNIFORM)
+    S = S_ref[6].max()
+    assert np.isfinite(A_ref).all() and np.abs(A_ref).max() > 0.0
+    assert (np.abs(Ad.cpu().numpy() - A_ref) <= TOL[qgbe.FP32] * S).all()
+
+
 def test_noalloc_refuses_what_it_cannot_do():
     torch = pytest.importorskip("torch")
     assert qgbe.qgbe_noalloc_scratch_bytes() == 64 << 20
