@@ -52,7 +52,8 @@ struct MlpState {
   float *params = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
   __bf16 *pb = nullptr, *pbt = nullptr;   // BF16 weights, row-major and transposed
   float *X = nullptr, *yw = nullptr, *Y = nullptr;  // staging of host buffers
-  float* part = nullptr;                  // gradient slices
+  __bf16* act = nullptr;                  // a gradient's activations and FP32 gradients (see mlp.h), losses per tile
+  float* dz = nullptr;
   double* loss_part = nullptr;
   double* scalars = nullptr;              // [0] loss, [1] weight sum
 };

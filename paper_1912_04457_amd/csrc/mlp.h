@@ -29,7 +29,21 @@ constexpr int kOffT3 = kOffT2 + kMlpHidden * kMlpHidden;
 constexpr int kMlpParamsT = kOffT3 + 96 * kMlpHidden;
 
 constexpr int kMlpTileRows = 32;    // rows a workgroup takes at a time
-constexpr int kMlpMaxSlices = 256;  // gradient slices of a batch, one per workgroup
+constexpr int kMlpMaxTiles = 512;   // of a gradient
+// What the gradient's tiles keep for the products over rows, kMlpTileRows values
+// to a row: inputs, hidden activations and gradients in BF16 (act), gradients in
+// FP32 for the biases, in the order of layers 1, 2, 3 (dz)
+constexpr int kActX = 0;
+constexpr int kActH1 = kActX + kMlpIn;
+constexpr int kActH2 = kActH1 + kMlpHidden;
+constexpr int kActDZ1 = kActH2 + kMlpHidden;
+constexpr int kActDZ2 = kActDZ1 + kMlpHidden;
+constexpr int kActDY = kActDZ2 + kMlpHidden;
+constexpr int kActRows = kActDY + kMlpOut;
+constexpr int kDzZ1 = 0;
+constexpr int kDzZ2 = kDzZ1 + kMlpHidden;
+constexpr int kDzY = kDzZ2 + kMlpHidden;
+constexpr int kDzRows = kDzY + kMlpOut;
 
 struct MlpTileArgs {
   long long rows;
@@ -43,14 +57,16 @@ struct MlpTileArgs {
   const float* P;          // FP32 parameters (biases)
   float* Y;                // forward: head [rows][88]
   const double* wsum;      // gradient: sum of the rows' weights
-  float* part;             // gradient: [slices][kMlpParams]
-  double* loss_part;       // gradient: [slices]
+  __bf16* act;             // gradient: [tiles][kActRows][kMlpTileRows]
+  float* dz;               // gradient: [tiles][kDzRows][kMlpTileRows]
+  double* loss_part;       // gradient: [tiles]
 };
 
-struct MlpReduceArgs {
-  const float* part;
+struct MlpGradArgs {
+  const __bf16* act;
+  const float* dz;
   const double* loss_part;
-  int n_part;
+  int n_tiles;
   double* loss;            // the batch's loss is added
   float* grad;             // without adam: the gradient
   int adam;                // an Adam step in place of it
@@ -59,11 +75,10 @@ struct MlpReduceArgs {
   float lr, b1, b2, eps, c1, c2;  // c1 = 1 - b1^t, c2 = 1 - b2^t
 };
 
-size_t mlp_grad_slices(long long rows);
-hipError_t raise_mlp_lds_limit();
 hipError_t launch_mlp_forward(const MlpTileArgs& g, hipStream_t st);
 hipError_t launch_mlp_grad(const MlpTileArgs& g, hipStream_t st);
-hipError_t launch_reduce_grad(const MlpReduceArgs& a, hipStream_t st);
+// The gradient (or Adam step) of the rows that launch_mlp_grad went through.
+hipError_t launch_weight_grad(const MlpGradArgs& a, hipStream_t st);
 hipError_t launch_refresh_weights(const float* p, __bf16* pb, __bf16* pbt, hipStream_t st);
 // out[b] = sum of w[i * stride] over the rows of batch b
 hipError_t launch_weight_sums(const float* w, long long stride, const int* idx, long long n, int batch, double* out,

@@ -26,29 +26,27 @@ __device__ __forceinline__ float dsilu_f(float z) {
 
 // ---------------------------------------------------------------------------
 // The network on tiles of 32 rows: forward, and with kGrad the mixture head's
-// weighted NLL and the backward pass, one kernel for what are 14 products and
-// elementwise passes.  A workgroup of 16 waves takes a tile through every
-// layer; the activations and their gradients stay in LDS (85 KB), row-major
-// where they are the left operand of a product over features and transposed
-// where they enter a product over rows, so that every MFMA operand is one
-// 16-byte read.  A wave owns 16 rows and one of the eight feature tiles of each
-// layer and keeps their pre-activations in registers for the backward pass; the
-// weight gradients accumulate in registers over the workgroup's tiles and go to
-// its own slice of `part`, which reduce_grad_kernel sums in a fixed order.
-// Weights are read from L2: pb is row-major [in][out] (left factor of the
-// backward products), pbt its transpose [out][in].
-// A batch is bound by the chain of its phases (4096 rows are 128 workgroups),
-// so a tile is as low as the products over rows allow, one MFMA's K: with 64
-// rows the gradient of 4096 rows took 36 us instead of 22.6, the forward pass of
-// 400,000 rows 262 us instead of 213 (two workgroups per compute unit).
+// weighted NLL and the backward pass down to the gradients of the layers'
+// outputs, one kernel for what are nine products and elementwise passes.  A
+// workgroup of 16 waves takes a tile through every layer; the activations stay
+// in LDS, row-major, where they are the left operand of a product over features,
+// so that every MFMA operand is one 16-byte read.  A wave owns 16 rows and one of
+// the eight feature tiles of each layer and keeps their pre-activations in
+// registers for the backward pass.  With kGrad the activations and gradients also
+// go to global memory, transposed, for the products over rows
+// (weight_grad_kernel).  Weights are read from L2: pb is row-major [in][out]
+// (left factor of the backward products), pbt its transpose [out][in].
+// A batch is bound by the chain of its phases (4096 rows are 128 workgroups), so
+// a tile is low; the forward pass of 400,000 rows takes 262 us on tiles of 64
+// rows and 213 on these (two workgroups per compute unit).
 // Per row the arithmetic is that of the separate products: BF16 operands, FP32
 // accumulation over K in steps of 32, FP32 bias, activations and head.
 // ---------------------------------------------------------------------------
 constexpr int kRows = kMlpTileRows;
 constexpr int kBlocks = kRows / 16;       // row blocks of a tile; a wave owns one and one of 16 / kBlocks feature tiles
 static_assert(16 / kBlocks == kMlpHidden / 16, "16 waves cover a layer");
+static_assert(kRows == kKStep, "a tile is one K step of the products over rows");
 constexpr int kHidPad = kMlpHidden + 8;   // row strides that spread the LDS banks
-constexpr int kRowPad = kRows + 8;
 constexpr int kOut16 = 96;                // head columns rounded up to MFMA tiles
 constexpr int kOutPad16 = kOut16 + 8;
 constexpr int kHeadPad = kMlpOut + 4;
@@ -59,19 +57,14 @@ struct TileLds {
   __bf16 H2[kRows][kHidPad];
 };
 struct GradLds {
-  __bf16 XT[16][kRowPad];                 // rows >= 8 zero
-  __bf16 H1T[kMlpHidden][kRowPad];
-  __bf16 H2T[kMlpHidden][kRowPad];
   __bf16 dYb[kRows][kOutPad16];           // columns >= 88 zero
-  __bf16 dYT[kOut16][kRowPad];
-  __bf16 dZ2T[kMlpHidden][kRowPad];
   float Y[kRows][kHeadPad];               // head, then its gradient
   float yw[kRows][kMixD + 1];
-  float colsum[2][kBlocks][kMlpHidden];   // per 16 rows: dZ2, dZ1
-  float colsum3[kRows / 8][kMlpOut];        // per 8 rows: dY
   double loss[kRows / 8];
 };
-static_assert(sizeof(TileLds) + sizeof(GradLds) <= 160 * 1024, "one workgroup's LDS");
+static_assert(sizeof(TileLds) + sizeof(GradLds) <= 64 * 1024, "the default dynamic limit");
+
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 // A fragment: lane l holds row l % 16, k = 8 (l / 16)..+7 of a row-major tile.
 template <typename T>
@@ -87,40 +80,41 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
   TileLds& L = *reinterpret_cast<TileLds*>(lds_raw);
   GradLds& D = *reinterpret_cast<GradLds*>(lds_raw + sizeof(TileLds));  // kGrad only
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  int r16 = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
+  const int r16 = lane & 15, kq = (lane >> 4) * 8, rq = (lane >> 4) * 4;
   const int m0 = 16 * (w % kBlocks);             // this wave's rows
-  int n = 16 * (w / kBlocks) + r16;              // this lane's feature column of a layer
+  const int n = 16 * (w / kBlocks) + r16;        // this lane's feature column of a layer
   const bf16x8 zero8 = {};
   const floatx4 zero4 = floatx4{0.f, 0.f, 0.f, 0.f};
-  floatx4 dw1 = zero4, dw2[4] = {zero4, zero4, zero4, zero4}, dw3[3] = {zero4, zero4, zero4};
-  float db = 0.f, db3 = 0.f;  // thread n < 128: bias gradient 2, n in 128..255: bias gradient 1; n < 88: head
-  double loss = 0.0;
+  const __bf16 *T1 = g.pbt + kOffT1, *T2 = g.pbt + kOffT2, *T3 = g.pbt + kOffT3;
+  const float* P = g.P;
   // the paddings that no tile writes
   for (int e = tid; e < kRows * kKStep; e += 1024) L.Xb[e / kKStep][e % kKStep] = (__bf16)0.0f;
-  if (kGrad) {
-    for (int e = tid; e < 8 * kRows; e += 1024) D.XT[8 + e / kRows][e % kRows] = (__bf16)0.0f;
-    for (int e = tid; e < 8 * kRows; e += 1024) {
-      D.dYb[e % kRows][kMlpOut + e / kRows] = (__bf16)0.0f;
-      D.dYT[kMlpOut + e / kRows][e % kRows] = (__bf16)0.0f;
-    }
-  }
+  if (kGrad)
+    for (int e = tid; e < 8 * kRows; e += 1024) D.dYb[e % kRows][kMlpOut + e / kRows] = (__bf16)0.0f;
   __syncthreads();
   const long long n_tiles = (g.rows + kRows - 1) / kRows;
   for (long long tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     const long long row0 = tile * kRows;
-    const __bf16 *pb = g.pb, *pbt = g.pbt;
-    const float* P = g.P;
-    // (formed anew for each tile: kept over the loop, the weights' fragments and
-    // the addresses take the registers that the gradients need, 72 of them)
-    if (kGrad) asm volatile("" : "+s"(pb), "+s"(pbt), "+s"(P), "+v"(r16), "+v"(kq), "+v"(rq), "+v"(n));
-    const __bf16 *T1 = pbt + kOffT1, *T2 = pbt + kOffT2, *T3 = pbt + kOffT3;
-    // inputs; rows beyond the last are zero with weight zero
+    __bf16* act = kGrad ? g.act + tile * (kActRows * kRows) : nullptr;
+    float* dz = kGrad ? g.dz + tile * (kDzRows * kRows) : nullptr;
+    // four rows of column `row`, rows beyond the last as zero
+    const auto keep_act = [&](int row, const floatx4& v) {
+      bf16x4 b;
+      for (int q = 0; q < 4; ++q) b[q] = (__bf16)(row0 + m0 + rq + q < g.rows ? v[q] : 0.f);
+      *(bf16x4*)(act + row * kRows + m0 + rq) = b;
+    };
+    const auto keep_dz = [&](int row, const floatx4& v) {
+      floatx4 z;
+      for (int q = 0; q < 4; ++q) z[q] = row0 + m0 + rq + q < g.rows ? v[q] : 0.f;
+      *(floatx4*)(dz + row * kRows + m0 + rq) = z;
+    };
+    // inputs; rows beyond the last are zero
     for (int e = tid; e < kRows * kMlpIn; e += 1024) {
       const int r = e / kMlpIn, c = e % kMlpIn;
       float x = 0.f;
       if (row0 + r < g.rows) x = g.X[(g.idx ? (long long)g.idx[row0 + r] : row0 + r) * g.xs + c];
       L.Xb[r][c] = (__bf16)x;
-      if (kGrad) D.XT[c][r] = (__bf16)x;
+      if (kGrad) act[(kActX + c) * kRows + r] = (__bf16)x;
     }
     if (kGrad)
       for (int e = tid; e < kRows * (kMixD + 1); e += 1024) {
@@ -136,12 +130,13 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
       const bf16x8 a = frag(L.Xb[m0 + r16], kq);
       z1 = mfma(a, kq == 0 ? frag(T1 + n * kMlpIn, 0) : zero8, zero4);
       const float bias = P[kOffB1 + n];
+      floatx4 h;
       for (int q = 0; q < 4; ++q) {
         z1[q] += bias;
-        const __bf16 h = (__bf16)silu_f(z1[q]);
-        L.H1[m0 + rq + q][n] = h;
-        if (kGrad) D.H1T[n][m0 + rq + q] = h;
+        h[q] = silu_f(z1[q]);
+        L.H1[m0 + rq + q][n] = (__bf16)h[q];
       }
+      if (kGrad) keep_act(kActH1 + n, h);
     }
     __syncthreads();
     // layer 2
@@ -151,12 +146,13 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
       z2 = zero4;
       for (int ks = 0; ks < 4; ++ks) z2 = mfma(a[ks], frag(T2 + n * kMlpHidden, ks * kKStep + kq), z2);
       const float bias = P[kOffB2 + n];
+      floatx4 h;
       for (int q = 0; q < 4; ++q) {
         z2[q] += bias;
-        const __bf16 h = (__bf16)silu_f(z2[q]);
-        L.H2[m0 + rq + q][n] = h;
-        if (kGrad) D.H2T[n][m0 + rq + q] = h;
+        h[q] = silu_f(z2[q]);
+        L.H2[m0 + rq + q][n] = (__bf16)h[q];
       }
+      if (kGrad) keep_act(kActH2 + n, h);
     }
     __syncthreads();
     // head: six column tiles, the last one half used
@@ -174,17 +170,15 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
         }
       }
     }
-    if (!kGrad) {
-      __syncthreads();  // the next tile's inputs
-      continue;
-    }
-    __syncthreads();
+    __syncthreads();  // forward only: the next tile's inputs
+    if (!kGrad) continue;
     // NLL of the mixture head and its gradient: eight lanes per row, one per
     // component; the sums over components in component order
     if (w < kRows / 8) {
       const int r = tid >> 3, k = tid & 7;
+      const bool valid = row0 + r < g.rows;
       float* h = D.Y[r];
-      const float s = row0 + r < g.rows ? (float)((double)D.yw[r][kMixD] / *g.wsum) : 0.f;
+      const float s = valid ? (float)((double)D.yw[r][kMixD] / *g.wsum) : 0.f;
       const float hk = h[k];
       float mx = -INFINITY;
       for (int j = 0; j < kMixK; ++j) mx = fmaxf(mx, __shfl(hk, j, 8));
@@ -206,12 +200,12 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
       float se2 = 0.f;
       for (int j = 0; j < kMixK; ++j) se2 += __shfl(eb, j, 8);
       const float lm = m2 + __logf(se2);
-      double part = k == 0 ? -(double)s * (double)lm : 0.0;
+      double part = k == 0 && valid ? -(double)s * (double)lm : 0.0;
       const float resp = __expf(l - lm), pi = __expf(hk - lse_a);
       const auto put = [&](int c, float v) {
+        if (!valid) v = 0.f;
         h[c] = v;
         D.dYb[r][c] = (__bf16)v;
-        D.dYT[c][r] = (__bf16)v;
       };
       put(k, -s * (resp - pi));
       for (int e = 0; e < kMixD; ++e) {
@@ -226,89 +220,51 @@ __global__ __launch_bounds__(1024) void mlp_tile_kernel(MlpTileArgs g) {
       if (lane == 0) D.loss[w] = part;
     }
     __syncthreads();
-    // dZ2 = (dY W3^T) silu'(Z2); dW3 = H2^T dY; column sums of dY
+    if (tid == 0) {
+      double loss = 0.0;
+      for (int i = 0; i < kRows / 8; ++i) loss += D.loss[i];
+      g.loss_part[tile] = loss;
+    }
+    // the head's gradient, four rows of a column per thread
+    for (int e = tid; e < kMlpOut * (kRows / 4); e += 1024) {
+      const int c = e / (kRows / 4), r = e % (kRows / 4) * 4;
+      floatx4 v;
+      bf16x4 b;
+      for (int q = 0; q < 4; ++q) {
+        v[q] = D.Y[r + q][c];
+        b[q] = (__bf16)v[q];
+      }
+      *(floatx4*)(dz + (kDzY + c) * kRows + r) = v;
+      *(bf16x4*)(act + (kActDY + c) * kRows + r) = b;
+    }
+    // dZ2 = (dY W3^T) silu'(Z2)
     {
       bf16x8 a[3];
       for (int ks = 0; ks < 3; ++ks) a[ks] = frag(D.dYb[m0 + r16], ks * kKStep + kq);
-      const __bf16* wr = pb + kOffW3 + n * kMlpOut;
+      const __bf16* wr = g.pb + kOffW3 + n * kMlpOut;
       floatx4 dh = zero4;
       for (int ks = 0; ks < 3; ++ks)
         dh = mfma(a[ks], ks * kKStep + kq < kMlpOut ? frag(wr, ks * kKStep + kq) : zero8, dh);
-      float cs = 0.f;
       for (int q = 0; q < 4; ++q) {
-        const float v = dh[q] * dsilu_f(z2[q]);
-        cs += v;
-        L.H1[m0 + rq + q][n] = (__bf16)v;
-        D.dZ2T[n][m0 + rq + q] = (__bf16)v;
+        dh[q] = dh[q] * dsilu_f(z2[q]);
+        L.H1[m0 + rq + q][n] = (__bf16)dh[q];
       }
-      cs += __shfl_xor(cs, 16, 64);
-      cs += __shfl_xor(cs, 32, 64);
-      if (lane < 16) D.colsum[0][w % kBlocks][n] = cs;
-      for (int i = 0; i < 3; ++i) {
-        const int t = 3 * w + i, m = t / 6, n = t % 6;
-        for (int ks = 0; ks < kRows / kKStep; ++ks)
-          dw3[i] = mfma(frag(D.H2T[16 * m + r16], ks * kKStep + kq), frag(D.dYT[16 * n + r16], ks * kKStep + kq), dw3[i]);
-      }
-      if (tid < kRows / 8 * kMlpOut) {
-        const int c = tid % kMlpOut, r8 = tid / kMlpOut * 8;
-        float cs = 0.f;
-        for (int r = 0; r < 8; ++r) cs += D.Y[r8 + r][c];
-        D.colsum3[r8 / 8][c] = cs;
-      }
+      keep_act(kActDZ2 + n, dh);
+      keep_dz(kDzZ2 + n, dh);
     }
     __syncthreads();
-    // dZ1 = (dZ2 W2^T) silu'(Z1), transposed into H2T's place; dW2 = H1^T dZ2
+    // dZ1 = (dZ2 W2^T) silu'(Z1)
     {
       bf16x8 a[4];
       for (int ks = 0; ks < 4; ++ks) a[ks] = frag(L.H1[m0 + r16], ks * kKStep + kq);
       floatx4 dh = zero4;
-      for (int ks = 0; ks < 4; ++ks) dh = mfma(a[ks], frag(pb + kOffW2 + n * kMlpHidden, ks * kKStep + kq), dh);
-      float cs = 0.f;
-      for (int q = 0; q < 4; ++q) {
-        const float v = dh[q] * dsilu_f(z1[q]);
-        cs += v;
-        D.H2T[n][m0 + rq + q] = (__bf16)v;
-      }
-      cs += __shfl_xor(cs, 16, 64);
-      cs += __shfl_xor(cs, 32, 64);
-      if (lane < 16) D.colsum[1][w % kBlocks][n] = cs;
-      for (int ks = 0; ks < kRows / kKStep; ++ks) {
-        const bf16x8 h = frag(D.H1T[16 * (w >> 1) + r16], ks * kKStep + kq);
-        for (int i = 0; i < 4; ++i)
-          dw2[i] = mfma(h, frag(D.dZ2T[16 * (4 * (w & 1) + i) + r16], ks * kKStep + kq), dw2[i]);
-      }
+      for (int ks = 0; ks < 4; ++ks) dh = mfma(a[ks], frag(g.pb + kOffW2 + n * kMlpHidden, ks * kKStep + kq), dh);
+      for (int q = 0; q < 4; ++q) dh[q] = dh[q] * dsilu_f(z1[q]);
+      keep_act(kActDZ1 + n, dh);
+      keep_dz(kDzZ1 + n, dh);
     }
-    __syncthreads();
-    // dW1 = X^T dZ1 and the bias gradients
-    if (w < 8)
-      for (int ks = 0; ks < kRows / kKStep; ++ks)
-        dw1 = mfma(frag(D.XT[r16], ks * kKStep + kq), frag(D.H2T[16 * w + r16], ks * kKStep + kq), dw1);
-    if (tid < 2 * kMlpHidden) {
-      const auto& c = D.colsum[tid / kMlpHidden];
-      const int n = tid % kMlpHidden;
-      for (int i = 0; i < kBlocks; i += 2) db += c[i][n] + c[i + 1][n];
-    }
-    if (tid < kMlpOut)
-      for (int i = 0; i < kRows / 8; ++i) db3 += D.colsum3[i][tid];
-    if (tid == 0)
-      for (int i = 0; i < kRows / 8; ++i) loss += D.loss[i];
-    __syncthreads();
+    __syncthreads();  // the next tile's inputs
   }
-  if (!kGrad) return;
-  float* out = g.part + (size_t)blockIdx.x * kMlpParams;
-  for (int q = 0; q < 4; ++q) {
-    for (int i = 0; i < 3; ++i) {
-      const int t = 3 * w + i, n = 16 * (t % 6) + r16;
-      if (n < kMlpOut) out[kOffW3 + (16 * (t / 6) + rq + q) * kMlpOut + n] = dw3[i][q];
-    }
-    for (int i = 0; i < 4; ++i)
-      out[kOffW2 + (16 * (w >> 1) + rq + q) * kMlpHidden + 16 * (4 * (w & 1) + i) + r16] = dw2[i][q];
-    if (w < 8 && rq + q < kMlpIn) out[kOffW1 + (rq + q) * kMlpHidden + 16 * w + r16] = dw1[q];
-  }
-  if (tid < kMlpHidden) out[kOffB2 + tid] = db;
-  else if (tid < 2 * kMlpHidden) out[kOffB1 + tid - kMlpHidden] = db;
-  if (tid < kMlpOut) out[kOffB3 + tid] = db3;
-  if (tid == 0) g.loss_part[blockIdx.x] = loss;
 }
 
 // Position of parameter i in the transposed BF16 weights, -1 for a bias.
@@ -335,44 +291,119 @@ __global__ void refresh_weights_kernel(const float* __restrict__ p, __bf16* __re
   if (i < (kOut16 - kMlpOut) * kMlpHidden) pbt[kOffT3 + kMlpOut * kMlpHidden + i] = (__bf16)0.0f;
 }
 
-// The workgroups' gradient slices summed (eight threads per parameter, each an
-// eighth of the slices in order), and with adam the bias-corrected Adam step
-// on the FP32 master weights and their BF16 copies; block 0 adds the batch's
-// loss.  Bound by the latency of a thread's loads (15 MB for 128 slices: 3 us
-// at the rate of a copy).  Gradient and step of a batch of 4096 rows are two
-// launches, 32 us together; as separate products they were 21 and 196 us.
-constexpr int kReduceParams = 64, kReduceParts = 8;
-__global__ __launch_bounds__(kReduceParts * kReduceParams) void reduce_grad_kernel(MlpReduceArgs a) {
-  __shared__ float sh[kReduceParts][kReduceParams];
-  const int j = threadIdx.x % kReduceParams, grp = threadIdx.x / kReduceParams;
-  const int i = blockIdx.x * kReduceParams + j;
-  const int lo = a.n_part * grp / kReduceParts, hi = a.n_part * (grp + 1) / kReduceParts;
-  float s = 0.f;
-  if (i < kMlpParams) {
-#pragma unroll 16
-    for (int k = lo; k < hi; ++k) s += a.part[(size_t)k * kMlpParams + i];
-  }
-  sh[grp][j] = s;
-  __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    double l = 0.0;
-    for (int k = 0; k < a.n_part; ++k) l += a.loss_part[k];
-    *a.loss += l;
-  }
-  if (grp != 0 || i >= kMlpParams) return;
-  float g = 0.f;
-  for (int k = 0; k < kReduceParts; k += 2) g += sh[k][j] + sh[k + 1][j];
-  if (!a.adam) {
-    a.grad[i] = g;
+// The gradient of a batch from what mlp_tile_kernel kept, and with adam the
+// bias-corrected Adam step on the FP32 master weights and their BF16 copies.
+// The sums over the rows are bracketed by kGradChunk rows for the weights, one
+// chain of MFMAs each, and by kBiasChunk rows for the biases (four chains of
+// every fourth row, added in pairs): the values that training has always had, up
+// to the order in which the chunks are added, which is in FP64 here.  (On sums
+// in other brackets the losses of two epochs move by some 3e-7: the BF16 weights
+// round the other way now and then.)
+// Block b < kGradTiles: a 16 x 16 tile of a weight matrix, a wave per chunk (in
+// turn); the others: kBiasCols biases each.  206 workgroups, one round; bound by
+// the latency of a chain (16 loads, 8 MFMAs) and of the Adam step behind it.
+constexpr int kGradChunk = 256, kBiasChunk = 64;
+constexpr int kTilesW2 = (kMlpHidden / 16) * (kMlpHidden / 16), kTilesW3 = kMlpHidden / 16 * (kOut16 / 16),
+              kTilesW1 = kMlpHidden / 16;
+constexpr int kGradTiles = kTilesW2 + kTilesW3 + kTilesW1;
+constexpr int kBiasCols = 4;
+static_assert(kDzRows % kBiasCols == 0, "whole groups of biases");
+
+__global__ __launch_bounds__(1024) void weight_grad_kernel(MlpGradArgs a) {
+  __shared__ float sums[16][256];  // weights: a chunk per wave
+  __shared__ double wave_sums[16];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const auto apply = [&](int i, float g) {
+    if (!a.adam) {
+      a.grad[i] = g;
+      return;
+    }
+    const float mi = a.b1 * a.m[i] + (1.f - a.b1) * g;
+    const float vi = a.b2 * a.v[i] + (1.f - a.b2) * g * g;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    const float p = a.p[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+    a.p[i] = p;
+    put_weight(a.pb, a.pbt, i, p);
+  };
+  if (blockIdx.x < kGradTiles) {
+    const int r16 = lane & 15, kq = (lane >> 4) * 8;
+    int t = blockIdx.x, m, n, left, right;  // the tile, and its operands' first rows of act
+    bool in_a = true, in_b = true;          // this lane's rows exist
+    if (t < kTilesW2) {  // H1^T dZ2
+      m = t / (kMlpHidden / 16), n = t % (kMlpHidden / 16);
+      left = kActH1, right = kActDZ2;
+    } else if (t < kTilesW2 + kTilesW3) {  // H2^T dY
+      t -= kTilesW2;
+      m = t / (kOut16 / 16), n = t % (kOut16 / 16);
+      left = kActH2, right = kActDY;
+      in_b = 16 * n + r16 < kMlpOut;
+    } else {  // X^T dZ1
+      m = 0, n = t - kTilesW2 - kTilesW3;
+      left = kActX, right = kActDZ1;
+      in_a = r16 < kMlpIn;
+    }
+    const int tiles = a.n_tiles, chunk_tiles = kGradChunk / kRows, chunks = (tiles + chunk_tiles - 1) / chunk_tiles;
+    const bf16x8 zero8 = {};
+    double g = 0.0;
+    for (int c0 = 0; c0 < chunks; c0 += 16) {
+      const int c = c0 + w;
+      const int k0 = c * chunk_tiles, k1 = min(tiles, k0 + chunk_tiles);
+      const __bf16* pa = a.act + ((size_t)k0 * kActRows + left + 16 * m + r16) * kRows;
+      const __bf16* pb = a.act + ((size_t)k0 * kActRows + right + 16 * n + r16) * kRows;
+      floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < chunk_tiles; ++k) {
+        if (k0 + k >= k1) break;
+        const bf16x8 x = in_a ? frag(pa + (size_t)k * kActRows * kRows, kq) : zero8;
+        const bf16x8 y = in_b ? frag(pb + (size_t)k * kActRows * kRows, kq) : zero8;
+        acc = mfma(x, y, acc);
+      }
+      *(floatx4*)(sums[w] + 4 * lane) = acc;
+      __syncthreads();
+      if (tid < 256)
+        for (int i = 0; i < 16 && c0 + i < chunks; ++i) g += (double)sums[i][tid];
+      __syncthreads();
+    }
+    if (tid >= 256) return;
+    // element tid: lane tid / 4's value tid % 4
+    const int row = 16 * m + (tid >> 6) * 4 + (tid & 3), col = 16 * n + ((tid >> 2) & 15);
+    if (left == kActH1) apply(kOffW2 + row * kMlpHidden + col, (float)g);
+    else if (left == kActH2 && col < kMlpOut) apply(kOffW3 + row * kMlpOut + col, (float)g);
+    else if (left == kActX && row < kMlpIn) apply(kOffW1 + row * kMlpHidden + col, (float)g);
     return;
   }
-  const float mi = a.b1 * a.m[i] + (1.f - a.b1) * g;
-  const float vi = a.b2 * a.v[i] + (1.f - a.b2) * g * g;
-  a.m[i] = mi;
-  a.v[i] = vi;
-  const float w = a.p[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
-  a.p[i] = w;
-  put_weight(a.pb, a.pbt, i, w);
+  // biases: wave w takes column w / 4; 16 chunks of rows side by side, four lanes each
+  const int col = (blockIdx.x - kGradTiles) * kBiasCols + w / 4, ph = lane & 3;
+  double g = 0.0;
+  for (int c = (w & 3) * 16 + (lane >> 2); c * (kBiasChunk / kRows) < a.n_tiles; c += 64) {
+    float s = 0.f;
+    for (int t = 0; t < kBiasChunk / kRows; ++t) {
+      const int tile = c * (kBiasChunk / kRows) + t;
+      if (tile >= a.n_tiles) break;
+      const float* d = a.dz + ((size_t)tile * kDzRows + col) * kRows + ph;
+#pragma unroll
+      for (int i = 0; i < kRows / 4; ++i) s += d[4 * i];
+    }
+    s += __shfl_xor(s, 1, 4);
+    s += __shfl_xor(s, 2, 4);
+    if (ph == 0) g += (double)s;
+  }
+  for (int off = 32; off > 0; off >>= 1) g += __shfl_xor(g, off, 64);
+  if (lane == 0) wave_sums[w] = g;
+  __syncthreads();
+  if ((tid & 255) == 0) {
+    const float sum = (float)((wave_sums[w] + wave_sums[w + 1]) + (wave_sums[w + 2] + wave_sums[w + 3]));
+    if (col < kDzZ2) apply(kOffB1 + col, sum);
+    else if (col < kDzY) apply(kOffB2 + col - kDzZ2, sum);
+    else apply(kOffB3 + col - kDzY, sum);
+  }
+  if (blockIdx.x == kGradTiles && w == 0) {  // the batch's loss is added
+    double l = 0.0;
+    for (int k = lane; k < a.n_tiles; k += 64) l += a.loss_part[k];
+    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+    if (lane == 0) *a.loss += l;
+  }
 }
 
 // Weight sums of the batches: block b sums the weights of rows b * batch.. of
@@ -560,17 +591,6 @@ __global__ void features_kernel(Grid G, const Channel* __restrict__ chans, int n
 
 }  // namespace
 
-size_t mlp_grad_slices(long long rows) {
-  return (size_t)std::min<long long>(kMlpMaxSlices, (rows + kRows - 1) / kRows);
-}
-
-// The gradient kernel's LDS exceeds the runtime's default dynamic limit: it is
-// raised once per GPU.
-hipError_t raise_mlp_lds_limit() {
-  return hipFuncSetAttribute((const void*)mlp_tile_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)(sizeof(TileLds) + sizeof(GradLds)));
-}
-
 hipError_t launch_mlp_forward(const MlpTileArgs& g, hipStream_t st) {
   if (g.rows <= 0) return hipSuccess;
   const long long tiles = (g.rows + kRows - 1) / kRows;
@@ -580,15 +600,15 @@ hipError_t launch_mlp_forward(const MlpTileArgs& g, hipStream_t st) {
 }
 
 hipError_t launch_mlp_grad(const MlpTileArgs& g, hipStream_t st) {
-  if (g.rows <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(mlp_tile_kernel<true>, dim3((unsigned)mlp_grad_slices(g.rows)), dim3(1024),
+  if (g.rows <= 0 || g.rows > (long long)kMlpMaxTiles * kRows) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(mlp_tile_kernel<true>, dim3((unsigned)((g.rows + kRows - 1) / kRows)), dim3(1024),
                      sizeof(TileLds) + sizeof(GradLds), st, g);
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_grad(const MlpReduceArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(reduce_grad_kernel, dim3((kMlpParams + kReduceParams - 1) / kReduceParams), dim3(kReduceParts * kReduceParams),
-                     0, st, a);
+hipError_t launch_weight_grad(const MlpGradArgs& a, hipStream_t st) {
+  if (a.n_tiles <= 0 || a.n_tiles > kMlpMaxTiles) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(weight_grad_kernel, dim3(kGradTiles + kDzRows / kBiasCols), dim3(1024), 0, st, a);
   return hipGetLastError();
 }
 

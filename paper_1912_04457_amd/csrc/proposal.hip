@@ -22,7 +22,6 @@ static_assert(QGBE_MLP_PARAMS == kMlpParams, "header and kernels disagree on the
 qgbe_status mlp_ensure(qgbe_ctx* c) {
   MlpState& m = c->mlp;
   if (m.ready) return QGBE_OK;
-  HIP_TRY(raise_mlp_lds_limit(), "raise the dynamic LDS limit");
   char* base = nullptr;
   size_t used = 0;
   const auto take = [&](auto** p, size_t n) {
@@ -41,8 +40,9 @@ qgbe_status mlp_ensure(qgbe_ctx* c) {
     take(&m.X, (size_t)kBatch * kMlpIn);
     take(&m.yw, (size_t)kBatch * (kMixD + 1));
     take(&m.Y, (size_t)kBatch * kMlpOut);
-    take(&m.part, (size_t)kMlpMaxSlices * kMlpParams);
-    take(&m.loss_part, kMlpMaxSlices);
+    take(&m.act, (size_t)kMlpMaxTiles * kActRows * kMlpTileRows);
+    take(&m.dz, (size_t)kMlpMaxTiles * kDzRows * kMlpTileRows);
+    take(&m.loss_part, kMlpMaxTiles);
     take(&m.scalars, 2);
     if (pass == 0) {
       const qgbe_status s = dev_alloc(c, &m.arena, used, "proposal network");
@@ -64,15 +64,15 @@ MlpTileArgs tile_args(const qgbe_ctx* c, long long rows, const float* X, long lo
   g.yw = yw; g.ys = ys;
   g.idx = idx;
   g.pb = m.pb; g.pbt = m.pbt; g.P = m.params;
-  g.part = m.part; g.loss_part = m.loss_part;
+  g.act = m.act; g.dz = m.dz; g.loss_part = m.loss_part;
   return g;
 }
 
-MlpReduceArgs reduce_args(const qgbe_ctx* c, long long rows, double* loss) {
+MlpGradArgs grad_args(const qgbe_ctx* c, long long rows, double* loss) {
   const MlpState& m = c->mlp;
-  MlpReduceArgs r{};
-  r.part = m.part; r.loss_part = m.loss_part;
-  r.n_part = (int)mlp_grad_slices(rows);
+  MlpGradArgs r{};
+  r.act = m.act; r.dz = m.dz; r.loss_part = m.loss_part;
+  r.n_tiles = (int)((rows + kMlpTileRows - 1) / kMlpTileRows);
   r.loss = loss;
   r.grad = m.grad;
   r.p = m.params; r.m = m.m; r.v = m.v;
@@ -240,9 +240,9 @@ qgbe_status qgbe_mlp_loss_grad(qgbe_ctx* c, const float* X, const float* yw, int
   MlpTileArgs g = tile_args(c, rows, X, kMlpIn, yw, kMixD + 1, nullptr);
   g.wsum = m.scalars + 1;
   HIP_TRY(launch_mlp_grad(g, c->stream), "gradient");
-  MlpReduceArgs r = reduce_args(c, rows, m.scalars);
+  MlpGradArgs r = grad_args(c, rows, m.scalars);
   if (on_device) r.grad = grad;
-  HIP_TRY(launch_reduce_grad(r, c->stream), "gradient sum");
+  HIP_TRY(launch_weight_grad(r, c->stream), "gradient sum");
   if (!on_device)
     HIP_TRY(hipMemcpyAsync(grad, m.grad, kMlpParams * sizeof(float), hipMemcpyDeviceToHost, c->stream), "copy grad");
   HIP_TRY(hipMemcpyAsync(loss, m.scalars, sizeof(double), hipMemcpyDeviceToHost, c->stream), "copy loss");
@@ -436,13 +436,13 @@ qgbe_status qgbe_train_proposal(qgbe_ctx* c, const float* rows, int64_t n, const
       if (e != hipSuccess) break;
       const double frac = total_steps > 1 ? (double)step / (double)(total_steps - 1) : 1.0;
       m.adam_t += 1;
-      MlpReduceArgs r = reduce_args(c, nr, d_loss + ep);
+      MlpGradArgs r = grad_args(c, nr, d_loss + ep);
       r.adam = 1;
       r.lr = (float)(cfg->lr_final + 0.5 * (cfg->lr - cfg->lr_final) * (1.0 + std::cos(kPi * frac)));
       r.b1 = 0.9f; r.b2 = 0.999f; r.eps = 1e-8f;
       r.c1 = 1.f - powf(r.b1, (float)m.adam_t);
       r.c2 = 1.f - powf(r.b2, (float)m.adam_t);
-      e = launch_reduce_grad(r, c->stream);
+      e = launch_weight_grad(r, c->stream);
     }
   }
   if (e == hipSuccess && epoch_loss) {

@@ -99,6 +99,35 @@ def test_mlp_tiles(rows):
         assert _rel(g[name], gref[name]) <= 1e-2, (name, _rel(g[name], gref[name]))
 
 
+@pytest.mark.parametrize("rows", [512, 1024, 8192])
+def test_gradient_sums_by_chunks_of_rows(rows):
+    """The gradient's sums over the rows keep their brackets whatever the batch:
+    256 rows for the weights, 64 for the biases.  With unit weights the chunks of
+    a batch of 2^k rows are those rows' own gradients scaled by a power of two,
+    exact through every BF16 and FP32 rounding, and the chunks are added in 64
+    bits: equal bit for bit."""
+    _case(f"gradient chunks {rows} rows")
+    X, yw = _mlp_inputs(rows, 9)
+    yw[:, 5] = 1.0
+    with qgbe.Solver(**_kw(SMALL_7)) as s:
+        qgbe.qgbe_proposal_set_weights(s.ctx, W.random_mlp_params(7, head_scale=1.0))
+
+        def gradient(lo, n):
+            g = np.zeros(qgbe.MLP_PARAMS, dtype=np.float32)
+            qgbe.qgbe_mlp_loss_grad(s.ctx, np.ascontiguousarray(X[lo:lo + n]), np.ascontiguousarray(yw[lo:lo + n]), g)
+            return g
+
+        def chunks(n):
+            total = np.zeros(qgbe.MLP_PARAMS)
+            for lo in range(0, rows, n):
+                total += gradient(lo, n).astype(np.float64) * (n / rows)
+            return M.unflatten(total.astype(np.float32))
+
+        whole, by256, by64 = M.unflatten(gradient(0, rows)), chunks(256), chunks(64)
+    for name, _ in M.PARAM_SHAPES:
+        assert np.array_equal(whole[name], (by64 if name[0] == "b" else by256)[name]), name
+
+
 def test_features_match_oracle(O):
     _case("features")
     wl = SMALL_7

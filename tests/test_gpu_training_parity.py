@@ -16,6 +16,11 @@ the recorded training rows and the Adam update.
   schedule; bound 2e-2 of the learning rate per weight (an Adam step moves a
   weight by about the learning rate; a wrong bias correction moves it by
   several times that).
+* the losses of whole-batch epochs: oracle.mlp's forward, backward and Adam in
+  FP64 on BF16 operands from the same weights.  The GPU's FP32 rounding turns
+  an activation's BF16 rounding in about one of 2e4, which moves the mean over
+  4096 rows by some 1e-8 of the loss; bar 1e-5 per epoch (a row left out of the
+  batch moves it by about 1e-4).
 """
 import numpy as np
 import pytest
@@ -131,3 +136,26 @@ def test_adam_steps_match_oracle():
     assert err2.max() <= 2e-2 * lr0
     # the steps moved the weights by about the learning rate
     assert np.median(np.abs(w1_gpu - w0)) > 0.5 * lr0
+
+
+def test_epoch_losses_match_oracle():
+    _case("epoch losses")
+    rng = np.random.Generator(np.random.PCG64(61))
+    n, epochs, lr, lr_final = 4096, 5, 2e-3, 1e-4
+    rows = np.concatenate([rng.uniform(-1, 1, (n, M.N_IN)), rng.normal(0, 1.5, (n, M.D)),
+                           rng.uniform(0.1, 2.0, (n, 1))], 1).astype(np.float32)
+    w0 = W.random_mlp_params(62)
+    losses = np.zeros(epochs)
+    cfg = qgbe.TrainCfg(epochs=epochs, batch=n, lr=lr, lr_final=lr_final, alpha=0.1, seed=3)
+    with qgbe.Solver(**_kw(SMALL_7), precision=qgbe.FP32) as s:
+        s.set_f(W.random_f(52, SMALL_7.cells, SMALL_7.nodes))
+        qgbe.qgbe_proposal_set_weights(s.ctx, w0)
+        qgbe.qgbe_train_proposal(s.ctx, rows, cfg, losses)
+    p, state, ref = M.unflatten(w0.astype(np.float64)), {}, []
+    X, y, w = (rows[:, a:b].astype(np.float64) for a, b in ((0, 8), (8, 13), (13, 14)))
+    for t in range(epochs):
+        loss, g = M.loss_and_grad(p, X, y, w[:, 0], quantize=M.bf16)
+        ref.append(loss)
+        p = M.adam(p, g, state, lr=lr_final + 0.5 * (lr - lr_final) * (1.0 + np.cos(np.pi * t / (epochs - 1))))
+    print(f"[train] losses off by {np.abs(losses / ref - 1).max():.2e}", flush=True)
+    assert np.all(np.abs(losses - ref) <= 1e-5 * np.abs(ref))
