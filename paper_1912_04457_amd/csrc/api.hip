@@ -171,6 +171,7 @@ void plan_groups(qgbe_ctx* c) {
   const bool f32 = c->d.precision == QGBE_FP32;  // FP64 reads f from the FP64 field
   c->group_index.clear();
   c->groups.clear();
+  for (std::vector<int>& m : c->match) m.clear();
   for (int nslot = 1; nslot <= 3; ++nslot) {
     Group g{(int)c->group_index.size(), 0, nslot, {}, {}, {c->G.nodes, c->G.nodes, c->G.nodes}, {0, 0}};
     for (int l = 0; l < 3; ++l) {
@@ -203,24 +204,20 @@ void plan_groups(qgbe_ctx* c) {
   }
   for (int l = 0; l < 3; ++l) {
     Replay& r = c->replay[l];
-    r.start = (int)c->group_index.size();
+    r = {};
     for (const Group& g : c->groups)
-      if (several_launches(c, g, l))
-        for (int i = 0; i < g.count; ++i) {
-          const int gi = (int)c->group_index.size() - r.start, ci = c->group_index[g.start + i];
-          for (int p = 1; p < 4; ++p) r.match[c->chans[ci].sp[p]].push_back(4 * gi + p);
-          c->group_index.push_back(ci);
-        }
-    r.count = (int)c->group_index.size() - r.start;
+      if (several_launches(c, g, l)) {
+        if (!r.count) r.start = g.start;
+        r.count += g.count;
+      }
   }
-  for (Replay& r : c->replay) {
-    if (!r.count) continue;
-    r.match_at = (int)c->group_index.size();
-    for (int y = 0; y < kSpecies; ++y) {
-      c->group_index.insert(c->group_index.end(), r.match[y].begin(), r.match[y].end());
-      c->group_index.resize(r.match_at + (size_t)(y + 1) * kMaxMatches, 0);
-    }
-  }
+  // The lists that go to the device do not depend on the grid: calls without a
+  // context share them, and a captured one reads them at each replay.
+  for (int gi = 0; gi < c->nch; ++gi)
+    for (int p = 1; p < 4; ++p) c->match[c->chans[c->group_index[gi]].sp[p]].push_back(4 * gi + p);
+  c->group_index.resize(kMaxGroupIndex, 0);
+  for (int y = 0; y < kSpecies; ++y)
+    std::copy(c->match[y].begin(), c->match[y].end(), c->group_index.begin() + kMatchAt + (size_t)y * kMaxMatches);
 }
 
 struct Chunking {
@@ -389,7 +386,8 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
   if (per > c->n_cu) per = per / c->n_cu * c->n_cu;
   ReplayArgs r{};
   r.G = c->G;
-  r.match = c->d_groups + rp.match_at;
+  r.match = c->d_groups + kMatchAt;
+  r.first = rp.start;
   r.n_group = rp.count;
   r.n_chunks = a.n_chunks;
   r.A = a.A;
@@ -412,9 +410,9 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
     const int gi_hi = r.n_cells > 1 ? rp.count - 1 : (int)((wg + n - 1) % per_cell / a.n_chunks);
     long long total = 0;
     for (int y = 0; y < kSpecies; ++y) {
-      const std::vector<int>& m = rp.match[y];
-      r.m_lo[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * gi_lo) - m.begin());
-      r.m_hi[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * (gi_hi + 1)) - m.begin());
+      const std::vector<int>& m = c->match[y];
+      r.m_lo[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * (rp.start + gi_lo)) - m.begin());
+      r.m_hi[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * (rp.start + gi_hi + 1)) - m.begin());
       total += r.m_hi[y] - r.m_lo[y];
     }
     for (int y = 0; y < kSpecies; ++y) {

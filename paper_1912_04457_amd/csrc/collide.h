@@ -82,7 +82,8 @@ constexpr int kMaxMatches = 3 * kMaxChannels;
 struct ReplayArgs {
   Grid G;
   RecordArgs rec;
-  const int* match;       // [7][kMaxMatches]: 4 * (index in the channel list) + position (1..3), ascending
+  const int* match;       // [7][kMaxMatches]: 4 * (index in the list of all channels) + position (1..3), ascending
+  int first;              // index there of the sampling launch's first channel
   int n_group, n_chunks;  // as the sampling launch
   int n_wg;               // workgroups of the batch
   int cell_lo, n_cells;   // cells of the batch

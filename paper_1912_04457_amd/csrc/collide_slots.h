@@ -871,7 +871,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(ReplayArgs a) {
   for (int j = part; j < jobs; j += a.parts[sp]) {
     const int m = a.match[sp * kMaxMatches + a.m_lo[sp] + j / a.n_chunks];
     const int pos = (m & 3) - 1;  // 0, 1, 2: positions 2, 3, 4
-    const long long wg = ((long long)cell * a.n_group + (m >> 2)) * a.n_chunks + j % a.n_chunks - a.rec.wg_base;
+    const long long wg = ((long long)cell * a.n_group + (m >> 2) - a.first) * a.n_chunks + j % a.n_chunks - a.rec.wg_base;
     if (wg < 0 || wg >= a.n_wg) continue;
     const int cnt = (int)a.rec.count[wg];
     const long long i0 = wg * a.rec.region;

@@ -36,11 +36,10 @@ struct Group {
 
 // Channels whose deposit accumulators need more than one launch (slots or node
 // windows): their samples are drawn once and their deposits recorded, then
-// replayed per (species, window).
+// replayed per (species, window).  A channel of more slots never needs fewer
+// launches, so they are the last ones of the channels in order of their slots.
 struct Replay {
   int start = 0, count = 0;        // range in the group index array
-  std::vector<int> match[kSpecies];  // as ReplayArgs::match
-  int match_at = 0;                // the lists in the group index array, kMaxMatches apart
 };
 
 // Device buffers of the proposal network (one allocation, on first use).
@@ -66,7 +65,8 @@ struct qgbe_ctx {
   hipStream_t stream = nullptr;
   int nch = 0;
   std::vector<qgbe::Channel> chans;
-  std::vector<int> group_index;
+  std::vector<int> group_index;    // the channels in order of their slots, then match: of the masks alone
+  std::vector<int> match[qgbe::kSpecies];  // as ReplayArgs::match, over all channels
   std::vector<qgbe::Group> groups;
   qgbe::Replay replay[3];          // [uniform, learned, root samplers]
   unsigned char* d_rec = nullptr;  // record buffers, an allocation of their own (NULL: none, every launch draws its samples again)
@@ -125,9 +125,10 @@ size_t field_len(const qgbe_ctx* c);
 qgbe_status validate(const qgbe_grid_desc* d);
 void make_grid(const qgbe_grid_desc* d, Grid& G);
 void plan_groups(qgbe_ctx* c);
-// Entries of the group index array: the groups, the replay lists and their
-// matches.
-constexpr size_t kMaxGroupIndex = 4 * (size_t)kMaxChannels + 3 * (size_t)kSpecies * kMaxMatches;
+// Entries of the group index array: the groups, and from kMatchAt on the
+// species' matches, kMaxMatches apart.
+constexpr size_t kMatchAt = kMaxChannels;
+constexpr size_t kMaxGroupIndex = kMatchAt + (size_t)kSpecies * kMaxMatches;
 // Record buffers in given memory (none if they would be too small to pay).
 void carve_records(qgbe_ctx* c, unsigned char* p, size_t bytes);
 // Masses, and the start of a collision term into A: A and the totals zeroed,

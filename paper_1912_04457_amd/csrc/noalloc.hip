@@ -23,7 +23,7 @@ constexpr size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
 
 // The group lists lie beyond the declared bytes, of which they count 1 KB (as
 // the two plain channel lists would): the grids that fit do not depend on
-// what the launch plan lists.
+// their length.
 constexpr size_t kListBytes = align256(kMaxGroupIndex * sizeof(int));
 constexpr size_t kListCounted = 2 * align256(kMaxChannels * sizeof(int));
 

@@ -1,0 +1,62 @@
+// Prints the launch plans that the library makes, for tests on the host: one
+// line of numbers in (see main), one JSON object out.
+#include <cstdio>
+#include <iostream>
+#include <sstream>
+#include <string>
+
+#include "context.h"
+
+using namespace qgbe;
+
+static void print(const char* name, const std::vector<int>& v) {
+  std::printf("\"%s\": [", name);
+  for (size_t i = 0; i < v.size(); ++i) std::printf("%s%d", i ? ", " : "", v[i]);
+  std::printf("], ");
+}
+
+int main() {
+  std::string line;
+  while (std::getline(std::cin, line)) {
+    std::istringstream in(line);
+    qgbe_grid_desc d{};
+    size_t plain, learned, roots, replay, queue[2][2];
+    in >> d.species_mask >> d.n_x[0] >> d.n_x[1] >> d.n_x[2] >> d.n_p[0] >> d.n_p[1] >> d.n_p[2] >> d.precision >>
+        d.symmetric >> plain >> learned >> roots >> replay >> queue[0][0] >> queue[0][1] >> queue[1][0] >> queue[1][1];
+    if (!in) return 2;
+    d.row_mask = 0x7F;
+    d.alpha_s = 0.5;
+    for (int a = 0; a < 3; ++a) d.x_half[a] = d.p_half[a] = 1.0;
+    if (validate(&d) != QGBE_OK) return 3;
+    qgbe_ctx c;
+    c.d = d;
+    make_grid(&d, c.G);
+    c.chans.resize(kMaxChannels);
+    c.nch = build_channels(d.species_mask, d.row_mask, c.chans.data(), kMaxChannels);
+    c.chans.resize(c.nch);
+    c.lds.plain = plain;
+    c.lds.learned = learned;
+    c.lds.roots = roots;
+    c.lds.replay = replay;
+    for (int i = 0; i < 4; ++i) c.lds.queue[i / 2][i % 2] = queue[i / 2][i % 2];
+    plan_groups(&c);
+    std::printf("{\"nch\": %d, ", c.nch);
+    print("lists", c.group_index);
+    std::vector<int> sp, slots;
+    for (const Channel& ch : c.chans) {
+      slots.push_back(ch.nslot);
+      for (int p = 0; p < 4; ++p) sp.push_back(ch.sp[p]);
+    }
+    print("species", sp);
+    print("nslot", slots);
+    std::vector<int> start, count;
+    for (const Replay& r : c.replay) {
+      start.push_back(r.start);
+      count.push_back(r.count);
+    }
+    print("replay_start", start);
+    print("replay_count", count);
+    std::printf("\"quads\": %d}\n", (int)c.need_quads[0]);
+  }
+  return 0;
+}

@@ -1,0 +1,71 @@
+"""Host tests of the launch plans (no GPU): a probe linked against libqgbe.so
+prints the plans that the library makes for given descriptors and LDS budgets.
+"""
+import json
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1912_04457_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+LDS = 160 * 1024
+# dynamic LDS beside the kernels' own: plain, learned, roots, replay, the queues
+# [ring, tight][long, short items]
+BUDGETS = {0: (LDS - 6168, LDS - 30840, LDS - 61464, LDS, 0, LDS - 110616, 0, LDS - 49176),
+           1: (LDS - 6168, LDS - 12360, LDS - 61464, LDS, LDS - 80280, LDS - 86040, LDS - 31128, LDS - 36888)}
+
+
+@pytest.fixture(scope="session")
+def probe(tmp_path_factory):
+    if not os.path.exists(CLANG):
+        pytest.skip("no clang with the HIP headers here")
+    if not os.path.exists(build.LIB):
+        build.build()
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_probe")
+    subprocess.run([CLANG, "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I", os.path.join(build.ROOT, "include"), "-I", os.path.join(build.PKG, "csrc"),
+                    os.path.join(HERE, "plan_probe.cpp"), build.LIB, "-Wl,-rpath," + build.PKG,
+                    "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-o", exe], check=True)
+
+    def run(cases):
+        text = "\n".join(" ".join(str(int(v)) for v in c) for c in cases) + "\n"
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        return [json.loads(line) for line in out.splitlines()]
+    return run
+
+
+def _case(mask, n_x, n_p, precision, symmetric, *more):
+    return (mask, *n_x, *n_p, precision, symmetric, *BUDGETS[precision], *more)
+
+
+GRIDS = [(2, 2, 2), (5, 6, 7), (16, 16, 16), (20, 20, 20), (22, 22, 22), (24, 24, 23), (30, 30, 30), (64, 64, 64),
+         (128, 100, 90)]
+
+
+@pytest.mark.parametrize("mask", [0x40, 0x49, 0x7F])
+def test_device_lists_depend_on_the_masks_alone(probe, mask):
+    """The channel and match lists that calls without a context share on a GPU,
+    and that a captured call reads again at each replay, are the same for every
+    grid and precision; the channels that take several launches are the last of
+    their order; and every deposit of a channel has its match."""
+    cases = [_case(mask, (1, 1, 1), n_p, precision, sym) for n_p in GRIDS for precision in (0, 1) for sym in (0, 1)]
+    plans = probe(cases)
+    first = plans[0]
+    nch = first["nch"]
+    sp = np.array(first["species"]).reshape(nch, 4)
+    order = first["lists"][:nch]
+    assert sorted(order) == list(range(nch))
+    assert [first["nslot"][c] for c in order] == sorted(first["nslot"])
+    per = (len(first["lists"]) - 70) // 7
+    for y in range(7):
+        want = [4 * i + p for i, c in enumerate(order) for p in (1, 2, 3) if sp[c, p] == y]
+        assert first["lists"][70 + y * per: 70 + y * per + len(want)] == want
+    for plan in plans:
+        assert plan["lists"] == first["lists"]
+        for start, count in zip(plan["replay_start"], plan["replay_count"]):
+            assert count == 0 or start + count == nch
+    assert any(p["replay_count"][0] for p in plans) and any(not p["replay_count"][0] for p in plans)

@@ -87,6 +87,68 @@ def test_noalloc_without_room_for_quads(n_x, n_p):
     assert (np.abs(Ad.cpu().numpy() - A_ref) <= TOL[qgbe.FP32] * S).all()
 
 
+@pytest.mark.parametrize("n_x,n_p,mask,n,precision,sampler", [
+    ((1, 1, 1), (30, 30, 30), 1 << 6, 20, qgbe.FP32, qgbe.SAMPLER_UNIFORM),
+    ((1, 1, 1), (20, 20, 20), 0x7F, 80, qgbe.FP32, qgbe.SAMPLER_UNIFORM),
+    ((2, 1, 1), (28, 28, 28), 1 << 6, 20, qgbe.FP64, qgbe.SAMPLER_UNIFORM),
+    ((1, 1, 1), (28, 27, 28), 1 << 6, 20, qgbe.FP32, qgbe.SAMPLER_ROOTS),
+    ((1, 1, 1), (16, 17, 18), 0x49, 20, qgbe.FP64, qgbe.SAMPLER_ROOTS_ALT)],
+    ids=["gluons", "batches", "f64_cells", "roots_f32", "roots_alt_f64"])
+def test_noalloc_records_deposits(n_x, n_p, mask, n, precision, sampler):
+    """Grids whose accumulators take several launches: the deposits are recorded
+    in what the array leaves, in one batch or several, in the precision of the
+    sampler; against the context's term that draws in every launch."""
+    torch = pytest.importorskip("torch")
+    print(f"\n[gpu case] noalloc records n_x={n_x} n_p={n_p} mask={mask:#x} n={n} {precision} {sampler}", flush=True)
+    kw = dict(n_x=n_x, n_p=n_p, x_half=(3.0, 3.0, 3.0), p_half=(2.0, 2.5, 1.5), species_mask=mask)
+    f = _f(kw, 12) * 0.6
+    desc = qgbe.make_desc(**kw, precision=precision, seed=SEED, device=0)
+    fd = torch.from_numpy(f).cuda()
+    Ad = torch.full_like(fd, np.nan)
+    qgbe.qgbe_collision_term_noalloc(desc, fd, 5, n, sampler, Ad)
+    torch.cuda.synchronize()
+    A = Ad.cpu().numpy()
+    A_ref, S_ref = _context_term(kw, f, precision, 5, n, sampler)
+    tol = TOL[qgbe.FP64 if sampler != qgbe.SAMPLER_UNIFORM else precision]
+    assert (np.abs(A - A_ref) <= tol * S_ref + 1e-300).all()
+    assert np.abs(A_ref).max() > 0.0
+    assert np.all(np.abs(A.sum(axis=(0, 2))) <= 1e-12 * S_ref.sum(axis=(0, 2)))
+
+
+def test_noalloc_captured_beside_other_grids():
+    """A captured call whose grid records its deposits, replayed after calls on
+    other grids of the same species: what the calls share on the GPU depends on
+    the species and rows alone."""
+    torch = pytest.importorskip("torch")
+    print("\n[gpu case] noalloc capture", flush=True)
+    grid = dict(n_x=(1, 1, 1), n_p=(30, 30, 30), x_half=(3.0, 3.0, 3.0), p_half=(2.0, 2.5, 1.5), species_mask=1 << 6)
+    f, small = _f(grid, 13), _f(SMALL, 14)
+    fd, sd = torch.from_numpy(f).cuda(), torch.from_numpy(small).cuda()
+    Ad, Sd = torch.empty_like(fd), torch.empty_like(sd)
+    stream = torch.cuda.Stream()
+    desc = qgbe.make_desc(**grid, precision=qgbe.FP32, seed=SEED, device=0, stream=stream.cuda_stream)
+    other = {p: qgbe.make_desc(**SMALL, precision=p, seed=SEED, device=0, stream=stream.cuda_stream)
+             for p in (qgbe.FP32, qgbe.FP64)}
+    stream.wait_stream(torch.cuda.current_stream())
+    qgbe.qgbe_collision_term_noalloc(desc, fd, 6, 20, qgbe.SAMPLER_UNIFORM, Ad)
+    stream.synchronize()
+    eager = Ad.cpu().numpy()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        qgbe.qgbe_collision_term_noalloc(desc, fd, 6, 20, qgbe.SAMPLER_UNIFORM, Ad)
+    A_ref, S_ref = _context_term(grid, f, qgbe.FP32, 6, 20, qgbe.SAMPLER_UNIFORM)
+    assert (np.abs(eager - A_ref) <= TOL[qgbe.FP32] * S_ref + 1e-300).all()
+    for p in (qgbe.FP32, qgbe.FP64, qgbe.FP32):
+        qgbe.qgbe_collision_term_noalloc(other[p], sd, 7, 16, qgbe.SAMPLER_UNIFORM, Sd)
+        with torch.cuda.stream(stream):
+            Ad.fill_(float("nan"))
+            graph.replay()
+        stream.synchronize()
+        B_ref, T_ref = _context_term(SMALL, small, p, 7, 16, qgbe.SAMPLER_UNIFORM)
+        assert (np.abs(Ad.cpu().numpy() - A_ref) <= TOL[qgbe.FP32] * S_ref + 1e-300).all()
+        assert (np.abs(Sd.cpu().numpy() - B_ref) <= TOL[p] * T_ref + 1e-300).all()
+
+
 def test_noalloc_refuses_what_it_cannot_do():
     torch = pytest.importorskip("torch")
     assert qgbe.qgbe_noalloc_scratch_bytes() == 64 << 20
