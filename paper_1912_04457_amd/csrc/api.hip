@@ -157,42 +157,63 @@ void make_grid(const qgbe_grid_desc* d, Grid& G) {
   G.species_mask = d->species_mask;
 }
 
-// Whether a group's accumulators take more than one launch (slots or windows).
 bool several_launches(const qgbe_ctx* c, const Group& g, int l) {
   return c->d.symmetric && (g.lds_acc[l] < g.nslot || g.win[l] < c->G.nodes);
 }
 
-// LDS plan per sampler: FP64 accumulators first (they replace global
-// atomics), then FP32 f tiles in what is left; slots that do not fit use
-// global memory.
-void plan_groups(qgbe_ctx* c) {
+// LDS plan of a group for sampler l within a budget: FP64 accumulators first
+// (they replace global atomics), then FP32 f tiles in what is left; tiles that
+// do not fit are read from global memory.
+static void plan_lds(const qgbe_ctx* c, Group& g, int l, size_t budget, bool long_form) {
+  const size_t acc_b = (size_t)c->G.nodes * sizeof(double), tile_b = (size_t)c->G.nodes * sizeof(float);
+  g.budget[l] = budget;
+  g.long_form[l] = long_form;
+  g.win[l] = c->G.nodes;
+  if (c->d.symmetric && budget < acc_b) {
+    // one slot's FP64 accumulators exceed LDS: node windows, one launch
+    // per window holding every slot's accumulators for that window, the
+    // same samples in each; f from the quads
+    const int fit = (int)(budget / (sizeof(double) * g.nslot));
+    const int n_win = (c->G.nodes + fit - 1) / fit;
+    g.win[l] = (c->G.nodes + n_win - 1) / n_win;
+    g.lds_acc[l] = g.nslot;
+    g.lds_tiles[l] = 0;
+    return;
+  }
+  g.lds_acc[l] = c->d.symmetric ? (int)std::min<size_t>(g.nslot, budget / acc_b) : 0;
+  // FP64 reads f from the FP64 field
+  g.lds_tiles[l] = c->d.precision == QGBE_FP32 && l < 2
+                       ? (int)std::min<size_t>(g.nslot, (budget - g.lds_acc[l] * acc_b) / tile_b) : 0;
+}
+
+// The plans of every group.  The short-item form's tables take 6 KB that the
+// long form leaves to the accumulators: where they are what a single launch
+// lacks, the long form runs whatever the items (gluons, 27x27x28 nodes x 512 and
+// 2048 samples: 0.49 and 1.83 ms recorded, 0.26 and 0.84 in one launch; learned
+// sampler, 26x27x27: 0.86 and 3.67, 0.50 and 1.80).
+void plan_groups(qgbe_ctx* c, bool long_form) {
   const size_t acc_b = (size_t)c->G.nodes * sizeof(double);
-  const size_t tile_b = (size_t)c->G.nodes * sizeof(float);
-  const bool f32 = c->d.precision == QGBE_FP32;  // FP64 reads f from the FP64 field
+  const bool f32 = c->d.precision == QGBE_FP32;
   c->group_index.clear();
   c->groups.clear();
   for (std::vector<int>& m : c->match) m.clear();
+  c->need_quads[0] = c->need_quads[1] = false;
   for (int nslot = 1; nslot <= 3; ++nslot) {
-    Group g{(int)c->group_index.size(), 0, nslot, {}, {}, {c->G.nodes, c->G.nodes, c->G.nodes}, {0, 0}};
+    Group g{};
+    g.start = (int)c->group_index.size();
+    g.nslot = nslot;
     for (int l = 0; l < 3; ++l) {
-      const size_t budget = l == 0 ? c->lds.plain : l == 1 ? c->lds.learned : c->lds.roots;
-      if (c->d.symmetric && budget < acc_b) {
-        // one slot's FP64 accumulators exceed LDS: node windows, one launch
-        // per window holding every slot's accumulators for that window, the
-        // same samples in each; f from the quads
-        const int fit = (int)(budget / (sizeof(double) * nslot));
-        const int n_win = (c->G.nodes + fit - 1) / fit;
-        g.win[l] = (c->G.nodes + n_win - 1) / n_win;
-        g.lds_acc[l] = nslot;
-        g.lds_tiles[l] = 0;
-        continue;
-      }
-      g.lds_acc[l] = c->d.symmetric ? (int)std::min<size_t>(nslot, budget / acc_b) : 0;
-      g.lds_tiles[l] = f32 && l < 2 ? (int)std::min<size_t>(nslot, (budget - g.lds_acc[l] * acc_b) / tile_b) : 0;
+      const size_t* form = l == 0 ? c->lds.plain : c->lds.learned;
+      plan_lds(c, g, l, l == 2 ? c->lds.roots : form[1], false);
+      if (!f32 || l == 2) continue;
+      Group h = g;
+      plan_lds(c, h, l, form[0], true);
+      if ((l == 0 && long_form) || (several_launches(c, g, l) && !several_launches(c, h, l))) g = h;
     }
     for (int i = 0; i < 2; ++i)
-      if (c->d.symmetric && g.lds_acc[0] == nslot && g.win[0] == c->G.nodes)
-        g.queue[i] = nslot * acc_b <= c->lds.queue[0][i] ? kRing : nslot * acc_b <= c->lds.queue[1][i] ? kTight : 0;
+      if (c->d.symmetric && g.lds_acc[0] == nslot && g.win[0] == c->G.nodes && !(long_form && i))
+        g.queue[i] = nslot * acc_b <= c->lds.queue[0][i] ? kRing
+                     : nslot * acc_b <= c->lds.queue[1][i] && !long_form ? kTight : 0;
     for (int i = 0; i < c->nch; ++i)
       if (c->chans[i].nslot == nslot) c->group_index.push_back(i);
     g.count = (int)c->group_index.size() - g.start;
@@ -228,7 +249,7 @@ struct Chunking {
 
 // Observed nodes per workgroup; acc: entries a workgroup zeroes and flushes.
 Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long long acc, int n_samples, bool queue,
-                     bool learned) {
+                     bool learned, bool long_form) {
   const int waves = collide_waves(queue);
   if (pairs >= c->n_cu) {
     // Enough (cell, channel) pairs to give every compute unit one: the nodes
@@ -243,7 +264,7 @@ Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long l
     const long long per_pair = std::max(1LL, 2LL * c->n_cu / pairs);
     long long chunk = std::max<long long>(waves, (nodes + per_pair - 1) / per_pair);
     int nb = collide_node_block(queue);
-    if (collide_short(c->d.precision, learned, 1, n_samples))  // the largest block that leaves every wave 4 turns
+    if (!long_form && collide_short(c->d.precision, learned, 1, n_samples))  // the largest block that leaves every wave 4 turns
       for (nb = kMaxNodeBlock; nb > 1 && chunk < 4LL * waves * nb; nb /= 2) {}
     const int unit = chunk < 16LL * waves * nb ? waves * nb : waves;
     chunk = (chunk + unit - 1) / unit * unit;
@@ -269,8 +290,8 @@ Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long l
     const long long want = std::max(1LL, rounds * c->n_cu / pairs);
     const long long even = (nodes + want - 1) / want;
     for (int split = 1; split <= waves; ++split) {
-      if (waves % split) continue;
-      const bool is_short = collide_short(c->d.precision, learned, split, n_samples);
+      if (waves % split || (long_form && split > 1)) continue;
+      const bool is_short = !long_form && collide_short(c->d.precision, learned, split, n_samples);
       for (long long unit = is_short ? kMaxNodeBlock : collide_node_block(queue); unit >= 1; unit /= 2) {
         const long long group = unit * (waves / split);  // nodes the workgroup takes at a time
         for (const long long step : {is_short ? 1LL : unit, group}) {
@@ -371,7 +392,7 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
   const long long nodes = c->G.nodes, all_pairs = (long long)c->G.cells * rp.count;
   const long long fit = record_capacity(c, l) / (per_sample * a.n_samples);  // items a batch holds
   const Chunking ck = plan_chunks(c, std::min(nodes, fit), std::max(1LL, std::min(all_pairs, fit / nodes)), 0,
-                                  a.n_samples, l == 0, l != 0);
+                                  a.n_samples, l == 0, l != 0, false);
   a.group = c->d_groups + rp.start;
   a.n_group = rp.count;
   a.split = ck.split;
@@ -450,10 +471,12 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
     a.group = c->d_groups + g.start;
     a.n_group = g.count;
     // the compacting variant when the whole group fits in LDS next to its queues
-    const bool is_short = roots || collide_short(c->d.precision, learned, 1, n_samples);
+    const bool is_short = roots || (!g.long_form[l] && collide_short(c->d.precision, learned, 1, n_samples));
+    a.long_form = g.long_form[l];
     int queue = l == 0 ? g.queue[is_short] : 0;
     const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
-    const Chunking ck = plan_chunks(c, c->G.nodes, (long long)c->G.cells * g.count, acc, n_samples, queue, learned || roots);
+    const Chunking ck = plan_chunks(c, c->G.nodes, (long long)c->G.cells * g.count, acc, n_samples, queue, learned || roots,
+                                    g.long_form[l]);
     if (!is_short && ck.split > 1 && queue) queue = g.queue[1];  // waves that share nodes take the short form
     a.split = ck.split;
     a.node_block = ck.block;
@@ -480,7 +503,7 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
         a.lds_tiles = g.lds_tiles[l];
         if (n_pass > 1 && n_win == 1) {
           const size_t used = (size_t)(a.slot_hi - a.slot_lo) * acc_b;
-          a.lds_tiles = f64_path || roots ? 0 : (int)std::min<size_t>(g.nslot, ((l ? c->lds.learned : c->lds.plain) - used) / tile_b);
+          a.lds_tiles = f64_path || roots ? 0 : (int)std::min<size_t>(g.nslot, (g.budget[l] - used) / tile_b);
         }
         if (queue) a.lds_tiles = 0;  // the compacting variant reads f from the node quads
         const int q = n_pass == 1 && n_win == 1 ? queue : 0;

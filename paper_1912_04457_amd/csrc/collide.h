@@ -44,6 +44,7 @@ struct CollideArgs {
   int split;              // waves that share a node, each a part of its samples: divides
                           // the workgroup's waves; > 1 only with chunk_items <= kSplitNodes
   int node_block;         // consecutive nodes a wave takes at a time in the short-item form
+  int long_form;          // the long-item form whatever the items (FP32): its own LDS is smaller
   int lds_tiles;          // f tiles staged in LDS
   int lds_acc;            // FP64 deposit accumulators in LDS
   int slot_lo, slot_hi;   // deposit slots [lo, hi) written by this launch; the
@@ -95,7 +96,7 @@ struct ReplayArgs {
 
 // Dynamic LDS of one precision's kernel variants.
 struct LdsBudget {
-  size_t plain = 0, learned = 0;  // uniform sampler, learned sampler
+  size_t plain[2] = {}, learned[2] = {};  // uniform sampler, learned sampler: [long, short items]
   size_t queue[2][2] = {};        // the compacting variant: [kRing, kTight][long, short items]
   size_t replay = 0;              // replay_kernel
   size_t roots = 0;               // the root samplers

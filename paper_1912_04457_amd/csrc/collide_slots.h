@@ -145,9 +145,9 @@ constexpr int kNodeBlock = 4;
 // A.node_block consecutive nodes at a time, computes their constants side by
 // side, a node per lane, and keeps them and the nodes' sums in LDS, so that
 // the variances and outputs of the block are side by side too; and several
-// waves may share a node (A.split).  The learned sampler is always in this
-// form; a long uniform item is not: what it holds across its item loop costs
-// more spilled registers in the sample loop than it saves.  One gluon cell,
+// waves may share a node (A.split).  The learned sampler is in this form at any
+// length (unless A.long_form); a long uniform item is not: what it holds across
+// its item loop costs more spilled registers in the sample loop than it saves.  One gluon cell,
 // collision term: 10^3 nodes x 1000 samples 255 -> 46 us, 16^3 x 2048 547 ->
 // 190 us, 20^3 x 256 98 -> 78 us; 7 species, 30^3 x 128 20.9 -> 19.5 ms.
 // ---------------------------------------------------------------------------
@@ -306,7 +306,6 @@ template <typename R, bool kSym, bool kScale, bool kAllLds, bool kLearned, int k
           bool kRec = false, int kRoot = 0>
 __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(CollideArgs A) {
   constexpr bool kF64 = std::is_same<R, double>::value;
-  static_assert(!kLearned || kShort, "the learned sampler's items are short");
   static_assert(!kRoot || (kF64 && kShort && !kLearned && !kQueue), "the root samplers: FP64, short form");
   static_assert(!kQueue || (kSym && kAllLds && !kLearned), "the queue serves the uniform sampler, slots in LDS");
   static_assert(!kRec || (kSym && !kScale && kShort), "deposits are recorded in the short form");
@@ -903,7 +902,7 @@ inline bool short_items(int split, int n_samples) { return split > 1 || n_sample
 // One precision's kernel variants: the launch of one, and all of them with
 // their LDS budget group (0 uniform sampler, 1 learned sampler, 2 to 5 the
 // compacting variant: kRing and kTight, each for long and short items, 6 the
-// replay kernel).
+// replay kernel, 7 and 8 as 0 and 1, long items).
 template <typename R>
 struct SlotsVariants {
   // the reference precision keeps one form of an item
@@ -939,8 +938,13 @@ struct SlotsVariants {
   template <bool kSym, bool kScale>
   static void launch_sampler(const CollideArgs& a, bool all_lds, int queue, dim3 grid, dim3 block, size_t lds,
                              hipStream_t st) {
+    if constexpr (!kF64)
+      if (a.long_form && a.learned) {
+        launch_variant<kSym, kScale, true, false>(a, all_lds, 0, grid, block, lds, st);
+        return;
+      }
     if (a.learned) launch_variant<kSym, kScale, true, true>(a, all_lds, 0, grid, block, lds, st);
-    else if (kF64 || short_items(a.split, a.n_samples)) launch_variant<kSym, kScale, false, true>(a, all_lds, queue, grid, block, lds, st);
+    else if (kF64 || (!a.long_form && short_items(a.split, a.n_samples))) launch_variant<kSym, kScale, false, true>(a, all_lds, queue, grid, block, lds, st);
     else if constexpr (!kF64) launch_variant<kSym, kScale, false, false>(a, all_lds, queue, grid, block, lds, st);
   }
 
@@ -984,8 +988,10 @@ struct SlotsVariants {
     if constexpr (!kF64) {
       add_all<false, false, true>(fns, 0);
       add_all<false, true, true>(fns, 1);
-      add_all<true, false, false>(fns, 0);
-      add_all<false, false, false>(fns, 0);
+      add_all<true, false, false>(fns, 7);
+      add_all<false, false, false>(fns, 7);
+      add_all<true, true, false>(fns, 8);
+      add_all<false, true, false>(fns, 8);
       add_queue<kRing, false>(fns);
       add_queue<kTight, false>(fns);
     }
@@ -1011,7 +1017,9 @@ hipError_t launch_slots(const CollideArgs& a, int nslot, int queue, hipStream_t 
   if (a.split < 1 || (threads / kWave) % a.split) return hipErrorInvalidValue;  // whole groups of waves
   if (a.split > 1 && a.chunk_items > kSplitNodes) return hipErrorInvalidValue;  // a shared chunk's sums fit in it_sum
   if (a.node_block < 1 || a.node_block > kMaxNodeBlock) return hipErrorInvalidValue;  // a block fits in node_tab
-  if (a.chunk_items % kNodeBlock != 0 && queue && !kF64 && !a.learned && !short_items(a.split, a.n_samples))
+  if (a.long_form && (kF64 || a.split > 1)) return hipErrorInvalidValue;
+  if (a.chunk_items % kNodeBlock != 0 && queue && !kF64 && !a.learned &&
+      (a.long_form || !short_items(a.split, a.n_samples)))
     return hipErrorInvalidValue;  // the long form's chunks start on node blocks
   const dim3 grid((unsigned)blocks), block(threads);
   using V = SlotsVariants<R>;
@@ -1083,11 +1091,14 @@ inline hipError_t raise_lds_limit(const void* fn, size_t lds_max, size_t* budget
 
 template <typename R>
 hipError_t slots_lds_limit(size_t lds_max, LdsBudget* out) {
-  size_t budget[7] = {lds_max, lds_max, lds_max, lds_max, lds_max, lds_max, lds_max};
+  size_t budget[9];
+  for (size_t& b : budget) b = lds_max;
   for (const auto& f : SlotsVariants<R>::all())
     if (const hipError_t e = raise_lds_limit(f.fn, lds_max, &budget[f.group])) return e;
-  out->plain = budget[0];
-  out->learned = budget[1];
+  out->plain[0] = budget[7];  // FP64 has the short form only: not used
+  out->plain[1] = budget[0];
+  out->learned[0] = budget[8];
+  out->learned[1] = budget[1];
   for (int f = 0; f < 2; ++f) {
     out->queue[f][0] = std::is_same<R, double>::value ? 0 : budget[2 + 2 * f];  // FP64 has the short form only
     out->queue[f][1] = budget[3 + 2 * f];

@@ -29,6 +29,8 @@ struct Group {
   int nslot;          // distinct species at positions 2..4
   int lds_acc[3];     // FP64 accumulators staged in LDS  [uniform, learned, root samplers]
   int lds_tiles[3];   // FP32 f tiles staged in LDS; none in FP64 and for the root samplers
+  size_t budget[3];   // dynamic LDS of the launches
+  bool long_form[3];  // the long-item form whatever the items: its budget is larger
   int win[3];         // nodes per accumulator window (= nodes unless one slot's FP64
                       // accumulators exceed LDS; then one launch per window and slot)
   int queue[2];       // the form of the uniform sampler's compacting variant that fits [long, short items]; 0: none
@@ -121,10 +123,14 @@ namespace qgbe {
 size_t field_len(const qgbe_ctx* c);
 // Descriptor checks (QGBE_EINVAL with a message), the grid it describes, and
 // the LDS plan of the channel groups (needs c->G, c->d, c->chans and the
-// LDS budgets).
+// LDS budgets; long_form: the uniform sampler of FP32 in the long-item form and
+// without the smaller queue, the plan that needs the node quads least).
 qgbe_status validate(const qgbe_grid_desc* d);
 void make_grid(const qgbe_grid_desc* d, Grid& G);
-void plan_groups(qgbe_ctx* c);
+void plan_groups(qgbe_ctx* c, bool long_form = false);
+// Whether a group's accumulators take more than one launch (slots or windows)
+// with sampler l (0 uniform, 1 learned, 2 roots).
+bool several_launches(const qgbe_ctx* c, const Group& g, int l);
 // Entries of the group index array: the groups, and from kMatchAt on the
 // species' matches, kMaxMatches apart.
 constexpr size_t kMatchAt = kMaxChannels;

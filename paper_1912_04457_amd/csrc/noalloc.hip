@@ -139,6 +139,8 @@ qgbe_status qgbe_collision_term_noalloc(const qgbe_grid_desc* desc, const double
       for (Group& g : c.groups) g.queue[0] = g.queue[1] = 0;
       c.need_quads[0] = false;
     }
+    if (c.need_quads[0] && cv.used + align256(n * sizeof(float4)) > limit)
+      plan_groups(&c, true);  // the tiles that only the long-item form's LDS holds: refused if they need quads too
     if (c.need_quads[0]) c.d_f32q = cv.take<float4>(n);
   }
   if (cv.used > limit)

@@ -20,9 +20,11 @@ int main() {
   while (std::getline(std::cin, line)) {
     std::istringstream in(line);
     qgbe_grid_desc d{};
-    size_t plain, learned, roots, replay, queue[2][2];
+    size_t plain[2], learned[2], roots, replay, queue[2][2];
+    bool long_form;
     in >> d.species_mask >> d.n_x[0] >> d.n_x[1] >> d.n_x[2] >> d.n_p[0] >> d.n_p[1] >> d.n_p[2] >> d.precision >>
-        d.symmetric >> plain >> learned >> roots >> replay >> queue[0][0] >> queue[0][1] >> queue[1][0] >> queue[1][1];
+        d.symmetric >> long_form >> plain[0] >> plain[1] >> learned[0] >> learned[1] >> roots >> replay >> queue[0][0] >>
+        queue[0][1] >> queue[1][0] >> queue[1][1];
     if (!in) return 2;
     d.row_mask = 0x7F;
     d.alpha_s = 0.5;
@@ -34,12 +36,14 @@ int main() {
     c.chans.resize(kMaxChannels);
     c.nch = build_channels(d.species_mask, d.row_mask, c.chans.data(), kMaxChannels);
     c.chans.resize(c.nch);
-    c.lds.plain = plain;
-    c.lds.learned = learned;
+    for (int i = 0; i < 2; ++i) {
+      c.lds.plain[i] = plain[i];
+      c.lds.learned[i] = learned[i];
+    }
     c.lds.roots = roots;
     c.lds.replay = replay;
     for (int i = 0; i < 4; ++i) c.lds.queue[i / 2][i % 2] = queue[i / 2][i % 2];
-    plan_groups(&c);
+    plan_groups(&c, long_form);
     std::printf("{\"nch\": %d, ", c.nch);
     print("lists", c.group_index);
     std::vector<int> sp, slots;
@@ -56,7 +60,16 @@ int main() {
     }
     print("replay_start", start);
     print("replay_count", count);
-    std::printf("\"quads\": %d}\n", (int)c.need_quads[0]);
+    std::printf("\"groups\": [");
+    for (size_t i = 0; i < c.groups.size(); ++i) {
+      const Group& g = c.groups[i];
+      std::printf("%s{\"nslot\": %d, \"queue\": [%d, %d]", i ? ", " : "", g.nslot, g.queue[0], g.queue[1]);
+      for (int l = 0; l < 3; ++l)
+        std::printf(", \"%d\": {\"acc\": %d, \"tiles\": %d, \"win\": %d, \"long\": %d, \"several\": %d}", l,
+                    g.lds_acc[l], g.lds_tiles[l], g.win[l], (int)g.long_form[l], (int)several_launches(&c, g, l));
+      std::printf("}");
+    }
+    std::printf("], \"quads\": %d}\n", (int)c.need_quads[0]);
   }
   return 0;
 }

@@ -415,3 +415,34 @@ def test_recorded_deposits(O, n_x, n_p, mask, N, precision, learned):
         assert abs(A[:, cell].sum()) <= 1e-13 * S_ref[:, cell].sum()
     assert st.n_accepted == st2.n_accepted
     assert st.mc_err_est == pytest.approx(st2.mc_err_est, rel=1e-9)
+
+
+@pytest.mark.parametrize("n_x,n_p,mask,N,learned", [((1, 1, 1), (27, 27, 28), 1 << 6, 70, False),
+                                                    ((2, 1, 1), (20, 20, 25), 0x49, 3, False),
+                                                    ((1, 1, 1), (26, 27, 27), 1 << 6, 70, True),
+                                                    ((2, 1, 1), (21, 20, 23), 0x49, 3, True)],
+                         ids=["one_slot", "two_slots", "learned", "learned_two_slots"])
+def test_long_form_of_short_items_fp32(O, n_x, n_p, mask, N, learned):
+    """Grids whose accumulators fit in one launch beside the long-item form's own
+    LDS only: that form runs for short items too."""
+    _case(f"long form {n_x} {n_p} mask={mask:#x} N={N} learned={learned}")
+    wl = W.Workload("long", n_x, n_p, (3.0, 3.0, 3.0), (2.0, 2.5, 1.5), mask, N, "f32", 1, 0.01)
+    f = W.random_f(28, wl.cells, wl.nodes, species_mask=mask)
+    g = O.Grid(n_x=n_x, n_p=n_p, x_half=wl.x_half, p_half=wl.p_half, species_mask=mask, alpha_s=wl.alpha_s)
+    with qgbe.Solver(**_grid_kw(wl), precision=qgbe.FP32, seed=SEED) as s:
+        s.set_f(f)
+        qgbe.qgbe_set_step_index(s.ctx, 4)
+        if learned:
+            table = W.random_mog_table(5, s.n_channels * wl.nodes)
+            qgbe.qgbe_set_proposal_table(s.ctx, *table)
+        sampler = qgbe.SAMPLER_LEARNED if learned else qgbe.SAMPLER_UNIFORM
+        A, _, I, _ = s.collision(N, sampler=sampler, items=True)
+        A2, _, I2, _ = s.collision(N, sampler=sampler, scale=True, items=True)
+        m = s.masses()
+    if learned:
+        A_ref, S_ref, I_ref = O.collision_learned(g, f, m, SEED, 4, N, *table, want_items=True)
+    else:
+        A_ref, S_ref, I_ref = O.collision(g, f, m, SEED, 4, N, want_items=True)
+    for a, i in ((A, I), (A2, I2)):
+        _compare(a, A_ref, S_ref, TOL[qgbe.FP32], "A")
+        assert np.allclose(i, I_ref, rtol=TOL[qgbe.FP32], atol=TOL[qgbe.FP32] * np.abs(I_ref).max())

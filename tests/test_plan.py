@@ -13,10 +13,11 @@ from paper_1912_04457_amd import build
 HERE = os.path.dirname(os.path.abspath(__file__))
 CLANG = "/opt/rocm/llvm/bin/clang++"
 LDS = 160 * 1024
-# dynamic LDS beside the kernels' own: plain, learned, roots, replay, the queues
-# [ring, tight][long, short items]
-BUDGETS = {0: (LDS - 6168, LDS - 30840, LDS - 61464, LDS, 0, LDS - 110616, 0, LDS - 49176),
-           1: (LDS - 6168, LDS - 12360, LDS - 61464, LDS, LDS - 80280, LDS - 86040, LDS - 31128, LDS - 36888)}
+# dynamic LDS beside the kernels' own: plain and learned [long, short items],
+# roots, replay, the queues [ring, tight][long, short items]
+BUDGETS = {0: (LDS, LDS - 6168, LDS, LDS - 30840, LDS - 61464, LDS, 0, LDS - 110616, 0, LDS - 49176),
+           1: (LDS - 24, LDS - 6168, LDS - 6216, LDS - 12360, LDS - 61464, LDS, LDS - 80280, LDS - 86040, LDS - 31128,
+               LDS - 36888)}
 
 
 @pytest.fixture(scope="session")
@@ -38,8 +39,8 @@ def probe(tmp_path_factory):
     return run
 
 
-def _case(mask, n_x, n_p, precision, symmetric, *more):
-    return (mask, *n_x, *n_p, precision, symmetric, *BUDGETS[precision], *more)
+def _case(mask, n_x, n_p, precision, symmetric, long_form=0):
+    return (mask, *n_x, *n_p, precision, symmetric, long_form, *BUDGETS[precision])
 
 
 GRIDS = [(2, 2, 2), (5, 6, 7), (16, 16, 16), (20, 20, 20), (22, 22, 22), (24, 24, 23), (30, 30, 30), (64, 64, 64),
@@ -69,3 +70,56 @@ def test_device_lists_depend_on_the_masks_alone(probe, mask):
         for start, count in zip(plan["replay_start"], plan["replay_count"]):
             assert count == 0 or start + count == nch
     assert any(p["replay_count"][0] for p in plans) and any(not p["replay_count"][0] for p in plans)
+
+
+def _boundary_grids():
+    """Grids around every node count at which one, two or three accumulators or
+    tiles, alone or together, stop fitting in a budget."""
+    rng = np.random.default_rng(3)
+    want = sorted({b // (8 * a + 4 * t) for b in BUDGETS[1] for a in range(4) for t in range(4) if a + t})
+    grids = set()
+    for n in want:
+        for _ in range(8):
+            x = int(np.clip(round(n ** (1 / 3) * np.exp(rng.normal(0, 0.2))), 2, n))
+            y = int(np.clip(round((n / x) ** 0.5 * np.exp(rng.normal(0, 0.2))), 2, n))
+            z = max(2, n // (x * y) + int(rng.integers(-1, 3)))
+            grids.add((x, y, z))
+    return sorted(grids)
+
+
+@pytest.mark.parametrize("symmetric", [0, 1])
+@pytest.mark.parametrize("mask", [0x40, 0x49, 0x7F])
+def test_long_form_where_the_short_one_lacks_lds(probe, mask, symmetric):
+    """FP32, uniform and learned sampler: a group takes several launches only
+    where the accumulators do not fit beside the long form's own LDS either, its
+    plan fits in the LDS of the form it runs in, and the plan that the call
+    without allocation falls back to needs node quads exactly where a tile does
+    not fit beside the long form or its ring of samples fits."""
+    grids = _boundary_grids()
+    plans = probe([_case(mask, (1, 1, 1), n_p, 1, symmetric) for n_p in grids])
+    long_plans = probe([_case(mask, (1, 1, 1), n_p, 1, symmetric, 1) for n_p in grids])
+    b = BUDGETS[1]
+    seen = {"long": 0, "several": 0}
+    for n_p, plan, long_plan in zip(grids, plans, long_plans):
+        nodes = int(np.prod(n_p))
+        quads = False
+        for g, h in zip(plan["groups"], long_plan["groups"]):
+            k = g["nslot"]
+            for l in (0, 1):
+                p, (long_b, short_b) = g[str(l)], b[2 * l:2 * l + 2]
+                assert p["several"] == (symmetric and 8 * nodes * k > long_b), (n_p, k, l)
+                assert p["long"] == (symmetric and not p["several"] and 8 * nodes * k > short_b)
+                if p["win"] == nodes:
+                    used = nodes * (8 * p["acc"] + 4 * p["tiles"])
+                else:
+                    used = 8 * p["win"] * p["acc"]
+                    assert p["acc"] == k and p["tiles"] == 0
+                assert used <= (long_b if p["long"] else short_b)
+                seen["long"] += p["long"]
+                seen["several"] += p["several"]
+            tiles = b[0] >= nodes * k * (12 if symmetric else 4)
+            ring = symmetric and 8 * nodes * k <= b[6]
+            quads = quads or not tiles or ring
+            assert h["0"]["long"] and h["queue"] == [int(ring), 0]
+        assert long_plan["quads"] == quads, n_p
+    assert not symmetric or min(seen.values()) > 0

@@ -87,6 +87,26 @@ def test_noalloc_without_room_for_quads(n_x, n_p):
     assert (np.abs(Ad.cpu().numpy() - A_ref) <= TOL[qgbe.FP32] * S).all()
 
 
+@pytest.mark.parametrize("n_x,n_p,mask,symmetric", [((60, 1, 1), (24, 24, 23), 1 << 6, 1), ((179, 1, 1), (24, 24, 23), 1 << 6, 1),
+                                                    ((50, 1, 1), (34, 34, 35), 1 << 6, 0)],
+                         ids=["one_slot", "largest", "direct"])
+def test_noalloc_tiles_beside_the_long_form(n_x, n_p, mask, symmetric):
+    """Grids whose f tiles fit in LDS beside the long-item form's own only, and
+    whose node quads do not fit in the scratch: that form runs."""
+    torch = pytest.importorskip("torch")
+    print(f"\n[gpu case] noalloc long form n_x={n_x} n_p={n_p} mask={mask:#x} symmetric={symmetric}", flush=True)
+    kw = dict(n_x=n_x, n_p=n_p, x_half=(3.0, 3.0, 3.0), p_half=(2.0, 2.0, 2.0), species_mask=mask, symmetric=symmetric)
+    f = _f(kw, 15)
+    desc = qgbe.make_desc(**kw, precision=qgbe.FP32, seed=SEED, device=0)
+    fd = torch.from_numpy(f).cuda()
+    Ad = torch.full_like(fd, np.nan)
+    qgbe.qgbe_collision_term_noalloc(desc, fd, 2, 3, qgbe.SAMPLER_UNIFORM, Ad)
+    torch.cuda.synchronize()
+    A_ref, S_ref = _context_term(kw, f, qgbe.FP32, 2, 3, qgbe.SAMPLER_UNIFORM)
+    assert np.isfinite(A_ref).all() and np.abs(A_ref).max() > 0.0
+    assert (np.abs(Ad.cpu().numpy() - A_ref) <= TOL[qgbe.FP32] * S_ref + 1e-300).all()
+
+
 @pytest.mark.parametrize("n_x,n_p,mask,n,precision,sampler", [
     ((1, 1, 1), (30, 30, 30), 1 << 6, 20, qgbe.FP32, qgbe.SAMPLER_UNIFORM),
     ((1, 1, 1), (20, 20, 20), 0x7F, 80, qgbe.FP32, qgbe.SAMPLER_UNIFORM),
