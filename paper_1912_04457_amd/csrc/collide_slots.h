@@ -719,7 +719,8 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         R yl[5];
         if constexpr (kF64) {
           mix_draw_row_f64(xw, A.mix_thr + mrow * A.mix_K, mix_rows[wid], A.mix_K, u, yl);
-          inv_q = rcp64(mix_density_f64(mix_rows[wid], A.mix_K, yl));  // finite: q >= alpha > 0
+          const double q = mix_density_f64(mix_rows[wid], A.mix_K, yl);
+          inv_q = q > 1e300 ? 0.0 : rcp64(q);  // q >= alpha > 0; rcp64 is for finite arguments
         } else {
           mix_draw_row(xw, A.mix_thr + mrow * A.mix_K, mix_rows[wid], A.mix_K, u, yl);
           inv_q = __builtin_amdgcn_rcpf(mix_density_f32(mix_rows[wid], A.mix_K, yl));  // about 1 ulp; q >= alpha

@@ -429,3 +429,26 @@ def test_learned_sixteen_components(O):
             assert e.value.status == qgbe.EUNSUPPORTED
         A, _, _, _ = s.collision(100, sampler=qgbe.SAMPLER_UNIFORM)   # the context still works
         assert np.isfinite(A).all()
+
+
+@pytest.mark.parametrize("precision,tol", [(qgbe.FP64, 1e-10), (qgbe.FP32, 1e-4)])
+def test_learned_infinite_density(O, precision, tol):
+    """A component so far out that the density at its samples exceeds the type:
+    they carry the weight 0, beside the uniform half of the samples."""
+    _case(f"learned infinite density precision={precision}")
+    wl = SMALL_7
+    f = W.random_f(41, wl.cells, wl.nodes)
+    g = O.Grid(n_x=wl.n_x, n_p=wl.n_p, x_half=wl.x_half, p_half=wl.p_half, species_mask=wl.species_mask)
+    rows = len(O.channels(g)) * wl.nodes
+    thr = np.full((rows, 1), 1 << 31, dtype=np.uint32)
+    mu = np.tile(np.array([250.0, -250.0, 250.0, 0.0, 0.0], dtype=np.float32), (rows, 1, 1))
+    sg = np.ones((rows, 1, 5), dtype=np.float32)
+    with qgbe.Solver(**_kw(wl), precision=precision) as s:
+        s.set_f(f)
+        qgbe.qgbe_set_step_index(s.ctx, 3)
+        qgbe.qgbe_set_proposal_table(s.ctx, thr, mu, sg)
+        A, _, _, _ = s.collision(200, sampler=qgbe.SAMPLER_LEARNED)
+    A_ref, S_ref, _ = O.collision_learned(g, f, O.masses(g, f), SEED, 3, 200, thr, mu, sg)
+    assert np.isfinite(A_ref).all() and np.abs(A_ref).max() > 0
+    assert np.isfinite(A).all()
+    assert np.all(np.abs(A - A_ref) <= tol * S_ref + 1e-300)
