@@ -337,51 +337,86 @@ void carve_records(qgbe_ctx* c, unsigned char* p, size_t bytes) {
   c->rec_bytes = bytes - counts;
 }
 
-void alloc_records(qgbe_ctx* c) {
+// Bytes of a context's record tiles.
+size_t record_buffer_bytes(const qgbe_ctx* c) {
   const long long items = (long long)c->G.cells * c->G.nodes *
                           std::max({c->replay[0].count, c->replay[1].count, c->replay[2].count});
-  const size_t tiles = (size_t)(std::max(kRecMin, std::min(kRecMax, items * 144)) + 63) / 64;
-  const size_t bytes = tiles * record_tile(c, false) + ((size_t)sizeof(uint32_t) << 16);
+  return (size_t)(std::max(kRecMin, std::min(kRecMax, items * 144)) + 63) / 64 * record_tile(c, false);
+}
+
+void alloc_records(qgbe_ctx* c) {
+  const size_t bytes = record_buffer_bytes(c) + ((size_t)sizeof(uint32_t) << 16);
   unsigned char* p = nullptr;
   if (dev_alloc(c, &p, bytes, "records")) (void)hipGetLastError();
   else carve_records(c, p, bytes);
 }
 
-// Records the buffers hold for a sampler (the root samplers' are FP64).
-long long record_capacity(const qgbe_ctx* c, int l) {
-  return 64 * (long long)(c->rec_bytes / record_tile(c, l == 2));
+// Samples whose deposits buffers of these bytes hold for a sampler (the root
+// samplers' records are FP64, up to two to a sample).
+long long record_capacity(const qgbe_ctx* c, int l, size_t bytes) {
+  return 64 * (long long)(bytes / record_tile(c, l == 2)) / (l == 2 ? 2 : 1);
 }
 
-// Whether the channels of more than one launch record their deposits in this call.
-// (The buffers are there from the start where the CM-angle samplers need them;
-// for the root samplers alone they are made by the first call that uses them,
-// unless its stream is being captured.)
-bool records(qgbe_ctx* c, int l, int n_samples, const double* scale) {
-  if (!c->replay[l].count || scale) return false;
-  if (!c->d_rec && l == 2 && c->d_arena) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) alloc_records(c);
-  }
-  const long long capacity = record_capacity(c, l) / (l == 2 ? 2 : 1);
-  if (!c->d_rec || n_samples > capacity) return false;
-  // Microseconds: 26 per million samples drawn (whole iterations of 64, and
-  // half a one for the item), 14 per million replayed, 45 per launch that
-  // draws and flushes, 40 per batch.  With the buffers of a context recording
-  // wins from two launches on (gluons at 30^3: 71 against 121 us with one
-  // sample, 156 against 216 with 128, 2.32 against 2.55 ms with 2048); in the few
-  // MB of the call without allocation, 1000 samples there take 25 batches and
-  // 2.1 ms instead of 1.3.
-  const double per_sample = 1e-6 * (double)c->G.cells * c->G.nodes;
-  const double drawn = per_sample * (64.0 * ((n_samples + 63) / 64) + 32.0);
+int replay_windows(const qgbe_ctx* c) {
+  const long long lds_nodes = (long long)(c->lds.replay / sizeof(double));
+  return (int)((c->G.nodes + lds_nodes - 1) / lds_nodes);
+}
+
+// How the channels whose accumulators take more than one launch deposit in this
+// call, estimated in microseconds per million samples: 26 to draw them (whole
+// iterations of 64, and half a one for the item; 60 with the learned sampler in
+// FP64), in every launch that draws them again, and 45 for such a launch; 14 to
+// record and replay them in up to two windows and 13 for each window more, and
+// 40 for a batch; global FP64 atomics 520 (20 G/s; 340 with the root samplers, which
+// accept fewer).  Drawing again ends early: gluons at 30^3, 128 samples, 216 us
+// and 156 recorded; only in the few MB of the call without allocation it wins
+// there (1000 samples: 25 batches and 2.1 ms instead of 1.3).  Records end where
+// the windows are many, global atomics (FP64) take over: one cell of gluons, 64
+// samples, drawn again / recorded / global atomics, in ms:
+//           48^3               64^3              80^3               96^3               128^3
+//   uniform 1.58 / 0.79 / 4.2  8.6 / 2.8 / 9.4   31 / 6.3 / 18.4    131 / 30.9 / 31.9  1206 / 138 / 75
+//   roots   2.5 / 0.76 / 2.8   12.9 / 2.5 / 6.3  49.7 / 5.5 / 12.4  163 / 29.7 / 21.3  1187 / 174 / 51
+//   learned 4.9 / 1.2 / 4.0    25.5 / 3.9 / 9.1  104 / 8.2 / 17.8   336 / 33.5 / 30.7
+// (512 samples at 96^3, uniform: 1037 / 398 / 255).  FP32 has no global form: its
+// grids took the windows before, too (96^3: 98.5 / 28.0).
+DepositRoute deposit_route(const qgbe_ctx* c, int l, int n_samples, bool scale, long long capacity) {
+  if (!c->replay[l].count) return DepositRoute::kAgain;
+  const double per_sample = 1e-6 * (double)c->G.cells * c->G.nodes, n = c->replay[l].count;
+  const bool f64 = l == 2 || c->d.precision == QGBE_FP64;
+  const double drawn = (l == 1 && f64 ? 60.0 : 26.0) * per_sample * (64.0 * ((n_samples + 63) / 64) + 32.0);
+  const double samples = per_sample * n_samples * n;
   double again = 0.0;
   for (const Group& g : c->groups)
     if (several_launches(c, g, l)) {
       const int passes = (g.nslot + g.lds_acc[l] - 1) / g.lds_acc[l];
       const int windows = (c->G.nodes + g.win[l] - 1) / g.win[l];
-      again += passes * windows * (26.0 * drawn * g.count + 45.0);
+      again += passes * windows * (drawn * g.count + 45.0);
     }
-  const double n = c->replay[l].count, replayed = per_sample * n_samples * n;
-  return 26.0 * drawn * n + 14.0 * replayed + 40.0 * std::ceil(1e6 * replayed / (double)capacity) < again;
+  DepositRoute best = DepositRoute::kAgain;
+  double least = again;
+  const auto offer = [&](DepositRoute r, double t) {
+    if (t < least) {
+      best = r;
+      least = t;
+    }
+  };
+  if (!scale && n_samples <= capacity)
+    offer(DepositRoute::kRecord, drawn * n + (14.0 + 13.0 * std::max(0, replay_windows(c) - 2)) * samples +
+                                     40.0 * std::ceil(1e6 * samples / (double)capacity));
+  if (f64) offer(DepositRoute::kGlobal, drawn * n + (l == 2 ? 340.0 : 520.0) * samples + 45.0);
+  return best;
+}
+
+// The route of this call.  (The record buffers are there from the start where the
+// CM-angle samplers need them; for the root samplers alone they are made by the
+// first call that uses them, unless its stream is being captured.)
+DepositRoute choose_route(qgbe_ctx* c, int l, int n_samples, const double* scale) {
+  if (!c->d_rec && l == 2 && c->d_arena && !scale &&
+      deposit_route(c, l, n_samples, false, record_capacity(c, l, record_buffer_bytes(c))) == DepositRoute::kRecord) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) alloc_records(c);
+  }
+  return deposit_route(c, l, n_samples, scale != nullptr, c->d_rec ? record_capacity(c, l, c->rec_bytes) : 0);
 }
 
 // Their samples and deposits, in batches that fit the record buffers.
@@ -390,7 +425,7 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
   const bool roots = l == 2, f64 = roots || c->d.precision == QGBE_FP64;
   const int per_sample = roots ? 2 : 1;
   const long long nodes = c->G.nodes, all_pairs = (long long)c->G.cells * rp.count;
-  const long long fit = record_capacity(c, l) / (per_sample * a.n_samples);  // items a batch holds
+  const long long fit = record_capacity(c, l, c->rec_bytes) / a.n_samples;  // items a batch holds
   const Chunking ck = plan_chunks(c, std::min(nodes, fit), std::max(1LL, std::min(all_pairs, fit / nodes)), 0,
                                   a.n_samples, l == 0, l != 0, false);
   a.group = c->d_groups + rp.start;
@@ -400,7 +435,7 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
   a.chunk_items = (int)std::min<long long>(ck.chunk, fit);
   a.n_chunks = (int)((nodes + a.chunk_items - 1) / a.chunk_items);
   a.rec = c->rec;
-  a.rec.capacity = record_capacity(c, l);
+  a.rec.capacity = per_sample * record_capacity(c, l, c->rec_bytes);
   a.rec.region = (long long)a.chunk_items * a.n_samples * per_sample;
   const long long wgs = all_pairs * a.n_chunks;
   long long per = std::min(c->rec_wgs, a.rec.capacity / a.rec.region);
@@ -412,8 +447,7 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
   r.n_group = rp.count;
   r.n_chunks = a.n_chunks;
   r.A = a.A;
-  const long long lds_nodes = (long long)(c->lds.replay / sizeof(double));
-  r.n_win = (int)((nodes + lds_nodes - 1) / lds_nodes);
+  r.n_win = replay_windows(c);
   r.win_n = (int)((nodes + r.n_win - 1) / r.n_win);
   // workgroups of a replay launch: two to a compute unit where their windows fit
   const double target = (double)c->n_cu * (2 * (size_t)r.win_n * sizeof(double) <= c->lds.replay ? 2 : 1);
@@ -460,21 +494,24 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
   const bool roots = sampler == QGBE_SAMPLER_ROOTS || sampler == QGBE_SAMPLER_ROOTS_ALT;
   const bool f64_path = c->d.precision == QGBE_FP64;
   const int l = roots ? 2 : learned ? 1 : 0;
-  const bool recorded = records(c, l, n_samples, scale);
+  const DepositRoute route = choose_route(c, l, n_samples, scale);
   a.f32q = c->d_f32q;
-  if (recorded) {
+  if (route == DepositRoute::kRecord) {
     const qgbe_status s = run_replay(c, a, l, sampler == QGBE_SAMPLER_ROOTS_ALT);
     if (s) return s;
   }
   for (const Group& g : c->groups) {
-    if (recorded && several_launches(c, g, l)) continue;
+    const bool several = several_launches(c, g, l);
+    if (several && route == DepositRoute::kRecord) continue;
+    const bool global = several && route == DepositRoute::kGlobal;  // one launch without accumulators
+    const int per = global ? 0 : g.lds_acc[l], win = global ? c->G.nodes : g.win[l];
     a.group = c->d_groups + g.start;
     a.n_group = g.count;
     // the compacting variant when the whole group fits in LDS next to its queues
     const bool is_short = roots || (!g.long_form[l] && collide_short(c->d.precision, learned, 1, n_samples));
     a.long_form = g.long_form[l];
     int queue = l == 0 ? g.queue[is_short] : 0;
-    const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, std::max(g.lds_acc[l], 0)) * g.win[l] : 0;
+    const long long acc = c->d.symmetric ? (long long)std::min(g.nslot, per) * win : 0;
     const Chunking ck = plan_chunks(c, c->G.nodes, (long long)c->G.cells * g.count, acc, n_samples, queue, learned || roots,
                                     g.long_form[l]);
     if (!is_short && ck.split > 1 && queue) queue = g.queue[1];  // waves that share nodes take the short form
@@ -485,13 +522,11 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
     a.n_chunks = (c->G.nodes + chunk - 1) / chunk;
     // Deposit slots whose FP64 accumulators do not all fit in LDS are split
     // over launches that each keep their slots' accumulators in LDS: the
-    // samples are recomputed (same draws), which costs far less than global
-    // FP64 atomics on every deposit.  The first launch also writes the direct
-    // sums.  Without room for even one accumulator, global atomics remain.
-    const int per = g.lds_acc[l];
+    // samples are recomputed (same draws).  The first launch also writes the
+    // direct sums.
     const int n_pass = (c->d.symmetric && per >= 1 && per < g.nslot) ? (g.nslot + per - 1) / per : 1;
     const size_t acc_b = (size_t)c->G.nodes * sizeof(double), tile_b = (size_t)c->G.nodes * sizeof(float);
-    const int win = g.win[l], n_win = (c->G.nodes + win - 1) / win;
+    const int n_win = (c->G.nodes + win - 1) / win;
     for (int pass = 0; pass < n_pass; ++pass) {
       for (int w = 0; w < n_win; ++w) {
         a.slot_lo = n_pass > 1 ? pass * per : 0;
@@ -499,7 +534,7 @@ qgbe_status run_collide(qgbe_ctx* c, int n_samples, int sampler, double* A, doub
         a.win_lo = w * win;
         a.win_n = std::min(win, c->G.nodes - a.win_lo);
         a.direct = pass == 0 && w == 0 ? 1 : 0;
-        a.lds_acc = g.lds_acc[l];
+        a.lds_acc = per;
         a.lds_tiles = g.lds_tiles[l];
         if (n_pass > 1 && n_win == 1) {
           const size_t used = (size_t)(a.slot_hi - a.slot_lo) * acc_b;

@@ -46,9 +46,8 @@ struct CollideArgs {
   int node_block;         // consecutive nodes a wave takes at a time in the short-item form
   int long_form;          // the long-item form whatever the items (FP32): its own LDS is smaller
   int lds_tiles;          // f tiles staged in LDS
-  int lds_acc;            // FP64 deposit accumulators in LDS
-  int slot_lo, slot_hi;   // deposit slots [lo, hi) written by this launch; the
-                          // first lds_acc of them accumulate in LDS, the rest in global memory
+  int lds_acc;            // FP64 deposit accumulators in LDS (0: global atomics, FP64 only)
+  int slot_lo, slot_hi;   // deposit slots [lo, hi) written by this launch, at most lds_acc
   int win_lo, win_n;      // LDS accumulators cover nodes [win_lo, win_lo + win_n);
                           // deposit corners outside belong to another launch
   int direct;             // this launch also writes the direct sums, items, scale and counts

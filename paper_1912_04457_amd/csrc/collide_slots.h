@@ -1,4 +1,5 @@
-// The collision kernel of the CM-angle samplers, in both precisions.
+// The collision kernel: the CM-angle samplers in both precisions and the root
+// samplers, and the replay of recorded deposits.
 #pragma once
 
 #include <algorithm>
@@ -12,10 +13,11 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // A workgroup owns (cell, channel, a chunk of observed nodes).  LDS holds FP64
-// accumulators for the first `lds_acc` deposit slots of the channel and, in
-// FP32, f tiles for the first `lds_tiles` slots; slots beyond those deposit
-// with FP64 atomics into the output / read f from global memory.  The
-// accumulators are flushed into the FP64 output once per workgroup.
+// accumulators for the deposit slots of the launch (all of the channel's, or a
+// part of them, or a window of their nodes) and, in FP32, f tiles for the first
+// `lds_tiles` slots; the others are read from global memory.  The accumulators
+// are flushed into the FP64 output once per workgroup.  On the largest grids the
+// FP64 kernels deposit with global atomics instead (see deposit_route).
 //
 // R = double is the reference precision: the integrand in FP64 and f from the
 // FP64 field in global memory.  It is bound as FP32 is, by VALU issue and the
@@ -76,13 +78,13 @@ __device__ __forceinline__ Stencil<double> widen(const Stencil<float>& st) {
 }
 __device__ __forceinline__ const Stencil<double>& widen(const Stencil<double>& st) { return st; }
 
-template <bool kAllLds, bool kWin, typename R>
-__device__ __forceinline__ void deposit_slot(int k, int slot_lo, int slot_hi, int n_acc, double* acc,
+template <bool kAccLds, bool kWin, typename R>
+__device__ __forceinline__ void deposit_slot(int k, int slot_lo, int slot_hi, double* acc,
                                              double* __restrict__ out, size_t off, const Stencil<R>& st,
                                              R v, int nodes, int ox, int oy, int win_lo, int win_n) {
   if (k < slot_lo || k >= slot_hi) return;  // deposited by another launch
   const int j = k - slot_lo;
-  if (kAllLds || j < n_acc) {
+  if (kAccLds) {
     if (!kWin || win_n == nodes)  // (wave-uniform) the whole grid in LDS
       deposit<double, double, __HIP_MEMORY_SCOPE_WORKGROUP>(acc + j * win_n, widen(st), (double)v, ox, oy);
     else
@@ -309,10 +311,10 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
   static_assert(!kRoot || (kF64 && kShort && !kLearned && !kQueue), "the root samplers: FP64, short form");
   static_assert(!kQueue || (kSym && kAllLds && !kLearned), "the queue serves the uniform sampler, slots in LDS");
   static_assert(!kRec || (kSym && !kScale && kShort), "deposits are recorded in the short form");
-  // kAllLds: every f tile and accumulator in LDS (the queue variant: every
-  // accumulator; f from the quads)
+  // kAllLds: FP32: every f tile in LDS (not in the queue variant: f from the
+  // quads); FP64: the accumulators in LDS
   constexpr bool kTilesLds = kAllLds && !kQueue && !kF64 && !kRec;
-  constexpr bool kAccLds = kAllLds;
+  constexpr bool kAccLds = kAllLds || !kF64;
   extern __shared__ double lds[];
   __shared__ R mix_rows[kLearned ? kSlotThreads / kWave : 1][kLearned ? (kF64 ? kMixRowF64 : kMixRow) : 1];
   __shared__ uint32_t q_v[kQueue == kRing ? kQueueWaves : 1][3][kQueue == kRing ? kQueueLen : 1];  // 23-bit uniforms of p2
@@ -510,11 +512,11 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         } else if (kQueue) {
           pd2 = s2; pd3 = s3; pd4 = s4; pdv = v;
         } else {
-          deposit_slot<kAccLds, true, R>(k2, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off2, s2, v,
+          deposit_slot<kAccLds, true, R>(k2, A.slot_lo, A.slot_hi, acc, A.A, off2, s2, v,
                                 nodes, G.ox, G.oy, win_lo, win_n);
-          deposit_slot<kAccLds, true, R>(k3, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off3, s3, -v,
+          deposit_slot<kAccLds, true, R>(k3, A.slot_lo, A.slot_hi, acc, A.A, off3, s3, -v,
                                 nodes, G.ox, G.oy, win_lo, win_n);
-          deposit_slot<kAccLds, true, R>(k4, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off4, s4, -v,
+          deposit_slot<kAccLds, true, R>(k4, A.slot_lo, A.slot_hi, acc, A.A, off4, s4, -v,
                                 nodes, G.ox, G.oy, win_lo, win_n);
         }
         if (kScale && A.direct) {
@@ -627,12 +629,12 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         const int s = base + lane;
         uint32_t x0 = (uint32_t)s, x1 = (uint32_t)p1_lin, x2 = (uint32_t)cell, x3 = ((uint32_t)ch.code << 8);
         philox4x32_10(x0, x1, x2, x3, A.key0, A.key1);
-        if (pending) deposit_slot<true, false, R>(k2, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off2, pd2, pdv,
+        if (pending) deposit_slot<true, false, R>(k2, A.slot_lo, A.slot_hi, acc, A.A, off2, pd2, pdv,
                                         nodes, G.ox, G.oy, win_lo, win_n);
         const SampleMap map = map_words(G, x0, x1, x2, x3);
         Geo g;
         const bool ok = s < A.n_samples && geometry(it, G, map, g);
-        if (pending) deposit_slot<true, false, R>(k3, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off3, pd3, -pdv,
+        if (pending) deposit_slot<true, false, R>(k3, A.slot_lo, A.slot_hi, acc, A.A, off3, pd3, -pdv,
                                         nodes, G.ox, G.oy, win_lo, win_n);
         // The accepted samples take the next places of the queue.
         const unsigned long long mask = __ballot(ok);
@@ -664,7 +666,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
             w2 = m2;
           }
         }
-        if (pending) deposit_slot<true, false, R>(k4, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off4, pd4, -pdv,
+        if (pending) deposit_slot<true, false, R>(k4, A.slot_lo, A.slot_hi, acc, A.A, off4, pd4, -pdv,
                                         nodes, G.ox, G.oy, win_lo, win_n);
         pending = false;
         tail += cnt;
@@ -688,11 +690,11 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
         }
       }
       auto flush = [&]() {
-        deposit_slot<true, false, R>(k2, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off2, pd2, pdv,
+        deposit_slot<true, false, R>(k2, A.slot_lo, A.slot_hi, acc, A.A, off2, pd2, pdv,
                            nodes, G.ox, G.oy, win_lo, win_n);
-        deposit_slot<true, false, R>(k3, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off3, pd3, -pdv,
+        deposit_slot<true, false, R>(k3, A.slot_lo, A.slot_hi, acc, A.A, off3, pd3, -pdv,
                            nodes, G.ox, G.oy, win_lo, win_n);
-        deposit_slot<true, false, R>(k4, A.slot_lo, A.slot_hi, n_acc, acc, A.A, off4, pd4, -pdv,
+        deposit_slot<true, false, R>(k4, A.slot_lo, A.slot_hi, acc, A.A, off4, pd4, -pdv,
                            nodes, G.ox, G.oy, win_lo, win_n);
       };
       if (pending) flush();  // the last full batch
@@ -941,7 +943,7 @@ struct SlotsVariants {
       }
     }
     if (all_lds) launch_user<kSym, kScale, true, kLearned, 0, kShort>(a, grid, block, lds, st);
-    else if constexpr (!kF64) launch_user<kSym, kScale, false, kLearned, 0, kShort>(a, grid, block, lds, st);
+    else if constexpr (!kF64 || kSym) launch_user<kSym, kScale, false, kLearned, 0, kShort>(a, grid, block, lds, st);
   }
 
   template <bool kSym, bool kScale>
@@ -1013,11 +1015,10 @@ hipError_t launch_slots(const CollideArgs& a, int nslot, int queue, hipStream_t 
   constexpr bool kF64 = std::is_same<R, double>::value;
   const int n_acc = a.symmetric ? std::min(a.slot_hi - a.slot_lo, a.lds_acc) : 0;
   const int n_tiles = kF64 ? 0 : std::min(nslot, a.lds_tiles);
-  // every tile (FP32) and every accumulator of this launch's slots in LDS:
-  // the variant without global-memory paths
   const bool all_acc = !a.symmetric || n_acc == a.slot_hi - a.slot_lo;
-  const bool all_lds = (kF64 || n_tiles == nslot) && all_acc;
-  if (kF64 && !all_acc) return hipErrorInvalidValue;
+  if (!all_acc && (!kF64 || n_acc || a.win_n != a.G.nodes)) return hipErrorInvalidValue;
+  // FP32: every tile in LDS; FP64: the accumulators
+  const bool all_lds = kF64 ? all_acc : n_tiles == nslot;
   if (!all_acc || !a.symmetric || a.learned || a.win_n != a.G.nodes) queue = 0;
   const int threads = slots_block(queue);
   const size_t lds = (size_t)n_acc * a.win_n * sizeof(double) + (size_t)n_tiles * a.G.nodes * sizeof(float);
@@ -1116,11 +1117,12 @@ hipError_t slots_lds_limit(size_t lds_max, LdsBudget* out) {
   return hipSuccess;
 }
 
-// The root samplers' kernel variants: [symmetric][scale][user terms].
+// The root samplers' kernel variants: [direct, symmetric, symmetric with global
+// atomics][scale][user terms].
 template <int kRoot>
 using RootFn = void (*)(CollideArgs);
 template <int kRoot>
-void root_variants(RootFn<kRoot> out[2][2][2]) {
+void root_variants(RootFn<kRoot> out[3][2][2]) {
   out[0][0][0] = collide_slots_kernel<double, false, false, true, false, 0, false, true, false, kRoot>;
   out[0][0][1] = collide_slots_kernel<double, false, false, true, false, 0, true, true, false, kRoot>;
   out[0][1][0] = collide_slots_kernel<double, false, true, true, false, 0, false, true, false, kRoot>;
@@ -1129,20 +1131,25 @@ void root_variants(RootFn<kRoot> out[2][2][2]) {
   out[1][0][1] = collide_slots_kernel<double, true, false, true, false, 0, true, true, false, kRoot>;
   out[1][1][0] = collide_slots_kernel<double, true, true, true, false, 0, false, true, false, kRoot>;
   out[1][1][1] = collide_slots_kernel<double, true, true, true, false, 0, true, true, false, kRoot>;
+  out[2][0][0] = collide_slots_kernel<double, true, false, false, false, 0, false, true, false, kRoot>;
+  out[2][0][1] = collide_slots_kernel<double, true, false, false, false, 0, true, true, false, kRoot>;
+  out[2][1][0] = collide_slots_kernel<double, true, true, false, false, 0, false, true, false, kRoot>;
+  out[2][1][1] = collide_slots_kernel<double, true, true, false, false, 0, true, true, false, kRoot>;
 }
 
 template <int kRoot>
 hipError_t launch_roots(const CollideArgs& a, hipStream_t stream) {
   const int n_acc = a.symmetric ? std::min(a.slot_hi - a.slot_lo, a.lds_acc) : 0;
-  if (a.symmetric && n_acc != a.slot_hi - a.slot_lo) return hipErrorInvalidValue;
+  const bool all_acc = !a.symmetric || n_acc == a.slot_hi - a.slot_lo;
+  if (!all_acc && (n_acc || a.win_n != a.G.nodes)) return hipErrorInvalidValue;
   const int waves = kSlotThreads / kWave;
   if (a.split < 1 || waves % a.split || (a.split > 1 && a.chunk_items > kSplitNodes)) return hipErrorInvalidValue;
   if (a.node_block < 1 || a.node_block > kMaxNodeBlock) return hipErrorInvalidValue;
   const long long blocks = (long long)a.G.cells * a.n_group * a.n_chunks;
   if (blocks <= 0) return hipSuccess;
-  RootFn<kRoot> fns[2][2][2];
+  RootFn<kRoot> fns[3][2][2];
   root_variants<kRoot>(fns);
-  hipLaunchKernelGGL(fns[a.symmetric ? 1 : 0][a.scale ? 1 : 0][a.msq_mask ? 1 : 0], dim3((unsigned)blocks),
+  hipLaunchKernelGGL(fns[!a.symmetric ? 0 : all_acc ? 1 : 2][a.scale ? 1 : 0][a.msq_mask ? 1 : 0], dim3((unsigned)blocks),
                      dim3(kSlotThreads), (size_t)n_acc * a.win_n * sizeof(double), stream, a);
   return hipGetLastError();
 }
@@ -1163,7 +1170,7 @@ hipError_t launch_roots_rec(const CollideArgs& a, int n_wg, hipStream_t stream) 
 
 template <int kRoot>
 hipError_t roots_lds_limit_of(size_t lds_max, size_t* out) {
-  RootFn<kRoot> fns[2][2][2];
+  RootFn<kRoot> fns[3][2][2];
   root_variants<kRoot>(fns);
   for (int i = 0; i < 8; ++i)
     if (const hipError_t e = raise_lds_limit((const void*)fns[i >> 2][(i >> 1) & 1][i & 1], lds_max, out)) return e;

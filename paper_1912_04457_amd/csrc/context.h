@@ -120,6 +120,13 @@ struct qgbe_ctx {
 
 namespace qgbe {
 
+// How channels whose deposit accumulators need more than one launch deposit:
+// every launch draws the samples again for its accumulators, the deposits are
+// recorded and replayed, or (FP64) one launch adds them with global atomics.
+enum class DepositRoute { kAgain, kRecord, kGlobal };
+// capacity: samples whose deposits the record buffers hold (0: no buffers).
+DepositRoute deposit_route(const qgbe_ctx* c, int l, int n_samples, bool scale, long long capacity);
+
 size_t field_len(const qgbe_ctx* c);
 // Descriptor checks (QGBE_EINVAL with a message), the grid it describes, and
 // the LDS plan of the channel groups (needs c->G, c->d, c->chans and the

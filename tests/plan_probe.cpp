@@ -22,9 +22,11 @@ int main() {
     qgbe_grid_desc d{};
     size_t plain[2], learned[2], roots, replay, queue[2][2];
     bool long_form;
+    int n_samples;
+    long long capacity;
     in >> d.species_mask >> d.n_x[0] >> d.n_x[1] >> d.n_x[2] >> d.n_p[0] >> d.n_p[1] >> d.n_p[2] >> d.precision >>
         d.symmetric >> long_form >> plain[0] >> plain[1] >> learned[0] >> learned[1] >> roots >> replay >> queue[0][0] >>
-        queue[0][1] >> queue[1][0] >> queue[1][1];
+        queue[0][1] >> queue[1][0] >> queue[1][1] >> n_samples >> capacity;
     if (!in) return 2;
     d.row_mask = 0x7F;
     d.alpha_s = 0.5;
@@ -69,7 +71,12 @@ int main() {
                     g.lds_acc[l], g.lds_tiles[l], g.win[l], (int)g.long_form[l], (int)several_launches(&c, g, l));
       std::printf("}");
     }
-    std::printf("], \"quads\": %d}\n", (int)c.need_quads[0]);
+    std::printf("], ");
+    std::vector<int> route;  // of each sampler, without and with the scale output
+    for (int l = 0; l < 3; ++l)
+      for (int scale = 0; scale < 2; ++scale) route.push_back((int)deposit_route(&c, l, n_samples, scale, capacity));
+    print("route", route);
+    std::printf("\"quads\": %d}\n", (int)c.need_quads[0]);
   }
   return 0;
 }

@@ -446,3 +446,39 @@ def test_long_form_of_short_items_fp32(O, n_x, n_p, mask, N, learned):
     for a, i in ((A, I), (A2, I2)):
         _compare(a, A_ref, S_ref, TOL[qgbe.FP32], "A")
         assert np.allclose(i, I_ref, rtol=TOL[qgbe.FP32], atol=TOL[qgbe.FP32] * np.abs(I_ref).max())
+
+
+@pytest.mark.parametrize("n_p,sampler", [((66, 68, 70), qgbe.SAMPLER_UNIFORM), ((56, 57, 58), qgbe.SAMPLER_ROOTS),
+                                         ((56, 57, 58), qgbe.SAMPLER_ROOTS_ALT), ((56, 57, 58), qgbe.SAMPLER_LEARNED)],
+                         ids=["uniform", "roots", "roots_alt", "learned"])
+def test_deposits_with_global_atomics(O, n_p, sampler):
+    """FP64 grids of so many node windows that, with the scale output, one launch
+    deposits with global atomics; against the oracle, and against the same term
+    without that output, which records its deposits."""
+    _case(f"global atomics {n_p} sampler={sampler}")
+    wl = W.Workload("large", (1, 1, 1), n_p, (3.0, 3.0, 3.0), (2.0, 2.5, 1.5), 1 << 6, 4, "f64", 1, 0.01)
+    f = W.random_f(28, 1, wl.nodes, species_mask=1 << 6) * 0.6
+    g = O.Grid(n_x=(1, 1, 1), n_p=n_p, x_half=wl.x_half, p_half=wl.p_half, species_mask=1 << 6, alpha_s=wl.alpha_s)
+    with qgbe.Solver(**_grid_kw(wl), precision=qgbe.FP64, seed=SEED) as s:
+        s.set_f(f)
+        if sampler == qgbe.SAMPLER_LEARNED:
+            table = W.random_mog_table(5, s.n_channels * wl.nodes)
+            qgbe.qgbe_set_proposal_table(s.ctx, *table)
+        A, S, I, st = s.collision(4, sampler=sampler, scale=True, items=True)
+        A2, _, I2, st2 = s.collision(4, sampler=sampler, items=True)
+        m = s.masses()
+    assert st.n_collide_launches == 1 and st2.n_collide_launches > 1
+    if sampler == qgbe.SAMPLER_LEARNED:
+        A_ref, S_ref, I_ref = O.collision_learned(g, f, m, SEED, 0, 4, *table, want_items=True)
+    else:
+        est = {qgbe.SAMPLER_UNIFORM: "cm", qgbe.SAMPLER_ROOTS: "root", qgbe.SAMPLER_ROOTS_ALT: "root_k3"}[sampler]
+        A_ref, S_ref, I_ref = O.collision(g, f, m, SEED, 0, 4, estimator=est, want_items=True)
+    # a node without a deposit may get the rounding of a stencil weight (a few
+    # 2^-53 of the grid coordinate) from a sample on the face of its cell
+    hit, most = S_ref > 0.0, S_ref.max()
+    for a in (A, A2):
+        assert np.all(np.abs(a - A_ref)[hit] <= 1e-10 * S_ref[hit])
+        assert np.all(np.abs(a)[~hit] <= 8 * 2.0 ** -53 * max(n_p) * most)
+        assert abs(a.sum()) <= 1e-13 * S_ref.sum()
+    assert np.abs(I - I2).max() <= 1e-12 * np.abs(I_ref).max()
+    assert st.n_accepted == st2.n_accepted > 0

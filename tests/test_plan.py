@@ -39,8 +39,8 @@ def probe(tmp_path_factory):
     return run
 
 
-def _case(mask, n_x, n_p, precision, symmetric, long_form=0):
-    return (mask, *n_x, *n_p, precision, symmetric, long_form, *BUDGETS[precision])
+def _case(mask, n_x, n_p, precision, symmetric, long_form=0, n_samples=64, capacity=1 << 23):
+    return (mask, *n_x, *n_p, precision, symmetric, long_form, *BUDGETS[precision], n_samples, capacity)
 
 
 GRIDS = [(2, 2, 2), (5, 6, 7), (16, 16, 16), (20, 20, 20), (22, 22, 22), (24, 24, 23), (30, 30, 30), (64, 64, 64),
@@ -123,3 +123,36 @@ def test_long_form_where_the_short_one_lacks_lds(probe, mask, symmetric):
             assert h["0"]["long"] and h["queue"] == [int(ring), 0]
         assert long_plan["quads"] == quads, n_p
     assert not symmetric or min(seen.values()) > 0
+
+
+AGAIN, RECORD, GLOBAL = 0, 1, 2
+
+
+def test_deposit_routes(probe):
+    """The route of the channels that take several launches, over grids, samples
+    and record buffers: never records without buffers, without room for a node's
+    samples, or with the scale output; global atomics in FP64 only; and the side
+    that was the faster one on the GPU where they were timed."""
+    ns = (16, 20, 24, 30, 40, 48, 64, 80, 96, 128)
+    cases = [(n, precision, mask, samples, cap) for n in ns for precision in (0, 1) for mask in (0x40, 0x7F)
+             for samples in (1, 64, 2048, 100000) for cap in (0, 1 << 16, 1 << 23) if not (mask == 0x7F and n > 96)]
+    plans = probe([_case(m, (1, 1, 1), (n, n, n), p, 1, 0, samples, cap) for n, p, m, samples, cap in cases])
+    for (n, precision, mask, samples, cap), plan in zip(cases, plans):
+        for l in range(3):
+            plain, scale = plan["route"][2 * l:2 * l + 2]
+            several = any(g[str(l)]["several"] for g in plan["groups"])
+            assert several or plain == scale == AGAIN
+            assert scale != RECORD and (plain != RECORD or samples <= cap)
+            if precision == 1 and l < 2:
+                assert GLOBAL not in (plain, scale)
+    faster = {  # (cube, samples, precision, sampler, buffers): the faster route of one gluon cell
+        (30, 128, 1, 0, 1): RECORD, (30, 2048, 1, 0, 1): RECORD, (48, 64, 0, 0, 1): RECORD, (64, 64, 0, 0, 1): RECORD,
+        (80, 64, 0, 0, 1): RECORD, (96, 512, 0, 0, 1): GLOBAL, (128, 64, 0, 0, 1): GLOBAL, (80, 64, 0, 2, 1): RECORD,
+        (96, 64, 0, 2, 1): GLOBAL, (128, 64, 0, 2, 1): GLOBAL, (80, 64, 0, 1, 1): RECORD, (96, 64, 0, 1, 1): GLOBAL,
+        (48, 64, 0, 0, 0): AGAIN, (80, 64, 0, 0, 0): GLOBAL, (128, 64, 0, 0, 0): GLOBAL, (40, 64, 0, 2, 0): AGAIN,
+        (64, 64, 0, 2, 0): GLOBAL, (64, 64, 0, 1, 0): GLOBAL, (128, 64, 1, 0, 1): RECORD, (96, 512, 1, 0, 1): RECORD,
+        (96, 64, 1, 0, 0): AGAIN}
+    plans = probe([_case(0x40, (1, 1, 1), (n, n, n), p, 1, 0, samples, buffers << 23)
+                   for n, samples, p, _, buffers in faster])
+    for (case, want), plan in zip(faster.items(), plans):
+        assert plan["route"][2 * case[3]] == want, case
