@@ -241,12 +241,6 @@ void plan_groups(qgbe_ctx* c, bool long_form) {
     std::copy(c->match[y].begin(), c->match[y].end(), c->group_index.begin() + kMatchAt + (size_t)y * kMaxMatches);
 }
 
-struct Chunking {
-  int chunk;  // observed nodes per workgroup
-  int split;  // waves that share a node
-  int block;  // nodes a wave takes at a time
-};
-
 // Observed nodes per workgroup; acc: entries a workgroup zeroes and flushes.
 Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long long acc, int n_samples, bool queue,
                      bool learned, bool long_form) {
@@ -419,27 +413,53 @@ DepositRoute choose_route(qgbe_ctx* c, int l, int n_samples, const double* scale
   return deposit_route(c, l, n_samples, scale != nullptr, c->d_rec ? record_capacity(c, l, c->rec_bytes) : 0);
 }
 
-// Their samples and deposits, in batches that fit the record buffers.
+// The recording launches of a call: workgroups of the kernel in batches that fit
+// the record buffers.
+ReplayPlan plan_replay(const qgbe_ctx* c, int l, int n_samples, long long capacity) {
+  const Replay& rp = c->replay[l];
+  ReplayPlan p{};
+  const int per_sample = l == 2 ? 2 : 1;
+  const long long nodes = c->G.nodes, all_pairs = (long long)c->G.cells * rp.count;
+  const long long fit = capacity / n_samples;  // items a batch holds
+  p.chunks = plan_chunks(c, std::min(nodes, fit), std::max(1LL, std::min(all_pairs, fit / nodes)), 0, n_samples, l == 0,
+                         l != 0, false);
+  p.chunks.chunk = (int)std::min<long long>(p.chunks.chunk, fit);
+  p.n_chunks = (int)((nodes + p.chunks.chunk - 1) / p.chunks.chunk);
+  p.n_group = rp.count;
+  p.capacity = per_sample * capacity;
+  p.region = (long long)p.chunks.chunk * n_samples * per_sample;
+  p.wgs = all_pairs * p.n_chunks;
+  p.per = std::min(c->rec_wgs, p.capacity / p.region);
+  if (p.per > c->n_cu) p.per = p.per / c->n_cu * c->n_cu;
+  return p;
+}
+
+ReplayBatch replay_batch(const ReplayPlan& p, long long wg) {
+  ReplayBatch b;
+  const long long per_cell = (long long)p.n_group * p.n_chunks, last = std::min(wg + p.per, p.wgs) - 1;
+  b.n_wg = (int)(last - wg + 1);
+  b.cell_lo = (int)(wg / per_cell);
+  b.wg_base = (int)(wg % per_cell);
+  b.n_cells = (int)(last / per_cell) - b.cell_lo + 1;
+  b.gi_lo = b.n_cells > 1 ? 0 : b.wg_base / p.n_chunks;
+  b.gi_hi = b.n_cells > 1 ? p.n_group - 1 : (int)(last % per_cell / p.n_chunks);
+  return b;
+}
+
+// Their samples and deposits.
 qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
   const Replay& rp = c->replay[l];
   const bool roots = l == 2, f64 = roots || c->d.precision == QGBE_FP64;
-  const int per_sample = roots ? 2 : 1;
-  const long long nodes = c->G.nodes, all_pairs = (long long)c->G.cells * rp.count;
-  const long long fit = record_capacity(c, l, c->rec_bytes) / a.n_samples;  // items a batch holds
-  const Chunking ck = plan_chunks(c, std::min(nodes, fit), std::max(1LL, std::min(all_pairs, fit / nodes)), 0,
-                                  a.n_samples, l == 0, l != 0, false);
+  const ReplayPlan p = plan_replay(c, l, a.n_samples, record_capacity(c, l, c->rec_bytes));
   a.group = c->d_groups + rp.start;
-  a.n_group = rp.count;
-  a.split = ck.split;
-  a.node_block = ck.block;
-  a.chunk_items = (int)std::min<long long>(ck.chunk, fit);
-  a.n_chunks = (int)((nodes + a.chunk_items - 1) / a.chunk_items);
+  a.n_group = p.n_group;
+  a.split = p.chunks.split;
+  a.node_block = p.chunks.block;
+  a.chunk_items = p.chunks.chunk;
+  a.n_chunks = p.n_chunks;
   a.rec = c->rec;
-  a.rec.capacity = per_sample * record_capacity(c, l, c->rec_bytes);
-  a.rec.region = (long long)a.chunk_items * a.n_samples * per_sample;
-  const long long wgs = all_pairs * a.n_chunks;
-  long long per = std::min(c->rec_wgs, a.rec.capacity / a.rec.region);
-  if (per > c->n_cu) per = per / c->n_cu * c->n_cu;
+  a.rec.capacity = p.capacity;
+  a.rec.region = p.region;
   ReplayArgs r{};
   r.G = c->G;
   r.match = c->d_groups + kMatchAt;
@@ -448,26 +468,24 @@ qgbe_status run_replay(qgbe_ctx* c, CollideArgs a, int l, bool alt) {
   r.n_chunks = a.n_chunks;
   r.A = a.A;
   r.n_win = replay_windows(c);
-  r.win_n = (int)((nodes + r.n_win - 1) / r.n_win);
+  r.win_n = (c->G.nodes + r.n_win - 1) / r.n_win;
   // workgroups of a replay launch: two to a compute unit where their windows fit
   const double target = (double)c->n_cu * (2 * (size_t)r.win_n * sizeof(double) <= c->lds.replay ? 2 : 1);
-  for (long long wg = 0; wg < wgs; wg += per) {
-    const int n = (int)std::min(per, wgs - wg);
-    a.rec.wg_base = (int)wg;
-    HIP_TRY(roots ? launch_record_roots(a, alt, n, c->stream)
-                  : f64 ? launch_record_f64(a, n, c->stream) : launch_record_f32(a, n, c->stream), "collide (record)");
+  for (long long wg = 0; wg < p.wgs; wg += p.per) {
+    const ReplayBatch b = replay_batch(p, wg);
+    a.rec.cell_lo = b.cell_lo;
+    a.rec.wg_base = b.wg_base;
+    HIP_TRY(roots ? launch_record_roots(a, alt, b.n_wg, c->stream)
+                  : f64 ? launch_record_f64(a, b.n_wg, c->stream) : launch_record_f32(a, b.n_wg, c->stream),
+            "collide (record)");
     r.rec = a.rec;
-    r.n_wg = n;
-    const long long per_cell = (long long)rp.count * a.n_chunks;
-    r.cell_lo = (int)(wg / per_cell);
-    r.n_cells = (int)((wg + n - 1) / per_cell) - r.cell_lo + 1;
-    const int gi_lo = r.n_cells > 1 ? 0 : (int)(wg % per_cell / a.n_chunks);
-    const int gi_hi = r.n_cells > 1 ? rp.count - 1 : (int)((wg + n - 1) % per_cell / a.n_chunks);
+    r.n_wg = b.n_wg;
+    r.n_cells = b.n_cells;
     long long total = 0;
     for (int y = 0; y < kSpecies; ++y) {
       const std::vector<int>& m = c->match[y];
-      r.m_lo[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * (rp.start + gi_lo)) - m.begin());
-      r.m_hi[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * (rp.start + gi_hi + 1)) - m.begin());
+      r.m_lo[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * (rp.start + b.gi_lo)) - m.begin());
+      r.m_hi[y] = (int)(std::lower_bound(m.begin(), m.end(), 4 * (rp.start + b.gi_hi + 1)) - m.begin());
       total += r.m_hi[y] - r.m_lo[y];
     }
     for (int y = 0; y < kSpecies; ++y) {

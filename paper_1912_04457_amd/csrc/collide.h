@@ -30,7 +30,8 @@ struct RecordArgs {
   uint32_t* count;    // [workgroups of the batch]
   long long capacity; // records the tiles hold, a multiple of 64
   long long region;   // records of a workgroup
-  int wg_base;       // first workgroup of the batch; workgroups run over (cell, channel, chunk)
+  int cell_lo;       // first cell of the batch
+  int wg_base;       // and its first workgroup there; workgroups run over (cell, channel, chunk)
 };
 
 struct CollideArgs {
@@ -86,7 +87,7 @@ struct ReplayArgs {
   int first;              // index there of the sampling launch's first channel
   int n_group, n_chunks;  // as the sampling launch
   int n_wg;               // workgroups of the batch
-  int cell_lo, n_cells;   // cells of the batch
+  int n_cells;            // cells of the batch, from rec.cell_lo on
   int win_n, n_win;       // nodes per LDS window, windows
   int m_lo[kSpecies], m_hi[kSpecies];  // matches of each species within the batch
   int parts[kSpecies];                 // workgroups per (cell, species, window)

@@ -357,7 +357,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
     cell = cb * kCellBlock + r % S;
   } else {
     gi = (lb / A.n_chunks) % A.n_group;
-    cell = lb / (A.n_chunks * A.n_group);
+    cell = (kRec ? A.rec.cell_lo : 0) + lb / (A.n_chunks * A.n_group);
   }
   const int ci = A.group[gi];
   const Channel ch = A.chans[ci];
@@ -867,7 +867,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(ReplayArgs a) {
   const Grid& G = a.G;
   int per_cell = 0;
   for (int y = 0; y < kSpecies; ++y) per_cell += a.parts[y] * a.n_win;
-  const int cell = a.cell_lo + blockIdx.x / per_cell;
+  const int in_batch = blockIdx.x / per_cell, cell = a.rec.cell_lo + in_batch;  // the cell
   int r = blockIdx.x % per_cell, sp = 0;
   while (r >= a.parts[sp] * a.n_win) {
     r -= a.parts[sp] * a.n_win;
@@ -881,7 +881,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(ReplayArgs a) {
   for (int j = part; j < jobs; j += a.parts[sp]) {
     const int m = a.match[sp * kMaxMatches + a.m_lo[sp] + j / a.n_chunks];
     const int pos = (m & 3) - 1;  // 0, 1, 2: positions 2, 3, 4
-    const long long wg = ((long long)cell * a.n_group + (m >> 2) - a.first) * a.n_chunks + j % a.n_chunks - a.rec.wg_base;
+    const long long wg = ((long long)in_batch * a.n_group + (m >> 2) - a.first) * a.n_chunks + j % a.n_chunks - a.rec.wg_base;
     if (wg < 0 || wg >= a.n_wg) continue;
     const int cnt = (int)a.rec.count[wg];
     const long long i0 = wg * a.rec.region;
@@ -1057,7 +1057,10 @@ inline bool record_fits(const CollideArgs& a, int n_wg, int per_sample) {
   if (a.node_block < 1 || a.node_block > kMaxNodeBlock) return false;
   if ((long long)a.chunk_items * a.n_samples * per_sample > a.rec.region || a.rec.region * n_wg > a.rec.capacity)
     return false;
-  return a.rec.wg_base + (long long)n_wg <= (long long)a.G.cells * a.n_group * a.n_chunks;
+  // the kernel counts the batch's workgroups from its first cell in 32 bits
+  const long long per_cell = (long long)a.n_group * a.n_chunks, end = (long long)a.rec.wg_base + n_wg;
+  if (a.rec.cell_lo < 0 || a.rec.wg_base < 0 || a.rec.wg_base >= per_cell || end > 0x7FFFFFFF) return false;
+  return a.rec.cell_lo * per_cell + end <= a.G.cells * per_cell;
 }
 
 template <typename R>

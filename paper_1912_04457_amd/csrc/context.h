@@ -124,7 +124,26 @@ namespace qgbe {
 // every launch draws the samples again for its accumulators, the deposits are
 // recorded and replayed, or (FP64) one launch adds them with global atomics.
 enum class DepositRoute { kAgain, kRecord, kGlobal };
+struct Chunking {
+  int chunk;  // observed nodes per workgroup
+  int split;  // waves that share a node
+  int block;  // nodes a wave takes at a time
+};
+// The recording launches of a call, and one of them: per workgroups from the
+// wg-th of all wgs on, as its first cell, its first workgroup there, cells and
+// (with one cell) channels of the group.
+struct ReplayPlan {
+  Chunking chunks;
+  int n_chunks, n_group;
+  long long capacity, region;  // as RecordArgs
+  long long wgs, per;
+};
+struct ReplayBatch {
+  int n_wg, cell_lo, wg_base, n_cells, gi_lo, gi_hi;
+};
 // capacity: samples whose deposits the record buffers hold (0: no buffers).
+ReplayPlan plan_replay(const qgbe_ctx* c, int l, int n_samples, long long capacity);
+ReplayBatch replay_batch(const ReplayPlan& p, long long wg);
 DepositRoute deposit_route(const qgbe_ctx* c, int l, int n_samples, bool scale, long long capacity);
 
 size_t field_len(const qgbe_ctx* c);

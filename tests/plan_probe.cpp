@@ -1,5 +1,6 @@
 // Prints the launch plans that the library makes, for tests on the host: one
 // line of numbers in (see main), one JSON object out.
+#include <algorithm>
 #include <cstdio>
 #include <iostream>
 #include <sstream>
@@ -76,6 +77,24 @@ int main() {
     for (int l = 0; l < 3; ++l)
       for (int scale = 0; scale < 2; ++scale) route.push_back((int)deposit_route(&c, l, n_samples, scale, capacity));
     print("route", route);
+    // the recording launches: some of them as [first workgroup, those of replay_batch]
+    std::printf("\"batches\": {");
+    c.rec_wgs = 1 << 16;
+    for (int l = 0; l < 3; ++l) {
+      std::printf("%s\"%d\": [", l ? ", " : "", l);
+      if (c.replay[l].count && n_samples <= capacity) {
+        const ReplayPlan p = plan_replay(&c, l, n_samples, capacity);
+        std::printf("[%d, %d, %d, %lld, %lld, %lld, %lld]", p.chunks.chunk, p.n_chunks, p.n_group, p.capacity, p.region, p.wgs,
+                    p.per);
+        const long long n = (p.wgs + p.per - 1) / p.per, step = std::max(1LL, n / 50);
+        for (long long i = 0; i < n; i += i + step < n || i == n - 1 ? step : n - 1 - i) {
+          const ReplayBatch b = replay_batch(p, i * p.per);
+          std::printf(", [%lld, %d, %d, %d, %d, %d, %d]", i * p.per, b.n_wg, b.cell_lo, b.wg_base, b.n_cells, b.gi_lo, b.gi_hi);
+        }
+      }
+      std::printf("]");
+    }
+    std::printf("}, ");
     std::printf("\"quads\": %d}\n", (int)c.need_quads[0]);
   }
   return 0;

@@ -156,3 +156,37 @@ def test_deposit_routes(probe):
                    for n, samples, p, _, buffers in faster])
     for (case, want), plan in zip(faster.items(), plans):
         assert plan["route"][2 * case[3]] == want, case
+
+
+@pytest.mark.parametrize("mask,n_x,n_p,precision,samples,capacity",
+                         [(0x40, (1, 1, 1), (30, 30, 30), 1, 128, 1 << 23), (0x7F, (1, 1, 1), (20, 20, 20), 1, 4096, 1 << 23),
+                          (0x7F, (3, 5, 7), (28, 27, 29), 0, 77, 1 << 20), (0x40, (1, 1, 1), (128, 128, 64), 1, 9, 1 << 23),
+                          (0x7F, (35, 13, 10), (30, 30, 30), 1, 8192, 1 << 23), (0x7F, (35, 13, 10), (30, 30, 30), 1, 1 << 23, 1 << 23)],
+                         ids=["gluons", "seven", "cells", "large", "beyond_32_bits", "a_node_per_batch"])
+def test_recording_batches(probe, mask, n_x, n_p, precision, samples, capacity):
+    """The batches of recorded deposits: their workgroups lie in the (cell,
+    channel, chunk) order that replay reads, in range also where all of them are
+    more than 32 bits count, and their records fit in the buffers."""
+    plan = probe([_case(mask, n_x, n_p, precision, 1, 0, samples, capacity)])[0]
+    cells, nodes = int(np.prod(n_x)), int(np.prod(n_p))
+    total = 0
+    for l in range(3):
+        if not plan["batches"][str(l)]:
+            continue
+        (chunk, n_chunks, n_group, cap, region, wgs, per), *batches = plan["batches"][str(l)]
+        total = max(total, wgs)
+        assert n_group == plan["replay_count"][l] and cap == capacity * (2 if l == 2 else 1)
+        assert region == chunk * samples * (2 if l == 2 else 1) and (n_chunks - 1) * chunk < nodes <= n_chunks * chunk
+        assert wgs == cells * n_group * n_chunks and 0 < per * region <= cap
+        per_cell = n_group * n_chunks
+        assert batches[0][0] == 0 and batches[-1][0] + batches[-1][1] == wgs
+        for wg, n, cell_lo, base, n_cells, gi_lo, gi_hi in batches:
+            assert 0 < n <= per and n == min(per, wgs - wg)
+            assert cell_lo * per_cell + base == wg and 0 <= base < per_cell
+            assert (cell_lo + n_cells - 1) == (wg + n - 1) // per_cell < cells
+            assert base + n < 1 << 31
+            first, last = wg % per_cell // n_chunks, (wg + n - 1) % per_cell // n_chunks
+            assert (gi_lo, gi_hi) == ((first, last) if n_cells == 1 else (0, n_group - 1))
+    assert total > 0
+    if cells == 4550:
+        assert total > 1 << 31
