@@ -30,6 +30,14 @@
  *              device buffers alive until the stream has finished with them.
  *              The library owns the context and the device workspace it
  *              allocates in qgbe_init_grid (reported by qgbe_workspace_bytes).
+ *              On grids whose deposit accumulators exceed the LDS of a
+ *              workgroup (from 12800 to 20500 momentum nodes on for gluons,
+ *              fewer for reactions of more species) that includes buffers for
+ *              recorded deposits, up to 450 MB (800 MB in QGBE_FP64), of at
+ *              most a sixteenth of the free memory; for the root samplers alone
+ *              they are allocated by the first call that uses them.  Without
+ *              them the collision term gives the same results, at up to twice
+ *              the time.
  * Errors       every entry point returns a qgbe_status; nothing is thrown
  *              across the ABI.  Argument errors are reported before any device
  *              work.  qgbe_last_error() gives a message for the calling thread.
@@ -158,7 +166,8 @@ typedef struct {
 
 /* Create a context: validates the descriptor, builds the channel table of
  * Eq. C_quark / Eq. C_gluon, allocates the device workspace (f in FP64 and its
- * FP32 shadow, masses, accumulators) and zeroes f.  *out is NULL on failure. */
+ * FP32 shadow, masses, accumulators, records of deposits) and zeroes f.  *out is
+ * NULL on failure. */
 qgbe_status qgbe_init_grid(const qgbe_grid_desc* desc, qgbe_ctx** out);
 
 /* Release the context and its workspace (waits for its stream). NULL is fine. */

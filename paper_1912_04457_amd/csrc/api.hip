@@ -313,8 +313,10 @@ Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long l
 
 // Record buffers: for 128 samples per item (and an eighth more, as whole
 // chunks of nodes count), between kRecMin and kRecMax samples (7 species at 30^3 x 128: 2 M samples 13.3 ms, 4 M 12.1, 8 M
-// 9.6, 16 M 9.2, 64 M 8.8; 52 B a sample, 92 B in FP64).  Without the memory
-// for them every launch draws its samples again.
+// 9.6, 16 M 9.2, 64 M 8.8; 52 B a sample, 92 B in FP64).  They take at most a
+// sixteenth of the memory that is free, so that contexts that hold them leave
+// what a caller's own allocations had; without them every launch draws its
+// samples again, or adds its deposits with global atomics.  A context asks once.
 constexpr long long kRecMin = 1LL << 21, kRecMax = 1LL << 23, kRecLeast = 1LL << 19;
 
 size_t record_tile(const qgbe_ctx* c, bool roots) {
@@ -339,10 +341,22 @@ size_t record_buffer_bytes(const qgbe_ctx* c) {
 }
 
 void alloc_records(qgbe_ctx* c) {
+  c->rec_asked = true;
   const size_t bytes = record_buffer_bytes(c) + ((size_t)sizeof(uint32_t) << 16);
-  unsigned char* p = nullptr;
-  if (dev_alloc(c, &p, bytes, "records")) (void)hipGetLastError();
-  else carve_records(c, p, bytes);
+  // an allocation takes nothing from a capture that another stream or thread is in
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  size_t free = 0, total = 0;
+  void* p = nullptr;
+  if (hipMemGetInfo(&free, &total) == hipSuccess && bytes <= free / 16 && hipMalloc(&p, bytes) == hipSuccess) {
+    c->ws += bytes;
+    carve_records(c, static_cast<unsigned char*>(p), bytes);
+  }
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  (void)hipGetLastError();  // a refusal is none of the caller's
 }
 
 // Samples whose deposits buffers of these bytes hold for a sampler (the root
@@ -405,10 +419,11 @@ DepositRoute deposit_route(const qgbe_ctx* c, int l, int n_samples, bool scale, 
 // CM-angle samplers need them; for the root samplers alone they are made by the
 // first call that uses them, unless its stream is being captured.)
 DepositRoute choose_route(qgbe_ctx* c, int l, int n_samples, const double* scale) {
-  if (!c->d_rec && l == 2 && c->d_arena && !scale &&
+  if (!c->rec_asked && l == 2 && c->d_arena && !scale &&
       deposit_route(c, l, n_samples, false, record_capacity(c, l, record_buffer_bytes(c))) == DepositRoute::kRecord) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) alloc_records(c);
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    else if (cap == hipStreamCaptureStatusNone) alloc_records(c);
   }
   return deposit_route(c, l, n_samples, scale != nullptr, c->d_rec ? record_capacity(c, l, c->rec_bytes) : 0);
 }

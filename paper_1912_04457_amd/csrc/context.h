@@ -72,6 +72,7 @@ struct qgbe_ctx {
   std::vector<qgbe::Group> groups;
   qgbe::Replay replay[3];          // [uniform, learned, root samplers]
   unsigned char* d_rec = nullptr;  // record buffers, an allocation of their own (NULL: none, every launch draws its samples again)
+  bool rec_asked = false;          // whether they have been asked for
   qgbe::RecordArgs rec{};          // their parts
   long long rec_wgs = 0;           // counters in rec.count
   size_t rec_bytes = 0;            // of the tiles

@@ -140,3 +140,40 @@ def test_roots_lds_plans(O, sampler, n_x, n_p, mask, N, precision):
     assert st.n_accepted == st2.n_accepted > 0
     for cell in range(g.cells):
         assert abs(A[:, cell].sum()) <= 1e-13 * S_ref[:, cell].sum()
+
+
+def test_first_roots_call_beside_a_capture():
+    """The first root-sampler call of a context allocates its record buffers; a
+    capture that another stream is in meanwhile goes on, and a call without the
+    buffers, captured first, gives the same term."""
+    torch = pytest.importorskip("torch")
+    _case("first roots call beside a capture")
+    grid = dict(n_x=(1, 1, 1), n_p=(24, 25, 24), x_half=(3.0, 3.0, 3.0), p_half=(2.0, 2.5, 1.5), species_mask=1 << 6)
+    f = torch.from_numpy(W.random_f(35, 1, 24 * 25 * 24, species_mask=1 << 6) * 0.6).cuda()
+    x = torch.arange(8.0, device="cuda")
+    A, B, C = (torch.full_like(f, float("nan")) for _ in range(3))
+    own, other = torch.cuda.Stream(), torch.cuda.Stream()
+    with qgbe.Solver(**grid, precision=qgbe.FP32, seed=SEED, stream=own.cuda_stream) as s:
+        qgbe.qgbe_set_distribution(s.ctx, -1, f)
+        torch.cuda.synchronize()
+        before = qgbe.qgbe_workspace_bytes(s.ctx)
+        captured = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(captured, stream=own):
+            qgbe.qgbe_collision_term(s.ctx, 70, qgbe.SAMPLER_ROOTS, A)
+        assert qgbe.qgbe_workspace_bytes(s.ctx) == before
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=other):
+            y = x + 1.0
+            qgbe.qgbe_collision_term(s.ctx, 70, qgbe.SAMPLER_ROOTS, B)
+        assert qgbe.qgbe_workspace_bytes(s.ctx) > before
+        for _ in range(2):
+            captured.replay()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, x + 1.0)
+            qgbe.qgbe_collision_term(s.ctx, 70, qgbe.SAMPLER_ROOTS, C)
+            torch.cuda.synchronize()
+        _, S, _, _ = s.collision(70, sampler=qgbe.SAMPLER_ROOTS, scale=True)
+    S = torch.from_numpy(S).cuda()
+    for out in (A, B, C):
+        assert bool(((out - A).abs() <= 1e-10 * S + 1e-300).all()) and float(A.abs().max()) > 0.0
