@@ -88,11 +88,13 @@ def test_noalloc_without_room_for_quads(n_x, n_p):
 
 
 @pytest.mark.parametrize("n_x,n_p,mask,symmetric", [((60, 1, 1), (24, 24, 23), 1 << 6, 1), ((179, 1, 1), (24, 24, 23), 1 << 6, 1),
-                                                    ((50, 1, 1), (34, 34, 35), 1 << 6, 0)],
-                         ids=["one_slot", "largest", "direct"])
+                                                    ((50, 1, 1), (34, 34, 35), 1 << 6, 0), ((222, 1, 1), (22, 22, 22), 1 << 6, 1),
+                                                    ((44, 1, 1), (22, 22, 22), 1 << 6, 1)],
+                         ids=["one_slot", "largest", "direct", "short_form", "short_form_quads"])
 def test_noalloc_tiles_beside_the_long_form(n_x, n_p, mask, symmetric):
     """Grids whose f tiles fit in LDS beside the long-item form's own only, and
-    whose node quads do not fit in the scratch: that form runs."""
+    whose node quads do not fit in the scratch: that form runs; and grids on which
+    the short form's tiles or the quads fit.  Element by element."""
     torch = pytest.importorskip("torch")
     print(f"\n[gpu case] noalloc long form n_x={n_x} n_p={n_p} mask={mask:#x} symmetric={symmetric}", flush=True)
     kw = dict(n_x=n_x, n_p=n_p, x_half=(3.0, 3.0, 3.0), p_half=(2.0, 2.0, 2.0), species_mask=mask, symmetric=symmetric)
