@@ -201,20 +201,23 @@ qgbe_status qgbe_mlp_forward(qgbe_ctx* c, const float* X, int64_t rows, float* Y
   if (s) return s;
   HIP_TRY(hipSetDevice(c->d.device), "hipSetDevice");
   MlpState& m = c->mlp;
-  if (on_device) {
+  // device rows in place, unless X and Y overlap: a tile would write what another has yet to read
+  const bool overlap = X < Y + rows * kMlpOut && Y < X + rows * kMlpIn;
+  const bool staged = !on_device || overlap;
+  const hipMemcpyKind in = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+  const hipMemcpyKind out = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+  if (!staged) {
     MlpTileArgs g = tile_args(c, rows, X, kMlpIn, nullptr, 0, nullptr);
     g.Y = Y;
     HIP_TRY(launch_mlp_forward(g, c->stream), "forward");
   }
-  for (int64_t r0 = 0; !on_device && r0 < rows; r0 += kBatch) {
+  for (int64_t r0 = 0; staged && r0 < rows; r0 += kBatch) {
     const int nr = (int)std::min<int64_t>(kBatch, rows - r0);
-    HIP_TRY(hipMemcpyAsync(m.X, X + r0 * kMlpIn, (size_t)nr * kMlpIn * sizeof(float), hipMemcpyHostToDevice, c->stream),
-            "copy X");
+    HIP_TRY(hipMemcpyAsync(m.X, X + r0 * kMlpIn, (size_t)nr * kMlpIn * sizeof(float), in, c->stream), "copy X");
     MlpTileArgs g = tile_args(c, nr, m.X, kMlpIn, nullptr, 0, nullptr);
     g.Y = m.Y;
     HIP_TRY(launch_mlp_forward(g, c->stream), "forward");
-    HIP_TRY(hipMemcpyAsync(Y + r0 * kMlpOut, m.Y, (size_t)nr * kMlpOut * sizeof(float), hipMemcpyDeviceToHost, c->stream),
-            "copy Y");
+    HIP_TRY(hipMemcpyAsync(Y + r0 * kMlpOut, m.Y, (size_t)nr * kMlpOut * sizeof(float), out, c->stream), "copy Y");
   }
   HIP_TRY(hipStreamSynchronize(c->stream), "synchronise");
   return QGBE_OK;

@@ -99,6 +99,26 @@ def test_mlp_tiles(rows):
         assert _rel(g[name], gref[name]) <= 1e-2, (name, _rel(g[name], gref[name]))
 
 
+@pytest.mark.parametrize("rows,at", [(1000, 0), (1000, 40), (16384, 0), (16384, 16384 * (M.N_OUT - M.N_IN))])
+def test_mlp_forward_in_one_buffer(rows, at):
+    """Inputs that lie where the head is written: read before, as the head of the
+    same inputs elsewhere."""
+    torch = pytest.importorskip("torch")
+    _case(f"mlp forward in one buffer, {rows} rows, inputs at {at}")
+    X, _ = _mlp_inputs(rows, 4)
+    buffer = torch.zeros(rows * M.N_OUT, device="cuda")
+    buffer[at:at + X.size] = torch.from_numpy(X.ravel()).cuda()
+    Y = torch.zeros(rows, M.N_OUT, device="cuda")
+    with qgbe.Solver(**_kw(SMALL_7)) as s:
+        qgbe.qgbe_proposal_set_weights(s.ctx, W.random_mlp_params(3, head_scale=1.0))
+        torch.cuda.synchronize()
+        qgbe.qgbe_mlp_forward(s.ctx, torch.from_numpy(X).cuda(), Y)
+        # the same call, with the inputs' place in the buffer
+        qgbe._check(qgbe.lib().qgbe_mlp_forward(s.ctx, buffer.data_ptr() + 4 * at, rows, buffer.data_ptr(), 1))
+        torch.cuda.synchronize()
+    assert torch.equal(buffer.reshape(rows, M.N_OUT), Y) and float(Y.abs().max()) > 0.0
+
+
 @pytest.mark.parametrize("rows", [512, 1024, 8192])
 def test_gradient_sums_by_chunks_of_rows(rows):
     """The gradient's sums over the rows keep their brackets whatever the batch:
