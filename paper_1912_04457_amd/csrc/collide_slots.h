@@ -430,11 +430,7 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
     r.store(2, s4);
     r.w[9 * 64] = v;
   };
-  int n_ok = 0;  // accepted samples: of the item, kShort of the wave's nodes
-  // kShort: the workgroup's nodes may accept more samples than 32 bits count
-  // (two per sample with the root samplers): then a lane's go to ok_wg with
-  // every block of nodes
-  const bool many = kShort && (long long)A.chunk_items * A.n_samples >= 1LL << 30;
+  int n_ok = 0;  // accepted samples: of the item, kShort of the wave
   const int s_first = split > 1 ? (wid % split) * kWave : 0, s_step = split * kWave;
   const size_t row1 = ((size_t)ch.sp[0] * G.cells + cell) * nodes;  // the observed species' output row
   // The samples of the observed node p1_lin; kShort: the j-th of the wave's
@@ -793,10 +789,6 @@ __global__ __launch_bounds__(slots_block(kQueue)) void collide_slots_kernel(Coll
       }
       wave_lds_sync();
       for (int j = 0; j < cnt; ++j) run_node(u0 + j, j);
-      if (many) {
-        __hip_atomic_fetch_add(&ok_wg, (unsigned long long)n_ok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        n_ok = 0;
-      }
       wave_lds_sync();
       if (A.direct && lane < cnt) {
         const double dsum = node_tab[wid][3][lane], dsq = node_tab[wid][4][lane];

@@ -127,23 +127,3 @@ def test_massless_node_at_origin(O, mask, precision):
     # the observed particle at p = 0: no direct sums
     assert np.all(I.reshape(2, -1, 105)[:, :, centre] == 0.0)
     assert np.all(I_ref.reshape(2, -1, 105)[:, :, centre] == 0.0)
-
-
-def test_accepted_samples_of_many(O):
-    """2^30 samples per point: from there on a workgroup's accepted samples are
-    counted in 64 bits as it goes.  Against one sample less per point, which is
-    counted in 32 bits: at most one more per point, and the share of a million."""
-    _case("accepted samples, 2^30 per point")
-    f = W.random_f(61, 1, 8, species_mask=1 << 6)
-    counts = []
-    with qgbe.Solver(n_x=(1, 1, 1), n_p=(2, 2, 2), x_half=(3.0, 3.0, 3.0), p_half=(2.0, 2.5, 1.5),
-                     species_mask=1 << 6, seed=SEED, precision=qgbe.FP64, symmetric=0) as s:
-        s.set_f(f)
-        for n in (1 << 20, (1 << 30) - 1, 1 << 30):
-            counts.append(s.collision(n)[3].n_accepted)
-    few, below, many = counts
-    assert 0 <= many - below <= 8
-    share = few / (8 << 20)
-    assert 0.1 < share < 0.9
-    # both are draws of the share: six deviations of the smaller sample
-    assert abs(many / (8 << 30) - share) <= 6.0 * np.sqrt(share * (1.0 - share) / (8 << 20))
