@@ -242,8 +242,8 @@ void plan_groups(qgbe_ctx* c, bool long_form) {
 }
 
 // Observed nodes per workgroup; acc: entries a workgroup zeroes and flushes.
-Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long long acc, int n_samples, bool queue,
-                     bool learned, bool long_form) {
+static Chunking plan_evenly(const qgbe_ctx* c, long long nodes, long long pairs, long long acc, int n_samples, bool queue,
+                            bool learned, bool long_form) {
   const int waves = collide_waves(queue);
   if (pairs >= c->n_cu) {
     // Enough (cell, channel) pairs to give every compute unit one: the nodes
@@ -309,6 +309,17 @@ Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long l
     }
   }
   return best;
+}
+
+// The same; the short-item form counts the accepted samples of a wave's nodes in
+// 32 bits (two per sample with the root samplers), so its workgroups take fewer
+// nodes of very many samples, which cost them nothing.
+Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long long acc, int n_samples, bool queue,
+                     bool learned, bool long_form) {
+  Chunking ck = plan_evenly(c, nodes, pairs, acc, n_samples, queue, learned, long_form);
+  if (!long_form && collide_short(c->d.precision, learned, ck.split, n_samples))
+    ck.chunk = (int)std::min<long long>(ck.chunk, std::max(1LL, ((1LL << 30) - 1) / n_samples));
+  return ck;
 }
 
 // Record buffers: for 128 samples per item (and an eighth more, as whole

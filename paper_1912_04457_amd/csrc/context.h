@@ -130,6 +130,9 @@ struct Chunking {
   int split;  // waves that share a node
   int block;  // nodes a wave takes at a time
 };
+// Observed nodes per workgroup; acc: entries a workgroup zeroes and flushes.
+Chunking plan_chunks(const qgbe_ctx* c, long long nodes, long long pairs, long long acc, int n_samples, bool queue,
+                     bool learned, bool long_form);
 // The recording launches of a call, and one of them: per workgroups from the
 // wg-th of all wgs on, as its first cell, its first workgroup there, cells and
 // (with one cell) channels of the group.

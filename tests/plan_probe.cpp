@@ -77,6 +77,12 @@ int main() {
     for (int l = 0; l < 3; ++l)
       for (int scale = 0; scale < 2; ++scale) route.push_back((int)deposit_route(&c, l, n_samples, scale, capacity));
     print("route", route);
+    // chunks without a queue and with one, for the uniform and the learned (or a root) sampler
+    std::vector<int> chunks;
+    for (int i = 0; i < 4; ++i)
+      chunks.push_back(plan_chunks(&c, c.G.nodes, (long long)c.G.cells * std::max(1, c.nch), c.G.nodes, n_samples, i & 1,
+                                   i & 2, long_form && d.precision == QGBE_FP32).chunk);
+    print("chunks", chunks);
     // the recording launches: some of them as [first workgroup, those of replay_batch]
     std::printf("\"batches\": {");
     c.rec_wgs = 1 << 16;

@@ -190,3 +190,20 @@ def test_recording_batches(probe, mask, n_x, n_p, precision, samples, capacity):
     assert total > 0
     if cells == 4550:
         assert total > 1 << 31
+
+
+@pytest.mark.parametrize("mask,n_x,n_p", [(0x40, (1, 1, 1), (2, 2, 2)), (0x40, (16, 16, 1), (20, 20, 20)),
+                                          (0x7F, (4, 1, 1), (20, 20, 20)), (0x7F, (1, 1, 1), (30, 30, 30))])
+def test_chunks_of_many_samples(probe, mask, n_x, n_p):
+    """A wave of the short-item form counts its nodes' accepted samples in 32
+    bits, two of them per sample with the root samplers: a workgroup of several
+    nodes has less than 2^30 samples.  (Beyond that a run takes minutes to hours.)"""
+    samples = (1, 100, 1023, 1024, 10 ** 5, 7 * 10 ** 6, 2 ** 29, 2 ** 30, 2 ** 31 - 1)
+    cells, nodes = int(np.prod(n_x)), int(np.prod(n_p))
+    for precision in (0, 1):
+        plans = probe([_case(mask, n_x, n_p, precision, 1, 0, n, 0) for n in samples])
+        for n, plan in zip(samples, plans):
+            for i, chunk in enumerate(plan["chunks"]):
+                assert 1 <= chunk and cells * plan["nch"] * -(-nodes // chunk) < 1 << 31
+                if precision == 0 or i >= 2:  # always in the short form
+                    assert chunk == 1 or chunk * n < 1 << 30
