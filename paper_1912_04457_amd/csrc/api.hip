@@ -245,7 +245,7 @@ void plan_groups(qgbe_ctx* c, bool long_form) {
 static Chunking plan_evenly(const qgbe_ctx* c, long long nodes, long long pairs, long long acc, int n_samples, bool queue,
                             bool learned, bool long_form) {
   const int waves = collide_waves(queue);
-  if (pairs >= c->n_cu) {
+  if (pairs >= c->n_cu && acc > 0) {
     // Enough (cell, channel) pairs to give every compute unit one: the nodes
     // of a pair are split over at most two workgroups per compute unit in all,
     // as each zeroes and flushes its accumulators (on the pure-gluon 16x16x1
@@ -265,7 +265,9 @@ static Chunking plan_evenly(const qgbe_ctx* c, long long nodes, long long pairs,
     chunk = std::min(chunk, (nodes + unit - 1) / unit * unit);
     return {(int)chunk, 1, nb};
   }
-  // Fewer pairs than compute units.  A workgroup has its compute unit to
+  // Fewer pairs than compute units, or (direct sums) no accumulators to pay for: 559
+  // pairs as one workgroup each are 2.2 rounds that take three (20^3 nodes x 300
+  // samples, FP64 direct 30.0 -> 22.9 ms).  A workgroup has its compute unit to
   // itself (LDS and registers), so their number is chosen near a multiple of
   // the compute units (up to eight rounds), and with few nodes per workgroup
   // several waves share a node.  The estimate, in sample iterations of a lone
@@ -281,7 +283,7 @@ static Chunking plan_evenly(const qgbe_ctx* c, long long nodes, long long pairs,
   Chunking best{0, 1, 1};
   double least = 0.0;
   for (int rounds = 1; rounds <= 8; ++rounds) {
-    const long long want = std::max(1LL, rounds * c->n_cu / pairs);
+    const long long want = pairs >= c->n_cu ? rounds : std::max(1LL, rounds * c->n_cu / pairs);
     const long long even = (nodes + want - 1) / want;
     for (int split = 1; split <= waves; ++split) {
       if (waves % split || (long_form && split > 1)) continue;

@@ -83,6 +83,9 @@ int main() {
       chunks.push_back(plan_chunks(&c, c.G.nodes, (long long)c.G.cells * std::max(1, c.nch), c.G.nodes, n_samples, i & 1,
                                    i & 2, long_form && d.precision == QGBE_FP32).chunk);
     print("chunks", chunks);
+    const Chunking direct = plan_chunks(&c, c.G.nodes, (long long)c.G.cells * std::max(1, c.nch), 0, n_samples, false,
+                                        false, false);
+    print("direct", {direct.chunk, direct.split, direct.block});
     // the recording launches: some of them as [first workgroup, those of replay_batch]
     std::printf("\"batches\": {");
     c.rec_wgs = 1 << 16;

@@ -207,3 +207,19 @@ def test_chunks_of_many_samples(probe, mask, n_x, n_p):
                 assert 1 <= chunk and cells * plan["nch"] * -(-nodes // chunk) < 1 << 31
                 if precision == 0 or i >= 2:  # always in the short form
                     assert chunk == 1 or chunk * n < 1 << 30
+
+
+@pytest.mark.parametrize("n_p", [(6, 6, 6), (9, 10, 11), (20, 20, 20)])
+def test_direct_sums_fill_the_compute_units(probe, n_p):
+    """Without accumulators a workgroup costs little, so the rounds of workgroups
+    over the 256 compute units are nearly full also where one for each (cell,
+    channel) pair would leave the last round nearly empty."""
+    cells = list(range(20, 120, 3))
+    nodes = int(np.prod(n_p))
+    for mask in (0x49, 0x7F):
+        for samples in (300, 2048):
+            plans = probe([_case(mask, (n, 1, 1), n_p, 0, 0, 0, samples, 0) for n in cells])
+            for n, plan in zip(cells, plans):
+                chunk, split, block = plan["direct"]
+                wgs = n * plan["nch"] * -(-nodes // chunk)
+                assert wgs / (256 * -(-wgs // 256)) >= 0.85, (mask, samples, n)
