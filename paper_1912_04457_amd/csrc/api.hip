@@ -265,9 +265,9 @@ static Chunking plan_evenly(const qgbe_ctx* c, long long nodes, long long pairs,
     chunk = std::min(chunk, (nodes + unit - 1) / unit * unit);
     return {(int)chunk, 1, nb};
   }
-  // Fewer pairs than compute units, or (direct sums) no accumulators to pay for: 559
-  // pairs as one workgroup each are 2.2 rounds that take three (20^3 nodes x 300
-  // samples, FP64 direct 30.0 -> 22.9 ms).  A workgroup has its compute unit to
+  // Fewer pairs than compute units, or (direct sums) no accumulators to pay for: 516
+  // pairs as one workgroup each are 2.02 rounds that take three (20^3 nodes x 300
+  // samples, FP64 direct 29.8 -> 22.7 ms).  A workgroup has its compute unit to
   // itself (LDS and registers), so their number is chosen near a multiple of
   // the compute units (up to eight rounds), and with few nodes per workgroup
   // several waves share a node.  The estimate, in sample iterations of a lone

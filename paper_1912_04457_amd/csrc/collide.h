@@ -75,7 +75,7 @@ struct CollideArgs {
   const float* mix_mu;       // [channels*nodes][K][5]
   const float* mix_sigma;    // [channels*nodes][K][5]
   const uint8_t* mix_on;     // [channels] 0: the channel falls back to the uniform sampler; NULL: all 1
-  RecordArgs rec;            // launch_record_deposits only
+  RecordArgs rec;            // launches that record only
 };
 
 // The (channel, position) pairs of a channel list that deposit into a species.

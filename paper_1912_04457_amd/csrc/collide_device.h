@@ -1,8 +1,9 @@
 // Monte Carlo collision term (Eq. C_a_b, Eq. MC C_gg, Eq. small c relation).
 //
-// Work item = (cell, channel, observed node p1).  One wavefront owns one item
-// at a time, so everything that depends only on the item (p1, E1, f1, masses,
-// channel) is wave-uniform; the 64 lanes draw samples s = lane, lane+64, ...
+// Work item = (cell, channel, observed node p1).  A wavefront works on one item
+// at a time (where items are few, several wavefronts on parts of its samples),
+// so everything that depends only on the item (p1, E1, f1, masses, channel) is
+// wave-uniform; the 64 lanes draw samples s = lane, lane+64, ...
 //
 // Per sample (CM-angle parameterisation of the 5-D integral):
 //   Philox4x32-10 block -> five 23-bit uniforms -> p2 in the box, cos theta*,
@@ -448,8 +449,7 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Wavefront sums.  The FP64 and root kernels, with one short item per
-// wavefront, use DPP: two quad permutations and two rotations within
+// Wavefront sums.  The short-item form uses DPP: two quad permutations and two rotations within
 // each 16-lane row leave every lane with its row's sum; the four row sums
 // are read from lanes 0, 16, 32, 48 and added in a fixed order.  Every lane
 // must be active.
@@ -473,7 +473,7 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Butterfly sums through lane permutes, for the FP32 kernel (long items).
+// Butterfly sums through lane permutes, for the long-item form.
 __device__ __forceinline__ int wave_count(int v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);

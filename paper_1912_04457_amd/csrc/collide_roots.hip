@@ -2,6 +2,75 @@
 #include "collide_slots.h"
 
 namespace qgbe {
+namespace {
+
+// The root samplers' kernel variants: [direct, symmetric, symmetric with global
+// atomics][scale][user terms].
+template <int kRoot>
+using RootFn = void (*)(CollideArgs);
+template <int kRoot>
+void root_variants(RootFn<kRoot> out[3][2][2]) {
+  out[0][0][0] = collide_slots_kernel<double, false, false, true, false, 0, false, true, false, kRoot>;
+  out[0][0][1] = collide_slots_kernel<double, false, false, true, false, 0, true, true, false, kRoot>;
+  out[0][1][0] = collide_slots_kernel<double, false, true, true, false, 0, false, true, false, kRoot>;
+  out[0][1][1] = collide_slots_kernel<double, false, true, true, false, 0, true, true, false, kRoot>;
+  out[1][0][0] = collide_slots_kernel<double, true, false, true, false, 0, false, true, false, kRoot>;
+  out[1][0][1] = collide_slots_kernel<double, true, false, true, false, 0, true, true, false, kRoot>;
+  out[1][1][0] = collide_slots_kernel<double, true, true, true, false, 0, false, true, false, kRoot>;
+  out[1][1][1] = collide_slots_kernel<double, true, true, true, false, 0, true, true, false, kRoot>;
+  out[2][0][0] = collide_slots_kernel<double, true, false, false, false, 0, false, true, false, kRoot>;
+  out[2][0][1] = collide_slots_kernel<double, true, false, false, false, 0, true, true, false, kRoot>;
+  out[2][1][0] = collide_slots_kernel<double, true, true, false, false, 0, false, true, false, kRoot>;
+  out[2][1][1] = collide_slots_kernel<double, true, true, false, false, 0, true, true, false, kRoot>;
+}
+
+template <int kRoot>
+hipError_t launch_roots(const CollideArgs& a, hipStream_t stream) {
+  const int n_acc = a.symmetric ? std::min(a.slot_hi - a.slot_lo, a.lds_acc) : 0;
+  const bool all_acc = !a.symmetric || n_acc == a.slot_hi - a.slot_lo;
+  if (!all_acc && (n_acc || a.win_n != a.G.nodes)) return hipErrorInvalidValue;
+  const int waves = kSlotThreads / kWave;
+  if (a.split < 1 || waves % a.split || (a.split > 1 && a.chunk_items > kSplitNodes)) return hipErrorInvalidValue;
+  if (a.node_block < 1 || a.node_block > kMaxNodeBlock) return hipErrorInvalidValue;
+  const long long blocks = (long long)a.G.cells * a.n_group * a.n_chunks;
+  if (blocks <= 0) return hipSuccess;
+  RootFn<kRoot> fns[3][2][2];
+  root_variants<kRoot>(fns);
+  hipLaunchKernelGGL(fns[!a.symmetric ? 0 : all_acc ? 1 : 2][a.scale ? 1 : 0][a.msq_mask ? 1 : 0], dim3((unsigned)blocks),
+                     dim3(kSlotThreads), (size_t)n_acc * a.win_n * sizeof(double), stream, a);
+  return hipGetLastError();
+}
+
+template <int kRoot>
+hipError_t launch_roots_rec(const CollideArgs& a, int n_wg, hipStream_t stream) {
+  if (n_wg <= 0) return hipSuccess;
+  if (!record_fits(a, n_wg, 2)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)n_wg), block(kSlotThreads);
+  if (a.msq_mask)
+    hipLaunchKernelGGL((collide_slots_kernel<double, true, false, true, false, 0, true, true, true, kRoot>), grid,
+                       block, 0, stream, a);
+  else
+    hipLaunchKernelGGL((collide_slots_kernel<double, true, false, true, false, 0, false, true, true, kRoot>), grid,
+                       block, 0, stream, a);
+  return hipGetLastError();
+}
+
+template <int kRoot>
+hipError_t roots_lds_limit_of(size_t lds_max, size_t* out) {
+  RootFn<kRoot> fns[3][2][2];
+  root_variants<kRoot>(fns);
+  for (int i = 0; i < 8; ++i)
+    if (const hipError_t e = raise_lds_limit((const void*)fns[i >> 2][(i >> 1) & 1][i & 1], lds_max, out)) return e;
+  return hipSuccess;
+}
+
+inline hipError_t roots_lds_limit(size_t lds_max, size_t* out) {
+  *out = lds_max;
+  const hipError_t e = roots_lds_limit_of<1>(lds_max, out);
+  return e != hipSuccess ? e : roots_lds_limit_of<2>(lds_max, out);
+}
+
+}  // namespace
 
 hipError_t launch_collide_roots(const CollideArgs& a, bool alt, hipStream_t stream) {
   return alt ? launch_roots<2>(a, stream) : launch_roots<1>(a, stream);

@@ -111,3 +111,42 @@ def test_table_one_as_user_terms_and_reset(O):
             qgbe.qgbe_set_matrix_element(s.ctx, 7, [(float("nan"), (0,) * 6)])
     assert np.all(np.abs(A1 - A0) <= 1e-12 * S0 + 1e-300)
     assert np.all(np.abs(A2 - A0) <= 1e-13 * S0 + 1e-300)
+
+
+@pytest.mark.parametrize("n_p,precision,sampler,launches", [
+    ((28, 27, 29), qgbe.FP32, qgbe.SAMPLER_UNIFORM, 2), ((28, 27, 29), qgbe.FP64, qgbe.SAMPLER_UNIFORM, 2),
+    ((28, 27, 29), qgbe.FP32, qgbe.SAMPLER_LEARNED, 2), ((28, 27, 29), qgbe.FP64, qgbe.SAMPLER_LEARNED, 2),
+    ((28, 27, 29), qgbe.FP32, qgbe.SAMPLER_ROOTS, 2), ((27, 27, 28), qgbe.FP32, qgbe.SAMPLER_UNIFORM, 1),
+    ((26, 27, 27), qgbe.FP32, qgbe.SAMPLER_LEARNED, 1), ((66, 68, 70), qgbe.FP64, qgbe.SAMPLER_UNIFORM, 2),
+    ((56, 57, 58), qgbe.FP64, qgbe.SAMPLER_ROOTS_ALT, 2)])
+def test_user_rows_by_every_route(O_user, n_p, precision, sampler, launches):
+    """User rows where the deposits are recorded, in the long-item form and with
+    global atomics: the item sums against the oracle, and the term without the
+    scale output (recorded, or one launch) against the one with it (several
+    launches, one launch, or global atomics)."""
+    _case(f"user msq routes n_p={n_p} precision={precision} sampler={sampler}")
+    O = O_user
+    g = O.Grid(n_p=n_p, p_half=(2.0, 2.5, 1.5), species_mask=1 << 6)
+    f = W.random_f(56, 1, g.nodes, species_mask=1 << 6) * 0.6
+    table = W.random_mog_table(57, g.nodes)
+    N = 5
+    with _solver(g, precision) as s:
+        qgbe.qgbe_set_matrix_element(s.ctx, 7, USER[7])
+        s.set_f(f)
+        qgbe.qgbe_set_proposal_table(s.ctx, *table)
+        A, _, I, st = s.collision(N, sampler=sampler, items=True)
+        B, S, _, _ = s.collision(N, sampler=sampler, scale=True)
+        m = s.masses()
+    assert st.n_collide_launches == launches
+    est = {qgbe.SAMPLER_UNIFORM: "cm", qgbe.SAMPLER_ROOTS: "root", qgbe.SAMPLER_ROOTS_ALT: "root_k3"}.get(sampler)
+    if est:
+        _, _, I_ref = O.collision(g, f, m, SEED, 0, N, estimator=est, want_items=True)
+    else:
+        _, _, I_ref = O.collision_learned(g, f, m, SEED, 0, N, *table, want_items=True)
+    f64 = precision == qgbe.FP64 or sampler in (qgbe.SAMPLER_ROOTS, qgbe.SAMPLER_ROOTS_ALT)
+    tol = 1e-10 if f64 else 1e-4
+    assert np.abs(I - I_ref).max() <= tol * np.abs(I_ref).max()
+    # beside a sample on the face of its cell: the rounding of a stencil weight (a
+    # few 2^-53 of the grid coordinate), in A and in S
+    assert np.all(np.abs(A - B) <= tol * np.abs(S) + 8 * 2.0 ** -53 * max(n_p) * S.max())
+    assert np.abs(A).max() > 0.0
