@@ -301,7 +301,10 @@ __global__ void refresh_weights_kernel(const float* __restrict__ p, __bf16* __re
 // round the other way now and then.)
 // Block b < kGradTiles: a 16 x 16 tile of a weight matrix, a wave per chunk (in
 // turn); the others: kBiasCols biases each.  206 workgroups, one round; bound by
-// the latency of a chain (16 loads, 8 MFMAs) and of the Adam step behind it.
+// the latency of a chain (16 loads, 8 MFMAs) and of the Adam step behind it.  A
+// batch of 4096 rows takes 18.4 us in mlp_tile_kernel and 7.6 here (with the
+// products over rows inside the tiles, and their slices summed, 22.6 and 9; as
+// separate products and passes 196 in 21 launches).
 constexpr int kGradChunk = 256, kBiasChunk = 64;
 constexpr int kTilesW2 = (kMlpHidden / 16) * (kMlpHidden / 16), kTilesW3 = kMlpHidden / 16 * (kOut16 / 16),
               kTilesW1 = kMlpHidden / 16;
